@@ -4,6 +4,7 @@
 #include "common.h"
 
 #include <climits>
+#include <cmath>
 #include <mutex>
 #include <string>
 
@@ -63,466 +64,546 @@ __global__ __launch_bounds__(256) void pad_rows_kernel(const bf16_t* __restrict_
 }
 
 // ---- sampling: one workgroup per row ----------------------------------------------------------------------
-// The row of logits (0.5 MB at a 128k vocabulary) does not fit on chip, so the cost is the number of passes over
-// it.  With top-k: pass 1 takes the maximum and counts the top byte of the logits' keys, pass 2 counts the second
-// byte inside the bin of the k-th largest, pass 3 gathers the tokens at or above that 16-bit prefix into a list
-// in LDS, on which the k-th largest is selected (rows whose candidates do not fit the list fall back to one pass
-// per key byte).  Then either
-//   * at most kCompact tokens survive top-k (the usual top_k = 20..100): nucleus and draw work on that short
-//     list, or
-//   * the nucleus threshold is searched over the whole row, 15 candidate thresholds per pass (8 passes), and the
-//     draw takes one more.
+// What bounds it: a row of logits (0.5 MB at a 128k vocabulary) does not fit on chip, so the cost is the number of
+// passes over it (6 to 8 us each for a compute unit of its own, 24 us for 256 rows: 5.5 TB/s) and the chains of barriers
+// behind them.  One workgroup per row, because a call has one row per sequence and the rows are independent; 64 registers
+// per thread and 34 KiB of LDS let two rows share a compute unit, so 257 rows are not two rounds.
+//
+// The row is read once.  Its first 16384 logits to be read (four blocks from all over it) stay in registers while a
+// bound is taken from them, and from there on every logit at or above the bound goes into a list in LDS:
+//   top-k     the bound has at least k logits at or above it, so the list holds the k largest;
+//   nucleus   the bound is a guess (the list comes to two or three thousand logits) that is checked at the end: the mass of the
+//             list must reach top_p of the mass of the row.
+// Everything else happens on the list: the k-th largest, the nucleus threshold and the draw are each a weighted radix
+// selection ("the largest key above which the weight reaches a value") with 12-bit digits and 64-bit integer weights --
+// masses in fixed point -- so the result does not depend on the order the atomics took.
+// Where the list overflows or the guess fails, a second pass takes a tighter bound from the maxima of the 1024 threads
+// over the whole row; where that fails too (nearly flat distributions, very large k, masses of ties), the selection
+// runs over the row, one pass per digit, and the draw takes a pass that sums masses per 4096 consecutive tokens.
+// Measured at a vocabulary of 128256 (before: four to ten passes per row, one row per compute unit; both in us):
+//   top-k 50 + nucleus 0.95   1 row 160 -> 28, 256 rows 171 -> 39, 257 rows 320 -> 48
+//   nucleus 0.95 (logits of standard deviation 4.3)   1 row 780 -> 30, 64 rows 880 -> 35, 257 rows 1740 -> 49
+//   nucleus 0.95 of a nearly flat row (the selection runs over the row)   1 row 750 -> 166
 constexpr int kSampleThreads = 1024;
 constexpr int kSampleWaves = kSampleThreads / 64;
-constexpr int kCompact = 1024;
-constexpr int kList = 4096;  // top-k candidates held in LDS while the k-th largest is selected among them
-// the short-list path gives every thread one list entry (sort, masses) and keeps the list in the reduction arrays;
-// the histogram is cleared by the first 256 threads; block_sums keeps up to 15 values per wave in those arrays
-static_assert(kCompact == kSampleThreads, "the short list has one entry per thread");
-static_assert(kSampleThreads >= 256 && 15 * kSampleWaves <= kSampleThreads, "reduction arrays too small");
+constexpr int kDigitBits = 12, kBins = 1 << kDigitBits;
+constexpr int kList = 4096, kPerThread = kList / kSampleThreads;  // candidates held in LDS, then in registers
+static_assert(kBins == 4 * kSampleThreads, "find_bin gives every thread four bins; a block of for_row is one bin of the draw");
 
-// order-preserving map from float to unsigned: a < b  <=>  key(a) < key(b) (for non-NaN values)
+// order-preserving map from float to unsigned: a < b  <=>  key(a) < key(b) (for non-NaN values), and back
 __device__ __forceinline__ uint32_t float_key(float f) {
     const uint32_t b = __float_as_uint(f);
     return b ^ ((b >> 31) ? 0xFFFFFFFFu : 0x80000000u);
 }
+__device__ __forceinline__ float key_float(uint32_t k) { return __uint_as_float((k & 0x80000000u) ? k ^ 0x80000000u : ~k); }
 
-// Calls f(index, logit) for the elements of a row that this thread owns, in increasing index order: groups of four
-// consecutive logits (16-byte loads, two in flight) when the row starts on a 16-byte boundary, single ones otherwise.
-template <class F>
-__device__ __forceinline__ void for_row(const float* __restrict__ lg, int vocab, F&& f) {
+// Calls f(block, index, logit, valid) for the elements of a row that this thread owns, in increasing index order, the
+// whole workgroup walking blocks of 4096 consecutive logits (block = index / 4096): 16-byte loads, `U` blocks in flight,
+// when the row starts on a 16-byte boundary, single ones otherwise.  block_end(block) follows the four calls of a block.
+template <int U, class F, class E>
+__device__ __forceinline__ void for_row(const float* __restrict__ lg, int vocab, F&& f, E&& block_end) {
     const int tid = threadIdx.x;
+    const int blocks = (vocab + 4095) >> 12, whole = vocab >> 12;
     if ((reinterpret_cast<uintptr_t>(lg) & 15) == 0) {
-        const int groups = vocab >> 2;
-        int g = tid;
-        for (; g + kSampleThreads < groups; g += 2 * kSampleThreads) {
-            const f32x4 a = *reinterpret_cast<const f32x4*>(lg + 4 * g);
-            const f32x4 b = *reinterpret_cast<const f32x4*>(lg + 4 * (g + kSampleThreads));
+        int b = 0;
+        for (; b + U <= whole; b += U) {
+            f32x4 v[U];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) f(4 * g + e, a[e]);
+            for (int q = 0; q < U; ++q) v[q] = *reinterpret_cast<const f32x4*>(lg + ((b + q) << 12) + 4 * tid);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) f(4 * (g + kSampleThreads) + e, b[e]);
+            for (int q = 0; q < U; ++q) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) f(((b + q) << 12) + 4 * tid + e, v[q][e]);
+                block_end(b + q);
+            }
         }
-        if (g < groups) {
-            const f32x4 a = *reinterpret_cast<const f32x4*>(lg + 4 * g);
+        for (; b < blocks; ++b) {
+            const int i = (b << 12) + 4 * tid;
+            if (i + 4 <= vocab) {
+                const f32x4 v = *reinterpret_cast<const f32x4*>(lg + i);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) f(4 * g + e, a[e]);
+                for (int e = 0; e < 4; ++e) f(i + e, v[e]);
+            } else {
+                for (int e = 0; e < 4; ++e)
+                    if (i + e < vocab) f(i + e, lg[i + e]);
+            }
+            block_end(b);
         }
-        const int t = 4 * groups + tid;
-        if (t < vocab) f(t, lg[t]);
     } else {
-        for (int i = tid; i < vocab; i += kSampleThreads) f(i, lg[i]);
+        for (int b = 0; b < blocks; ++b) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int i = (b << 12) + 4 * tid + e;
+                if (i < vocab) f(i, lg[i]);
+            }
+            block_end(b);
+        }
     }
 }
 
-// hist[bin] += 1 for every lane with `on`.  Lanes of a wave that hit the same bin are counted together (the top
-// byte of the keys takes two or three values in a whole row, and same-address LDS atomics run one after the
-// other); after three such rounds the rest adds singly (many different bins: those run in parallel).
-__device__ __forceinline__ void hist_add(unsigned* hist, bool on, uint32_t bin) {
-    const int lane = threadIdx.x & 63;
-    uint64_t todo = __ballot(on);
-    for (int round = 0; round < 3 && todo; ++round) {
-        const int leader = __ffsll((long long)todo) - 1;
-        const uint32_t b = (uint32_t)__shfl((int)bin, leader);
-        const uint64_t same = __ballot(on && bin == b) & todo;
-        if (lane == leader) atomicAdd(&hist[b], (unsigned)__popcll(same));
-        todo &= ~same;
-    }
-    if ((todo >> lane) & 1) atomicAdd(&hist[bin], 1u);
+struct SampleShared {
+    union {
+        uint64_t bins[kBins];       // weights per digit value
+        struct {
+            float v[kList];         // candidates: logit and token id
+            int id[kList];
+        } list;
+        uint32_t keys[kSampleThreads];
+    };
+    uint64_t wave_sum[kSampleWaves];
+    uint64_t above;
+    float wave_f[kSampleWaves];
+    int wave_i[kSampleWaves];
+    uint32_t digit;
+    int count;
+};
+
+// Lane l receives v of lane l - N of its row of 16 (row_shr), or of the last lane of the row(s) before it (row_bcast),
+// 0 where there is none: the steps of a scan without a trip through LDS.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint64_t dpp_add(uint64_t v) {
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)v, CTRL, ROWS, 0xF, true);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(v >> 32), CTRL, ROWS, 0xF, true);
+    return v + ((uint64_t)hi << 32 | lo);
+}
+__device__ __forceinline__ uint64_t row_scan(uint64_t v) {  // inclusive, within rows of 16 lanes
+    v = dpp_add<0x111, 0xF>(v);
+    v = dpp_add<0x112, 0xF>(v);
+    v = dpp_add<0x114, 0xF>(v);
+    return dpp_add<0x118, 0xF>(v);
+}
+__device__ __forceinline__ uint64_t wave_scan(uint64_t v) {  // inclusive
+    v = row_scan(v);
+    v = dpp_add<0x142, 0xA>(v);
+    return dpp_add<0x143, 0xC>(v);
+}
+__device__ __forceinline__ uint64_t lane_value(uint64_t v, int lane) {
+    return (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), lane) << 32 |
+           (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, lane);
 }
 
-// Sum over the workgroup with a fixed association (lanes by butterfly, then the 16 wave sums in order), so that a
-// row always gives the same token.  `scratch` holds kSampleWaves floats per value.
+// Place of a digit value in sh.bins: the four bins a thread sums (see find_bin) lie 1024 apart, so that its and its
+// neighbours' reads hit different banks.
+__device__ __forceinline__ uint32_t bin_place(uint32_t digit) { return (digit & 3u) * kSampleThreads + (digit >> 2); }
+
+__device__ __forceinline__ void clear_bins(SampleShared& sh) {
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < kBins / kSampleThreads; ++j) sh.bins[j * kSampleThreads + threadIdx.x] = 0;
+    __syncthreads();
+}
+__device__ __forceinline__ void add_to_bin(SampleShared& sh, uint32_t digit, uint64_t w) {
+    atomicAdd((unsigned long long*)&sh.bins[bin_place(digit)], (unsigned long long)w);
+}
+
+// The largest digit d with weight(digits >= d) >= need, and the weight above it; digit 0 when the whole does not reach
+// `need`.  Called when every thread has added its weights; leaves the bins cleared for the next selection.
+__device__ __forceinline__ uint32_t find_bin(SampleShared& sh, uint64_t need, uint64_t& above) {
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    __syncthreads();
+    // thread t owns the t-th quadruple of digits counted from the top
+    const int quad = kSampleThreads - 1 - tid;
+    uint64_t w[4], mine = 0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        w[j] = sh.bins[j * kSampleThreads + quad];
+        sh.bins[j * kSampleThreads + quad] = 0;
+        mine += w[j];
+    }
+    const uint64_t incl = wave_scan(mine);
+    if (lane == 63) sh.wave_sum[wave] = incl;
+    __syncthreads();
+    const uint64_t waves = row_scan(sh.wave_sum[lane & (kSampleWaves - 1)]);
+    const uint64_t all = lane_value(waves, kSampleWaves - 1);
+    const bool reached = all >= need;
+    uint64_t before = incl - mine + (wave > 0 ? lane_value(waves, wave - 1) : 0);
+    // the thread in whose bins the sum passes `need`; the last one (it owns digit 0) if none
+    if (reached ? before < need && before + mine >= need : tid == kSampleThreads - 1) {
+        int d = 4 * quad + 3;
+#pragma unroll
+        for (int j = 3; j > 0; --j) {
+            const bool on = d == 4 * quad + j && (!reached || before + w[j] < need);
+            before += on ? w[j] : 0;
+            d -= on ? 1 : 0;
+        }
+        sh.digit = (uint32_t)d;
+        sh.above = before;
+    }
+    __syncthreads();
+    above = sh.above;
+    return sh.digit;
+}
+
+// The largest key t with weight(entries with key >= t) >= need, over the workgroup's list (kPerThread entries per
+// thread, weight 0 where there is none); `bits` (at most 32) is the width of the keys.  The bins must be clear.
+__device__ __forceinline__ uint32_t select_key(SampleShared& sh, const uint32_t (&key)[kPerThread],
+                                               const uint64_t (&weight)[kPerThread], int bits, uint64_t need) {
+    uint32_t prefix = 0;
+    int low = bits;  // bits below `low` are still open
+    while (low > 0) {
+        const int step = low < kDigitBits ? low : kDigitBits, shift = low - step;
+        const uint32_t digit_mask = (1u << step) - 1u;
+#pragma unroll
+        for (int j = 0; j < kPerThread; ++j) {
+            const bool same = low == 32 || (key[j] >> low) == (prefix >> low);
+            if (same && weight[j]) add_to_bin(sh, (key[j] >> shift) & digit_mask, weight[j]);
+        }
+        uint64_t above;
+        const uint32_t d = find_bin(sh, need, above);
+        prefix |= d << shift;
+        need = need > above ? need - above : 1;
+        low = shift;
+    }
+    return prefix;
+}
+
+// Sum over the workgroup with a fixed association (lanes by butterfly, then the wave sums in order).
+__device__ __forceinline__ float block_sum(SampleShared& sh, float v) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) sh.wave_f[threadIdx.x >> 6] = v;
+    __syncthreads();
+    float s = 0.f;
+#pragma unroll
+    for (int w = 0; w < kSampleWaves; ++w) s += sh.wave_f[w];
+    return s;
+}
+__device__ __forceinline__ uint64_t block_sum(SampleShared& sh, uint64_t v) {
+    v = wave_scan(v);
+    __syncthreads();
+    if ((threadIdx.x & 63) == 63) sh.wave_sum[threadIdx.x >> 6] = v;
+    __syncthreads();
+    return lane_value(row_scan(sh.wave_sum[threadIdx.x & (kSampleWaves - 1)]), kSampleWaves - 1);
+}
+
+// A lower bound (its low 12 bits are 0) of the k-th largest of N x 64 keys, N per lane, found bit by bit with ballots;
+// 0 when there are not k of them.
 template <int N>
-__device__ __forceinline__ void block_sums(float (&v)[N], float* scratch) {
-    const int tid = threadIdx.x;
+__device__ __forceinline__ uint32_t wave_kth(const uint32_t (&keys)[N], int k) {
+    uint32_t t = 0;
+    for (int bit = 31; bit >= 12; --bit) {
+        const uint32_t probe = t | (1u << bit);
+        int n = 0;
 #pragma unroll
-    for (int j = 0; j < N; ++j) {
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) v[j] += __shfl_xor(v[j], o);
-        if ((tid & 63) == 0) scratch[j * kSampleWaves + (tid >> 6)] = v[j];
+        for (int j = 0; j < N; ++j) n += __popcll(__ballot(keys[j] >= probe));
+        if (n >= k) t = probe;
+        if (n == k) break;  // exactly the k largest: a finer bound gains nothing
     }
+    return t;
+}
+// A value with at least k of the 1024 threads' keys at or above it, 1 <= k <= 1024.  Exact: the k-th largest of all
+// (wave 0 searches, 2 us).  Otherwise the lowest of the waves' own (k/16)-th largest: a little lower, a tenth of the time.
+template <bool EXACT>
+__device__ __forceinline__ uint32_t kth_of_threads(SampleShared& sh, uint32_t key, int k) {
+    uint32_t t = 0xFFFFFFFFu;
+    __syncthreads();
+    if constexpr (EXACT) {
+        sh.keys[threadIdx.x] = key;
+        __syncthreads();
+        if (threadIdx.x < 64) {
+            uint32_t mine[kSampleWaves];
+#pragma unroll
+            for (int j = 0; j < kSampleWaves; ++j) mine[j] = sh.keys[j * 64 + threadIdx.x];
+            t = wave_kth(mine, k);
+            if (threadIdx.x == 0) sh.wave_i[0] = (int)t;
+        }
+        __syncthreads();
+        t = (uint32_t)sh.wave_i[0];
+    } else {
+        const uint32_t mine[1] = {key};
+        const uint32_t own = wave_kth(mine, (k + kSampleWaves - 1) / kSampleWaves);
+        if ((threadIdx.x & 63) == 0) sh.wave_i[threadIdx.x >> 6] = (int)own;
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < kSampleWaves; ++q) t = min(t, (uint32_t)sh.wave_i[q]);
+    }
+    return t;
+}
+// Largest value of the workgroup.
+__device__ __forceinline__ float block_max(SampleShared& sh, float v) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) sh.wave_f[threadIdx.x >> 6] = v;
     __syncthreads();
 #pragma unroll
-    for (int j = 0; j < N; ++j) {
-        float s = 0.f;
-#pragma unroll
-        for (int w = 0; w < kSampleWaves; ++w) s += scratch[j * kSampleWaves + w];
-        v[j] = s;
-    }
-    __syncthreads();
+    for (int w = 0; w < kSampleWaves; ++w) v = fmaxf(v, sh.wave_f[w]);
+    return v;
 }
 
-__global__ __launch_bounds__(kSampleThreads) void sample_kernel(const float* __restrict__ logits, int64_t ld, int vocab,
-                                                                const float* __restrict__ temperature,
-                                                                const int32_t* __restrict__ top_k,
-                                                                const float* __restrict__ top_p,
-                                                                const float* __restrict__ uniform,
-                                                                int32_t* __restrict__ out) {
-    __shared__ float fs[kSampleThreads];   // reductions; later the probabilities of the compact list
-    __shared__ int is[kSampleThreads];     // reductions; later the token ids of the compact list
-    __shared__ unsigned hist[256];
-    __shared__ uint32_t list_key[kList];   // key(z) and token id of the top-k candidates
-    __shared__ int list_id[kList];
-    __shared__ uint32_t sh_key;
-    __shared__ int sh_int;
-    const int tid = threadIdx.x, row = blockIdx.x;
-    const float* lg = logits + (int64_t)row * ld;
+// nucleus: the weight that has to be reached, of `total`
+__device__ __forceinline__ uint64_t nucleus_need(float p, uint64_t total) {
+    const double need = ceil((double)p * (double)total);
+    return need >= 1.0 ? (uint64_t)need : 1;
+}
+// draw: the first token whose running sum exceeds u * total
+__device__ __forceinline__ uint64_t draw_need(float u, uint64_t total) {
+    const double target = floor((double)u * (double)total);
+    const uint64_t need = (target > 0.0 ? (uint64_t)target : 0) + 1;
+    return need < total ? need : total;
+}
 
-    const float temp = temperature[row];
-    const int k = top_k[row];
-    const bool select = temp > 0.f && k > 0 && k < vocab;  // top-k is on: the first pass also counts top bytes
-
-    // pass 1: the largest logit and its lowest index (greedy; also the softmax reference); with top-k, the
-    // histogram of the top byte of the logits' own keys (dividing by the temperature keeps their order)
-    if (tid < 256) hist[tid] = 0;
-    __syncthreads();
+// Greedy: the lowest index among the largest logits.
+__device__ __forceinline__ int row_argmax(SampleShared& sh, const float* __restrict__ lg, int vocab) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     float best = -INFINITY;
     int best_i = INT_MAX;
-    for_row(lg, vocab, [&](int i, float v) {
+    for_row<4>(lg, vocab, [&](int i, float v) {
         if (v > best) {
             best = v;
             best_i = i;
         }
-        if (select) hist_add(hist, true, float_key(v) >> 24);
-    });
-    fs[tid] = best;
-    is[tid] = best_i;
-    __syncthreads();
-    for (int s = kSampleThreads / 2; s > 0; s >>= 1) {
-        if (tid < s) {
-            const float ov = fs[tid + s];
-            const int oi = is[tid + s];
-            if (ov > fs[tid] || (ov == fs[tid] && oi < is[tid])) {
-                fs[tid] = ov;
-                is[tid] = oi;
-            }
+    }, [](int) {});
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        const float ov = __shfl_xor(best, o);
+        const int oi = __shfl_xor(best_i, o);
+        if (ov > best || (ov == best && oi < best_i)) {
+            best = ov;
+            best_i = oi;
         }
-        __syncthreads();
     }
-    best = fs[0];
-    best_i = is[0] == INT_MAX ? 0 : is[0];
+    if (lane == 0) {
+        sh.wave_f[wave] = best;
+        sh.wave_i[wave] = best_i;
+    }
     __syncthreads();
+#pragma unroll
+    for (int w = 0; w < kSampleWaves; ++w) {
+        const float ov = sh.wave_f[w];
+        const int oi = sh.wave_i[w];
+        if (ov > best || (ov == best && oi < best_i)) {
+            best = ov;
+            best_i = oi;
+        }
+    }
+    return best_i == INT_MAX ? 0 : best_i;
+}
+
+constexpr int kFirstList = 1400;     // first bound of a nucleus: taken so that the list comes to 1.5 - 2 times this many
+constexpr int kMaxFirstK = 256;      // largest k for which the list taken with the first bound is expected to fit
+constexpr int kSecondKeys = 960;     // second bound of a nucleus: 960 of the thread maxima of the whole row, about 2800 logits
+
+__global__ __launch_bounds__(kSampleThreads, 8) void sample_kernel(const float* __restrict__ logits, int64_t ld, int vocab,
+                                                                   float mass_one, const float* __restrict__ temperature,
+                                                                   const int32_t* __restrict__ top_k,
+                                                                   const float* __restrict__ top_p,
+                                                                   const float* __restrict__ uniform,
+                                                                   int32_t* __restrict__ out) {
+    __shared__ SampleShared sh;
+    const int tid = threadIdx.x, lane = tid & 63, row = blockIdx.x;
+    const float* lg = logits + (int64_t)row * ld;
+    const float temp = temperature[row];
     if (!(temp > 0.f)) {
+        const int best_i = row_argmax(sh, lg, vocab);
         if (tid == 0) out[row] = best_i;
         return;
     }
-    const float zmax = best / temp;
-    const float p = top_p[row];
-    const float u = uniform[row];
+    const int k = top_k[row];
+    const float p = top_p[row], u = uniform[row];
+    const bool by_k = k > 0 && k < vocab, by_p = p < 1.f;
+    const float c = 1.4426950408889634f / temp;
+    const auto no_end = [](int) {};
 
-    // The bin that holds the want-th largest entry of the 256-bin histogram goes to sh_key (bin 0 when there are
-    // fewer entries than that), the number of entries above that bin to sh_int, the bin's own count to hist[0].
-    // Wave 0 does it: lane l owns bins 4l .. 4l+3, a shuffle scan gives the count above each lane's bins.
-    auto pick_bin = [&](int want) {
-        if (tid < 64) {
-            int c[4];
+    // ---- the pass over the row: maxima of the threads, and, where it is likely to work, the list ----
+    const int blocks = (vocab + 4095) >> 12, quarter = vocab >> 14;
+    const bool first_list = quarter > 0 && (reinterpret_cast<uintptr_t>(lg) & 15) == 0 && (by_k ? k <= kMaxFirstK : by_p);
+    if (tid == 0) sh.count = 0;
+    float bound = -INFINITY, ref = 0.f;
+    float rest = 0.f;            // mass of the tokens that are not on the list, relative to a token with logit `ref`
+    float own_max = -INFINITY;
+    auto push = [&](int i, float v) {
+        const int slot = atomicAdd(&sh.count, 1);
+        if (slot < kList) {
+            sh.list.v[slot] = v;
+            sh.list.id[slot] = i;
+        }
+    };
+    auto take = [&](int i, float v) {
+        own_max = fmaxf(own_max, v);
+        const bool in = v >= bound;
+        if (in) push(i, v);
+        if (!by_k) rest += in ? 0.f : __builtin_amdgcn_exp2f((v - ref) * c);
+    };
+    // a bound on logits from a key: division by the temperature may round smaller logits to the same z (they tie)
+    auto bound_of = [&](uint32_t key) {
+        const float edge = key_float(key);
+        return edge == edge ? edge - fabsf(edge) * 0x1p-20f - temp * 0x1p-148f : -INFINITY;
+    };
+    if (first_list) {
+        f32x4 v[4];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) c[j] = (int)hist[4 * tid + j];
-            const int mine = c[0] + c[1] + c[2] + c[3];
-            int incl = mine;  // entries in this lane's bins and all higher ones
+        for (int q = 0; q < 4; ++q) v[q] = *reinterpret_cast<const f32x4*>(lg + ((q * quarter) << 12) + 4 * tid);
 #pragma unroll
-            for (int o = 1; o < 64; o <<= 1) {
-                const int other = __shfl_down(incl, o);
-                if (tid + o < 64) incl += other;
-            }
-            int above = incl - mine, found = -1, found_above = 0;
+        for (int q = 0; q < 4; ++q)
 #pragma unroll
-            for (int j = 3; j >= 0; --j) {
-                if (found < 0 && above + c[j] >= want && 4 * tid + j > 0) {
-                    found = 4 * tid + j;
-                    found_above = above;
-                }
-                above += c[j];
-            }
-            // the highest bin that qualifies wins; lane 0 reports bin 0 when none does
-            const uint64_t have = __ballot(found >= 0);
-            const int winner = have ? 63 - __clzll((long long)have) : 0;
-            if (tid == winner) {
-                const int bin = have ? found : 0;
-                sh_key = (uint32_t)bin;
-                sh_int = have ? found_above : incl - c[0];
-                hist[0] = hist[bin];
+            for (int e = 0; e < 4; ++e) own_max = fmaxf(own_max, v[q][e]);
+        bound = bound_of(kth_of_threads<false>(sh, float_key(own_max), by_k ? k : kSampleWaves * min(40, max(4, kFirstList * 1024 / vocab))));
+        if (!by_k) ref = block_max(sh, own_max);
+        for (int i = 0;;) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) take(((q * quarter + i) << 12) + 4 * tid + e, v[q][e]);
+            if (++i >= quarter) break;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) v[q] = *reinterpret_cast<const f32x4*>(lg + ((q * quarter + i) << 12) + 4 * tid);
+        }
+        for (int b = 4 * quarter; b < blocks; ++b) {
+            const int i = (b << 12) + 4 * tid;
+            for (int e = 0; e < 4; ++e)
+                if (i + e < vocab) take(i + e, lg[i + e]);
+        }
+    } else {
+        for_row<4>(lg, vocab, [&](int, float v) { own_max = fmaxf(own_max, v); }, no_end);
+    }
+    const float best = block_max(sh, own_max);
+    // probability of a token relative to the most probable one; a mass is that in units of 1 / mass_one
+    auto prob = [&](float v) { return __builtin_amdgcn_exp2f((v - best) * c); };
+    auto mass = [&](float v) { return (uint64_t)(prob(v) * mass_one); };
+
+    // Finishes the row on the list of n candidates; false when the guess of a nucleus does not hold.
+    auto finish_on_list = [&](int n, float others) -> bool {
+        uint32_t key[kPerThread], ikey[kPerThread];
+        uint64_t weight[kPerThread];
+        uint64_t own = 0;
+#pragma unroll
+        for (int j = 0; j < kPerThread; ++j) {
+            const int s = j * kSampleThreads + tid;
+            key[j] = ikey[j] = 0;
+            weight[j] = 0;
+            if (s < n) {
+                const float v = sh.list.v[s];
+                key[j] = float_key(v / temp);
+                ikey[j] = 0xFFFFFFu - (uint32_t)sh.list.id[s];  // larger for tokens that come first
+                weight[j] = mass(v);
+                own += weight[j];
             }
         }
-        __syncthreads();
+        clear_bins(sh);
+        uint64_t total;
+        if (by_k) {
+            uint64_t one[kPerThread];
+#pragma unroll
+            for (int j = 0; j < kPerThread; ++j) one[j] = j * kSampleThreads + tid < n ? 1 : 0;
+            const uint32_t floor_key = select_key(sh, key, one, 32, (uint64_t)k);
+            own = 0;
+#pragma unroll
+            for (int j = 0; j < kPerThread; ++j) {
+                if (key[j] < floor_key) weight[j] = 0;
+                own += weight[j];
+            }
+            total = block_sum(sh, own);
+        } else {
+            const uint64_t listed = block_sum(sh, own);
+            total = listed + (uint64_t)((double)block_sum(sh, others) * (double)mass_one);
+            if (listed < nucleus_need(p, total)) return false;
+        }
+        if (by_p) {
+            const uint32_t t = select_key(sh, key, weight, 32, nucleus_need(p, total));
+            own = 0;
+#pragma unroll
+            for (int j = 0; j < kPerThread; ++j) {
+                if (key[j] < t) weight[j] = 0;
+                own += weight[j];
+            }
+            total = block_sum(sh, own);
+        }
+        const uint32_t first = select_key(sh, ikey, weight, 24, draw_need(u, total));
+        if (tid == 0) out[row] = total ? (int)(0xFFFFFFu - first) : 0;
+        return true;
     };
 
-    // top-k: tokens with key(z) >= floor_key are kept, z = logit / temperature (all of them when top-k is off)
-    uint32_t floor_key = 0;
-    int kept = vocab;
-    bool listed = false;  // is[0 .. sh_int) already holds the ids of the kept tokens
-    if (select) {
-        // Two more bytes would cost two more passes over the row.  Instead: one pass for the second byte, then
-        // every token whose logit key is at or above the 16-bit prefix of the k-th largest goes into a short
-        // list in LDS (with its exact key(z)), and the k-th largest z is selected on that list.  The list is taken
-        // by z, not by logit -- z >= (smallest logit of the prefix) / temperature -- so tokens whose z ties with a
-        // listed one are listed too, whatever their logit.
-        pick_bin(k);
-        const uint32_t b3 = sh_key;
-        const int above3 = sh_int;
-        __syncthreads();
-        if (tid < 256) hist[tid] = 0;
-        __syncthreads();
-        for_row(lg, vocab, [&](int, float v) {
-            const uint32_t key = float_key(v);
-            hist_add(hist, (key >> 24) == b3, (key >> 16) & 255u);
-        });
-        __syncthreads();
-        pick_bin(k - above3);
-        const uint32_t prefix16 = (b3 << 8) | sh_key;
-        const int candidates = above3 + sh_int + (int)hist[0];
-        __syncthreads();
-        bool done = false;
-        if (candidates <= kList) {
-            const uint32_t edge_key = prefix16 << 16;  // smallest key with that prefix; back to the float it encodes
-            const float edge = __uint_as_float((edge_key & 0x80000000u) ? edge_key ^ 0x80000000u : ~edge_key);
-            const uint32_t edge_z = float_key(edge / temp);
-            if (tid == 0) sh_int = 0;
+    for (int attempt = first_list ? 0 : 1; attempt < 2; ++attempt) {
+        if (attempt == 1) {
+            // a second pass, with a bound from the whole row
+            if (!(by_k ? k <= kSampleThreads : by_p)) break;
+            bound = bound_of(kth_of_threads<true>(sh, float_key(own_max), by_k ? k : kSecondKeys));
             __syncthreads();
-            for_row(lg, vocab, [&](int i, float v) {
-                const uint32_t zk = float_key(v / temp);
-                if (zk >= edge_z) {
-                    const int slot = atomicAdd(&sh_int, 1);
-                    if (slot < kList) {
-                        list_key[slot] = zk;
-                        list_id[slot] = i;
-                    }
-                }
-            });
+            if (tid == 0) sh.count = 0;
             __syncthreads();
-            const int n_list = sh_int;
+            ref = best;
+            rest = 0.f;
+            for_row<4>(lg, vocab, take, no_end);
             __syncthreads();
-            if (n_list <= kList) {  // (ties in z can add entries beyond the count taken on logits)
-                // radix select of the k-th largest key(z) on the list, most significant byte first
-                uint32_t prefix = 0;
-                int want = k, above_total = 0;
-                for (int byte = 3; byte >= 0; --byte) {
-                    if (tid < 256) hist[tid] = 0;
-                    __syncthreads();
-                    const int shift = byte * 8;
-                    const uint32_t high_mask = byte == 3 ? 0u : 0xFFFFFFFFu << (shift + 8);
-                    for (int j = tid; j < n_list; j += kSampleThreads) {
-                        const uint32_t key = list_key[j];
-                        if ((key & high_mask) == (prefix & high_mask)) atomicAdd(&hist[(key >> shift) & 255u], 1u);
-                    }
-                    __syncthreads();
-                    pick_bin(want);
-                    prefix |= sh_key << shift;
-                    want -= sh_int;
-                    above_total += sh_int;
-                    if (byte == 0) kept = above_total + (int)hist[0];
-                    __syncthreads();
-                }
-                floor_key = prefix;
-                done = true;
-                if (kept <= kCompact) {
-                    if (tid == 0) sh_int = 0;
-                    __syncthreads();
-                    for (int j = tid; j < n_list; j += kSampleThreads)
-                        if (list_key[j] >= floor_key) is[atomicAdd(&sh_int, 1)] = list_id[j];
-                    __syncthreads();
-                    listed = true;
-                }
-            }
         }
-        if (!done) {
-            // many near-equal logits around the k-th largest: radix select over the four bytes of key(z) on the
-            // whole row, one pass per byte
-            uint32_t prefix = 0;
-            int want = k, above_total = 0;
-            for (int byte = 3; byte >= 0; --byte) {
-                if (tid < 256) hist[tid] = 0;
-                __syncthreads();
-                const int shift = byte * 8;
-                const uint32_t high_mask = byte == 3 ? 0u : 0xFFFFFFFFu << (shift + 8);
-                for_row(lg, vocab, [&](int, float v) {
-                    const uint32_t key = float_key(v / temp);
-                    hist_add(hist, (key & high_mask) == (prefix & high_mask), (key >> shift) & 255u);
-                });
-                __syncthreads();
-                pick_bin(want);
-                prefix |= sh_key << shift;
-                want -= sh_int;
-                above_total += sh_int;
-                if (byte == 0) kept = above_total + (int)hist[0];
-                __syncthreads();
-            }
-            floor_key = prefix;
-        }
+        const int n = sh.count;
+        if (n <= kList && finish_on_list(n, rest * __builtin_amdgcn_exp2f((ref - best) * c))) return;
     }
 
-    if (kept <= kCompact) {
-        // ---- short list: gather the ids, order by id, nucleus and draw on the list ----
-        if (!listed) {
-            if (tid == 0) sh_int = 0;
-            __syncthreads();
-            for_row(lg, vocab, [&](int i, float v) {
-                if (float_key(v / temp) >= floor_key) {
-                    const int slot = atomicAdd(&sh_int, 1);
-                    is[slot] = i;
-                }
-            });
-            __syncthreads();
-        }
-        const int n = sh_int;
-        // bitonic sort of the ids (padding sorts last): the list is in index order whatever order the atomics took
-        if (tid >= n) is[tid] = INT_MAX;
-        __syncthreads();
-        for (int size = 2; size <= kCompact; size <<= 1)
-            for (int stride = size >> 1; stride > 0; stride >>= 1) {
-                const int partner = tid ^ stride;
-                if (partner > tid) {
-                    const int a = is[tid], b = is[partner];
-                    const bool up = (tid & size) == 0;
-                    if ((a > b) == up) {
-                        is[tid] = b;
-                        is[partner] = a;
-                    }
-                }
-                __syncthreads();
-            }
-        float z = 0.f, e = 0.f;
-        if (tid < n) {
-            z = lg[is[tid]] / temp;
-            e = __expf(z - zmax);
-        }
-        const uint32_t my_key = tid < n ? float_key(z) : 0u;
-        float tot[1] = {e};
-        block_sums(tot, fs);
-        float total = tot[0];
-        if (p < 1.f) {
-            // the largest key t with mass(key >= t) >= p * total: bisection, the list stays in registers
-            const float need = p * total;
-            uint32_t lo = floor_key, hi = float_key(zmax);
-            while (lo < hi) {
-                const uint32_t mid = lo + (hi - lo + 1) / 2;
-                float m[1] = {(tid < n && my_key >= mid) ? e : 0.f};
-                block_sums(m, fs);
-                if (m[0] >= need) lo = mid;
-                else hi = mid - 1;
-            }
-            if (my_key < lo) e = 0.f;
-            float t2[1] = {e};
-            block_sums(t2, fs);
-            total = t2[0];
-        }
-        fs[tid] = e;
-        __syncthreads();
-        if (tid == 0) {  // the draw: first token in index order whose running sum exceeds u * total
-            const float target = u * total;
-            float running = 0.f;
-            int pick = -1, last = -1;
-            for (int j = 0; j < n; ++j) {
-                if (fs[j] > 0.f) {
-                    last = is[j];
-                    running += fs[j];
-                    if (running > target) {
-                        pick = last;
-                        break;
-                    }
-                }
-            }
-            out[row] = pick >= 0 ? pick : (last >= 0 ? last : best_i);
-        }
-        return;
-    }
-
-    // ---- long list: work on the whole row ----
-    auto masses = [&](const uint32_t (&from)[15], float (&m)[15]) {  // m[j] = sum of exp(z - zmax) over key >= from[j]
-#pragma unroll
-        for (int j = 0; j < 15; ++j) m[j] = 0.f;
-        for_row(lg, vocab, [&](int, float v) {
-            const float z = v / temp;
-            const uint32_t key = float_key(z);
-            const float e = __expf(z - zmax);
-#pragma unroll
-            for (int j = 0; j < 15; ++j) m[j] += key >= from[j] ? e : 0.f;
-        });
-        block_sums(m, fs);
-    };
-    uint32_t probe[15];
-    float m[15];
-#pragma unroll
-    for (int j = 0; j < 15; ++j) probe[j] = floor_key;
-    masses(probe, m);
-    float total = m[0];
-    if (p < 1.f) {
-        // the largest key t with mass(key >= t) >= p * total; the interval [lo, hi] shrinks 16-fold per pass
-        const float need = p * total;
-        uint32_t lo = floor_key, hi = float_key(zmax);
+    // ---- on the row ----
+    // The largest key t >= lo with weight(key(z) >= t) >= need: the interval up to the
+    // largest key is cut into up to 4096 bins per pass.  `skip` is a logit below which no key of the interval lies.
+    auto select_row = [&](uint32_t lo, float skip, uint64_t need, auto&& weight_of) -> uint32_t {
+        uint32_t hi = float_key(best / temp);
         while (lo < hi) {
-            const uint64_t span = (uint64_t)hi - lo;  // candidates lo < c_1 <= ... <= c_15 <= hi
-#pragma unroll
-            for (int j = 0; j < 15; ++j) probe[j] = lo + (uint32_t)((span * (j + 1) + 15) / 16);
-            masses(probe, m);
-            uint32_t new_lo = lo, new_hi = hi;
-            bool closed = false;
-#pragma unroll
-            for (int j = 0; j < 15; ++j) {
-                if (closed) continue;
-                if (m[j] >= need) new_lo = probe[j];
-                else {
-                    new_hi = probe[j] - 1;
-                    closed = true;
+            const uint32_t span = hi - lo;
+            const int bits = 32 - __clz((int)span);
+            const int shift = bits > kDigitBits ? bits - kDigitBits : 0;
+            for_row<2>(lg, vocab, [&](int, float v) {
+                if (v >= skip) {
+                    const uint32_t zk = float_key(v / temp);
+                    if (zk >= lo && zk <= hi) {
+                        const uint64_t w = weight_of(v);
+                        if (w) add_to_bin(sh, (zk - lo) >> shift, w);
+                    }
                 }
-            }
-            lo = new_lo;
-            hi = new_hi;
+            }, no_end);
+            uint64_t above;
+            const uint32_t d = find_bin(sh, need, above);
+            need = need > above ? need - above : 1;
+            lo += d << shift;
+            hi = min(hi, lo + ((1u << shift) - 1u));
+            const float z = key_float(lo) * temp;  // back to a logit, minus what the division may have rounded
+            const float s = z - fabsf(z) * 0x1p-20f - temp * 0x1p-148f;
+            if (s > skip) skip = s;
         }
-        floor_key = lo;
+        return lo;
+    };
+    uint32_t floor_key = 0;
+    clear_bins(sh);
+    if (by_k) floor_key = select_row(0u, -INFINITY, (uint64_t)k, [](float) -> uint64_t { return 1; });
+    if (by_p) {
+        float own = 0.f;
+        if (by_k) for_row<4>(lg, vocab, [&](int, float v) { own += float_key(v / temp) >= floor_key ? prob(v) : 0.f; }, no_end);
+        else for_row<4>(lg, vocab, [&](int, float v) { own += prob(v); }, no_end);
+        const float row_mass = block_sum(sh, own);
+        float skip = -INFINITY;
+        if (!by_k) {
+            // tokens below `skip` hold less than half of what the nucleus may leave out, even if all of the vocabulary
+            // lay there
+            const float edge = best + log2f((1.f - p) * row_mass / (2.f * (float)vocab)) / c;
+            if (edge == edge) skip = edge - fabsf(edge) * 0x1p-20f;
+            if (skip > -INFINITY) floor_key = float_key(skip / temp);
+        }
+        floor_key = select_row(floor_key, skip, nucleus_need(p, (uint64_t)((double)row_mass * (double)mass_one)), mass);
+    }
+    // the draw: masses of 4096 consecutive tokens each, then the tokens of the block it falls into
+    const bool all = !by_k && !by_p;
+    auto kept_mass = [&](float v) -> uint64_t { return all || float_key(v / temp) >= floor_key ? mass(v) : 0; };
+    uint64_t in_block = 0, own_total = 0;
+    for_row<2>(lg, vocab, [&](int, float v) { in_block += kept_mass(v); }, [&](int b) {
+        own_total += in_block;
+        in_block = wave_scan(in_block);
+        if (lane == 63) add_to_bin(sh, (uint32_t)(kBins - 1 - b), in_block);
+        in_block = 0;
+    });
+    const uint64_t total = block_sum(sh, own_total);
+    const uint64_t need = draw_need(u, total);
+    uint64_t above;
+    const int b = kBins - 1 - (int)find_bin(sh, need, above);
 #pragma unroll
-        for (int j = 0; j < 15; ++j) probe[j] = floor_key;
-        masses(probe, m);
-        total = m[0];
+    for (int e = 0; e < 4; ++e) {
+        const int o = 4 * tid + e, i = (b << 12) + o;
+        if (i < vocab) sh.bins[bin_place((uint32_t)(kBins - 1 - o))] = kept_mass(lg[i]);
     }
-
-    // the draw in index order: every thread owns a run of consecutive tokens
-    const float target = u * total;
-    const int run = (vocab + kSampleThreads - 1) / kSampleThreads;
-    const int i0 = min(tid * run, vocab), i1 = min(i0 + run, vocab);
-    float own = 0.f;
-    int last_kept = -1;
-    for (int i = i0; i < i1; ++i) {
-        const float z = lg[i] / temp;
-        if (float_key(z) >= floor_key) {
-            own += __expf(z - zmax);
-            last_kept = i;
-        }
-    }
-    fs[tid] = own;
-    is[tid] = last_kept;
-    __syncthreads();
-    if (tid == 0) {  // serial prefix over 1024 partial sums: fixed order, negligible next to the passes above
-        float before = 0.f;
-        int winner = -1, last = -1;
-        for (int t = 0; t < kSampleThreads; ++t) {
-            const float v = fs[t];
-            if (winner < 0 && before + v > target) {
-                winner = t;
-                sh_key = __float_as_uint(before);
-            }
-            before += v;
-            if (is[t] >= 0) last = is[t];
-        }
-        sh_int = winner;
-        if (winner < 0) out[row] = last < 0 ? best_i : last;  // u * total rounded up to the total: the last kept token
-    }
-    __syncthreads();
-    if (tid == sh_int) {
-        float running = __uint_as_float(sh_key);
-        int pick = last_kept;
-        for (int i = i0; i < i1; ++i) {
-            const float z = lg[i] / temp;
-            if (float_key(z) >= floor_key) {
-                running += __expf(z - zmax);
-                if (running > target) {
-                    pick = i;
-                    break;
-                }
-            }
-        }
-        out[row] = pick;
+    uint64_t unused;
+    const int o = kBins - 1 - (int)find_bin(sh, need > above ? need - above : 1, unused);
+    if (tid == 0) {
+        const int i = (b << 12) + o;
+        out[row] = total && i < vocab ? i : 0;
     }
 }
 
@@ -692,8 +773,11 @@ gllm_status gllm_op_sample(const float* logits, int64_t ld_logits, int32_t num_r
         ld_logits < vocab)
         return GLLM_E_INVALID;
     if (num_rows == 0) return GLLM_OK;
-    sample_kernel<<<num_rows, kSampleThreads, 0, (hipStream_t)stream>>>(logits, ld_logits, vocab, temperature, top_k, top_p, u,
-                                                                        out_ids);
+    // unit of the fixed-point masses: the sum of a whole row stays below 2^63
+    int log_vocab = 0;
+    while ((1 << log_vocab) < vocab) ++log_vocab;
+    sample_kernel<<<num_rows, kSampleThreads, 0, (hipStream_t)stream>>>(logits, ld_logits, vocab, ldexpf(1.f, 62 - log_vocab),
+                                                                        temperature, top_k, top_p, u, out_ids);
     return hipGetLastError() == hipSuccess ? GLLM_OK : GLLM_E_HIP;
 }
 

@@ -165,3 +165,30 @@ def test_sampler_with_many_equal_logits():
     p = rng.choice([1.0, 0.9, 0.3], size=M).astype(np.float32)
     u = rng.random(M).astype(np.float32)
     check_against_oracle(lg, temp, k, p, u, "ties")
+
+
+@pytest.mark.parametrize("V,sigma,k,p", [
+    (4096, 2.0, 1024, 0.9),       # the largest k the thread maxima can bound; one block of 4096 tokens exactly
+    (4097, 2.0, 1025, 1.0),       # one more of each: selection over the row
+    (8191, 0.01, 0, 0.5),         # nearly flat: every token is a candidate of the nucleus, more than the list holds
+    (8192, 6.0, 0, 0.95),         # peaked: the list holds the nucleus
+    (3, 1.0, 2, 1.0), (1, 1.0, 0, 0.5),
+    (40000, 1.0, 0, 1.0),         # no limit at all: the draw over the whole row
+    (40001, 1.5, 7000, 0.8),      # a large k with a nucleus inside, rows off the 16-byte grid
+    (16384, 4.0, 256, 0.9), (16388, 4.0, 257, 1.0),   # the list taken with the first bound: its smallest row, its largest k
+    (33000, 4.0, 50, 0.95), (66000, 4.0, 0, 0.9), (66000, 2.0, 0, 0.7),
+])
+def test_sampler_at_the_edges_of_its_paths(V, sigma, k, p):
+    print(f"sampler: V={V} k={k} p={p}", flush=True)
+    M = 12
+    lg = (torch.randn(M, V, generator=torch.Generator().manual_seed(V + k)) * sigma).to(torch.float32)
+    if V > 64:
+        lg[1, 5:V // 2] = -float("inf")                               # masked tokens are never drawn
+        lg[2, :] = 1.25                                               # every token tied
+        lg[4] = lg[4].sort().values                                   # the first bound is far too low, ...
+        lg[5] = lg[5].sort(descending=True).values                    # ... or as high as it can be
+        lg[6, V - 2] = lg[6].max() + 30.0                             # one token takes all
+    u = np.random.default_rng(V).random(M).astype(np.float32)
+    u[0], u[3] = 0.0, np.float32(1.0 - 2 ** -24)
+    full = lambda v, t: np.full(M, v, dtype=t)
+    check_against_oracle(lg, full(0.9, np.float32), full(k, np.int32), full(p, np.float32), u, f"edges V={V} k={k} p={p}", slack=1)
