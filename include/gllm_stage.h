@@ -197,21 +197,20 @@ const char* gllm_profile_class_name(int32_t i);
 gllm_status gllm_op_pack_weight(const void* w, int64_t ldw, int32_t n, int32_t k, void* out, void* stream);
 
 /* out[m][n] (op)= sum_k a[m][k] * w[n][k];  a: bf16 [m_rows][lda] with lda >= k, w: bf16, n rows, tiled as above with
- * k extent ldw (a multiple of 64, >= k: the product may use a leading part of the k range).
+ * k extent ldw (a multiple of 64, >= k, below 2^23: the product may use a leading part of the k range).
  * Requirements: k a multiple of 64 and n a multiple of 128 (the stage pads its operands);
  * a must be readable for round_up(m,256) rows.  mode: 0 store fp32 to out[m][ldc];
  * 1 add into fp32 out[m][ldc]; 2 SwiGLU: columns come in groups of 64 = 32 gate + 32 up
  * outputs, out is bf16 [m][ldc] with n/2 columns, out = silu(gate) * up.
- * tile: -1 lets the library choose the workgroup tile; 0 = 128x128, 1 = 256x128, 2 = 256x256
- * (4 wavefronts), 3 = 256x256 (8 wavefronts), 4 = 256x256 tiles for whole rounds of the compute units plus
- * 256x128 tiles for the remainder (only for shapes with such a remainder), 5 = 256x192 (n a multiple of 192,
- * not for SwiGLU), 6 = 128x128 with four LDS stages instead of two (for few rows, where the weights stream
- * from HBM), 7 = 64x128 with three LDS stages (picked up to 64 rows: two workgroups per compute unit keep more
- * of the weight stream in flight), 8 = 256x256 tiles for the whole bands of 256 rows plus 64x256 or 128x256 tiles
- * for a last band of at most 128 rows (only for m > 256 with 0 < m mod 256 <= 128 and n a multiple of 256), 9 = 288x192
- * (six wavefronts; only for 256 < m <= 288, n a multiple of 192, not for SwiGLU: all rows in one band, so the weights
- * are read once), 10 / 11 / 12 = tiles 3 / 4 / 8 with a third LDS stage for the weight tile (all 160 KiB of LDS: the
- * weight loads get two k-steps to land; picked for long k and for few rows); a forced tile that does not fit the
+ * tile: -1 lets the library choose the workgroup tile; 0 = 128x128 (two workgroups per compute unit), 1 = 256x128
+ * (192x128 where bands of 192 rows cover m with less padding), 2, 3 and 10 = 256x256, 4 and 11 = 256x256 tiles for whole
+ * rounds of the compute units plus 256x128 tiles for the remainder (only for shapes with such a remainder), 5 = 256x192
+ * (n a multiple of 192, not for SwiGLU), 6 = 128x128 with four LDS stages (for few rows, where the weights stream
+ * from HBM), 7 = 64x128 (picked up to 64 rows: two workgroups per compute unit keep more of the weight stream in
+ * flight), 8 and 12 = 256x256 tiles for the whole bands of 256 rows plus 64x256 or 128x256 tiles for a last band of at
+ * most 128 rows, or two bands of 192x256 tiles for all rows up to 384 (only for m > 256 with 0 < m mod 256 <= 128 and
+ * n a multiple of 256), 9 = 288x192 (six wavefronts; only for 256 < m <= 288, n a multiple of 192, not for SwiGLU: all
+ * rows in one band, so the weights are read once); a forced tile that does not fit the
  * shape gives GLLM_E_UNSUPPORTED. */
 gllm_status gllm_op_gemm_bf16(const void* a, int64_t lda, const void* w, int64_t ldw, void* out, int64_t ldc,
                               int32_t m, int32_t n, int32_t k, int32_t mode, int32_t tile, void* stream);

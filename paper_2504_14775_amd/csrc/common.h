@@ -43,22 +43,24 @@ enum GemmMode { GEMM_STORE_F32 = 0, GEMM_ADD_F32 = 1, GEMM_SWIGLU_BF16 = 2 };
 
 // out (op)= a[m x k] * w[n x k]^T, see gllm_op_gemm_bf16 in the public header; w is tiled (w_tiled_index) with ldw its k
 // extent (a multiple of 64, >= k).
-// tile: -1 picks a tile shape from m and n; 0..3 force one (128x128, 256x128, 256x256, 256x256 with 8 waves);
-// 4 forces the mixed 256x256 + 256x128 launch (only where gemm_mixed_rem_cols(m, n) > 0); 5 = 256x192 (not SwiGLU);
-// 6 = 128x128 with four LDS stages; 7 = 64x128 with three LDS stages (up to 64 rows per tile row: weight streaming);
-// 8 = 256x256 tiles for the whole bands of 256 rows plus 64x256 or 128x256 tiles for a last band of at most 128 rows
-// (only where gemm_rowmix_rem_rows(m, n) > 0); 9 = 288x192; 10, 11, 12 = tiles 3, 4, 8 with a third LDS stage for the W tile.
+// tile: -1 picks a tile shape from m, n and k; 0 = 128x128 (two workgroups share a compute unit); 1 = 256x128, or 192x128
+// where bands of 192 rows cover m with less padding; 2, 3 and 10 = 256x256; 4 and 11 = the mixed 256x256 + 256x128 launch
+// (only where gemm_mixed_rem_cols(m, n) > 0); 5 = 256x192 (not SwiGLU); 6 = 128x128 with four LDS stages; 7 = 64x128
+// (up to 64 rows: weight streaming); 8 and 12 = 256x256 tiles for the whole bands of 256 rows plus 64x256 or 128x256
+// tiles for a last band of at most 128 rows, two bands of 192x256 tiles up to 384 rows (only where
+// gemm_rowmix_rem_rows(m, n) > 0); 9 = 288x192.
 // splits > 1 (store mode only): split s covers k range [s*k/splits, (s+1)*k/splits) and writes its partial
 // product to out + s*split_stride floats; the consumer sums the planes in order.
 hipError_t launch_gemm_bf16(const bf16_t* a, int64_t lda, const bf16_t* w, int64_t ldw, void* out, int64_t ldc,
                             int m, int n, int k, int mode, int tile, int splits, int64_t split_stride,
                             hipStream_t stream);
+bool gemm_low_bands(int m);
 int gemm_mixed_rem_cols(int m, int n);
 int gemm_rowmix_rem_rows(int m, int n);
 // Tile id and split-K factor the cost model prefers (splits stays 1 unless mode is GEMM_STORE_F32); row_mixed says
-// whether it may pick tile 8.
+// whether it may pick tile 8, read_planes that the caller reads the result planes back (they then count twice).
 struct GemmPlan { int tile; int splits; };
-GemmPlan gemm_plan(int m, int n, int k, int mode, int max_splits, bool row_mixed = true);
+GemmPlan gemm_plan(int m, int n, int k, int mode, int max_splits, bool row_mixed = true, bool read_planes = false);
 
 // Residual stream entry: x = float(in_bf16), h = bf16(rmsnorm(x) * gamma).
 hipError_t launch_rmsnorm_from_bf16(const bf16_t* in, float* x, const bf16_t* gamma, bf16_t* h, int64_t ldh,

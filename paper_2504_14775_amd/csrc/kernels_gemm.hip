@@ -3,16 +3,23 @@
 // Both operands are contiguous along k, which is the order the MFMA operand registers want
 // (each lane feeds 8 consecutive k of one row), so tiles go global -> LDS -> registers without
 // any transposition.  A workgroup of WGM x WGN wavefronts owns a BM x BN output tile and walks k
-// in steps of 64 through two LDS stages.  Tiles are brought in with global_load_lds (16 bytes per
-// lane straight into LDS, no staging registers): the loads of step i+1 are issued right after the
-// barrier that ends step i-1 and complete under the MFMAs of step i.
+// in steps of 64 through two to four LDS stages, filled by buffer loads that write 16 bytes per lane straight
+// into LDS (no staging registers, no address arithmetic: the k position is the scalar offset).
+//
+// What bounds it: many rows, the 1400 W power limit (a bare MFMA loop on random operands reaches 1.6-1.8 PFLOP/s); few
+// rows, the stream of the weights (5.5-6 TB/s) and the ~5 us a launch costs before and after it; in between both.  Under
+// the power limit the clock follows the busy share of the matrix cores, so cycles in the k-loop count in full.  Four
+// waves with a wave tile of 128x128 read each operand from LDS half as often as eight of 128x64, and with the order of
+// MFMAs, LDS reads and global loads written out (see step) the loop has nothing in it that is not hidden under MFMAs:
+// 4096x8192x8192 437 -> 386 us (1257 -> 1426 TFLOP/s), gate/up at 2048 rows 406 -> 372, at 197 rows 74 -> 56, at 322
+// rows 100 -> 77, the down projection at 2048 rows 200 -> 175, at 197 rows 42 -> 35, at 322 rows 71 -> 44 us.
 //
 // LDS stage layout: rows of 64 k-values (128 bytes = eight 16-byte groups), A rows first, then W
 // rows.  Two consecutive rows form a 256-byte line of 16 group positions (the width of the 64 LDS
 // banks); group c of row r sits at position ((r & 1) * 8 + c) ^ ((r >> 1) & 7) of line r >> 1.  The
 // 16-byte operand reads of the MFMA loop take, per 16 lanes, one group index of 16 consecutive rows:
 // with this placement those 16 reads fall into 16 different bank groups (measured: the plain
-// c ^ (r & 7) placement costs a 2-way bank conflict on every read).  A global_load_lds instruction
+// c ^ (r & 7) placement costs a 2-way bank conflict on every read).  A load instruction
 // fills 1 KiB = 4 lines: lane l owns position l % 16 of line l / 16 and fetches the global group that
 // belongs there; the 16 lanes of a line still cover the full 128 bytes of both of its rows.
 //
@@ -22,19 +29,19 @@
 // the tiles an XCD works on at one time share a few A row-panels and W row-panels in its L2.
 #include "common.h"
 
+#include <algorithm>
 #include <cmath>
 
 namespace {
 
 constexpr int BK = 64;
-constexpr int kAuxNonTemporal = 2;  // cache-policy operand of global_load_lds: the nt bit
+constexpr int kMaxTileM = 288;            // tallest tile
 
 // silu(z) = z / (1 + e^-z) with the hardware exp2 and reciprocal (1 ulp each; the result is rounded to bf16)
 __device__ __forceinline__ float silu(float z) {
     return z * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * z));
 }
 
-typedef const __attribute__((address_space(1))) void* gptr_t;
 typedef __attribute__((address_space(3))) void* lptr_t;
 
 // Hardware hands consecutive workgroup ids to the 8 XCDs in turn; this turns id `wg` of `count` into a work number such
@@ -49,8 +56,8 @@ __device__ __forceinline__ int xcd_contiguous(int wg, int count) {
 // The work of one workgroup: output tile number `tile_idx` (in XCD-contiguous numbering, see above) of a tiles_m x
 // tiles_n grid of BM x BN tiles whose first column is n_base and whose first row is m_base, k-share `split` of
 // `num_splits` (each share has its own output plane).
-// NS LDS stages of 64 k-values for the A tile and NSW (NS or NS + 1) for the W tile.  The weights stream from HBM,
-// the activations are re-read from the caches by every tile column, so where LDS cannot hold one more stage of both
+// NS LDS stages of 64 k-values for the A tile and NSW (NS or NS + 1, at least 3) for the W tile.  The weights stream from
+// HBM, the activations are re-read from the caches by every tile column, so where LDS cannot hold one more stage of both
 // (256x256: two of each fill 128 of the 160 KiB) the W tile alone gets the third: its loads then have two k-steps
 // to land instead of one.
 template <int BM, int BN, int WGM, int WGN, int MODE, int NS = 2, int NSW = NS, bool W_ONCE = false>
@@ -58,6 +65,9 @@ __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ A, int64_t 
                                           int64_t ldw, void* __restrict__ out, int64_t ldc, int M, int K,
                                           int tiles_m, int tiles_n, int n_base, int tile_idx, int split, int num_splits,
                                           int64_t split_stride, int m_base = 0) {
+#if defined(__HIP_DEVICE_COMPILE__)  // (the buffer resource type exists in device code only)
+    constexpr int kAuxNonTemporal = 2;        // cache-policy operand of a buffer load: the nt bit
+    constexpr int kBufferFlags = 0x00027000;  // raw buffer of 32-bit words, bounds checked in bytes
     constexpr int NW = WGM * WGN;
     constexpr int WTM = BM / WGM, WTN = BN / WGN;  // wave tile
     constexpr int TM = WTM / 32, TN = WTN / 32;    // 32x32 blocks per wave
@@ -94,34 +104,37 @@ __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ A, int64_t 
     const int lline = lane >> 4;
     const int lq = (lane & 15) ^ ((4 * (wave & 1) + lline) & 7);
     const int lrow = 2 * lline + (lq >> 3), lgrp = lq & 7;
-    const uint32_t voff_a = (uint32_t)(lrow * lda + lgrp * 8) * 2u;
-    // W is tiled (see w_tiled_index): a group's 8 rows x 64 k values are 1 KiB in a row, a 64-row block 8 KiB, so a load
-    // instruction reads one contiguous KiB and a k-step of the tile whole 8 KiB pieces
-    const uint32_t voff_w = (uint32_t)(lrow * 64 + lgrp * 8) * 2u;
+    // Buffer addressing: the k position is the scalar offset of a load, everything else one precomputed register per
+    // group, so that a load costs no address arithmetic.  Rows past M lie outside the buffer: they read as zero.
     const int64_t w_blocks_k = ldw >> 6;
-    const char* a_tile = reinterpret_cast<const char*>(A + (int64_t)m0 * lda);
-    const char* w_tile = reinterpret_cast<const char*>(W) + (int64_t)(n0 >> 6) * w_blocks_k * kWBlockBytes;
-    // tile kt of A into A stage `stage` / of W into W stage `stage` (wave w fills groups w, w + NW, ...)
-    auto issue_a = [&](int kt, int stage) {
-        unsigned char* sbase = smem + stage * A_STAGE;
-        const int64_t kbyte = (int64_t)(kt + kt_base) * (BK * 2);
+    const uint32_t a_rows = (uint32_t)min(BM, M - m0);
+    const auto a_buf = __builtin_amdgcn_make_buffer_rsrc((void*)(A + (int64_t)m0 * lda), 0, (int)(uint32_t)(a_rows * lda * 2), kBufferFlags);
+    const auto w_buf = __builtin_amdgcn_make_buffer_rsrc((void*)((const char*)W + (int64_t)(n0 >> 6) * w_blocks_k * kWBlockBytes), 0,
+                                                         (int)(uint32_t)((BN >> 6) * w_blocks_k * kWBlockBytes), kBufferFlags);
+    uint32_t off_a[GA], off_w[GW];
 #pragma unroll
-        for (int i = 0; i < GA; ++i) {
-            const int g = wave + i * NW;  // wave-uniform
-            __builtin_amdgcn_global_load_lds((gptr_t)(a_tile + (int64_t)(g * 8) * lda * 2 + kbyte + voff_a), (lptr_t)(sbase + g * 1024), 16, 0, 0);
-        }
-    };
-    auto issue_w = [&](int kt, int stage) {
-        unsigned char* sbase = smem + W_BASE + stage * W_STAGE;
-        const char* w_kt = w_tile + (int64_t)(kt + kt_base) * kWBlockBytes + voff_w;
-        // group g = rows 8g .. 8g+7 of the tile: row block g / 8, KiB g % 8 of that block.  With one band of rows
-        // (W_ONCE) every byte of W is read by one workgroup, once: those loads carry the non-temporal hint, which
-        // keeps the one-pass stream from displacing the A panel in L2 (5-10 % on the weight-streaming products).
+    for (int i = 0; i < GA; ++i) {
+        const uint32_t r = (wave + i * NW) * 8 + lrow;
+        off_a[i] = r < a_rows ? (uint32_t)(r * lda + lgrp * 8) * 2u : 0xFFFFFFF0u;
+    }
+    // W is tiled (see w_tiled_index): a group's 8 rows x 64 k values are 1 KiB in a row, a 64-row block 8 KiB, so a load
+    // instruction reads one contiguous KiB and a k-step of the tile whole 8 KiB pieces; group g = KiB g % 8 of row block g / 8
 #pragma unroll
-        for (int i = 0; i < GW; ++i) {
-            const int g = wave + i * NW;
-            __builtin_amdgcn_global_load_lds((gptr_t)(w_kt + (int64_t)(g >> 3) * w_blocks_k * kWBlockBytes + (g & 7) * 1024), (lptr_t)(sbase + g * 1024), 16, 0, W_ONCE ? kAuxNonTemporal : 0);
-        }
+    for (int i = 0; i < GW; ++i) {
+        const int g = wave + i * NW;
+        off_w[i] = (uint32_t)(g >> 3) * (uint32_t)(w_blocks_k * kWBlockBytes) + (g & 7) * 1024u + (lrow * 64 + lgrp * 8) * 2u;
+    }
+    // Load i of a k-step (A: i < GA, W: the rest) into the stages at byte sa / sw of LDS.  Tiles past the last one re-read
+    // the last into a stage nobody reads again.  With one band of rows (W_ONCE) every byte of W is read by one workgroup,
+    // once: those loads carry the non-temporal hint, which keeps the one-pass stream from displacing the A panel in L2
+    // (5-10 % on the weight-streaming products).
+    auto issue = [&](int i, int kt_a, int sa, int kt_w, int sw) {
+        if (i < GA)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(a_buf, (lptr_t)(smem + sa + (wave + i * NW) * 1024), 16, off_a[i],
+                                                     (min(kt_a, KT - 1) + kt_base) * (BK * 2), 0, 0);
+        else
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(w_buf, (lptr_t)(smem + sw + (wave + (i - GA) * NW) * 1024), 16, off_w[i - GA],
+                                                     (min(kt_w, KT - 1) + kt_base) * kWBlockBytes, 0, W_ONCE ? kAuxNonTemporal : 0);
     };
 
     f32x16 acc[TM][TN];
@@ -132,103 +145,90 @@ __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ A, int64_t 
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
 
-    // operand reads: lane supplies row (lane % 32), k-group (lane / 32) of each 16-wide k step
-    const int frow = lane & 31, fgrp = lane >> 5;
-    bf16x8 fa[2][TM], fw[2][TN];
-    auto mfmas = [&](int buf) {
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-            for (int j = 0; j < TN; ++j)
-                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[buf][i], fw[buf][j], acc[i][j], 0, 0, 0);
-    };
-    constexpr int kReads = TM + TN, kMfma = TM * TN;
-    constexpr int kPaired = kReads < kMfma ? kReads : kMfma;
-
     {
+        // operand reads: lane supplies row (lane % 32), k-group (lane / 32) of each 16-wide k step
+        constexpr int KK = BK / 16;
+        constexpr int kReads = TM + TN, kMfma = TM * TN;
+        constexpr int kPart = (GPW + KK - 1) / KK;  // global loads issued per k-step
+        const int frow = lane & 31, fgrp = lane >> 5;
         const int fsw = (frow >> 1) & 7, fpar = (frow & 1) * 8;
-        const int a_off = (wm * WTM + (frow & ~1)) * (BK * 2);
-        const int w_off = W_BASE + (wn * WTN + (frow & ~1)) * (BK * 2);
-        auto load_frags = [&](int kt, int kk, int buf) {  // fragments of k-step kk of tile kt
-            const unsigned char* sa = smem + (kt % NS) * A_STAGE + a_off;
-            const unsigned char* sw = smem + (kt % NSW) * W_STAGE + w_off;
-            const int g = ((fpar + kk * 2 + fgrp) ^ fsw) * 16;
+        const int a_off = (wm * WTM + (frow & ~1)) * (BK * 2), w_off = (wn * WTN + (frow & ~1)) * (BK * 2);
+        int fg[KK];
 #pragma unroll
-            for (int i = 0; i < TM; ++i) fa[buf][i] = *reinterpret_cast<const bf16x8*>(sa + i * 32 * (BK * 2) + g);
-#pragma unroll
-            for (int j = 0; j < TN; ++j) fw[buf][j] = *reinterpret_cast<const bf16x8*>(sw + j * 32 * (BK * 2) + g);
+        for (int kk = 0; kk < KK; ++kk) fg[kk] = ((fpar + kk * 2 + fgrp) ^ fsw) * 16;
+        bf16x8 fa[2][TM], fw[2][TN];
+        // operand read r of k-step kk of the tile in the stages at sa, sw, in the order the MFMAs want them
+        auto read_frag = [&](int r, int kk, int sa, int sw, int buf) {
+            if (r == 0) fa[buf][0] = *reinterpret_cast<const bf16x8*>(smem + sa + a_off + fg[kk]);
+            else if (r <= TN) fw[buf][r - 1] = *reinterpret_cast<const bf16x8*>(smem + sw + w_off + fg[kk] + (r - 1) * 32 * (BK * 2));
+            else fa[buf][r - TN] = *reinterpret_cast<const bf16x8*>(smem + sa + a_off + fg[kk] + (r - TN) * 32 * (BK * 2));
         };
-        // scheduling hint for one "fetch fragments of the next k-step, multiply the current one" step:
-        // spread the LDS reads between the MFMAs so that their latency is covered
-        auto interleave = [&]() {
-            // reads first, one per MFMA, so that the MFMAs left over cover the latency of the last read
-#pragma unroll
-            for (int r = 0; r < kPaired; ++r) {
-                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // one MFMA (first, so that the wait for the
-                __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);  // previous reads precedes every new read)
-            }
-            __builtin_amdgcn_sched_group_barrier(0x100, kReads - kPaired, 0);
-            __builtin_amdgcn_sched_group_barrier(0x008, kMfma - kPaired, 0);
-        };
-        // the step after the barrier also issues the next tile's global loads: one per MFMA, so that the
-        // matrix cores keep running while the loads are handed to the memory pipeline
-        constexpr int kLoadsPerMfma = (GPW + kMfma - 1) / kMfma;
-        auto interleave_with_loads = [&]() {
+        // One k-step: multiply the fragments in `buf`, fetch those of k-step kk_next of the tile in the stages at ra, rw
+        // into the other buffer, issue part q of the global loads.  The order is written out and held by scheduling
+        // barriers: one operand read behind each of the first MFMAs, so that those left over cover the latency of the last
+        // read, the global loads spread over all of them.  (Given groups to interleave instead, the compiler packs reads
+        // into bursts with full waits between them.)
+        auto step = [&](int buf, bool fetch, int kk_next, int ra, int rw, int q, int kt_a, int sa, int kt_w, int sw) {
+            const int loads = q < 0 ? 0 : max(0, min(kPart, GPW - q * kPart));
 #pragma unroll
             for (int r = 0; r < kMfma; ++r) {
-                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                if (r * kLoadsPerMfma < GPW) __builtin_amdgcn_sched_group_barrier(0x020, kLoadsPerMfma, 0);
-                if (r < kReads) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+                acc[r / TN][r % TN] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[buf][r / TN], fw[buf][r % TN], acc[r / TN][r % TN], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int f = 0; f < kReads; ++f)
+                    if (fetch && f * kMfma / (kReads < kMfma ? kMfma : kReads) == r) read_frag(f, kk_next, ra, rw, buf ^ 1);
+#pragma unroll
+                for (int l = 0; l < kPart; ++l)
+                    if (l < loads && l * kMfma / loads == r) issue(q * kPart + l, kt_a, sa, kt_w, sw);
+                __builtin_amdgcn_sched_barrier(0);
             }
         };
 
         // Software pipeline.  Global: tiles kt+1 .. kt+NS-1 of A (.. kt+NSW-1 of W) are in flight while tile kt is
         // multiplied.  LDS -> registers: the fragments of k-step kk+1 are fetched while k-step kk is multiplied, also
         // across the tile boundary: the barrier sits before the last k-step of a tile, after which the next tile's
-        // first fragments are fetched under the MFMAs of that last k-step.  Loads past the last tile re-read it into
-        // a stage nobody reads again, so every iteration issues the same number of loads and the wait counts are
-        // compile-time constants.  Loads complete in issue order: each step issues its A tile before its W tile, so
-        // "all but the newest ..." leaves exactly the tiles that may still be in flight.
-        constexpr int KK = BK / 16;
+        // first fragments are fetched under the MFMAs of that last k-step.  The loads into the stages vacated at that
+        // barrier are issued in four parts, one per k-step from there on (part 0 behind the barrier, part q + 1 in
+        // k-step q of the next tile), A before W: a load instruction keeps the address unit busy for 16 cycles, and all
+        // of them at once stall every wave behind the barrier for longer than the MFMAs of one k-step last.
+        // Every iteration issues the same number of loads (see issue), so the wait counts are compile-time constants.
+        // Loads complete in issue order, so "all but the newest ..." leaves exactly the tiles that may be in flight.
         constexpr int kInFlight = (NS - 2) * GPW + (NSW - NS) * GW;  // loads that may be outstanding at a step's barrier
+        constexpr int kFirstPart = kPart < GPW ? kPart : GPW;
+        static_assert(NSW >= 3, "the loads of a tile are spread over a whole k-step of 64: its W tile needs one more to land");
         static_assert(kInFlight + GPW < 64, "outstanding loads must fit the vmcnt field");
 #pragma unroll
-        for (int i = 0; i < NS; ++i) {
-            issue_a(min(i, KT - 1), i);
-            issue_w(min(i, KT - 1), i);
+        for (int t = 0; t < NSW - 1; ++t) {
+#pragma unroll
+            for (int i = t < NS - 1 ? 0 : GA; i < GPW; ++i) issue(i, t, t * A_STAGE, t, W_BASE + t * W_STAGE);
         }
-        if (NSW > NS) issue_w(min(NS, KT - 1), NS);
-        asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NS - 1) * GPW + (NSW - NS) * GW) : "memory");
+        int fill_a = (NS - 1) * A_STAGE, fill_w = W_BASE + (NSW - 1) * W_STAGE;  // stages being filled
+        int read_a = 0, read_w = W_BASE;                                         // stages being multiplied
+#pragma unroll
+        for (int l = 0; l < kFirstPart; ++l) issue(l, NS - 1, fill_a, NSW - 1, fill_w);
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NS - 2) * GA + (NSW - 2) * GW + kFirstPart) : "memory");
         __builtin_amdgcn_s_barrier();
-        load_frags(0, 0, 0);
+#pragma unroll
+        for (int f = 0; f < kReads; ++f) read_frag(f, 0, read_a, read_w, 0);
+        __builtin_amdgcn_sched_barrier(0);
         for (int kt = 0; kt < KT - 1; ++kt) {
 #pragma unroll
-            for (int kk = 0; kk < KK - 1; ++kk) {
-                load_frags(kt, kk + 1, (kk + 1) & 1);
-                mfmas(kk & 1);
-                interleave();
-            }
+            for (int kk = 0; kk < KK - 1; ++kk)
+                step(kk & 1, true, kk + 1, read_a, read_w, kk + 1, kt - 1 + NS, fill_a, kt - 1 + NSW, fill_w);
             // tile kt+1 must have landed (later tiles may still be in flight) and this wave's last fragments of
             // tile kt must be in registers before anybody overwrites its stages
             asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(kInFlight) : "memory");
             __builtin_amdgcn_s_barrier();
-            // branch-free tail (one scheduling region): the loads into the stages just vacated, the first fragments
-            // of tile kt+1, the last MFMAs of tile kt
-            issue_a(min(kt + NS, KT - 1), kt % NS);
-            issue_w(min(kt + NSW, KT - 1), kt % NSW);
-            load_frags(kt + 1, 0, KK & 1);
-            mfmas((KK - 1) & 1);
-            interleave_with_loads();
+            __builtin_amdgcn_sched_barrier(0);
+            // the stages just vacated are filled next; the first fragments of tile kt+1 are fetched
+            fill_a = read_a;
+            fill_w = read_w;
+            read_a = read_a == (NS - 1) * A_STAGE ? 0 : read_a + A_STAGE;
+            read_w = read_w == W_BASE + (NSW - 1) * W_STAGE ? W_BASE : read_w + W_STAGE;
+            step((KK - 1) & 1, true, 0, read_a, read_w, 0, kt + NS, fill_a, kt + NSW, fill_w);
         }
-        {
 #pragma unroll
-            for (int kk = 0; kk < KK - 1; ++kk) {
-                load_frags(KT - 1, kk + 1, (kk + 1) & 1);
-                mfmas(kk & 1);
-                interleave();
-            }
-            mfmas((KK - 1) & 1);
-        }
+        for (int kk = 0; kk < KK; ++kk) step(kk & 1, kk < KK - 1, kk + 1 < KK ? kk + 1 : 0, read_a, read_w, -1, 0, 0, 0, 0);
     }
 
     // ---- epilogue, staged through LDS so that every global access is a 16-byte piece of a long row
@@ -288,6 +288,7 @@ __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ A, int64_t 
             }
         }
     }
+#endif
 }
 
 template <int BM, int BN, int WGM, int WGN, int MODE, int NS = 2, int NSW = NS, bool W_ONCE = false>
@@ -308,37 +309,37 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_kernel(const bf16_t*
 
 // Two tile shapes in one launch: the first big_tiles workgroups cover columns [0, n_split) with 256x256
 // tiles (whole rounds of the 256 compute units), the rest cover [n_split, N) with 256x128 tiles, so that
-// the last, partial round still gives every compute unit a (half-size) tile.  8 waves either way.
-template <int MODE, int NSW>
-__global__ __launch_bounds__(512) void gemm_bf16_mixed_kernel(const bf16_t* __restrict__ A, int64_t lda,
+// the last, partial round still gives every compute unit a (half-size) tile.
+template <int MODE>
+__global__ __launch_bounds__(256) void gemm_bf16_mixed_kernel(const bf16_t* __restrict__ A, int64_t lda,
                                                                const bf16_t* __restrict__ W, int64_t ldw,
                                                                void* __restrict__ out, int64_t ldc, int M, int K,
                                                                int tiles_m, int big_cols, int small_cols) {
     const int big_tiles = tiles_m * big_cols;
     if ((int)blockIdx.x < big_tiles)
-        gemm_tile<256, 256, 2, 4, MODE, 2, NSW>(A, lda, W, ldw, out, ldc, M, K, tiles_m, big_cols, 0,
-                                                xcd_contiguous(blockIdx.x, big_tiles), 0, 1, 0);
+        gemm_tile<256, 256, 2, 2, MODE, 2, 3>(A, lda, W, ldw, out, ldc, M, K, tiles_m, big_cols, 0,
+                                              xcd_contiguous(blockIdx.x, big_tiles), 0, 1, 0);
     else
-        gemm_tile<256, 128, 4, 2, MODE, 2, NSW>(A, lda, W, ldw, out, ldc, M, K, tiles_m, small_cols, big_cols * 256,
-                                                xcd_contiguous(blockIdx.x - big_tiles, tiles_m * small_cols), 0, 1, 0);
+        gemm_tile<256, 128, 2, 2, MODE, 3>(A, lda, W, ldw, out, ldc, M, K, tiles_m, small_cols, big_cols * 256,
+                                           xcd_contiguous(blockIdx.x - big_tiles, tiles_m * small_cols), 0, 1, 0);
 }
 
 // Two tile heights in one launch: the first big_tiles workgroups cover the whole bands of 256 rows with 256x256
 // tiles, the rest cover the last band -- at most BMR rows are left -- with BMR x 256 tiles, so a row count just above a
-// multiple of 256 does not pay for a whole band of padding.  8 waves either way; blockIdx.y is the split-K share.
-template <int MODE, int BMR, int NSW>
-__global__ __launch_bounds__(512) void gemm_bf16_rowmix_kernel(const bf16_t* __restrict__ A, int64_t lda,
+// multiple of 256 does not pay for a whole band of padding.  blockIdx.y is the split-K share.
+template <int MODE, int BMR>
+__global__ __launch_bounds__(256) void gemm_bf16_rowmix_kernel(const bf16_t* __restrict__ A, int64_t lda,
                                                                 const bf16_t* __restrict__ W, int64_t ldw,
                                                                 void* __restrict__ out, int64_t ldc, int M, int K,
                                                                 int bands, int tiles_n, int64_t split_stride) {
     const int big_tiles = bands * tiles_n;
     if ((int)blockIdx.x < big_tiles)
-        gemm_tile<256, 256, 2, 4, MODE, 2, NSW>(A, lda, W, ldw, out, ldc, M, K, bands, tiles_n, 0,
-                                                xcd_contiguous(blockIdx.x, big_tiles), blockIdx.y, gridDim.y, split_stride);
+        gemm_tile<256, 256, 2, 2, MODE, 2, 3>(A, lda, W, ldw, out, ldc, M, K, bands, tiles_n, 0,
+                                              xcd_contiguous(blockIdx.x, big_tiles), blockIdx.y, gridDim.y, split_stride);
     else
-        gemm_tile<BMR, 256, 2, 4, MODE, 2, NSW>(A, lda, W, ldw, out, ldc, M, K, 1, tiles_n, 0,
-                                                xcd_contiguous(blockIdx.x - big_tiles, tiles_n), blockIdx.y, gridDim.y,
-                                                split_stride, bands * 256);
+        gemm_tile<BMR, 256, 2, 2, MODE, 3>(A, lda, W, ldw, out, ldc, M, K, 1, tiles_n, 0,
+                                           xcd_contiguous(blockIdx.x - big_tiles, tiles_n), blockIdx.y, gridDim.y,
+                                           split_stride, bands * 256);
 }
 
 template <int BM, int BN, int WGM, int WGN, int MODE, int NS, int NSW, bool W_ONCE>
@@ -373,72 +374,71 @@ hipError_t launch_mode(const bf16_t* a, int64_t lda, const bf16_t* w, int64_t ld
                        int n, int k, int tile, int splits, int64_t split_stride, hipStream_t stream) {
 #define GLLM_TILE_ARGS a, lda, w, ldw, out, ldc, m, n, k, splits, split_stride, stream
     switch (tile) {
-        case 0: return launch_tile<128, 128, 2, 2, MODE>(GLLM_TILE_ARGS);
-        case 1: return launch_tile<256, 128, 2, 2, MODE>(GLLM_TILE_ARGS);
-        case 2: return launch_tile<256, 256, 2, 2, MODE>(GLLM_TILE_ARGS);
-        case 3: return launch_tile<256, 256, 2, 4, MODE>(GLLM_TILE_ARGS);
-        case 10: return launch_tile<256, 256, 2, 4, MODE, 2, 3>(GLLM_TILE_ARGS);  // third LDS stage for the W tile: all 160 KiB
+        case 0: return launch_tile<128, 128, 2, 2, MODE, 2, 3>(GLLM_TILE_ARGS);  // 80 KiB of LDS: two workgroups per compute unit
+        case 1:
+            if (gemm_low_bands(m)) return launch_tile<192, 128, 2, 2, MODE, 4>(GLLM_TILE_ARGS);
+            return launch_tile<256, 128, 2, 2, MODE, 3>(GLLM_TILE_ARGS);
+        case 2: case 3: case 10: return launch_tile<256, 256, 2, 2, MODE, 2, 3>(GLLM_TILE_ARGS);
         case 6: return launch_tile<128, 128, 2, 2, MODE, 4>(GLLM_TILE_ARGS);
         case 7: return launch_tile<64, 128, 2, 2, MODE, 3>(GLLM_TILE_ARGS);
-        case 9:  // one 288-row tile covers all rows; it reads 288 of them, which the row padding (to 256) covers above 256
+        case 8: case 12:  // 257..384 rows: see gemm_rowmix_rem_rows
+            if (m <= 256 || m > 384) return hipErrorInvalidValue;
+            return launch_tile<192, 256, 2, 2, MODE, 2, 3>(GLLM_TILE_ARGS);
+        case 9:  // one 288-row tile covers all rows
             if constexpr (MODE != GEMM_SWIGLU_BF16) {
                 if (m <= 256 || m > 288) return hipErrorInvalidValue;
-                return launch_tile<288, 192, 3, 2, MODE>(GLLM_TILE_ARGS);
+                return launch_tile<288, 192, 3, 2, MODE, 2, 3>(GLLM_TILE_ARGS);
             } else return hipErrorInvalidValue;
         case 5:
-            if constexpr (MODE != GEMM_SWIGLU_BF16) return launch_tile<256, 192, 4, 2, MODE>(GLLM_TILE_ARGS);
+            if constexpr (MODE != GEMM_SWIGLU_BF16) return launch_tile<256, 192, 2, 2, MODE, 2, 3>(GLLM_TILE_ARGS);
             else return hipErrorInvalidValue;
         default: return hipErrorInvalidValue;
     }
 #undef GLLM_TILE_ARGS
 }
 
+constexpr size_t kWideTileLds = (2 * 256 + 3 * 256) * BK * sizeof(bf16_t);  // 256x256 tile: all 160 KiB
+
 // Mixed launch (see gemm_bf16_mixed_kernel); rem_cols 256-wide tile columns are turned into 2*rem_cols
 // 128-wide ones.
-template <int MODE, int NSW>
+template <int MODE>
 hipError_t launch_mixed(const bf16_t* a, int64_t lda, const bf16_t* w, int64_t ldw, void* out, int64_t ldc, int m,
                         int n, int k, int rem_cols, hipStream_t stream) {
     const int tiles_m = (int)ceil_div(m, 256), big_cols = n / 256 - rem_cols, small_cols = 2 * rem_cols;
-    const size_t smem = (2 * 256 + NSW * 256) * BK * sizeof(bf16_t);
-    auto kern = gemm_bf16_mixed_kernel<MODE, NSW>;
+    auto kern = gemm_bf16_mixed_kernel<MODE>;
     static bool configured = false;
     if (!configured) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)kWideTileLds);
         if (e != hipSuccess) return e;
         configured = true;
     }
-    kern<<<tiles_m * (big_cols + small_cols), 512, smem, stream>>>(a, lda, w, ldw, out, ldc, m, k, tiles_m, big_cols,
-                                                                   small_cols);
+    kern<<<tiles_m * (big_cols + small_cols), 256, kWideTileLds, stream>>>(a, lda, w, ldw, out, ldc, m, k, tiles_m, big_cols,
+                                                                           small_cols);
     return hipGetLastError();
 }
 
-// Row-mixed launch (see gemm_bf16_rowmix_kernel); rem_rows is 64 or 128.
-template <int MODE, int NSW>
+// Row-mixed launch (see gemm_bf16_rowmix_kernel); BMR is 64 or 128.
+template <int MODE, int BMR>
 hipError_t launch_rowmix(const bf16_t* a, int64_t lda, const bf16_t* w, int64_t ldw, void* out, int64_t ldc, int m,
-                         int n, int k, int rem_rows, int splits, int64_t split_stride, hipStream_t stream) {
+                         int n, int k, int splits, int64_t split_stride, hipStream_t stream) {
     const int bands = m / 256, tiles_n = n / 256;
-    const size_t smem = (2 * 256 + NSW * 256) * BK * sizeof(bf16_t);
-    const dim3 grid((bands + 1) * tiles_n, splits);
-#define GLLM_ROWMIX(R)                                                                                             \
-    do {                                                                                                           \
-        auto kern = gemm_bf16_rowmix_kernel<MODE, R, NSW>;                                                           \
-        static bool configured = false;                                                                            \
-        if (!configured) {                                                                                         \
-            hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),                                \
-                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);             \
-            if (e != hipSuccess) return e;                                                                         \
-            configured = true;                                                                                     \
-        }                                                                                                          \
-        kern<<<grid, 512, smem, stream>>>(a, lda, w, ldw, out, ldc, m, k, bands, tiles_n, split_stride);          \
-    } while (0)
-    if (rem_rows == 64) GLLM_ROWMIX(64);
-    else GLLM_ROWMIX(128);
-#undef GLLM_ROWMIX
+    auto kern = gemm_bf16_rowmix_kernel<MODE, BMR>;
+    static bool configured = false;
+    if (!configured) {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)kWideTileLds);
+        if (e != hipSuccess) return e;
+        configured = true;
+    }
+    kern<<<dim3((bands + 1) * tiles_n, splits), 256, kWideTileLds, stream>>>(a, lda, w, ldw, out, ldc, m, k, bands, tiles_n, split_stride);
     return hipGetLastError();
 }
 
 }  // namespace
+
+// Whether bands of 192 rows cover m rows with less padding than bands of 256.
+bool gemm_low_bands(int m) { return round_up(m, 192) < round_up(m, 256); }
 
 // Height of the last row band for a row-mixed launch (64 or 128), or 0 when the shape does not call for one: at
 // least one whole band of 256 rows and at most 128 rows left over.
@@ -458,100 +458,88 @@ int gemm_mixed_rem_cols(int m, int n) {
     return rem / tiles_m;
 }
 
-// Tile shape and split-K factor for a problem, from a small cost model fitted to measurements on MI355X with
-// operands streaming from HBM (weights are cold in the stage).  Unit: the time of one k-step of a 256x256 tile
-// (~1.65 us).  A 256x256 tile (8 waves, one workgroup per compute unit) costs k_steps + 6 (prologue, epilogue)
-// per round of 256 tiles; a 256x192 tile 0.88 k_steps + 6; a 128x128 tile 0.70 k_steps + 2.3 per round of 512
-// tiles when two share a compute unit, 0.49 k_steps + 2.3 when alone (15 % less with four LDS stages, used
-// for few rows).  A partial last round of 256x256 tiles that covers at most half of the compute units can be
-// run with half-width tiles instead (mixed launch, ~0.55 of a round).  Split-K multiplies the number of tiles
-// and divides the k-steps, at the price of writing one fp32 plane per split (mostly hidden under other tiles).
-// For 257..288 rows a 288x192 tile (6 waves, wave tile 96x96) covers all rows in one band.
-// Up to 64 rows the product is a stream of the weights: a 64x128 tile with three LDS stages (two workgroups per
-// compute unit, 64 KiB of weights in flight on each, half the activation traffic of a 128-row tile) costs
-// 0.30 k_steps per tile, but not less than the weights take at 5.5 TB/s, plus 2; measured 20-35 % faster than
-// every other shape there, so it is the only candidate for such problems and the model only picks its split.
-GemmPlan gemm_plan(int m, int n, int k, int mode, int max_splits, bool row_mixed) {
+namespace {
+
+// Cost of a launch of one tile shape in us, fitted to measurements on MI355X with operands streaming from HBM (weights
+// are cold in the stage; four stage shapes and two vocabularies, 65 to 4160 rows, every tile and split):
+// fixed + rounds * (step * k_steps + per_tile) + plane * (us to read the fp32 result at 6 TB/s).  A round is one tile per
+// compute unit (two for a shape of which two share one); a last round that fills a share x of them counts
+// lone + (1 - lone) x, because fewer tiles run faster: the chip is power- and bandwidth-limited.  The errors of the fit
+// are 5 % (tall tiles) to 9 % (128-row tiles); the pick it makes is 2 % behind the best one on average.
+struct TileCost {
+    int slots;
+    double step, fixed, lone, per_tile, plane;
+};
+constexpr TileCost kCost128x128{512, 0.97, 6.4, 0.25, 0.95, 0.75}, kCost128x128Deep{256, 0.49, 3.6, 0.70, 2.5, 1.0},
+    kCost192x128{256, 0.684, 3.5, 0.575, 2.7, 1.0}, kCost256x128{256, 0.822, 4.7, 0.59, 5.4, 0.26},
+    kCost256x192{256, 1.175, 3.9, 0.70, 0.4, 1.0}, kCost256x256{256, 1.454, 4.4, 0.547, 2.5, 0.92},
+    kCost192x256{256, 1.20, 0.8, 0.51, 6.0, 0.81}, kCost288x192{256, 1.587, 0.0, 0.516, 7.1, 1.0};
+
+double rounds_of(const TileCost& c, double tiles) {
+    const double full = std::floor(tiles / c.slots), rest = tiles / c.slots - full;
+    return full + (rest > 1e-9 ? c.lone + (1.0 - c.lone) * rest : 0.0);
+}
+
+// Tile shape and split-K factor (a power of two in [min_splits, max_splits]) of the lowest cost.  Up to 64 rows the
+// product is a stream of the weights and the 64x128 tile (two workgroups per compute unit, 64 KiB of weights in flight on
+// each, half the activation traffic of a 128-row tile) the only candidate: 0.30 x 1.65 us per k-step of a tile, but not
+// less than the weights take at 5.5 TB/s.  read_planes: the result planes are read back by the next kernel (the stage),
+// so a product that is split less is worth the time of that.
+GemmPlan cheapest(int m, int n, int k, int mode, int min_splits, int max_splits, bool row_mixed, bool read_planes) {
     const int its = k / BK;
-    GemmPlan best{0, 1};
+    GemmPlan best{0, min_splits};
     double best_cost = 1e30;
     if (mode != GEMM_STORE_F32) max_splits = 1;
-    for (int s = 1; s <= max_splits; s *= 2) {
-        if (its % s != 0 || (s > 1 && its / s < 8)) continue;
+    for (int s = min_splits; s <= max_splits; s *= 2) {
+        if (its % s != 0 || (s > 1 && s > min_splits && its / s < 8)) continue;
         const double steps = (double)its / s;
-        const double plane_cost = (double)m * n * 4.0 * s / 8e12 / 1.65e-6;  // mostly hidden under other tiles
-        const bool skinny = m <= 64 && n % 128 == 0;
-        if (row_mixed && gemm_rowmix_rem_rows(m, n) > 0) {
-            // (evaluated first: on equal cost it is kept -- whole rounds hide that it always does less work)
-            // whole bands as 256x256 tiles; the last band's tiles go first into the compute units the last round of
-            // big tiles leaves idle; those that do not fit there stream their weights from HBM once more and cost
-            // 0.8 (64 rows) or 0.9 (128 rows) of a big tile (measured on the 128256-column vocabulary projection)
-            const int rr = gemm_rowmix_rem_rows(m, n);
-            const double frac = rr == 64 ? 0.8 : 0.9;
-            const int64_t big = (int64_t)(m / 256) * (n / 256) * s, small = (int64_t)(n / 256) * s;
-            const int64_t rem_big = big % 256;
-            const int64_t room = rem_big > 0 ? (256 - rem_big) * (rr == 64 ? 2 : 1) : 0;
-            double rounds = (double)ceil_div(big, 256);
-            if (small > room) rounds += frac * (double)ceil_div(small - room, 256);
-            const double cost = rounds * (steps + 6.0) + plane_cost;
-            if (cost < best_cost) { best_cost = cost; best = GemmPlan{8, s}; }
-        }
-        if (n % 256 == 0 && !skinny) {
-            const int64_t tiles = ceil_div(m, 256) * (int64_t)(n / 256) * s;
-            const bool mixed = s == 1 && gemm_mixed_rem_cols(m, n) > 0;
-            const double rounds = mixed ? (double)(tiles / 256) + 0.55 : (double)ceil_div(tiles, 256);
-            const double cost = rounds * (steps + 6.0) + plane_cost;
-            if (cost < best_cost) { best_cost = cost; best = GemmPlan{mixed ? 4 : 3, s}; }
-        }
-        if (n % 192 == 0 && mode != GEMM_SWIGLU_BF16 && !skinny) {
-            const int64_t tiles = ceil_div(m, 256) * (int64_t)(n / 192) * s;
-            const double cost = (double)ceil_div(tiles, 256) * (steps * 0.88 + 6.0) + plane_cost;
-            if (cost < best_cost) { best_cost = cost; best = GemmPlan{5, s}; }
-        }
-        if (m > 256 && m <= 288 && n % 192 == 0 && mode != GEMM_SWIGLU_BF16) {
-            // 257..288 rows (a micro-batch of 256 decode rows plus the ends of a few chunks): one 288x192 tile per
-            // column block reads the weights once where every 256-row shape needs a second band; a k-step of it costs
-            // 1.07 of a 256x256 one when the weights stream from HBM
-            const int64_t tiles = (int64_t)(n / 192) * s;
-            const double cost = (double)ceil_div(tiles, 256) * (steps * 1.07 + 6.0) + plane_cost;
-            if (cost < best_cost) { best_cost = cost; best = GemmPlan{9, s}; }
-        }
-        if (n % 128 == 0 && !skinny) {
-            const int64_t tiles = ceil_div(m, 128) * (int64_t)(n / 128) * s;
-            const int64_t full = tiles / 512, rem = tiles % 512;
-            double cost = (double)full * (steps * 0.70 + 2.3) + plane_cost;
-            if (rem > 256) cost += steps * 0.70 + 2.3;
-            else if (rem > 0) cost += steps * 0.49 + 2.3;
-            // few rows: every tile is alone on its compute unit; the 4-stage variant keeps three k-steps of
-            // loads in flight (measured +10..20 % there)
-            const bool deep = m <= 256 && tiles <= 256;
-            if (deep) cost *= 0.85;
-            if (cost < best_cost) { best_cost = cost; best = GemmPlan{deep ? 6 : 0, s}; }
-        }
-        if (m > 128 && m <= 256 && n % 128 == 0) {
-            // 129..256 rows: 256x128 tiles take all rows in one band, so the weights are read once (with the
-            // non-temporal hint) where the 128-row shapes read them twice; measured 0.67 of a 256x256 k-step and a
-            // fixed 3; wins where the product cannot be split along k (gate/up: 4-9 % over the 128x128 tiles)
-            const int64_t tiles = (int64_t)(n / 128) * s;
-            const double cost = (double)ceil_div(tiles, 256) * (steps * 0.67 + 3.0) + plane_cost;
-            if (cost < best_cost) { best_cost = cost; best = GemmPlan{1, s}; }
-        }
-        if (skinny) {
-            const int64_t tiles = (int64_t)(n / 128) * s;
-            const double stream = (double)n * k * 2.0 / 5.5e12 / 1.65e-6;
-            const double cost = std::max((double)ceil_div(tiles, 512) * steps * 0.30, stream) + 2.0 + plane_cost;
+        const double plane = mode == GEMM_STORE_F32 ? (double)m * n * 4.0 * s / 6e6 : 0.0;  // us to read the result
+        const double stream = (double)n * k * 2.0 / 5.9e6 + 2.0;
+        auto consider = [&](int tile, const TileCost& c, double tiles) {
+            double cost = c.fixed + rounds_of(c, tiles * s) * (c.step * steps + c.per_tile) + c.plane * plane;
+            cost = std::max(cost, stream) + (read_planes ? plane : 0.0);
+            if (cost < best_cost) { best_cost = cost; best = GemmPlan{tile, s}; }
+        };
+        if (m <= 64 && n % 128 == 0) {
+            const double cost = std::max((double)ceil_div((int64_t)(n / 128) * s, 512) * steps * 0.30, (double)n * k * 2.0 / 5.5e12 / 1.65e-6) +
+                                2.0 + (double)m * n * 4.0 * s / 8e12 / 1.65e-6;
             if (cost < best_cost) { best_cost = cost; best = GemmPlan{7, s}; }
+            continue;
+        }
+        const double b128 = (double)ceil_div(m, 128), b192 = (double)ceil_div(m, 192), b256 = (double)ceil_div(m, 256);
+        if (n % 256 == 0) {
+            const double cols = n / 256;
+            const int rr = row_mixed ? gemm_rowmix_rem_rows(m, n) : 0;
+            if (rr > 0 && m <= 384) consider(8, kCost192x256, 2 * cols);
+            else if (rr > 0) consider(8, kCost256x256, (m / 256 + (rr == 64 ? 0.6 : 0.8)) * cols);
+            // (half-width tiles in a last round that they cover: half a round of big tiles)
+            if (s == 1 && gemm_mixed_rem_cols(m, n) > 0)
+                consider(4, kCost256x256, std::floor(b256 * cols / 256) * 256 + 256 * (0.5 - kCost256x256.lone) / (1 - kCost256x256.lone));
+            consider(3, kCost256x256, b256 * cols);
+        }
+        if (n % 192 == 0 && mode != GEMM_SWIGLU_BF16) {
+            consider(5, kCost256x192, b256 * (n / 192));
+            if (m > 256 && m <= 288) consider(9, kCost288x192, n / 192);
+        }
+        if (n % 128 == 0) {
+            const double cols = n / 128;
+            if (gemm_low_bands(m)) consider(1, kCost192x128, b192 * cols);
+            else consider(1, kCost256x128, b256 * cols);
+            consider(6, kCost128x128Deep, b128 * cols);
+            consider(0, kCost128x128, b128 * cols);
         }
     }
-    // The 256x256 tile shapes exist with a third LDS stage for the W tile (ids 10, 11, 12 for 3, 4, 8): two k-steps for the
-    // weight loads to land instead of one.  Measured against the two-stage forms on the four stage shapes (weights cold):
-    // +3..5 % where a tile walks 80 or more k-steps (hidden >= 5120; the down projection), +15..20 % at 512 rows and
-    // below, where the product is bound by the weight stream; even or -2 % on short k with many rows (hidden 4096 at
-    // 2048 rows), where the loads land in time anyway.
+    // (ids 10, 11, 12 and 3, 4, 8 are the same launches)
     const int steps = its / best.splits;
     if ((best.tile == 3 || best.tile == 4 || best.tile == 8) && (steps >= 80 || m <= 1024))
         best.tile = best.tile == 3 ? 10 : best.tile == 4 ? 11 : 12;
     return best;
+}
+
+}  // namespace
+
+GemmPlan gemm_plan(int m, int n, int k, int mode, int max_splits, bool row_mixed, bool read_planes) {
+    return cheapest(m, n, k, mode, 1, max_splits, row_mixed, read_planes);
 }
 
 hipError_t launch_gemm_bf16(const bf16_t* a, int64_t lda, const bf16_t* w, int64_t ldw, void* out, int64_t ldc,
@@ -560,47 +548,48 @@ hipError_t launch_gemm_bf16(const bf16_t* a, int64_t lda, const bf16_t* w, int64
     if (m <= 0) return hipSuccess;
     if (n <= 0 || k <= 0 || n % 64 != 0 || k % BK != 0) return hipErrorInvalidValue;
     if (lda * 16 >= (int64_t)1 << 31 || ldw % kWBlock != 0 || ldw < k) return hipErrorInvalidValue;
+    // the kernels address the rows of a tile and a tile's weight panel by 32-bit byte offsets
+    if (ldw >= (int64_t)1 << 23) return hipErrorInvalidValue;
+    const int64_t rows32 = (((int64_t)1 << 32) - 1) / (2 * std::max<int64_t>(lda, 1));
+    if (m > rows32 && rows32 < kMaxTileM) {
+        const int elem = mode == GEMM_SWIGLU_BF16 ? 2 : 4;
+        for (int64_t r = 0; r < m; r += rows32) {
+            const hipError_t e = launch_gemm_bf16(a + r * lda, lda, w, ldw, (char*)out + r * ldc * elem, ldc, (int)std::min<int64_t>(rows32, m - r),
+                                                  n, k, mode, -1, splits, split_stride, stream);
+            if (e != hipSuccess) return e;
+        }
+        return hipSuccess;
+    }
     if (splits < 1 || (k / BK) % splits != 0) return hipErrorInvalidValue;
     if (splits > 1 && mode != GEMM_STORE_F32) return hipErrorInvalidValue;
     if (tile < 0) {
-        tile = gemm_plan(m, n, k, splits == 1 ? mode : GEMM_ADD_F32, 1).tile;  // tile for the given split count
-        if (splits > 1) {
-            // splits fixed by the caller: compare the two tile shapes at that split count
-            const int64_t t3 = ceil_div(m, 256) * (int64_t)(n / 256) * splits, t0 = ceil_div(m, 128) * (int64_t)(n / 128) * splits;
-            const double steps = (double)(k / BK) / splits;
-            const double c3 = n % 256 == 0 ? (double)ceil_div(t3, 256) * (steps + 6.0) : 1e30;
-            const double c0 = (double)(t0 / 512) * (steps * 0.70 + 2.3) +
-                              (t0 % 512 > 256 ? steps * 0.70 + 2.3 : t0 % 512 > 0 ? steps * 0.49 + 2.3 : 0.0);
-            tile = m <= 64 ? 7 : c3 <= c0 ? ((steps >= 80 || m <= 1024) ? 10 : 3) : (m <= 256 && t0 <= 256) ? 6 : 0;
-        }
+        tile = cheapest(m, n, k, splits == 1 ? mode : GEMM_STORE_F32, splits, splits, true, false).tile;
     }
-    if (tile == 8 || tile == 12) {  // 256x256 tiles plus a last band of 64 or 128 rows (12: third W stage)
+    if (tile == 8 || tile == 12) {
         const int rem_rows = gemm_rowmix_rem_rows(m, n);
         if (rem_rows == 0) return hipErrorInvalidValue;
+        if (m > 384) {
 #define GLLM_ROWMIX_MODE(MODE_)                                                                                              \
-    (tile == 8 ? launch_rowmix<MODE_, 2>(a, lda, w, ldw, out, ldc, m, n, k, rem_rows, splits, split_stride, stream)          \
-               : launch_rowmix<MODE_, 3>(a, lda, w, ldw, out, ldc, m, n, k, rem_rows, splits, split_stride, stream))
-        switch (mode) {
-            case GEMM_STORE_F32: return GLLM_ROWMIX_MODE(GEMM_STORE_F32);
-            case GEMM_ADD_F32: return GLLM_ROWMIX_MODE(GEMM_ADD_F32);
-            case GEMM_SWIGLU_BF16: return GLLM_ROWMIX_MODE(GEMM_SWIGLU_BF16);
-            default: return hipErrorInvalidValue;
-        }
+    (rem_rows == 64 ? launch_rowmix<MODE_, 64>(a, lda, w, ldw, out, ldc, m, n, k, splits, split_stride, stream)              \
+                    : launch_rowmix<MODE_, 128>(a, lda, w, ldw, out, ldc, m, n, k, splits, split_stride, stream))
+            switch (mode) {
+                case GEMM_STORE_F32: return GLLM_ROWMIX_MODE(GEMM_STORE_F32);
+                case GEMM_ADD_F32: return GLLM_ROWMIX_MODE(GEMM_ADD_F32);
+                case GEMM_SWIGLU_BF16: return GLLM_ROWMIX_MODE(GEMM_SWIGLU_BF16);
+                default: return hipErrorInvalidValue;
+            }
 #undef GLLM_ROWMIX_MODE
+        }
     }
-    if (tile == 4 || tile == 11) {  // mixed 256x256 / 256x128 launch (11: third W stage)
+    if (tile == 4 || tile == 11) {
         const int rem_cols = gemm_mixed_rem_cols(m, n);
         if (rem_cols == 0 || splits != 1) return hipErrorInvalidValue;
-#define GLLM_MIXED_MODE(MODE_)                                                                    \
-    (tile == 4 ? launch_mixed<MODE_, 2>(a, lda, w, ldw, out, ldc, m, n, k, rem_cols, stream)      \
-               : launch_mixed<MODE_, 3>(a, lda, w, ldw, out, ldc, m, n, k, rem_cols, stream))
         switch (mode) {
-            case GEMM_STORE_F32: return GLLM_MIXED_MODE(GEMM_STORE_F32);
-            case GEMM_ADD_F32: return GLLM_MIXED_MODE(GEMM_ADD_F32);
-            case GEMM_SWIGLU_BF16: return GLLM_MIXED_MODE(GEMM_SWIGLU_BF16);
+            case GEMM_STORE_F32: return launch_mixed<GEMM_STORE_F32>(a, lda, w, ldw, out, ldc, m, n, k, rem_cols, stream);
+            case GEMM_ADD_F32: return launch_mixed<GEMM_ADD_F32>(a, lda, w, ldw, out, ldc, m, n, k, rem_cols, stream);
+            case GEMM_SWIGLU_BF16: return launch_mixed<GEMM_SWIGLU_BF16>(a, lda, w, ldw, out, ldc, m, n, k, rem_cols, stream);
             default: return hipErrorInvalidValue;
         }
-#undef GLLM_MIXED_MODE
     }
     switch (mode) {
         case GEMM_STORE_F32:

@@ -236,6 +236,43 @@ def test_gemm_third_weight_stage_changes_no_bit():
         assert torch.equal(outs[0], outs[1]), (M, N, K, pair, splits)
 
 
+@pytest.mark.parametrize("tile", [0, 1, 5, 6, 7, 10, 12])
+@pytest.mark.parametrize("K", [64, 128, 448])
+def test_gemm_tiles_at_their_edges(tile, K):
+    """Row counts on both sides of every tile height, as few k-steps as LDS stages and fewer.  The rows behind the last
+    one hold NaN (a tile must not use them) and the result has canaries behind its last row.  fp32 sums of K products of
+    bf16 values: K roundings of 2^-24 of the sum of magnitudes bound the error."""
+    N = 768
+    for M in (1, 33, 64, 129, 192, 193, 256, 257, 300, 384, 385, 449, 577):
+        if tile == 12 and not (M > 256 and 0 < M % 256 <= 128):
+            continue
+        print(f"gemm edges tile={tile} K={K} M={M}", flush=True)
+        a, w = rand_bits(12, M, (M, K), 1.0), rand_bits(12, 2, (N, K), 0.05)
+        ap = np.full(((M + 511) // 256 * 256, K + 64), 0x7FC0, dtype=np.uint16)      # row stride larger than k
+        ap[:M, :K] = a
+        out = torch.full((M + 40, N), 7.0, dtype=torch.float32, device=DEV)
+        B.gllm_op_gemm_bf16(to_dev_bits(ap), to_dev_weight(w), out, M, N, K, B.GEMM_STORE_F32, tile)
+        torch.cuda.synchronize()
+        x, y = oracle.bf16_to_f64(a), oracle.bf16_to_f64(w)
+        bound = (np.abs(x) @ np.abs(y).T) * K * 2.0 ** -24
+        got = out.cpu().numpy().astype(np.float64)
+        assert np.all(np.abs(got[:M] - x @ y.T) <= bound), (tile, K, M)
+        assert np.all(got[M:] == 7.0)
+
+
+def test_gemm_rows_farther_apart_than_32_bit_offsets_reach():
+    """A row stride of 2^23 elements: 300 rows span more than 4 GiB, which the launch cuts into bands."""
+    M, N, K, ld = 300, 256, 128, 1 << 23
+    a, w = rand_bits(13, 1, (M, K), 1.0), rand_bits(13, 2, (N, K), 0.05)
+    far = torch.empty(M * ld, dtype=torch.bfloat16, device=DEV).as_strided((M, K), (ld, 1))
+    far.copy_(to_dev_bits(a).view(torch.bfloat16))
+    out = torch.zeros((M, N), dtype=torch.float32, device=DEV)
+    B.gllm_op_gemm_bf16(far, to_dev_weight(w), out, M, N, K, B.GEMM_STORE_F32)
+    torch.cuda.synchronize()
+    x, y = oracle.bf16_to_f64(a), oracle.bf16_to_f64(w)
+    assert np.all(np.abs(out.cpu().numpy() - x @ y.T) <= (np.abs(x) @ np.abs(y).T) * K * 2.0 ** -24)
+
+
 def test_pack_weight_writes_the_documented_tiled_layout():
     """gllm_op_pack_weight against the layout as the header states it (gpu_util.tiled_bits), bit for bit: a whole matrix,
     and a part of a wider one (row stride above k); then the product on a leading part of the packed k range."""
