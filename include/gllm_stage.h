@@ -148,12 +148,8 @@ gllm_status gllm_stage_set_alias_check(gllm_stage* stage, int32_t on);
  *   "decode_min_workgroups" (default 2048): a partition size (256 .. 16384 keys, a power of two) is chosen as
  *   the largest for which partitions x KV heads reaches this many workgroups; a decode row with more keys than
  *   that is cut into equal shares of whole 32-key blocks, and the longest shares are launched first.
- *   "overlap_attention" (default 1): prefill attention of a layer runs on an internal side stream next to
- *   decode attention (forked from and joined back into the caller's stream with events); 0 keeps every
- *   kernel on the caller's stream.  Per-kernel profiling always uses the single-stream order.  (The runtime maps
- *   streams onto a few hardware queues; when the side stream happens to share the caller's queue the two kernels
- *   simply run one after the other.  Callers that run several stages on several streams of their own may do better
- *   with 0: every further stream competes for those queues.)
+ *   "overlap_attention" (default 1): prefill and decode attention of a layer share one launch where the prefill part is
+ *   small; 0 always launches them one after the other, as per-kernel profiling does.  The results are the same bits.
  *   "gemm_row_mixed" (default 1; a property of this stage only): the stage's GEMM planner may cover a last band of at
  *   most 128 token rows with 64- or 128-row tiles instead of a whole band of 256 (tile 8 of gllm_op_gemm_bf16).
  *   "layer_begin" (default 0), "layer_end" (default num_layers): forward() runs only layers layer_begin .. layer_end-1

@@ -138,9 +138,14 @@ struct DecodeRow {
     int32_t num_items;
     int32_t pad;
 };
-// order[i] = index of the item that workgroup group i works on (a permutation of 0 .. num_items-1)
-hipError_t launch_decode_attention(const AttnArgs& a, const DecodeItem* items, const int32_t* order, int num_items,
-                                   float* part_o, float* part_ml, hipStream_t stream);
+struct DecodeArgs {
+    const DecodeItem* items;
+    const int32_t* order;  // order[i] = index of the item that workgroup group i works on (a permutation of 0 .. num_items-1)
+    int num_items;
+    float* part_o;         // partials of the items whose row has more than one
+    float* part_ml;
+};
+hipError_t launch_decode_attention(const AttnArgs& a, const DecodeArgs& dec, hipStream_t stream);
 hipError_t launch_decode_combine(const AttnArgs& a, const DecodeRow* rows, int num_rows, const float* part_o,
                                  const float* part_ml, hipStream_t stream);
 
@@ -153,6 +158,9 @@ struct PrefillItem {
     int32_t bt_off;    // offset of the sequence's first page id in bt_flat
 };
 hipError_t launch_prefill_attention(const AttnArgs& a, const PrefillItem* items, int num_items, hipStream_t stream);
+// Prefill and decode items of one batch in one launch, and whether that pays.
+bool attention_in_one_launch(const AttnArgs& a, int num_items, int num_decode_items);
+hipError_t launch_hybrid_attention(const AttnArgs& a, const PrefillItem* items, int num_items, const DecodeArgs& dec, hipStream_t stream);
 
 // Ceiling probes (see kernels_peak.hip).  peak_mfma: workgroups x 4 waves x iters x 16 MFMAs of
 // 2*32*32*16 flop each.  peak_read: reads `bytes` once.

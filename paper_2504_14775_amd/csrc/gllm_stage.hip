@@ -79,11 +79,7 @@ struct gllm_stage {
     hipEvent_t staging_ev[kStagingSlots] = {};
     bool staging_used[kStagingSlots] = {};
     int next_slot = 0;
-    // prefill attention runs on a side stream, concurrently with decode attention (one is bound by the matrix
-    // cores and latency, the other by HBM); fork/join events order it inside the caller's stream
-    hipStream_t side = nullptr;
-    hipEvent_t fork_ev[8] = {}, join_ev[8] = {};
-    bool overlap_attention = true;
+    bool overlap_attention = true;  // a small prefill part of a batch shares the launch of decode attention
     bool alias_check = true;
     bool gemm_row_mixed = true;  // the GEMM planner may cover a short last row band with 64- or 128-row tiles
     int layer_begin = 0, layer_end = 0;  // forward() runs layers [layer_begin, layer_end) (layer_end is set at creation)
@@ -304,11 +300,6 @@ gllm_status gllm_stage_create(const gllm_stage_config* cfg, gllm_stage** out) {
                 return bail(e, "hipEventCreate");
         }
     }
-    if ((e = hipStreamCreateWithFlags(&s->side, hipStreamNonBlocking)) != hipSuccess) return bail(e, "hipStreamCreate");
-    for (int i = 0; i < 8; ++i) {
-        if ((e = hipEventCreateWithFlags(&s->fork_ev[i], hipEventDisableTiming)) != hipSuccess) return bail(e, "hipEventCreate");
-        if ((e = hipEventCreateWithFlags(&s->join_ev[i], hipEventDisableTiming)) != hipSuccess) return bail(e, "hipEventCreate");
-    }
     s->ws_bytes = workspace_layout(s, nullptr);
     *out = s;
     return GLLM_OK;
@@ -325,11 +316,6 @@ void gllm_stage_destroy(gllm_stage* s) {
         if (s->staging[i]) (void)hipHostFree(s->staging[i]);
         if (s->staging_ev[i]) (void)hipEventDestroy(s->staging_ev[i]);
     }
-    for (int i = 0; i < 8; ++i) {
-        if (s->fork_ev[i]) (void)hipEventDestroy(s->fork_ev[i]);
-        if (s->join_ev[i]) (void)hipEventDestroy(s->join_ev[i]);
-    }
-    if (s->side) (void)hipStreamDestroy(s->side);
     for (auto& sp : s->spans) { (void)hipEventDestroy(sp.a); (void)hipEventDestroy(sp.b); }
     for (auto ev : s->ev_pool) (void)hipEventDestroy(ev);
     delete s;
@@ -676,28 +662,24 @@ gllm_status gllm_stage_forward(gllm_stage* s, const gllm_batch* b, const void* h
         aa.bt_flat = d_bt; aa.out = s->attn; aa.ld_o = s->q_dim;
         aa.n_q = c.n_q_heads; aa.n_kv = c.n_kv_heads; aa.d = d;
         aa.scale_log2 = (float)(1.4426950408889634 / std::sqrt((double)d));
-        // both attention kernels read q and the pool and write disjoint rows of attn
-        const bool fork = n_pre > 0 && n_items > 0 && s->overlap_attention && !s->profiling;
-        if (n_pre > 0) {
-            hipStream_t ps_stream = st;
-            if (fork) {
-                HIP_TRY(s, hipEventRecord(s->fork_ev[l & 7], st));
-                HIP_TRY(s, hipStreamWaitEvent(s->side, s->fork_ev[l & 7], 0));
-                ps_stream = s->side;
+        const DecodeArgs da{d_items, d_order, n_items, s->part_o, s->part_ml};
+        // both kinds of attention read q and the pool and write disjoint rows of attn
+        if (s->overlap_attention && !s->profiling && attention_in_one_launch(aa, n_pre, n_items)) {
+            HIP_TRY(s, launch_hybrid_attention(aa, d_pre, n_pre, da, st));
+        } else {
+            if (n_pre > 0) {
+                ProfScope ps(s, st, PC_ATTN_PREFILL);
+                HIP_TRY(s, launch_prefill_attention(aa, d_pre, n_pre, st));
             }
-            ProfScope ps(s, ps_stream, PC_ATTN_PREFILL);
-            HIP_TRY(s, launch_prefill_attention(aa, d_pre, n_pre, ps_stream));
-            if (fork) HIP_TRY(s, hipEventRecord(s->join_ev[l & 7], s->side));
+            if (n_items > 0) {
+                ProfScope ps(s, st, PC_ATTN_DECODE);
+                HIP_TRY(s, launch_decode_attention(aa, da, st));
+            }
         }
         if (n_items > 0) {
-            {
-                ProfScope ps(s, st, PC_ATTN_DECODE);
-                HIP_TRY(s, launch_decode_attention(aa, d_items, d_order, n_items, s->part_o, s->part_ml, st));
-            }
             ProfScope ps(s, st, PC_ATTN_MERGE);
             HIP_TRY(s, launch_decode_combine(aa, d_rows, n_rows, s->part_o, s->part_ml, st));
         }
-        if (fork) HIP_TRY(s, hipStreamWaitEvent(st, s->join_ev[l & 7], 0));
         {
             // the projection writes split_o partial products; the next RMSNorm adds them to the residual stream
             ProfScope ps(s, st, PC_GEMM_O);

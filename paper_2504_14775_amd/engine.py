@@ -147,11 +147,6 @@ class Engine:
             self.stages.append(st)
             self._ws.append(ws)
         self.stage = self.stages[0]
-        if lanes > 1:
-            # with a second lane the stage's own fork (prefill attention on a side stream) only adds streams that
-            # compete for the few hardware queues: measured 27.3k tokens/s with it against 29.0k without
-            for st in self.stages:
-                st.set_option("overlap_attention", 0)
         # streams that do not share a hardware queue: the lanes first, then the one for the last-stage extras
         own = independent_streams((lanes if lanes > 1 else 0) + (1 if overlap_head else 0), device,
                                   beside=() if lanes > 1 else (torch.cuda.current_stream(),))
