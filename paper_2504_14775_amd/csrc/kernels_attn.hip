@@ -8,12 +8,13 @@
 //     O^T[dim][col] += V^T[dim][key] . P^T[key][col]  one 16x16x32 MFMA per 16 dims
 // A 16x16x32 MFMA takes, per lane (r = lane % 16, G = lane / 16), 8 consecutive k-values of row r
 // (A operand) or column r (B operand), k-slots 8G..8G+7, and returns for column r the rows
-// 4G..4G+3.  The 32 keys are dealt to the rows of the two S^T tiles so that the 4 + 4 results a lane holds for
-// its column are the 8 consecutive keys 8G..8G+7 of the block (tile t, row i = slot 8((i>>2)&1) + 4t + (i&3) of
-// page i>>3) -- exactly the 8 k-slots it must supply as the B operand of the P.V product.  The pool layouts
-// make the matching A operands 16-byte pieces:
-//   K page [d/8][16 slots][8]: k-step s, tile t reads (group 4s + G, the slot above) of page r>>3;
-//   V page [d][16 slots]:      dims 16b..16b+15 of P.V read slots 8(G&1)..+7 of dim 16b + r of page G>>1.
+// 4G..4G+3.  The 4 + 4 results a lane holds for its column are the 8 k-slots 8G..8G+7 it must supply as the B operand of
+// the P.V product: which keys they are is a matter of how the keys are dealt to the rows of the two S^T tiles, as long as
+// the V operand holds the same ones.
+//   prefill (operands from LDS): 8 consecutive keys 8G..8G+7 of the block (tile t, row i = slot 8((i>>2)&1) + 4t + (i&3)
+//     of page i>>3), so V is one 16-byte piece, slots 8(G&1)..+7 of dim 16b + r of page G>>1 in the V page [d][16 slots];
+//   decode (operands from HBM): tile t is page t, so every load instruction takes whole lines of the K page
+//     [d/8][16 slots][8], and V is two 8-byte pieces, slots 4G..4G+3 of dim 16b + r of either page.
 // Softmax is the running-reference form in base 2 (exponent s*log2(e)/sqrt(d) - m, see update_group);
 // all reductions follow logical key order, so the result does not depend on which physical pages
 // hold the keys.
@@ -26,31 +27,41 @@ namespace {
 
 constexpr float kNegBig = -1.0e30f;
 
-// K and V operands of one block of 32 keys (two pages) in the layout score_group expects: a lane owns the 8
-// consecutive keys 8G .. 8G+7 of the block.
+// K and V operands of one block of 32 keys (two pages) for a decode row.  Score tile t is page t, so a lane of group G ends
+// up with keys 4G .. 4G+3 of either page, and its V operand is those slots of both.
 template <int D>
 struct KvFrag {
-    u32x4 k[2][D / 32];  // [fragment t][k-step]: operand row r = slot 8 ((r >> 2) & 1) + 4 t + (r & 3) of page r >> 3
-    u32x4 v[D / 16];     // [16-dim block]: slots 8 (G & 1) .. + 7 of dim r of page G >> 1
+    u32x4 k[2][D / 32];  // [page][k-step]: operand row r = slot r
+    u32x4 v[D / 16];     // [16-dim block]: slots 4G .. 4G+3 of dim r, first page in the low half
 };
 
-// The loads carry the non-temporal hint: a decode row's K and V are read once and never again, and without the hint the
-// stream is allocated in the caches on its way (measured: 5.78 -> 6.20 TB/s on 256 rows of 512 .. 4096 keys, 5.94 -> 6.35
-// on 512 rows of 1024 .. 8192 keys; a bare streaming read without the hint sustains 5.9 - 6.2).
+// Every instruction takes whole 128-byte lines: with lane groups owning 8 consecutive keys (as in the prefill kernel) a
+// K line is split over two instructions, and a line loaded with the non-temporal hint is fetched for each (4 % more
+// traffic: 512 rows of 1024 .. 8192 keys, 3 layers 4313 -> 4216 us; 251 rows of 64 .. 1100 keys, 8 layers 2224 -> 2182 us).
+// The hint itself: a decode row's K and V are read once and never again, and without it the stream is allocated in the
+// caches on its way (5.78 -> 6.20 TB/s on 256 rows of 512 .. 4096 keys; a bare streaming read without the hint sustains
+// 5.9 - 6.2, with it 6.5).
 template <int D>
 __device__ __forceinline__ void load_kv(KvFrag<D>& f, const bf16_t* __restrict__ kp, const bf16_t* __restrict__ vp,
                                         int64_t page0, int64_t page1, int n_kv, int kvh, int lane) {
     constexpr int64_t PH = (int64_t)D * kPage;  // elements of one (page, head)
     const int r = lane & 15, G = lane >> 4;
     // K page layout [d/8 groups][16 slots][8]: 16 bytes per (group, slot); V page layout [d][16 slots]
-    const bf16_t* kb = kp + (((r >> 3) ? page1 : page0) * n_kv + kvh) * PH + (G * kPage + ((r >> 2) & 1) * 8 + (r & 3)) * 8;
-    const bf16_t* vb = vp + (((G >> 1) ? page1 : page0) * n_kv + kvh) * PH + r * kPage + (G & 1) * 8;
+    const bf16_t* k0 = kp + (page0 * n_kv + kvh) * PH + (G * kPage + r) * 8;
+    const bf16_t* k1 = kp + (page1 * n_kv + kvh) * PH + (G * kPage + r) * 8;
+    const bf16_t* v0 = vp + (page0 * n_kv + kvh) * PH + r * kPage + G * 4;
+    const bf16_t* v1 = vp + (page1 * n_kv + kvh) * PH + r * kPage + G * 4;
 #pragma unroll
-    for (int t = 0; t < 2; ++t)
+    for (int s = 0; s < D / 32; ++s) {
+        f.k[0][s] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(k0 + s * 512));
+        f.k[1][s] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(k1 + s * 512));
+    }
 #pragma unroll
-        for (int s = 0; s < D / 32; ++s) f.k[t][s] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(kb + s * 512 + t * 32));
-#pragma unroll
-    for (int b = 0; b < D / 16; ++b) f.v[b] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(vb + b * 256));
+    for (int b = 0; b < D / 16; ++b) {
+        const u32x2 lo = __builtin_nontemporal_load(reinterpret_cast<const u32x2*>(v0 + b * 256));
+        const u32x2 hi = __builtin_nontemporal_load(reinterpret_cast<const u32x2*>(v1 + b * 256));
+        f.v[b] = u32x4{lo[0], lo[1], hi[0], hi[1]};
+    }
 }
 
 // State of NB column groups across the key loop.
@@ -62,35 +73,29 @@ struct AttnState {
 };
 
 // Masks the V fragments of keys >= valid_end (slots that hold no data yet may contain any bit pattern,
-// also NaN, and 0 * NaN would poison the P.V product).  v[b] holds this lane's 8 keys tb + 8G .. tb + 8G + 7 of dims
-// block b, two per register.
+// also NaN, and 0 * NaN would poison the P.V product).  v[b] holds this lane's keys key0 .. key0+3 and key1 .. key1+3 of
+// dims block b, two per register.
 template <int D>
-__device__ __forceinline__ void mask_unwritten_v(u32x4 (&v)[D / 16], int tb, int valid_end, int lane) {
-    const int G = lane >> 4;
-    int nv = valid_end - (tb + G * 8);
-    nv = nv < 0 ? 0 : (nv > 8 ? 8 : nv);
+__device__ __forceinline__ void mask_unwritten_v(u32x4 (&v)[D / 16], int key0, int key1, int valid_end) {
     uint32_t m[4];
 #pragma unroll
-    for (int w = 0; w < 4; ++w) m[w] = nv >= 2 * w + 2 ? 0xFFFFFFFFu : (nv == 2 * w + 1 ? 0x0000FFFFu : 0u);
+    for (int w = 0; w < 4; ++w) {
+        const int nv = valid_end - ((w < 2 ? key0 : key1) + 2 * (w & 1));
+        m[w] = nv >= 2 ? 0xFFFFFFFFu : (nv == 1 ? 0x0000FFFFu : 0u);
+    }
 #pragma unroll
     for (int b = 0; b < D / 16; ++b)
 #pragma unroll
         for (int w = 0; w < 4; ++w) v[b][w] &= m[w];
 }
 
-// One column group against one block of 32 keys starting at key index tb, in two phases so that callers
+// One column group against one block of 32 keys, in two phases so that callers
 // can fetch the V fragments only after the K fragments are dead.
-// Phase 1: raw scores q.k of this lane's 8 keys (not yet scaled), masked keys set to a huge negative.
-// The rows of the two K operands are permuted -- row i of fragment t is key tb + 16 (i >> 3) + 8 ((i >> 2) & 1) +
-// 4 t + (i & 3) -- so that the accumulators of lane group G are the 8 consecutive keys tb + 8G .. tb + 8G + 7
-// (fragment 0 gives the first four, fragment 1 the last four): exactly the 8 k-values this lane supplies to the
-// P.V product, whose V operand is then 8 consecutive slots of one page (16 contiguous bytes).
-//   limit     : last key visible to this lane's column (causal / partition limit)
-//   need_mask : wave-uniform, false when the whole block is visible to every column of the group
+// Phase 1: raw scores q.k of this lane's 8 keys (not yet scaled).  Lane group G receives rows 4G .. 4G+3 of both operand
+// fragments; the caller's choice of the keys in those rows decides which keys these are (key0 .. key0+3 from fragment 0,
+// key1 .. key1+3 from fragment 1), and the V operand of the P.V product has to hold the same ones.
 template <int D>
-__device__ __forceinline__ void score_group(float (&sc)[8], const u32x4 (&kf)[2][D / 32], const bf16x8 (&qf)[D / 32],
-                                            int tb, int limit, bool need_mask, int lane) {
-    const int G = lane >> 4;
+__device__ __forceinline__ void score_group(float (&sc)[8], const u32x4 (&kf)[2][D / 32], const bf16x8 (&qf)[D / 32]) {
     f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int s = 0; s < D / 32; ++s) {
@@ -102,11 +107,13 @@ __device__ __forceinline__ void score_group(float (&sc)[8], const u32x4 (&kf)[2]
         sc[v] = s0[v];
         sc[4 + v] = s1[v];
     }
-    if (need_mask) {
-        const int t0 = tb + G * 8;
+}
+// Scores of keys past `limit` (the last key visible to this lane's column) become a huge negative.
+__device__ __forceinline__ void mask_scores(float (&sc)[8], int key0, int key1, int limit) {
 #pragma unroll
-        for (int v = 0; v < 8; ++v)
-            if (t0 + v > limit) sc[v] = kNegBig;
+    for (int v = 0; v < 4; ++v) {
+        if (key0 + v > limit) sc[v] = kNegBig;
+        if (key1 + v > limit) sc[4 + v] = kNegBig;
     }
 }
 
@@ -182,11 +189,15 @@ template <int D, int NB>
 __device__ __forceinline__ void attend_block(AttnState<D, NB>& st, KvFrag<D>& f, const bf16x8 (&qf)[NB][D / 32],
                                              int tb, const int (&limit)[NB], int min_limit, int valid_end,
                                              float scale_log2, int lane) {
-    if (tb + 32 > valid_end) mask_unwritten_v<D>(f.v, tb, valid_end, lane);  // wave-uniform
-    const bool need_mask = tb + 31 > min_limit;                              // wave-uniform
+    const int key0 = tb + (lane >> 4) * 4, key1 = key0 + kPage;
+    if (tb + 32 > valid_end) mask_unwritten_v<D>(f.v, key0, key1, valid_end);  // wave-uniform
+    const bool need_mask = tb + 31 > min_limit;                                // wave-uniform
     float sc[NB][8];
 #pragma unroll
-    for (int c = 0; c < NB; ++c) score_group<D>(sc[c], f.k, qf[c], tb, limit[c], need_mask, lane);
+    for (int c = 0; c < NB; ++c) {
+        score_group<D>(sc[c], f.k, qf[c]);
+        if (need_mask) mask_scores(sc[c], key0, key1, limit[c]);
+    }
     update_groups<D, NB, false>(st, sc, scale_log2, []() {}, [&]() -> const u32x4 (&)[D / 16] { return f.v; });
 }
 
@@ -411,7 +422,7 @@ __device__ __forceinline__ void await_lds(u32x4 (&v)[N]) {
 // that all share the same K/V: every 32-key block is brought into LDS once (global_load_lds into a ring
 // of 3 stages, two blocks in flight while one is processed: a block is only ~0.5 us of work, far less
 // than the memory latency) and read by all 4 waves.
-// A lane owns 8 consecutive keys of the block (the K operand rows are permuted accordingly, see score_group),
+// A lane owns 8 consecutive keys of the block (the K operand rows are permuted accordingly),
 // so a V operand is one 16-byte LDS read of 8 slots of one page; LDS holds the pages as the pool does, except
 // that the second K page is shifted by four slots (see issue_block).
 // Column group cb = 2*wave + c covers head (cb % HW) and query rows 16*(cb / HW) .. +15 of the item.
@@ -481,7 +492,8 @@ __device__ __forceinline__ void prefill_workgroup(const AttnArgs& a, const Prefi
         constexpr bool MASKED = decltype(masked)::value;
         float sc[NB][8];
         {
-            // fragment t, row r of the operand = slot 8 ((r >> 2) & 1) + 4 t + (r & 3) of page r >> 3 (see score_group)
+            // fragment t, row r of the operand = slot 8 ((r >> 2) & 1) + 4 t + (r & 3) of page r >> 3: lane group G gets the
+            // 8 consecutive keys 8G .. 8G+7 of the block
             u32x4 kf[2][D / 32];
             const int kpage = r >> 3, kslot = ((r >> 2) & 1) * 8 + (r & 3);
 #pragma unroll
@@ -491,7 +503,10 @@ __device__ __forceinline__ void prefill_workgroup(const AttnArgs& a, const Prefi
                     kf[t][s] = *reinterpret_cast<const u32x4*>(
                         &lds[stage][kpage][((s * 4 + G) * 16 + ((kslot + 4 * t) ^ (4 * kpage))) * 16]);
 #pragma unroll
-            for (int c = 0; c < NB; ++c) score_group<D>(sc[c], kf, qf[c], tb, limit[c], MASKED, lane);
+            for (int c = 0; c < NB; ++c) {
+                score_group<D>(sc[c], kf, qf[c]);
+                if (MASKED) mask_scores(sc[c], tb + G * 8, tb + G * 8 + 4, limit[c]);
+            }
         }
         // V^T operands: dims block b needs this lane's 8 consecutive keys of one dim: the 16 bytes of slots 0-7 or
         // 8-15 of page G >> 1.  The reads are issued before the exponentials and awaited after them.
@@ -504,7 +519,7 @@ __device__ __forceinline__ void prefill_workgroup(const AttnArgs& a, const Prefi
             },
             [&]() -> const u32x4 (&)[D / 16] {
                 await_lds(vf);
-                if (MASKED) mask_unwritten_v<D>(vf, tb, last_pos + 1, lane);
+                if (MASKED) mask_unwritten_v<D>(vf, tb + G * 8, tb + G * 8 + 4, last_pos + 1);
                 return vf;
             });
     };
