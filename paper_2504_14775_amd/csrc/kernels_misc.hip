@@ -169,21 +169,26 @@ __device__ __forceinline__ void write_v_tile(const RopeKvArgs& a, const VTile vt
     }
 }
 
-// One workgroup per token row.  q heads and k heads are rotated (rotate-half pairing: element j
+// `parts` workgroups per token row.  q heads and k heads are rotated (rotate-half pairing: element j
 // pairs with j + d/2, angle pos * theta^(-2j/d) taken from the table); k and v are rounded to
 // bf16 and stored at (page, slot = pos % 16) in the layer's pool:
 //   K element (head h, dim e) -> ((page*n_kv + h)*d*16) + (e/8)*128 + slot*8 + e%8
 //   V element (head h, dim e) -> ((page*n_kv + h)*d*16) + e*16 + slot
 // PLANES >= 1 fixes the number of split-K planes at compile time (their loads are then issued together), PLANES < 0
 // takes it from the arguments.
+// With few tokens the kernel is a chain of memory latencies, one per pass of a workgroup over its token's columns; then a
+// token gets as many workgroups as it has passes (64 rows, 4 planes 7.1 -> 4.8 us, one row 5.7 -> 4.4).  From 129 rows on
+// one workgroup per token is as good or better (197 rows 6.2 against 7.2 us): the chip is full, and the lookups of a
+// token's position and page are shared.
+constexpr int kRopePartsMaxTokens = 128;
 template <int PLANES>
-__global__ __launch_bounds__(256) void rope_kv_write_kernel(RopeKvArgs a) {
+__global__ __launch_bounds__(256) void rope_kv_write_kernel(RopeKvArgs a, int parts) {
     const int v_wgs = a.n_vtiles * a.n_kv;  // the first workgroups write the V runs, one (run, head) each
     if ((int)blockIdx.x < v_wgs) {
         write_v_tile(a, a.v_tiles[blockIdx.x / a.n_kv], blockIdx.x % a.n_kv);
         return;
     }
-    const int t = blockIdx.x - v_wgs;
+    const int t = (blockIdx.x - v_wgs) / parts, first = (blockIdx.x - v_wgs) % parts * 256 + threadIdx.x, step = parts * 256;
     const int d = a.d, half = d / 2, hq = half / 4;  // a thread handles 4 consecutive pairs
     const int pos = a.tok_pos[t];
     const int64_t page = a.tok_page[t];
@@ -206,7 +211,7 @@ __global__ __launch_bounds__(256) void rope_kv_write_kernel(RopeKvArgs a) {
         if (a.bias) v += __builtin_convertvector(*reinterpret_cast<const bf16x4*>(a.bias + col), f32x4);
         return v;
     };
-    for (int i = threadIdx.x; i < q_quads + k_quads; i += 256) {
+    for (int i = first; i < q_quads + k_quads; i += step) {
         const bool is_q = i < q_quads;
         const int ii = is_q ? i : i - q_quads;
         const int hd = ii / hq, j = (ii % hq) * 4;
@@ -234,7 +239,8 @@ __global__ __launch_bounds__(256) void rope_kv_write_kernel(RopeKvArgs a) {
     }
     if (a.tok_own_v && !a.tok_own_v[t]) return;  // wave-uniform: a V run covers this token
     const int v_quads = a.n_kv * d / 4;
-    for (int i = threadIdx.x; i < v_quads; i += 256) {
+    for (int i = parts == 1 ? threadIdx.x : first - (q_quads + k_quads); i < v_quads; i += step) {  // the parts number q, k and v quads in one row
+        if (i < 0) continue;
         const int hd = (i * 4) / d, e = (i * 4) % d;
         const bf16x4 v = __builtin_convertvector(gather(v_col0 + i * 4), bf16x4);
         bf16_t* vb = a.v_pool + (page * a.n_kv + hd) * (int64_t)(d * kPage) + e * kPage + slot;
@@ -390,9 +396,10 @@ hipError_t launch_pack_gate_up(const bf16_t* gate, const bf16_t* up, int inter, 
 hipError_t launch_rope_kv_write(const RopeKvArgs& a, hipStream_t stream) {
     if (a.T <= 0) return hipSuccess;
     if (a.n_vtiles < 0 || (a.n_vtiles > 0 && (!a.v_tiles || !a.tok_own_v))) return hipErrorInvalidValue;
-    const int grid = a.T + a.n_vtiles * a.n_kv;
     const int units = ((a.n_q + a.n_kv) * (a.d / 8) + a.n_kv * a.d / 4 + 255) / 256;  // passes of 256 four-column units
-    if (a.planes == 1 && units <= 8) {
+    const int parts = a.T <= kRopePartsMaxTokens ? units : 1;
+    const int grid = a.T * parts + a.n_vtiles * a.n_kv;
+    if (parts == 1 && a.planes == 1 && units <= 8) {
         switch (units) {
             case 1: rope_kv_write_batched_kernel<1><<<grid, 256, 0, stream>>>(a); break;
             case 2: rope_kv_write_batched_kernel<2><<<grid, 256, 0, stream>>>(a); break;
@@ -406,11 +413,11 @@ hipError_t launch_rope_kv_write(const RopeKvArgs& a, hipStream_t stream) {
         return hipGetLastError();
     }
     switch (a.planes) {
-        case 1: rope_kv_write_kernel<1><<<grid, 256, 0, stream>>>(a); break;
-        case 2: rope_kv_write_kernel<2><<<grid, 256, 0, stream>>>(a); break;
-        case 4: rope_kv_write_kernel<4><<<grid, 256, 0, stream>>>(a); break;
-        case 8: rope_kv_write_kernel<8><<<grid, 256, 0, stream>>>(a); break;
-        default: rope_kv_write_kernel<-1><<<grid, 256, 0, stream>>>(a); break;
+        case 1: rope_kv_write_kernel<1><<<grid, 256, 0, stream>>>(a, parts); break;
+        case 2: rope_kv_write_kernel<2><<<grid, 256, 0, stream>>>(a, parts); break;
+        case 4: rope_kv_write_kernel<4><<<grid, 256, 0, stream>>>(a, parts); break;
+        case 8: rope_kv_write_kernel<8><<<grid, 256, 0, stream>>>(a, parts); break;
+        default: rope_kv_write_kernel<-1><<<grid, 256, 0, stream>>>(a, parts); break;
     }
     return hipGetLastError();
 }
