@@ -145,8 +145,9 @@ gllm_status gllm_stage_share_weights(gllm_stage* stage, const gllm_stage* owner)
 gllm_status gllm_stage_set_alias_check(gllm_stage* stage, int32_t on);
 
 /* Tuning knobs (defaults are chosen for MI355X).  Known names:
- *   "decode_min_workgroups" (default 2048): a partition size (256 .. 16384 keys, a power of two) is chosen as
- *   the largest for which partitions x KV heads reaches this many workgroups; a decode row with more keys than
+ *   "decode_min_workgroups" (at least 1; unset by default): a partition size (256 .. 16384 keys, a power of two) is chosen
+ *   as the largest for which partitions x KV heads reaches this many workgroups.  Unset, it is 1.5 times the keys that each
+ *   of the chip's workgroup slots gets on average, at least 256.  A decode row with more keys than
  *   that is cut into equal shares of whole 32-key blocks, and the longest shares are launched first.
  *   "overlap_attention" (default 1): prefill and decode attention of a layer share one launch where the prefill part is
  *   small; 0 always launches them one after the other, as per-kernel profiling does.  The results are the same bits.

@@ -38,6 +38,7 @@ struct LayerBuffers {
 };
 
 constexpr int kStagingSlots = 4;
+constexpr int kDecodeSlots = 512;  // decode attention workgroups that run at one time
 constexpr int kMaxSplits = kMaxPlanes;
 
 struct MetaLayout {  // offsets in bytes inside the metadata block (host staging and device copy alike)
@@ -83,7 +84,7 @@ struct gllm_stage {
     bool alias_check = true;
     bool gemm_row_mixed = true;  // the GEMM planner may cover a short last row band with 64- or 128-row tiles
     int layer_begin = 0, layer_end = 0;  // forward() runs layers [layer_begin, layer_end) (layer_end is set at creation)
-    int64_t decode_min_workgroups = 2048;  // partition the keys of decode rows until at least this many workgroups exist
+    int64_t decode_min_workgroups = 0;  // > 0: partition the keys of decode rows until at least this many workgroups exist
     // profiling
     bool profiling = false;
     struct Span { int cls; hipEvent_t a, b; };
@@ -510,11 +511,19 @@ gllm_status gllm_stage_forward(gllm_stage* s, const gllm_batch* b, const void* h
                 if (b->new_tokens[i] == 1) n += ceil_div((int64_t)b->cached_len[i] + 1, P);
             return n;
         };
-        // largest partition that still yields a few workgroups per compute unit
-        const int64_t want = s->decode_min_workgroups;
-        part = 256;
-        for (int P = 16384; P >= 256; P >>= 1)
-            if (items_for(P) * c.n_kv_heads >= want) { part = P; break; }
+        if (s->decode_min_workgroups > 0) {
+            for (int P = 16384; P >= 256; P >>= 1)
+                if (items_for(P) * c.n_kv_heads >= s->decode_min_workgroups) { part = P; break; }
+        } else {
+            // a row is cut only where its share would hold up the launch: where it is more than 1.5 times what each of the
+            // workgroup slots gets on average (two per compute unit).  Against partitions of at least 2048 workgroups:
+            // 128 rows of 512 .. 4096 keys 2682 -> 2571 us per batch (8 layers), 64 rows of 1500 .. 3500 keys 1735 -> 1699,
+            // 40 rows of 256 .. 8192 keys 606 -> 588 (3 layers); rows never cut: 681 there.
+            int64_t keys = 0;
+            for (int i = 0; i < S; ++i)
+                if (b->new_tokens[i] == 1) keys += (int64_t)b->cached_len[i] + 1;
+            part = (int)std::max<int64_t>(256, round_up(ceil_div(keys * c.n_kv_heads * 3, 2 * kDecodeSlots), 32));
+        }
         while (items_for(part) > s->max_items) part <<= 1;
     }
 
