@@ -62,9 +62,11 @@ int gemm_rowmix_rem_rows(int m, int n);
 struct GemmPlan { int tile; int splits; };
 GemmPlan gemm_plan(int m, int n, int k, int mode, int max_splits, bool row_mixed = true, bool read_planes = false);
 
-// Residual stream entry: x = float(in_bf16), h = bf16(rmsnorm(x) * gamma).
+// Residual stream entry: x = float(in_bf16), h = bf16(rmsnorm(x) * gamma).  The launch also copies copy_bytes (a multiple
+// of 16) from copy_src, which may be pinned host memory, to copy_dst; both 16-byte aligned.
 hipError_t launch_rmsnorm_from_bf16(const bf16_t* in, float* x, const bf16_t* gamma, bf16_t* h, int64_t ldh,
-                                    int rows, int hidden, float eps, hipStream_t stream);
+                                    int rows, int hidden, float eps, const void* copy_src, void* copy_dst, size_t copy_bytes,
+                                    hipStream_t stream);
 // x += y[0] + ... + y[planes-1] (planes may be 0; plane p at y + p*plane_stride), then
 // h = bf16(rmsnorm(x) * gamma).  x is updated in place when planes > 0.
 hipError_t launch_add_rmsnorm(float* x, const float* y, int planes, int64_t plane_stride, const bf16_t* gamma,

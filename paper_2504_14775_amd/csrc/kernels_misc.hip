@@ -22,8 +22,17 @@ __device__ __forceinline__ float block_sum_256(float v, float* red /*[4]*/) {
     return t;
 }
 
+// What an rmsnorm launch copies on the side: `vecs` 16-byte pieces, kCopyVecs per thread.
+constexpr int kCopyVecs = 4;
+struct CopyIn {
+    const u32x4* src;
+    u32x4* dst;
+    int vecs, workgroups;
+};
+
 // One workgroup per row.  FROM_BF16: the row comes from the bf16 stage input and is also written out
-// as the fp32 residual stream.  Otherwise the row is the fp32 residual stream plus `planes` partial
+// as the fp32 residual stream; the workgroups in front of the rows' bring the batch's metadata from pinned host memory to
+// the device (see CopyIn), beside the rows and without a launch or a copy engine of its own.  Otherwise the row is the fp32 residual stream plus `planes` partial
 // GEMM outputs (summed in plane order and written back), so the residual add costs no extra pass.
 // The row is kept in registers between the two phases (MAXV 16-byte pieces per thread).  PLANES >= 0 fixes the
 // number of planes at compile time (the loop unrolls and all loads of a piece are issued together: with a few
@@ -32,9 +41,23 @@ template <bool FROM_BF16, int MAXV, int PLANES>
 __global__ __launch_bounds__(256) void rmsnorm_kernel(const bf16_t* __restrict__ in, float* __restrict__ x,
                                                        const float* __restrict__ y, int planes, int64_t plane_stride,
                                                        const bf16_t* __restrict__ gamma, bf16_t* __restrict__ h,
-                                                       int64_t ldh, int hidden, float eps) {
+                                                       int64_t ldh, int hidden, float eps, CopyIn copy) {
     __shared__ float red[4];
-    const int64_t row = blockIdx.x;
+    int64_t row = blockIdx.x;
+    if constexpr (FROM_BF16) {
+        if ((int)blockIdx.x < copy.workgroups) {
+            u32x4 v[kCopyVecs];
+            const int i0 = blockIdx.x * (256 * kCopyVecs) + threadIdx.x;
+#pragma unroll
+            for (int k = 0; k < kCopyVecs; ++k)
+                if (i0 + k * 256 < copy.vecs) v[k] = copy.src[i0 + k * 256];
+#pragma unroll
+            for (int k = 0; k < kCopyVecs; ++k)
+                if (i0 + k * 256 < copy.vecs) copy.dst[i0 + k * 256] = v[k];
+            return;
+        }
+        row -= copy.workgroups;
+    }
     float* xr = x + row * hidden;
     f32x4 keep[MAXV];
     float ss = 0.f;
@@ -332,11 +355,11 @@ __global__ __launch_bounds__(256) void rope_kv_write_batched_kernel(RopeKvArgs a
 template <bool FROM_BF16>
 hipError_t launch_rmsnorm_any(const bf16_t* in, float* x, const float* y, int planes, int64_t plane_stride,
                               const bf16_t* gamma, bf16_t* h, int64_t ldh, int rows, int hidden, float eps,
-                              hipStream_t stream) {
+                              const CopyIn& copy, hipStream_t stream) {
     if (rows <= 0) return hipSuccess;
     if (hidden % 4 != 0 || hidden > 16 * 1024 || planes < 0 || planes > kMaxPlanes) return hipErrorInvalidValue;
     const int vecs = (int)ceil_div(hidden, 1024);
-#define GLLM_RMS_P(V, P) rmsnorm_kernel<FROM_BF16, V, P><<<rows, 256, 0, stream>>>(in, x, y, planes, plane_stride, gamma, h, ldh, hidden, eps)
+#define GLLM_RMS_P(V, P) rmsnorm_kernel<FROM_BF16, V, P><<<rows + copy.workgroups, 256, 0, stream>>>(in, x, y, planes, plane_stride, gamma, h, ldh, hidden, eps, copy)
 #define GLLM_RMS(V)                                              \
     do {                                                         \
         if (FROM_BF16 || planes == 0) GLLM_RMS_P(V, 0);          \
@@ -358,13 +381,16 @@ hipError_t launch_rmsnorm_any(const bf16_t* in, float* x, const float* y, int pl
 }
 
 hipError_t launch_rmsnorm_from_bf16(const bf16_t* in, float* x, const bf16_t* gamma, bf16_t* h, int64_t ldh,
-                                    int rows, int hidden, float eps, hipStream_t stream) {
-    return launch_rmsnorm_any<true>(in, x, nullptr, 0, 0, gamma, h, ldh, rows, hidden, eps, stream);
+                                    int rows, int hidden, float eps, const void* copy_src, void* copy_dst, size_t copy_bytes,
+                                    hipStream_t stream) {
+    const CopyIn copy{(const u32x4*)copy_src, (u32x4*)copy_dst, (int)(copy_bytes / 16), (int)ceil_div(copy_bytes / 16, 256 * kCopyVecs)};
+    if (copy_bytes % 16 != 0 || copy_bytes / 16 > INT32_MAX / 2 || (((uintptr_t)copy_src | (uintptr_t)copy_dst) & 15)) return hipErrorInvalidValue;
+    return launch_rmsnorm_any<true>(in, x, nullptr, 0, 0, gamma, h, ldh, rows, hidden, eps, copy, stream);
 }
 
 hipError_t launch_add_rmsnorm(float* x, const float* y, int planes, int64_t plane_stride, const bf16_t* gamma,
                               bf16_t* h, int64_t ldh, int rows, int hidden, float eps, hipStream_t stream) {
-    return launch_rmsnorm_any<false>(nullptr, x, y, planes, plane_stride, gamma, h, ldh, rows, hidden, eps, stream);
+    return launch_rmsnorm_any<false>(nullptr, x, y, planes, plane_stride, gamma, h, ldh, rows, hidden, eps, CopyIn{}, stream);
 }
 
 hipError_t launch_add_cast_out(const float* x, const float* y, int planes, int64_t plane_stride, bf16_t* out,
