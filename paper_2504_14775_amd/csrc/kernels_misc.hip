@@ -11,14 +11,16 @@ __device__ __forceinline__ float wave_sum(float v) {
     return v;
 }
 
-// Sum over the 256 threads of a workgroup; every thread receives the total.
-__device__ __forceinline__ float block_sum_256(float v, float* red /*[4]*/) {
+// Sum over the THREADS threads of a workgroup; every thread receives the total.
+template <int THREADS>
+__device__ __forceinline__ float block_sum(float v, float* red /*[THREADS / 64]*/) {
     v = wave_sum(v);
     int w = threadIdx.x >> 6;
     if ((threadIdx.x & 63) == 0) red[w] = v;
     __syncthreads();
-    float t = red[0] + red[1] + red[2] + red[3];
-    __syncthreads();
+    float t = 0.f;
+#pragma unroll
+    for (int i = 0; i < THREADS / 64; ++i) t += red[i];
     return t;
 }
 
@@ -37,23 +39,23 @@ struct CopyIn {
 // The row is kept in registers between the two phases (MAXV 16-byte pieces per thread).  PLANES >= 0 fixes the
 // number of planes at compile time (the loop unrolls and all loads of a piece are issued together: with a few
 // hundred rows the kernel is all latency); PLANES < 0 takes it from the argument.
-template <bool FROM_BF16, int MAXV, int PLANES>
-__global__ __launch_bounds__(256) void rmsnorm_kernel(const bf16_t* __restrict__ in, float* __restrict__ x,
+template <bool FROM_BF16, int MAXV, int PLANES, int THREADS>
+__global__ __launch_bounds__(THREADS) void rmsnorm_kernel(const bf16_t* __restrict__ in, float* __restrict__ x,
                                                        const float* __restrict__ y, int planes, int64_t plane_stride,
                                                        const bf16_t* __restrict__ gamma, bf16_t* __restrict__ h,
                                                        int64_t ldh, int hidden, float eps, CopyIn copy) {
-    __shared__ float red[4];
+    __shared__ float red[THREADS / 64];
     int64_t row = blockIdx.x;
     if constexpr (FROM_BF16) {
         if ((int)blockIdx.x < copy.workgroups) {
             u32x4 v[kCopyVecs];
-            const int i0 = blockIdx.x * (256 * kCopyVecs) + threadIdx.x;
+            const int i0 = blockIdx.x * (THREADS * kCopyVecs) + threadIdx.x;
 #pragma unroll
             for (int k = 0; k < kCopyVecs; ++k)
-                if (i0 + k * 256 < copy.vecs) v[k] = copy.src[i0 + k * 256];
+                if (i0 + k * THREADS < copy.vecs) v[k] = copy.src[i0 + k * THREADS];
 #pragma unroll
             for (int k = 0; k < kCopyVecs; ++k)
-                if (i0 + k * 256 < copy.vecs) copy.dst[i0 + k * 256] = v[k];
+                if (i0 + k * THREADS < copy.vecs) copy.dst[i0 + k * THREADS] = v[k];
             return;
         }
         row -= copy.workgroups;
@@ -63,7 +65,7 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(const bf16_t* __restrict__
     float ss = 0.f;
 #pragma unroll
     for (int i = 0; i < MAXV; ++i) {
-        const int j = (threadIdx.x + i * 256) * 4;
+        const int j = (threadIdx.x + i * THREADS) * 4;
         f32x4 v = {0.f, 0.f, 0.f, 0.f};
         if (j < hidden) {
             if (FROM_BF16) {
@@ -93,16 +95,16 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(const bf16_t* __restrict__
     f32x4 gain[MAXV];
 #pragma unroll
     for (int i = 0; i < MAXV; ++i) {
-        const int j = (threadIdx.x + i * 256) * 4;
+        const int j = (threadIdx.x + i * THREADS) * 4;
         gain[i] = f32x4{0.f, 0.f, 0.f, 0.f};
         if (j < hidden) gain[i] = __builtin_convertvector(*reinterpret_cast<const bf16x4*>(gamma + j), f32x4);
     }
-    const float total = block_sum_256(ss, red);
+    const float total = block_sum<THREADS>(ss, red);
     const float inv = 1.0f / sqrtf(total / (float)hidden + eps);
     bf16_t* hr = h + row * ldh;
 #pragma unroll
     for (int i = 0; i < MAXV; ++i) {
-        const int j = (threadIdx.x + i * 256) * 4;
+        const int j = (threadIdx.x + i * THREADS) * 4;
         if (j < hidden) {
             f32x4 o;
 #pragma unroll
@@ -352,29 +354,47 @@ __global__ __launch_bounds__(256) void rope_kv_write_batched_kernel(RopeKvArgs a
 
 }  // namespace
 
+// Few rows: one workgroup per row leaves most of the chip idle and the kernel is the latency of one row, so a row gets 1024
+// threads, one 16-byte piece of every plane each (64 rows of 4096, 8 planes 5.8 -> 5.1 us, 197 rows, 4 planes 7.7 -> 6.4).
+// From 257 rows on every compute unit has a row and it makes no difference (322 rows: 7.2 / 7.1 us, 4 planes 8.7 / 9.0).
+constexpr int kWideRmsMaxRows = 256;
+
 template <bool FROM_BF16>
 hipError_t launch_rmsnorm_any(const bf16_t* in, float* x, const float* y, int planes, int64_t plane_stride,
                               const bf16_t* gamma, bf16_t* h, int64_t ldh, int rows, int hidden, float eps,
                               const CopyIn& copy, hipStream_t stream) {
     if (rows <= 0) return hipSuccess;
     if (hidden % 4 != 0 || hidden > 16 * 1024 || planes < 0 || planes > kMaxPlanes) return hipErrorInvalidValue;
-    const int vecs = (int)ceil_div(hidden, 1024);
-#define GLLM_RMS_P(V, P) rmsnorm_kernel<FROM_BF16, V, P><<<rows + copy.workgroups, 256, 0, stream>>>(in, x, y, planes, plane_stride, gamma, h, ldh, hidden, eps, copy)
-#define GLLM_RMS(V)                                              \
-    do {                                                         \
-        if (FROM_BF16 || planes == 0) GLLM_RMS_P(V, 0);          \
-        else if (planes == 1) GLLM_RMS_P(V, 1);                  \
-        else if (planes == 2) GLLM_RMS_P(V, 2);                  \
-        else if (planes == 4) GLLM_RMS_P(V, 4);                  \
-        else if (planes == 8) GLLM_RMS_P(V, 8);                  \
-        else GLLM_RMS_P(V, -1);                                  \
+#define GLLM_RMS_P(V, P, N)                                                                                              \
+    do {                                                                                                                 \
+        const int copy_wgs = (int)ceil_div(copy.vecs, N * kCopyVecs);                                                      \
+        CopyIn c = copy;                                                                                                 \
+        c.workgroups = copy_wgs;                                                                                         \
+        rmsnorm_kernel<FROM_BF16, V, P, N><<<rows + copy_wgs, N, 0, stream>>>(in, x, y, planes, plane_stride, gamma, h, ldh, hidden, eps, c); \
     } while (0)
-    if (vecs <= 1) GLLM_RMS(1);
-    else if (vecs <= 2) GLLM_RMS(2);
-    else if (vecs <= 4) GLLM_RMS(4);
-    else if (vecs <= 5) GLLM_RMS(5);
-    else if (vecs <= 8) GLLM_RMS(8);
-    else GLLM_RMS(16);
+#define GLLM_RMS(V, N)                                           \
+    do {                                                         \
+        if (FROM_BF16 || planes == 0) GLLM_RMS_P(V, 0, N);       \
+        else if (planes == 1) GLLM_RMS_P(V, 1, N);               \
+        else if (planes == 2) GLLM_RMS_P(V, 2, N);               \
+        else if (planes == 4) GLLM_RMS_P(V, 4, N);               \
+        else if (planes == 8) GLLM_RMS_P(V, 8, N);               \
+        else GLLM_RMS_P(V, -1, N);                               \
+    } while (0)
+    if (rows <= kWideRmsMaxRows && hidden > 1024) {
+        const int vecs = (int)ceil_div(hidden, 4096);
+        if (vecs <= 1) GLLM_RMS(1, 1024);
+        else if (vecs <= 2) GLLM_RMS(2, 1024);
+        else GLLM_RMS(4, 1024);
+        return hipGetLastError();
+    }
+    const int vecs = (int)ceil_div(hidden, 1024);
+    if (vecs <= 1) GLLM_RMS(1, 256);
+    else if (vecs <= 2) GLLM_RMS(2, 256);
+    else if (vecs <= 4) GLLM_RMS(4, 256);
+    else if (vecs <= 5) GLLM_RMS(5, 256);
+    else if (vecs <= 8) GLLM_RMS(8, 256);
+    else GLLM_RMS(16, 256);
 #undef GLLM_RMS
 #undef GLLM_RMS_P
     return hipGetLastError();
@@ -383,7 +403,7 @@ hipError_t launch_rmsnorm_any(const bf16_t* in, float* x, const float* y, int pl
 hipError_t launch_rmsnorm_from_bf16(const bf16_t* in, float* x, const bf16_t* gamma, bf16_t* h, int64_t ldh,
                                     int rows, int hidden, float eps, const void* copy_src, void* copy_dst, size_t copy_bytes,
                                     hipStream_t stream) {
-    const CopyIn copy{(const u32x4*)copy_src, (u32x4*)copy_dst, (int)(copy_bytes / 16), (int)ceil_div(copy_bytes / 16, 256 * kCopyVecs)};
+    const CopyIn copy{(const u32x4*)copy_src, (u32x4*)copy_dst, (int)(copy_bytes / 16), 0};
     if (copy_bytes % 16 != 0 || copy_bytes / 16 > INT32_MAX / 2 || (((uintptr_t)copy_src | (uintptr_t)copy_dst) & 15)) return hipErrorInvalidValue;
     return launch_rmsnorm_any<true>(in, x, nullptr, 0, 0, gamma, h, ldh, rows, hidden, eps, copy, stream);
 }
