@@ -194,7 +194,8 @@ const char* gllm_profile_class_name(int32_t i);
 gllm_status gllm_op_pack_weight(const void* w, int64_t ldw, int32_t n, int32_t k, void* out, void* stream);
 
 /* out[m][n] (op)= sum_k a[m][k] * w[n][k];  a: bf16 [m_rows][lda] with lda >= k, w: bf16, n rows, tiled as above with
- * k extent ldw (a multiple of 64, >= k, below 2^23: the product may use a leading part of the k range).
+ * k extent ldw (a multiple of 64, >= k: the product may use a leading part of the k range).  Rows of a that start off a
+ * 4-byte boundary are multiplied by a plain, slow kernel.
  * Requirements: k a multiple of 64 and n a multiple of 128 (the stage pads its operands);
  * a must be readable for round_up(m,256) rows.  mode: 0 store fp32 to out[m][ldc];
  * 1 add into fp32 out[m][ldc]; 2 SwiGLU: columns come in groups of 64 = 32 gate + 32 up

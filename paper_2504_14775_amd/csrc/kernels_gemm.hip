@@ -9,7 +9,7 @@
 // What bounds it: many rows, the 1400 W power limit (a bare MFMA loop on random operands reaches 1.6-1.8 PFLOP/s); few
 // rows, the stream of the weights (5.5-6 TB/s) and the ~5 us a launch costs before and after it; in between both.  Under
 // the power limit the clock follows the busy share of the matrix cores, so cycles in the k-loop count in full.  Four
-// waves with a wave tile of 128x128 read each operand from LDS half as often as eight of 128x64, and with the order of
+// waves with a wave tile of 128x128 read LDS two thirds as often per MFMA as eight of 128x64, and with the order of
 // MFMAs, LDS reads and global loads written out (see step) the loop has nothing in it that is not hidden under MFMAs:
 // 4096x8192x8192 437 -> 386 us (1257 -> 1426 TFLOP/s), gate/up at 2048 rows 406 -> 372, at 197 rows 74 -> 56, at 322
 // rows 100 -> 77, the down projection at 2048 rows 200 -> 175, at 197 rows 42 -> 35, at 322 rows 71 -> 44 us.
@@ -342,6 +342,30 @@ __global__ __launch_bounds__(256) void gemm_bf16_rowmix_kernel(const bf16_t* __r
                                            split_stride, bands * 256);
 }
 
+// Operands that the tiles cannot address: a row of A or the start of W off a 4-byte boundary (what a buffer load needs), or
+// a weight panel of 4 GiB and more.  One thread per result, products summed in order of k; such operands come from
+// callers' views, not from the stage or the head, so this is for completeness and not for speed.
+template <int MODE>
+__global__ __launch_bounds__(256) void gemm_any_address_kernel(const bf16_t* __restrict__ A, int64_t lda, const bf16_t* __restrict__ W,
+                                                                int64_t ldw, void* __restrict__ out, int64_t ldc, int M, int cols, int K,
+                                                                int64_t split_stride) {
+    const int64_t at = (int64_t)blockIdx.x * 256 + threadIdx.x, m = at / cols;
+    const int c = (int)(at % cols);
+    if (m >= M) return;
+    const int share = K / (int)gridDim.y, k0 = share * (int)blockIdx.y;
+    const int64_t row = MODE == GEMM_SWIGLU_BF16 ? c / kSwigluGroup * (2 * kSwigluGroup) + c % kSwigluGroup : c;
+    float sum = 0.f, up = 0.f;
+    for (int k = k0; k < k0 + share; ++k) {
+        const float x = (float)A[m * lda + k];
+        sum += x * (float)W[w_tiled_index(row, k, ldw)];
+        if (MODE == GEMM_SWIGLU_BF16) up += x * (float)W[w_tiled_index(row + kSwigluGroup, k, ldw)];
+    }
+    float* f = reinterpret_cast<float*>(out) + blockIdx.y * split_stride + m * ldc + c;
+    if (MODE == GEMM_SWIGLU_BF16) reinterpret_cast<bf16_t*>(out)[m * ldc + c] = (bf16_t)(silu(sum) * up);
+    else if (MODE == GEMM_ADD_F32) *f += sum;
+    else *f = sum;
+}
+
 template <int BM, int BN, int WGM, int WGN, int MODE, int NS, int NSW, bool W_ONCE>
 hipError_t launch_tile_w(const bf16_t* a, int64_t lda, const bf16_t* w, int64_t ldw, void* out, int64_t ldc, int m,
                          int n, int k, int splits, int64_t split_stride, hipStream_t stream) {
@@ -548,8 +572,24 @@ hipError_t launch_gemm_bf16(const bf16_t* a, int64_t lda, const bf16_t* w, int64
     if (m <= 0) return hipSuccess;
     if (n <= 0 || k <= 0 || n % 64 != 0 || k % BK != 0) return hipErrorInvalidValue;
     if (lda * 16 >= (int64_t)1 << 31 || ldw % kWBlock != 0 || ldw < k) return hipErrorInvalidValue;
-    // the kernels address the rows of a tile and a tile's weight panel by 32-bit byte offsets
-    if (ldw >= (int64_t)1 << 23) return hipErrorInvalidValue;
+    if (splits < 1 || (k / BK) % splits != 0) return hipErrorInvalidValue;
+    if (splits > 1 && mode != GEMM_STORE_F32) return hipErrorInvalidValue;
+    if (tile < 0) {
+        tile = cheapest(m, n, k, splits == 1 ? mode : GEMM_STORE_F32, splits, splits, true, false).tile;
+    }
+    if ((((uintptr_t)a | (uintptr_t)w) & 3) || (m > 1 && lda % 2 != 0) || ldw >= (int64_t)1 << 23) {
+        if (n % 128 != 0) return hipErrorInvalidValue;
+        const int cols = mode == GEMM_SWIGLU_BF16 ? n / 2 : n;
+        const int64_t blocks = ceil_div((int64_t)m * cols, 256);
+        if (blocks > 0x7FFFFFFF) return hipErrorInvalidValue;
+        const dim3 grid((unsigned)blocks, splits);
+        if (mode == GEMM_STORE_F32) gemm_any_address_kernel<GEMM_STORE_F32><<<grid, 256, 0, stream>>>(a, lda, w, ldw, out, ldc, m, cols, k, split_stride);
+        else if (mode == GEMM_ADD_F32) gemm_any_address_kernel<GEMM_ADD_F32><<<grid, 256, 0, stream>>>(a, lda, w, ldw, out, ldc, m, cols, k, split_stride);
+        else if (mode == GEMM_SWIGLU_BF16) gemm_any_address_kernel<GEMM_SWIGLU_BF16><<<grid, 256, 0, stream>>>(a, lda, w, ldw, out, ldc, m, cols, k, split_stride);
+        else return hipErrorInvalidValue;
+        return hipGetLastError();
+    }
+    // the kernels address the rows of a tile by 32-bit byte offsets
     const int64_t rows32 = (((int64_t)1 << 32) - 1) / (2 * std::max<int64_t>(lda, 1));
     if (m > rows32 && rows32 < kMaxTileM) {
         const int elem = mode == GEMM_SWIGLU_BF16 ? 2 : 4;
@@ -559,11 +599,6 @@ hipError_t launch_gemm_bf16(const bf16_t* a, int64_t lda, const bf16_t* w, int64
             if (e != hipSuccess) return e;
         }
         return hipSuccess;
-    }
-    if (splits < 1 || (k / BK) % splits != 0) return hipErrorInvalidValue;
-    if (splits > 1 && mode != GEMM_STORE_F32) return hipErrorInvalidValue;
-    if (tile < 0) {
-        tile = cheapest(m, n, k, splits == 1 ? mode : GEMM_STORE_F32, splits, splits, true, false).tile;
     }
     if (tile == 8 || tile == 12) {
         const int rem_rows = gemm_rowmix_rem_rows(m, n);

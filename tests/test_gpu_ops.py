@@ -260,6 +260,38 @@ def test_gemm_tiles_at_their_edges(tile, K):
         assert np.all(got[M:] == 7.0)
 
 
+@pytest.mark.parametrize("mode", ["store", "add", "swiglu", "split"])
+def test_gemm_rows_off_a_four_byte_boundary(mode):
+    """An odd row stride and an operand that starts two bytes behind a boundary: the tiles cannot load these rows."""
+    M, N, K = 37, 256, 128
+    a, w = rand_bits(14, 1, (M, K), 1.0), rand_bits(14, 2, (N, K), 0.05)
+    x, y = oracle.bf16_to_f64(a), oracle.bf16_to_f64(w)
+    bound = (np.abs(x) @ np.abs(y).T) * K * 2.0 ** -24
+    for ld, start in ((K + 1, 0), (K + 2, 1)):
+        print(f"gemm unaligned rows mode={mode} ld={ld} start={start}", flush=True)
+        da = torch.zeros(M * ld + 1, dtype=torch.bfloat16, device=DEV)[start:].as_strided((M, K), (ld, 1))
+        da.copy_(to_dev_bits(a).view(torch.bfloat16))
+        dw = to_dev_weight(w)
+        out = torch.full((M, N), 2.0, dtype=torch.float32, device=DEV)
+        if mode == "split":
+            planes = torch.zeros((2, M, N), dtype=torch.float32, device=DEV)
+            B.gllm_op_gemm_bf16_splitk(da, dw, planes, M, N, K, -1, 2)
+            out = planes.sum(dim=0)
+        elif mode == "swiglu":
+            out = torch.zeros((M, N // 2), dtype=torch.bfloat16, device=DEV)
+            B.gllm_op_gemm_bf16(da, dw, out, M, N, K, B.GEMM_SWIGLU_BF16)
+        else:
+            B.gllm_op_gemm_bf16(da, dw, out, M, N, K, B.GEMM_STORE_F32 if mode == "store" else B.GEMM_ADD_F32)
+        torch.cuda.synchronize()
+        if mode == "swiglu":
+            gate, up = (np.concatenate([y[64 * b + o:64 * b + o + 32] for b in range(N // 64)]) for o in (0, 32))
+            ref = oracle.swiglu(x @ gate.T, x @ up.T)
+            assert np.all(np.abs(oracle.bf16_to_f64(bits_of(out)) - ref) <= np.abs(ref) * 2.0 ** -7 + 1e-4)
+        else:
+            got = out.cpu().numpy().astype(np.float64) - (2.0 if mode == "add" else 0.0)
+            assert np.all(np.abs(got - x @ y.T) <= bound + 2.0 ** -22)
+
+
 def test_gemm_rows_farther_apart_than_32_bit_offsets_reach():
     """A row stride of 2^23 elements: 300 rows span more than 4 GiB, which the launch cuts into bands."""
     M, N, K, ld = 300, 256, 128, 1 << 23
