@@ -80,6 +80,13 @@ def test_rmsnorm(T, H):
     assert np.all(np.abs(got - ref) <= np.abs(ref) * 2.0 ** -8 * 1.01 + 1e-6)
 
 
+@pytest.mark.parametrize("T,H", [(1, 1024), (1, 1028), (200, 4100), (256, 8192), (257, 8192), (256, 16384), (257, 16384)])
+def test_rmsnorm_rows_and_widths_at_the_edges_of_its_forms(T, H):
+    """Up to 256 rows a row has 1024 threads, more rows or at most 1024 columns 256: both sides of each edge, same bound as
+    above (one rounding to bf16, plus 1 % of it for the fp32 sum)."""
+    test_rmsnorm(T, H)
+
+
 @pytest.mark.parametrize("M,N,K", [(300, 768, 192), (2, 192, 64), (513, 1536, 128)])
 def test_gemm_256x192_tile(M, N, K):
     print(f"gemm 256x192 tile M={M} N={N} K={K}", flush=True)

@@ -186,6 +186,37 @@ def test_decode_rows_whole_or_partitioned_match_the_oracle(min_wgs):
     assert np.abs(r["out32"] - base32.cpu().numpy()).max() <= 1e-3 * max(1.0, rms)
 
 
+@pytest.mark.parametrize("chunks", [[(2, 0)], [(40, 9), (17, 100)], [(1100, 70)]])
+def test_prefill_and_decode_attention_in_one_launch_or_two_give_the_same_bits(chunks):
+    """A prefill part of a few workgroups shares the launch of the decode rows, a large one does not; the option
+    overlap_attention = 0 keeps them apart.  Row and key order, and so every bit, are the same."""
+    print(f"one launch or two, chunks {chunks}", flush=True)
+    one_layer = dataclasses.replace(MID, num_layers=1, name="mid1")
+    batch = synth.build_batch(chunks + [(1, 0), (1, 300), (1, 1500), (1, 31)], 13, spare_blocks=5, label="one")
+    w = layer_weights_np(one_layer, 13)
+    kp0, vp0 = pool_np(one_layer, 13, batch.num_blocks)
+    x = hidden_np(one_layer, 13, batch.num_tokens)
+    outs = []
+    for overlap in (1, 0):
+        stage = GpuStage(one_layer, w, [batch])
+        stage.stage.set_option("overlap_attention", overlap)
+        outs.append(stage.run(batch, to_dev_bits(kp0), to_dev_bits(vp0), to_dev_bits(x))[1].clone())
+    torch.cuda.synchronize()
+    assert torch.equal(outs[0], outs[1])
+
+
+def test_decode_rows_of_very_different_lengths_match_the_oracle():
+    """The default rule cuts a row only where it has far more keys than the others: a long one among short ones is cut, rows
+    of like length are not."""
+    print("decode rows of very different lengths", flush=True)
+    one_layer = dataclasses.replace(MID, num_layers=1, name="mid1")
+    batch = synth.build_batch([(1, 3000)] + [(1, 7 + 5 * i) for i in range(30)], 15, spare_blocks=5, label="skew")
+    w = layer_weights_np(one_layer, 15)
+    kp0, vp0 = pool_np(one_layer, 15, batch.num_blocks)
+    r = run_both(one_layer, w, batch, kp0, vp0, hidden_np(one_layer, 15, batch.num_tokens))
+    assert_output("skew", r, literal=False)
+
+
 def test_qkv_bias_and_nan_sentinels_in_unused_slots():
     print("qkv bias + NaN sentinel in never-written slots", flush=True)
     shape = dataclasses.replace(synth.SHAPES["tiny"], has_qkv_bias=True, name="tiny_bias")
