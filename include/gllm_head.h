@@ -84,6 +84,9 @@ size_t gllm_head_static_scratch_bytes(void);
  *   whose mass reaches top_p[i] (top_p >= 1 keeps all; tokens as probable as the last one needed all stay);
  *   draw: the first token, in index order, at which the running sum of kept probabilities exceeds u[i] times their
  *   total, u[i] in [0, 1) supplied by the caller (the library draws no random numbers).
+ *   A logit that is not a number is never drawn, nor does it count among the top_k.  Where the softmax is not defined --
+ *   the largest logit is infinite (a forced token, a row masked as a whole), or the temperature so small that its
+ *   reciprocal overflows -- the row is sampled greedily; a row without any logit above -infinity gives token 0.
  *   logits DEVICE float [num_rows][ld_logits]; temperature, top_p, u DEVICE float [num_rows]; top_k DEVICE int32
  *   [num_rows]; out_ids DEVICE int32 [num_rows].  vocab <= 2^24. */
 gllm_status gllm_op_sample(const float* logits, int64_t ld_logits, int32_t num_rows, int32_t vocab,

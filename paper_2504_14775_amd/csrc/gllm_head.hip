@@ -197,10 +197,11 @@ __device__ __forceinline__ void add_to_bin(SampleShared& sh, uint32_t digit, uin
 }
 
 // The largest digit d with weight(digits >= d) >= need, and the weight above it; digit 0 when the whole does not reach
-// `need`.  Called when every thread has added its weights; leaves the bins cleared for the next selection.
+// `need`, and a need of 0 counts as 1: whatever the weights, exactly one thread writes the result.  Called when every thread has added its weights; leaves the bins cleared for the next selection.
 __device__ __forceinline__ uint32_t find_bin(SampleShared& sh, uint64_t need, uint64_t& above) {
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    need = need > 0 ? need : 1;
     __syncthreads();
     // thread t owns the t-th quadruple of digits counted from the top
     const int quad = kSampleThreads - 1 - tid;
@@ -425,7 +426,7 @@ __global__ __launch_bounds__(kSampleThreads, 8) void sample_kernel(const float* 
         own_max = fmaxf(own_max, v);
         const bool in = v >= bound;
         if (in) push(i, v);
-        if (!by_k) rest += in ? 0.f : __builtin_amdgcn_exp2f((v - ref) * c);
+        if (!by_k) rest += in ? 0.f : fmaxf(__builtin_amdgcn_exp2f((v - ref) * c), 0.f);
     };
     // a bound on logits from a key: division by the temperature may round smaller logits to the same z (they tie)
     auto bound_of = [&](uint32_t key) {
@@ -460,9 +461,19 @@ __global__ __launch_bounds__(kSampleThreads, 8) void sample_kernel(const float* 
         for_row<4>(lg, vocab, [&](int, float v) { own_max = fmaxf(own_max, v); }, no_end);
     }
     const float best = block_max(sh, own_max);
-    // probability of a token relative to the most probable one; a mass is that in units of 1 / mass_one
-    auto prob = [&](float v) { return __builtin_amdgcn_exp2f((v - best) * c); };
+    // probability of a token relative to the most probable one (0 for a logit that is no number); a mass is that in units
+    // of 1 / mass_one
+    auto prob = [&](float v) { return fmaxf(__builtin_amdgcn_exp2f((v - best) * c), 0.f); };
     auto mass = [&](float v) { return (uint64_t)(prob(v) * mass_one); };
+    // Nothing has mass where the largest logit is infinite (a forced token, a row that is masked as a whole) or the
+    // temperature so small that its reciprocal overflows: the row goes to its largest logit.  Past this point the token
+    // with logit `best` has mass_one, on the list and on the row.
+    if (!(prob(best) > 0.f)) {
+        __syncthreads();
+        const int best_i = row_argmax(sh, lg, vocab);
+        if (tid == 0) out[row] = best_i;
+        return;
+    }
 
     // Finishes the row on the list of n candidates; false when the guess of a nucleus does not hold.
     auto finish_on_list = [&](int n, float others) -> bool {

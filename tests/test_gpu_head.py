@@ -192,3 +192,36 @@ def test_sampler_at_the_edges_of_its_paths(V, sigma, k, p):
     u[0], u[3] = 0.0, np.float32(1.0 - 2 ** -24)
     full = lambda v, t: np.full(M, v, dtype=t)
     check_against_oracle(lg, full(0.9, np.float32), full(k, np.int32), full(p, np.float32), u, f"edges V={V} k={k} p={p}", slack=1)
+
+
+def largest(row):
+    """Lowest index of the largest logit, NaN left out; 0 when no logit lies above -infinity."""
+    return int(np.argmax(np.where(np.isnan(row), -np.inf, row)))
+
+
+@pytest.mark.parametrize("V", [1, 1000, 4097, 20000, 20001, 70000])
+@pytest.mark.parametrize("k,p", [(0, 1.0), (50, 1.0), (0, 0.9), (50, 0.9), (3000, 1.0), (3000, 0.9)])
+def test_rows_without_a_finite_softmax_go_to_their_largest_logit(V, k, p):
+    """A row masked as a whole, one without a number, one or two infinite logits, a temperature whose reciprocal overflows:
+    nothing of such a row has a mass, and the answer is the greedy one for every k, p and u.  NaN among ordinary logits
+    counts as a masked token."""
+    print(f"sampler: no finite softmax V={V} k={k} p={p}", flush=True)
+    base = (torch.randn(8, V, generator=torch.Generator().manual_seed(V + k)) * 3.0).to(torch.float32)
+    base[0] = -float("inf")
+    base[1] = float("nan")
+    base[2, V // 3] = float("inf")
+    base[3, [V // 2, V - 1]] = float("inf")
+    base[4] = -float("inf")
+    base[4, V - 1] = float("inf")
+    base[5, ::2], base[5, V - 1] = float("nan"), float("inf")
+    temp = np.full(8, 0.8, np.float32)
+    temp[6] = np.float32(1e-40)
+    want = [largest(r) for r in base.numpy()]
+    for u in (0.0, 0.5, float(np.float32(1.0 - 2 ** -24))):
+        got = run_sampler(base.to(DEV), V, temp.tolist(), [k] * 8, [p] * 8, [u] * 8)
+        assert got[:7].tolist() == want[:7], (u, got, want)
+        holes = base[7:].clone()
+        holes[0, 1::3] = float("nan")
+        masked = torch.nan_to_num(holes, nan=-float("inf"))
+        a, b = (run_sampler(x.to(DEV), V, [0.8], [k], [p], [u])[0] for x in (holes, masked))
+        assert a == b and not np.isnan(holes[0, int(a)].item()), (u, a, b)
