@@ -58,9 +58,9 @@ bool gemm_low_bands(int m);
 int gemm_mixed_rem_cols(int m, int n);
 int gemm_rowmix_rem_rows(int m, int n);
 // Tile id and split-K factor the cost model prefers (splits stays 1 unless mode is GEMM_STORE_F32); row_mixed says
-// whether it may pick tile 8, read_planes that the caller reads the result planes back (they then count twice).
+// whether it may pick tile 8.  Result planes count twice: as they are written and as the next kernel reads them back.
 struct GemmPlan { int tile; int splits; };
-GemmPlan gemm_plan(int m, int n, int k, int mode, int max_splits, bool row_mixed = true, bool read_planes = false);
+GemmPlan gemm_plan(int m, int n, int k, int mode, int max_splits, bool row_mixed = true);
 
 // Residual stream entry: x = float(in_bf16), h = bf16(rmsnorm(x) * gamma).  The launch also copies copy_bytes (a multiple
 // of 16) from copy_src, which may be pinned host memory, to copy_dst; both 16-byte aligned.

@@ -634,10 +634,10 @@ gllm_status gllm_stage_forward(gllm_stage* s, const gllm_batch* b, const void* h
     const int64_t y_plane = (int64_t)c.max_tokens * H;
     // tile shapes and split-K factors for this batch size (the consumers sum the partial planes in order)
     const bool rm = s->gemm_row_mixed;
-    const GemmPlan plan_qkv = gemm_plan(Ti, s->n_qkv_pad, H, GEMM_STORE_F32, kMaxSplits, rm, true);
-    const GemmPlan plan_o = gemm_plan(Ti, H, s->q_dim, GEMM_STORE_F32, kMaxSplits, rm, true);
+    const GemmPlan plan_qkv = gemm_plan(Ti, s->n_qkv_pad, H, GEMM_STORE_F32, kMaxSplits, rm);
+    const GemmPlan plan_o = gemm_plan(Ti, H, s->q_dim, GEMM_STORE_F32, kMaxSplits, rm);
     const GemmPlan plan_gu = gemm_plan(Ti, 2 * s->inter_pad, H, GEMM_SWIGLU_BF16, 1, rm);
-    const GemmPlan plan_d = gemm_plan(Ti, H, s->inter_pad, GEMM_STORE_F32, kMaxSplits, rm, true);
+    const GemmPlan plan_d = gemm_plan(Ti, H, s->inter_pad, GEMM_STORE_F32, kMaxSplits, rm);
     const int split_o = plan_o.splits, split_d = plan_d.splits;
     const int64_t qkv_plane = (int64_t)c.max_tokens * s->n_qkv_pad;
     int pending = 0;  // planes of y still to be added to the residual stream

@@ -507,9 +507,9 @@ double rounds_of(const TileCost& c, double tiles) {
 // Tile shape and split-K factor (a power of two in [min_splits, max_splits]) of the lowest cost.  Up to 64 rows the
 // product is a stream of the weights and the 64x128 tile (two workgroups per compute unit, 64 KiB of weights in flight on
 // each, half the activation traffic of a 128-row tile) the only candidate: 0.30 x 1.65 us per k-step of a tile, but not
-// less than the weights take at 5.5 TB/s.  read_planes: the result planes are read back by the next kernel (the stage),
-// so a product that is split less is worth the time of that.
-GemmPlan cheapest(int m, int n, int k, int mode, int min_splits, int max_splits, bool row_mixed, bool read_planes) {
+// less than the weights take at 5.5 TB/s.  A result plane is read back by the next kernel, so a product that is split
+// less is worth the time of that.
+GemmPlan cheapest(int m, int n, int k, int mode, int min_splits, int max_splits, bool row_mixed) {
     const int its = k / BK;
     GemmPlan best{0, min_splits};
     double best_cost = 1e30;
@@ -521,7 +521,7 @@ GemmPlan cheapest(int m, int n, int k, int mode, int min_splits, int max_splits,
         const double stream = (double)n * k * 2.0 / 5.9e6 + 2.0;
         auto consider = [&](int tile, const TileCost& c, double tiles) {
             double cost = c.fixed + rounds_of(c, tiles * s) * (c.step * steps + c.per_tile) + c.plane * plane;
-            cost = std::max(cost, stream) + (read_planes ? plane : 0.0);
+            cost = std::max(cost, stream) + plane;
             if (cost < best_cost) { best_cost = cost; best = GemmPlan{tile, s}; }
         };
         if (m <= 64 && n % 128 == 0) {
@@ -562,8 +562,8 @@ GemmPlan cheapest(int m, int n, int k, int mode, int min_splits, int max_splits,
 
 }  // namespace
 
-GemmPlan gemm_plan(int m, int n, int k, int mode, int max_splits, bool row_mixed, bool read_planes) {
-    return cheapest(m, n, k, mode, 1, max_splits, row_mixed, read_planes);
+GemmPlan gemm_plan(int m, int n, int k, int mode, int max_splits, bool row_mixed) {
+    return cheapest(m, n, k, mode, 1, max_splits, row_mixed);
 }
 
 hipError_t launch_gemm_bf16(const bf16_t* a, int64_t lda, const bf16_t* w, int64_t ldw, void* out, int64_t ldc,
@@ -575,7 +575,7 @@ hipError_t launch_gemm_bf16(const bf16_t* a, int64_t lda, const bf16_t* w, int64
     if (splits < 1 || (k / BK) % splits != 0) return hipErrorInvalidValue;
     if (splits > 1 && mode != GEMM_STORE_F32) return hipErrorInvalidValue;
     if (tile < 0) {
-        tile = cheapest(m, n, k, splits == 1 ? mode : GEMM_STORE_F32, splits, splits, true, false).tile;
+        tile = cheapest(m, n, k, splits == 1 ? mode : GEMM_STORE_F32, splits, splits, true).tile;
     }
     if ((((uintptr_t)a | (uintptr_t)w) & 3) || (m > 1 && lda % 2 != 0) || ldw >= (int64_t)1 << 23) {
         if (n % 128 != 0) return hipErrorInvalidValue;

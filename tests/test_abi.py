@@ -99,6 +99,6 @@ def test_gemm_planner_choices_are_launchable():
     # the vocabulary projection of a micro-batch of 256 decode rows plus one chunk end: one 288-row band
     assert B.gllm_op_gemm_plan(257, 128256, 4096, 0, 1) == (9, 1)
     assert B.gllm_op_gemm_plan(256, 128256, 4096, 0, 1)[0] == 10 and B.gllm_op_gemm_plan(289, 128256, 4096, 0, 1)[0] == 12
-    assert B.gllm_op_gemm_plan(2048, 4096, 14336, 0, 8) == (10, 2) and B.gllm_op_gemm_plan(2048, 4096, 4096, 0, 8) == (3, 2)
+    assert B.gllm_op_gemm_plan(2048, 4096, 14336, 0, 8) == (10, 2) and B.gllm_op_gemm_plan(2048, 4096, 4096, 0, 8) == (1, 1)
     with pytest.raises(B.GllmError):
         B.gllm_op_gemm_plan(128, 100, 4096, 0, 8)
