@@ -485,19 +485,22 @@ int gemm_mixed_rem_cols(int m, int n) {
 namespace {
 
 // Cost of a launch of one tile shape in us, fitted to measurements on MI355X with operands streaming from HBM (weights
-// are cold in the stage; four stage shapes and two vocabularies, 65 to 4160 rows, every tile and split):
+// are cold in the stage; four stage shapes and two vocabularies, 65 to 4160 rows, every tile and split: 985 products):
 // fixed + rounds * (step * k_steps + per_tile) + plane * (us to read the fp32 result at 6 TB/s).  A round is one tile per
 // compute unit (two for a shape of which two share one); a last round that fills a share x of them counts
-// lone + (1 - lone) x, because fewer tiles run faster: the chip is power- and bandwidth-limited.  The errors of the fit
-// are 5 % (tall tiles) to 9 % (128-row tiles); the pick it makes is 2 % behind the best one on average.
+// lone + (1 - lone) x, because fewer tiles run faster: the chip is power- and bandwidth-limited.  No launch is faster than
+// its loads: the weights at `stream` TB/s and the activations, once per tile column, at 62 TB/s from the caches, both
+// slower by as much as the last round is short of tiles.  (Decides from 65 to 192 rows: with one bound for all tiles,
+// 128256 x 4096 at 128 rows ran on 128x128 tiles with a compute unit each in 253 us; two of them sharing one take 207.)
+// The picks are 0.8 % behind the best ones on average (profiles/gemm_plan_sweep.txt).
 struct TileCost {
-    int slots;
-    double step, fixed, lone, per_tile, plane;
+    int slots, width;  // tiles in a round, columns of a tile
+    double step, fixed, lone, per_tile, plane, stream;
 };
-constexpr TileCost kCost128x128{512, 0.97, 6.4, 0.25, 0.95, 0.75}, kCost128x128Deep{256, 0.49, 3.6, 0.70, 2.5, 1.0},
-    kCost192x128{256, 0.684, 3.5, 0.575, 2.7, 1.0}, kCost256x128{256, 0.822, 4.7, 0.59, 5.4, 0.26},
-    kCost256x192{256, 1.175, 3.9, 0.70, 0.4, 1.0}, kCost256x256{256, 1.454, 4.4, 0.547, 2.5, 0.92},
-    kCost192x256{256, 1.20, 0.8, 0.51, 6.0, 0.81}, kCost288x192{256, 1.587, 0.0, 0.516, 7.1, 1.0};
+constexpr TileCost kCost128x128{512, 128, 0.955, 8.21, 0.44, 0.08, 0.7, 5.96}, kCost128x128Deep{256, 128, 0.507, 3.44, 0.7, 0.76, 0.95, 5.54},
+    kCost192x128{256, 128, 0.684, 3.9, 0.54, 2.31, 0.69, 5.38}, kCost256x128{256, 128, 0.812, 4.38, 0.62, 3.69, 0.4, 5.28},
+    kCost256x192{256, 192, 1.175, 4.32, 0.59, 0.0, 0.99, 5.07}, kCost256x256{256, 256, 1.456, 4.35, 0.52, 2.38, 0.93, 5.55},
+    kCost192x256{256, 256, 1.2, 0.47, 0.44, 7.24, 0.54, 7.46}, kCost288x192{256, 192, 1.587, 2.25, 0.68, 0.0, 1.09, 6.17};
 
 double rounds_of(const TileCost& c, double tiles) {
     const double full = std::floor(tiles / c.slots), rest = tiles / c.slots - full;
@@ -518,11 +521,16 @@ GemmPlan cheapest(int m, int n, int k, int mode, int min_splits, int max_splits,
         if (its % s != 0 || (s > 1 && s > min_splits && its / s < 8)) continue;
         const double steps = (double)its / s;
         const double plane = mode == GEMM_STORE_F32 ? (double)m * n * 4.0 * s / 6e6 : 0.0;  // us to read the result
-        const double stream = (double)n * k * 2.0 / 5.9e6 + 2.0;
-        auto consider = [&](int tile, const TileCost& c, double tiles) {
-            double cost = c.fixed + rounds_of(c, tiles * s) * (c.step * steps + c.per_tile) + c.plane * plane;
-            cost = std::max(cost, stream) + plane;
+        auto round_us = [&](const TileCost& c) { return c.step * steps + c.per_tile; };
+        // `rounds` as they count, `full` if the last one were as good as the others
+        auto consider_rounds = [&](int tile, const TileCost& c, double rounds, double full) {
+            const double work = c.fixed + rounds * round_us(c) + c.plane * plane;
+            const double loads = (double)n * k * 2e-6 * (1.0 / c.stream + 0.016 * m / c.width) * rounds / full;
+            const double cost = std::max(work, loads) + plane + 1e-3 * work;  // of two that their loads bound, the lighter one
             if (cost < best_cost) { best_cost = cost; best = GemmPlan{tile, s}; }
+        };
+        auto consider = [&](int tile, const TileCost& c, double tiles) {
+            consider_rounds(tile, c, rounds_of(c, tiles * s), tiles * s / c.slots);
         };
         if (m <= 64 && n % 128 == 0) {
             const double cost = std::max((double)ceil_div((int64_t)(n / 128) * s, 512) * steps * 0.30, (double)n * k * 2.0 / 5.5e12 / 1.65e-6) +
@@ -536,9 +544,10 @@ GemmPlan cheapest(int m, int n, int k, int mode, int min_splits, int max_splits,
             const int rr = row_mixed ? gemm_rowmix_rem_rows(m, n) : 0;
             if (rr > 0 && m <= 384) consider(8, kCost192x256, 2 * cols);
             else if (rr > 0) consider(8, kCost256x256, (m / 256 + (rr == 64 ? 0.6 : 0.8)) * cols);
-            // (half-width tiles in a last round that they cover: half a round of big tiles)
-            if (s == 1 && gemm_mixed_rem_cols(m, n) > 0)
-                consider(4, kCost256x256, std::floor(b256 * cols / 256) * 256 + 256 * (0.5 - kCost256x256.lone) / (1 - kCost256x256.lone));
+            if (s == 1 && gemm_mixed_rem_cols(m, n) > 0) {  // whole rounds of big tiles and one of half-width ones
+                const double tiles = b256 * cols, whole = std::floor(tiles / 256), half = rounds_of(kCost256x128, 2 * (tiles - whole * 256));
+                consider_rounds(4, kCost256x256, whole + half * round_us(kCost256x128) / round_us(kCost256x256), tiles / 256);
+            }
             consider(3, kCost256x256, b256 * cols);
         }
         if (n % 192 == 0 && mode != GEMM_SWIGLU_BF16) {
