@@ -194,10 +194,9 @@ const char* gllm_profile_class_name(int32_t i);
 gllm_status gllm_op_pack_weight(const void* w, int64_t ldw, int32_t n, int32_t k, void* out, void* stream);
 
 /* out[m][n] (op)= sum_k a[m][k] * w[n][k];  a: bf16 [m_rows][lda] with lda >= k, w: bf16, n rows, tiled as above with
- * k extent ldw (a multiple of 64, >= k: the product may use a leading part of the k range).  Rows of a that start off a
- * 4-byte boundary are multiplied by a plain, slow kernel.
- * Requirements: k a multiple of 64 and n a multiple of 128 (the stage pads its operands);
- * a must be readable for round_up(m,256) rows.  mode: 0 store fp32 to out[m][ldc];
+ * k extent ldw (a multiple of 64, >= k: the product may use a leading part of the k range).
+ * Requirements: k a multiple of 64; n a multiple of 128, or of 192 for modes 0 and 1 (the stage pads its operands).  Rows
+ * of a past m are not read.  mode: 0 store fp32 to out[m][ldc];
  * 1 add into fp32 out[m][ldc]; 2 SwiGLU: columns come in groups of 64 = 32 gate + 32 up
  * outputs, out is bf16 [m][ldc] with n/2 columns, out = silu(gate) * up.
  * tile: -1 lets the library choose the workgroup tile; 0 = 128x128 (two workgroups per compute unit), 1 = 256x128
@@ -209,7 +208,11 @@ gllm_status gllm_op_pack_weight(const void* w, int64_t ldw, int32_t n, int32_t k
  * most 128 rows, or two bands of 192x256 tiles for all rows up to 384 (only for m > 256 with 0 < m mod 256 <= 128 and
  * n a multiple of 256), 9 = 288x192 (six wavefronts; only for 256 < m <= 288, n a multiple of 192, not for SwiGLU: all
  * rows in one band, so the weights are read once); a forced tile that does not fit the
- * shape gives GLLM_E_UNSUPPORTED. */
+ * shape gives GLLM_E_UNSUPPORTED.
+ * Alignment: operands are loaded in 16-byte pieces from any 4-byte boundary.  Where a, one of its rows (lda odd, m > 1) or
+ * w starts off a 4-byte boundary, a plain, slow kernel does the product; where the rows of a lie so far apart that a tile
+ * of them spans 4 GiB, it runs in bands of fewer rows.  On both paths a forced tile only decides whether the call is
+ * accepted. */
 gllm_status gllm_op_gemm_bf16(const void* a, int64_t lda, const void* w, int64_t ldw, void* out, int64_t ldc,
                               int32_t m, int32_t n, int32_t k, int32_t mode, int32_t tile, void* stream);
 

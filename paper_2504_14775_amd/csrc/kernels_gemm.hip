@@ -388,7 +388,6 @@ hipError_t launch_tile_w(const bf16_t* a, int64_t lda, const bf16_t* w, int64_t 
 template <int BM, int BN, int WGM, int WGN, int MODE, int NS = 2, int NSW = NS>
 hipError_t launch_tile(const bf16_t* a, int64_t lda, const bf16_t* w, int64_t ldw, void* out, int64_t ldc, int m,
                        int n, int k, int splits, int64_t split_stride, hipStream_t stream) {
-    if (n % BN != 0) return hipErrorInvalidValue;
     return m <= BM ? launch_tile_w<BM, BN, WGM, WGN, MODE, NS, NSW, true>(a, lda, w, ldw, out, ldc, m, n, k, splits, split_stride, stream)
                    : launch_tile_w<BM, BN, WGM, WGN, MODE, NS, NSW, false>(a, lda, w, ldw, out, ldc, m, n, k, splits, split_stride, stream);
 }
@@ -405,14 +404,11 @@ hipError_t launch_mode(const bf16_t* a, int64_t lda, const bf16_t* w, int64_t ld
         case 2: case 3: case 10: return launch_tile<256, 256, 2, 2, MODE, 2, 3>(GLLM_TILE_ARGS);
         case 6: return launch_tile<128, 128, 2, 2, MODE, 4>(GLLM_TILE_ARGS);
         case 7: return launch_tile<64, 128, 2, 2, MODE, 3>(GLLM_TILE_ARGS);
-        case 8: case 12:  // 257..384 rows: see gemm_rowmix_rem_rows
-            if (m <= 256 || m > 384) return hipErrorInvalidValue;
+        case 8: case 12:  // 257..384 rows
             return launch_tile<192, 256, 2, 2, MODE, 2, 3>(GLLM_TILE_ARGS);
         case 9:  // one 288-row tile covers all rows
-            if constexpr (MODE != GEMM_SWIGLU_BF16) {
-                if (m <= 256 || m > 288) return hipErrorInvalidValue;
-                return launch_tile<288, 192, 3, 2, MODE, 2, 3>(GLLM_TILE_ARGS);
-            } else return hipErrorInvalidValue;
+            if constexpr (MODE != GEMM_SWIGLU_BF16) return launch_tile<288, 192, 3, 2, MODE, 2, 3>(GLLM_TILE_ARGS);
+            else return hipErrorInvalidValue;
         case 5:
             if constexpr (MODE != GEMM_SWIGLU_BF16) return launch_tile<256, 192, 2, 2, MODE, 2, 3>(GLLM_TILE_ARGS);
             else return hipErrorInvalidValue;
@@ -575,6 +571,23 @@ GemmPlan gemm_plan(int m, int n, int k, int mode, int max_splits, bool row_mixed
     return cheapest(m, n, k, mode, 1, max_splits, row_mixed);
 }
 
+namespace {
+
+// Whether launches of this tile id cover a product of these sizes (the rule is the same whatever path addresses it).
+bool tile_fits(int tile, int m, int n, int mode, int splits) {
+    switch (tile) {
+        case 0: case 1: case 6: case 7: return n % 128 == 0;
+        case 2: case 3: case 10: return n % 256 == 0;
+        case 4: case 11: return splits == 1 && gemm_mixed_rem_cols(m, n) > 0;
+        case 5: return n % 192 == 0 && mode != GEMM_SWIGLU_BF16;
+        case 8: case 12: return gemm_rowmix_rem_rows(m, n) > 0;
+        case 9: return m > 256 && m <= 288 && n % 192 == 0 && mode != GEMM_SWIGLU_BF16;
+        default: return false;
+    }
+}
+
+}  // namespace
+
 hipError_t launch_gemm_bf16(const bf16_t* a, int64_t lda, const bf16_t* w, int64_t ldw, void* out, int64_t ldc,
                             int m, int n, int k, int mode, int tile, int splits, int64_t split_stride,
                             hipStream_t stream) {
@@ -586,8 +599,8 @@ hipError_t launch_gemm_bf16(const bf16_t* a, int64_t lda, const bf16_t* w, int64
     if (tile < 0) {
         tile = cheapest(m, n, k, splits == 1 ? mode : GEMM_STORE_F32, splits, splits, true).tile;
     }
+    if (!tile_fits(tile, m, n, mode, splits)) return hipErrorInvalidValue;
     if ((((uintptr_t)a | (uintptr_t)w) & 3) || (m > 1 && lda % 2 != 0) || ldw >= (int64_t)1 << 23) {
-        if (n % 128 != 0) return hipErrorInvalidValue;
         const int cols = mode == GEMM_SWIGLU_BF16 ? n / 2 : n;
         const int64_t blocks = ceil_div((int64_t)m * cols, 256);
         if (blocks > 0x7FFFFFFF) return hipErrorInvalidValue;
@@ -598,7 +611,8 @@ hipError_t launch_gemm_bf16(const bf16_t* a, int64_t lda, const bf16_t* w, int64
         else return hipErrorInvalidValue;
         return hipGetLastError();
     }
-    // the kernels address the rows of a tile by 32-bit byte offsets
+    // the kernels address the rows of a tile by 32-bit byte offsets: rows too far apart for that are multiplied in bands of
+    // fewer rows, each with the tile the planner picks for it (a forced one need not fit a band)
     const int64_t rows32 = (((int64_t)1 << 32) - 1) / (2 * std::max<int64_t>(lda, 1));
     if (m > rows32 && rows32 < kMaxTileM) {
         const int elem = mode == GEMM_SWIGLU_BF16 ? 2 : 4;
@@ -610,9 +624,8 @@ hipError_t launch_gemm_bf16(const bf16_t* a, int64_t lda, const bf16_t* w, int64
         return hipSuccess;
     }
     if (tile == 8 || tile == 12) {
-        const int rem_rows = gemm_rowmix_rem_rows(m, n);
-        if (rem_rows == 0) return hipErrorInvalidValue;
-        if (m > 384) {
+        if (m > 384) {  // up to 384 rows: two bands of 192, see launch_mode
+            const int rem_rows = gemm_rowmix_rem_rows(m, n);
 #define GLLM_ROWMIX_MODE(MODE_)                                                                                              \
     (rem_rows == 64 ? launch_rowmix<MODE_, 64>(a, lda, w, ldw, out, ldc, m, n, k, splits, split_stride, stream)              \
                     : launch_rowmix<MODE_, 128>(a, lda, w, ldw, out, ldc, m, n, k, splits, split_stride, stream))
@@ -627,7 +640,6 @@ hipError_t launch_gemm_bf16(const bf16_t* a, int64_t lda, const bf16_t* w, int64
     }
     if (tile == 4 || tile == 11) {
         const int rem_cols = gemm_mixed_rem_cols(m, n);
-        if (rem_cols == 0 || splits != 1) return hipErrorInvalidValue;
         switch (mode) {
             case GEMM_STORE_F32: return launch_mixed<GEMM_STORE_F32>(a, lda, w, ldw, out, ldc, m, n, k, rem_cols, stream);
             case GEMM_ADD_F32: return launch_mixed<GEMM_ADD_F32>(a, lda, w, ldw, out, ldc, m, n, k, rem_cols, stream);

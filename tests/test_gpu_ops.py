@@ -299,6 +299,28 @@ def test_gemm_rows_off_a_four_byte_boundary(mode):
             assert np.all(np.abs(got - x @ y.T) <= bound + 2.0 ** -22)
 
 
+def test_gemm_forced_tile_is_checked_on_every_path():
+    """A forced tile that does not fit the product is refused wherever the rows lie -- aligned, off a 4-byte boundary, too far
+    apart for a tile -- and one that fits is accepted, also the 192-column one where n is no multiple of 128."""
+    M, N, K = 37, 192, 128
+    a, w = rand_bits(16, 1, (M, K), 1.0), rand_bits(16, 2, (N, K), 0.05)
+    x, y = oracle.bf16_to_f64(a), oracle.bf16_to_f64(w)
+    dw = to_dev_weight(w)
+    for ld in (K, K + 1, 1 << 26):
+        print(f"gemm forced tiles ld={ld}", flush=True)
+        da = torch.empty((M - 1) * ld + K, dtype=torch.bfloat16, device=DEV).as_strided((M, K), (ld, 1))
+        da.copy_(to_dev_bits(a).view(torch.bfloat16))
+        for tile in (0, 1, 2, 3, 4, 6, 7, 8, 9, 10, 11, 12, 13):
+            with pytest.raises(B.GllmError) as e:
+                B.gllm_op_gemm_bf16(da, dw, torch.empty(M, N, device=DEV), M, N, K, B.GEMM_STORE_F32, tile)
+            assert e.value.status == -7, tile          # GLLM_E_UNSUPPORTED
+        for tile in (5, -1):
+            out = torch.zeros((M, N), dtype=torch.float32, device=DEV)
+            B.gllm_op_gemm_bf16(da, dw, out, M, N, K, B.GEMM_STORE_F32, tile)
+            torch.cuda.synchronize()
+            assert np.all(np.abs(out.cpu().numpy() - x @ y.T) <= (np.abs(x) @ np.abs(y).T) * K * 2.0 ** -24), (ld, tile)
+
+
 def test_gemm_rows_farther_apart_than_32_bit_offsets_reach():
     """A row stride of 2^23 elements: 300 rows span more than 4 GiB, which the launch cuts into bands."""
     M, N, K, ld = 300, 256, 128, 1 << 23
