@@ -211,8 +211,8 @@ gllm_status gllm_op_pack_weight(const void* w, int64_t ldw, int32_t n, int32_t k
  * shape gives GLLM_E_UNSUPPORTED.
  * Alignment: operands are loaded in 16-byte pieces from any 4-byte boundary.  Where a, one of its rows (lda odd, m > 1) or
  * w starts off a 4-byte boundary, a plain, slow kernel does the product; where the rows of a lie so far apart that a tile
- * of them spans 4 GiB, it runs in bands of fewer rows.  On both paths a forced tile only decides whether the call is
- * accepted. */
+ * of them spans 4 GiB, it runs in bands of fewer rows; where ldw is 2^23 or more, in 128x64 tiles.  On these paths a forced
+ * tile only decides whether the call is accepted. */
 gllm_status gllm_op_gemm_bf16(const void* a, int64_t lda, const void* w, int64_t ldw, void* out, int64_t ldc,
                               int32_t m, int32_t n, int32_t k, int32_t mode, int32_t tile, void* stream);
 

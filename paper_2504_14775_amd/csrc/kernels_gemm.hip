@@ -60,7 +60,9 @@ __device__ __forceinline__ int xcd_contiguous(int wg, int count) {
 // HBM, the activations are re-read from the caches by every tile column, so where LDS cannot hold one more stage of both
 // (256x256: two of each fill 128 of the 160 KiB) the W tile alone gets the third: its loads then have two k-steps
 // to land instead of one.
-template <int BM, int BN, int WGM, int WGN, int MODE, int NS = 2, int NSW = NS, bool W_ONCE = false>
+// W_FAR: 32-bit offsets do not reach over the row blocks of W in a tile or along its k range, so each block of each k-step
+// gets a buffer of its own (two scalar additions per load).
+template <int BM, int BN, int WGM, int WGN, int MODE, int NS = 2, int NSW = NS, bool W_ONCE = false, bool W_FAR = false>
 __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ A, int64_t lda, const bf16_t* __restrict__ W,
                                           int64_t ldw, void* __restrict__ out, int64_t ldc, int M, int K,
                                           int tiles_m, int tiles_n, int n_base, int tile_idx, int split, int num_splits,
@@ -111,6 +113,7 @@ __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ A, int64_t 
     const auto a_buf = __builtin_amdgcn_make_buffer_rsrc((void*)(A + (int64_t)m0 * lda), 0, (int)(uint32_t)(a_rows * lda * 2), kBufferFlags);
     const auto w_buf = __builtin_amdgcn_make_buffer_rsrc((void*)((const char*)W + (int64_t)(n0 >> 6) * w_blocks_k * kWBlockBytes), 0,
                                                          (int)(uint32_t)((BN >> 6) * w_blocks_k * kWBlockBytes), kBufferFlags);
+    static_assert(!W_FAR || NW == 4, "the row block of a load must not depend on the wave");
     uint32_t off_a[GA], off_w[GW];
 #pragma unroll
     for (int i = 0; i < GA; ++i) {
@@ -122,7 +125,7 @@ __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ A, int64_t 
 #pragma unroll
     for (int i = 0; i < GW; ++i) {
         const int g = wave + i * NW;
-        off_w[i] = (uint32_t)(g >> 3) * (uint32_t)(w_blocks_k * kWBlockBytes) + (g & 7) * 1024u + (lrow * 64 + lgrp * 8) * 2u;
+        off_w[i] = (W_FAR ? 0u : (uint32_t)(g >> 3) * (uint32_t)(w_blocks_k * kWBlockBytes)) + (g & 7) * 1024u + (lrow * 64 + lgrp * 8) * 2u;
     }
     // Load i of a k-step (A: i < GA, W: the rest) into the stages at byte sa / sw of LDS.  Tiles past the last one re-read
     // the last into a stage nobody reads again.  With one band of rows (W_ONCE) every byte of W is read by one workgroup,
@@ -132,7 +135,11 @@ __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ A, int64_t 
         if (i < GA)
             __builtin_amdgcn_raw_ptr_buffer_load_lds(a_buf, (lptr_t)(smem + sa + (wave + i * NW) * 1024), 16, off_a[i],
                                                      (min(kt_a, KT - 1) + kt_base) * (BK * 2), 0, 0);
-        else
+        else if constexpr (W_FAR) {  // load i - GA fills rows 8 (wave + 4 (i - GA)) .. + 7: row block (i - GA) / 2
+            const int64_t block = (int64_t)((n0 >> 6) + (i - GA) / 2) * w_blocks_k + min(kt_w, KT - 1) + kt_base;
+            const auto buf = __builtin_amdgcn_make_buffer_rsrc((void*)((const char*)W + block * kWBlockBytes), 0, kWBlockBytes, kBufferFlags);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(buf, (lptr_t)(smem + sw + (wave + (i - GA) * NW) * 1024), 16, off_w[i - GA], 0, 0, 0);
+        } else
             __builtin_amdgcn_raw_ptr_buffer_load_lds(w_buf, (lptr_t)(smem + sw + (wave + (i - GA) * NW) * 1024), 16, off_w[i - GA],
                                                      (min(kt_w, KT - 1) + kt_base) * kWBlockBytes, 0, W_ONCE ? kAuxNonTemporal : 0);
     };
@@ -291,7 +298,7 @@ __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ A, int64_t 
 #endif
 }
 
-template <int BM, int BN, int WGM, int WGN, int MODE, int NS = 2, int NSW = NS, bool W_ONCE = false>
+template <int BM, int BN, int WGM, int WGN, int MODE, int NS = 2, int NSW = NS, bool W_ONCE = false, bool W_FAR = false>
 __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_kernel(const bf16_t* __restrict__ A, int64_t lda,
                                                                     const bf16_t* __restrict__ W, int64_t ldw,
                                                                     void* __restrict__ out, int64_t ldc, int M,
@@ -303,7 +310,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_kernel(const bf16_t*
     // as the plain per-share numbering would place them, the L2 sees half as many tiles per panel).
     const int num_tiles = tiles_m * tiles_n;
     const int v = xcd_contiguous(blockIdx.x + blockIdx.y * num_tiles, num_tiles * (int)gridDim.y);
-    gemm_tile<BM, BN, WGM, WGN, MODE, NS, NSW, W_ONCE>(A, lda, W, ldw, out, ldc, M, K, tiles_m, tiles_n, 0, v % num_tiles,
+    gemm_tile<BM, BN, WGM, WGN, MODE, NS, NSW, W_ONCE, W_FAR>(A, lda, W, ldw, out, ldc, M, K, tiles_m, tiles_n, 0, v % num_tiles,
                                                        v / num_tiles, gridDim.y, split_stride);
 }
 
@@ -342,8 +349,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_rowmix_kernel(const bf16_t* __r
                                            split_stride, bands * 256);
 }
 
-// Operands that the tiles cannot address: a row of A or the start of W off a 4-byte boundary (what a buffer load needs), or
-// a weight panel of 4 GiB and more.  One thread per result, products summed in order of k; such operands come from
+// Operands that the tiles cannot address: a row of A or the start of W off a 4-byte boundary (what a buffer load needs).  One thread per result, products summed in order of k; such operands come from
 // callers' views, not from the stage or the head, so this is for completeness and not for speed.
 template <int MODE>
 __global__ __launch_bounds__(256) void gemm_any_address_kernel(const bf16_t* __restrict__ A, int64_t lda, const bf16_t* __restrict__ W,
@@ -366,12 +372,12 @@ __global__ __launch_bounds__(256) void gemm_any_address_kernel(const bf16_t* __r
     else *f = sum;
 }
 
-template <int BM, int BN, int WGM, int WGN, int MODE, int NS, int NSW, bool W_ONCE>
+template <int BM, int BN, int WGM, int WGN, int MODE, int NS, int NSW, bool W_ONCE, bool W_FAR = false>
 hipError_t launch_tile_w(const bf16_t* a, int64_t lda, const bf16_t* w, int64_t ldw, void* out, int64_t ldc, int m,
                          int n, int k, int splits, int64_t split_stride, hipStream_t stream) {
     const int tiles_m = (int)ceil_div(m, BM), tiles_n = n / BN;
     const size_t smem = (NS * BM + NSW * BN) * BK * sizeof(bf16_t);
-    auto kern = gemm_bf16_kernel<BM, BN, WGM, WGN, MODE, NS, NSW, W_ONCE>;
+    auto kern = gemm_bf16_kernel<BM, BN, WGM, WGN, MODE, NS, NSW, W_ONCE, W_FAR>;
     static bool configured = false;
     if (!configured) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
@@ -415,6 +421,13 @@ hipError_t launch_mode(const bf16_t* a, int64_t lda, const bf16_t* w, int64_t ld
         default: return hipErrorInvalidValue;
     }
 #undef GLLM_TILE_ARGS
+}
+
+// Weights whose k extent is so large that the row blocks of a tile span 4 GiB: 64-column tiles, which every n allows.
+template <int MODE>
+hipError_t launch_far(const bf16_t* a, int64_t lda, const bf16_t* w, int64_t ldw, void* out, int64_t ldc, int m,
+                      int n, int k, int splits, int64_t split_stride, hipStream_t stream) {
+    return launch_tile_w<128, 64, 4, 1, MODE, 4, 4, false, true>(a, lda, w, ldw, out, ldc, m, n, k, splits, split_stride, stream);
 }
 
 constexpr size_t kWideTileLds = (2 * 256 + 3 * 256) * BK * sizeof(bf16_t);  // 256x256 tile: all 160 KiB
@@ -600,7 +613,7 @@ hipError_t launch_gemm_bf16(const bf16_t* a, int64_t lda, const bf16_t* w, int64
         tile = cheapest(m, n, k, splits == 1 ? mode : GEMM_STORE_F32, splits, splits, true).tile;
     }
     if (!tile_fits(tile, m, n, mode, splits)) return hipErrorInvalidValue;
-    if ((((uintptr_t)a | (uintptr_t)w) & 3) || (m > 1 && lda % 2 != 0) || ldw >= (int64_t)1 << 23) {
+    if ((((uintptr_t)a | (uintptr_t)w) & 3) || (m > 1 && lda % 2 != 0)) {
         const int cols = mode == GEMM_SWIGLU_BF16 ? n / 2 : n;
         const int64_t blocks = ceil_div((int64_t)m * cols, 256);
         if (blocks > 0x7FFFFFFF) return hipErrorInvalidValue;
@@ -622,6 +635,14 @@ hipError_t launch_gemm_bf16(const bf16_t* a, int64_t lda, const bf16_t* w, int64
             if (e != hipSuccess) return e;
         }
         return hipSuccess;
+    }
+    if (ldw >= (int64_t)1 << 23) {  // (256 columns of W, the widest tile, are 4 GiB)
+        switch (mode) {
+            case GEMM_STORE_F32: return launch_far<GEMM_STORE_F32>(a, lda, w, ldw, out, ldc, m, n, k, splits, split_stride, stream);
+            case GEMM_ADD_F32: return launch_far<GEMM_ADD_F32>(a, lda, w, ldw, out, ldc, m, n, k, splits, split_stride, stream);
+            case GEMM_SWIGLU_BF16: return launch_far<GEMM_SWIGLU_BF16>(a, lda, w, ldw, out, ldc, m, n, k, splits, split_stride, stream);
+            default: return hipErrorInvalidValue;
+        }
     }
     if (tile == 8 || tile == 12) {
         if (m > 384) {  // up to 384 rows: two bands of 192, see launch_mode

@@ -334,6 +334,42 @@ def test_gemm_rows_farther_apart_than_32_bit_offsets_reach():
     assert np.all(np.abs(out.cpu().numpy() - x @ y.T) <= (np.abs(x) @ np.abs(y).T) * K * 2.0 ** -24)
 
 
+@pytest.mark.parametrize("ldw,N,whole", [(1 << 23, 128, False), (1 << 23, 192, False), (1 << 25, 128, False), (1 << 25, 128, True)])
+def test_gemm_weights_with_a_k_extent_beyond_32_bit_offsets(ldw, N, whole):
+    """Row blocks of W that lie 1 and 4 GiB apart: the product over a leading part of k, and over all of it with values in the
+    first and the last 64 columns only (so that K = 128 in the error bound), in every mode and with a k-split."""
+    M, K = 3 if whole else 150, ldw if whole else 192
+    cols = np.concatenate([np.arange(64), np.arange(K - 64, K)]) if whole else np.arange(K)
+    print(f"gemm far weights ldw={ldw} N={N} K={K}", flush=True)
+    a, w = rand_bits(17, 1, (M, len(cols)), 1.0), rand_bits(17, 2, (N, len(cols)), 0.05)
+    x, y = oracle.bf16_to_f64(a), oracle.bf16_to_f64(w)
+    far = torch.zeros(N // 64, ldw // 64, 64, 64, dtype=torch.bfloat16, device=DEV)          # the tiled layout, block by block
+    for i, c in enumerate(cols[::64]):
+        far[:, int(c) // 64] = to_dev_bits(w[:, 64 * i:64 * i + 64]).view(N // 64, 64, 64)
+    da = torch.zeros(M, K, dtype=torch.bfloat16, device=DEV)
+    da[:, torch.from_numpy(cols).to(DEV)] = to_dev_bits(a)
+    bound = (np.abs(x) @ np.abs(y).T) * len(cols) * 2.0 ** -24
+    out = torch.zeros((M, N), dtype=torch.float32, device=DEV)
+    B.gllm_op_gemm_bf16(da, far, out, M, N, K, B.GEMM_STORE_F32, -1, ldw=ldw)
+    torch.cuda.synchronize()
+    assert np.all(np.abs(out.cpu().numpy() - x @ y.T) <= bound)
+    B.gllm_op_gemm_bf16(da, far, out, M, N, K, B.GEMM_ADD_F32, -1, ldw=ldw)
+    torch.cuda.synchronize()
+    assert np.all(np.abs(out.cpu().numpy() - 2 * (x @ y.T)) <= 2 * bound + 2.0 ** -23 * np.abs(2 * (x @ y.T)))
+    s = 2 if whole else 3
+    planes = torch.zeros((s, M, N), dtype=torch.float32, device=DEV)
+    B.gllm_op_gemm_bf16_splitk(da, far.view(N, ldw), planes, M, N, K, -1, s)
+    torch.cuda.synchronize()
+    assert np.all(np.abs(planes.cpu().numpy().astype(np.float64).sum(axis=0) - x @ y.T) <= bound)
+    if N % 128 == 0:
+        act = torch.zeros((M, N // 2), dtype=torch.bfloat16, device=DEV)
+        B.gllm_op_gemm_bf16(da, far, act, M, N, K, B.GEMM_SWIGLU_BF16, -1, ldw=ldw)
+        torch.cuda.synchronize()
+        gate, up = (np.concatenate([y[64 * b + o:64 * b + o + 32] for b in range(N // 64)]) for o in (0, 32))
+        ref = oracle.swiglu(x @ gate.T, x @ up.T)
+        assert np.all(np.abs(oracle.bf16_to_f64(bits_of(act)) - ref) <= np.abs(ref) * 2.0 ** -7 + 1e-4)
+
+
 def test_pack_weight_writes_the_documented_tiled_layout():
     """gllm_op_pack_weight against the layout as the header states it (gpu_util.tiled_bits), bit for bit: a whole matrix,
     and a part of a wider one (row stride above k); then the product on a leading part of the packed k range."""
