@@ -571,10 +571,6 @@ GemmPlan cheapest(int m, int n, int k, int mode, int min_splits, int max_splits,
             consider(0, kCost128x128, b128 * cols);
         }
     }
-    // (ids 10, 11, 12 and 3, 4, 8 are the same launches)
-    const int steps = its / best.splits;
-    if ((best.tile == 3 || best.tile == 4 || best.tile == 8) && (steps >= 80 || m <= 1024))
-        best.tile = best.tile == 3 ? 10 : best.tile == 4 ? 11 : 12;
     return best;
 }
 
