@@ -186,10 +186,11 @@ def test_decode_rows_whole_or_partitioned_match_the_oracle(min_wgs):
     assert np.abs(r["out32"] - base32.cpu().numpy()).max() <= 1e-3 * max(1.0, rms)
 
 
-@pytest.mark.parametrize("chunks", [[(2, 0)], [(40, 9), (17, 100)], [(1100, 70)]])
+@pytest.mark.parametrize("chunks", [[(2, 0)], [(40, 9), (17, 100)], [(512, 70)], [(513, 70)]])
 def test_prefill_and_decode_attention_in_one_launch_or_two_give_the_same_bits(chunks):
-    """A prefill part of a few workgroups shares the launch of the decode rows, a large one does not; the option
-    overlap_attention = 0 keeps them apart.  Row and key order, and so every bit, are the same."""
+    """A prefill part of at most 64 workgroups (here 512 rows: 32 items of 16 rows, two groups of 8 heads) shares the launch
+    of the decode rows, one row more does not; the option overlap_attention = 0 keeps them apart.  Row and key order, and so
+    every bit, are the same, and the result is the oracle's."""
     print(f"one launch or two, chunks {chunks}", flush=True)
     one_layer = dataclasses.replace(MID, num_layers=1, name="mid1")
     batch = synth.build_batch(chunks + [(1, 0), (1, 300), (1, 1500), (1, 31)], 13, spare_blocks=5, label="one")
@@ -200,9 +201,10 @@ def test_prefill_and_decode_attention_in_one_launch_or_two_give_the_same_bits(ch
     for overlap in (1, 0):
         stage = GpuStage(one_layer, w, [batch])
         stage.stage.set_option("overlap_attention", overlap)
-        outs.append(stage.run(batch, to_dev_bits(kp0), to_dev_bits(vp0), to_dev_bits(x))[1].clone())
-    torch.cuda.synchronize()
-    assert torch.equal(outs[0], outs[1])
+        r = run_both(one_layer, w, batch, kp0, vp0, x, stage)
+        assert_output(f"one launch {overlap}", r, literal=False)
+        outs.append(r["out32"].copy())
+    assert np.array_equal(outs[0], outs[1])
 
 
 def test_decode_rows_of_very_different_lengths_match_the_oracle():
