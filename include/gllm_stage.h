@@ -145,8 +145,8 @@ gllm_status gllm_stage_share_weights(gllm_stage* stage, const gllm_stage* owner)
 gllm_status gllm_stage_set_alias_check(gllm_stage* stage, int32_t on);
 
 /* Tuning knobs (defaults are chosen for MI355X).  Known names:
- *   "decode_min_workgroups" (at least 1; unset by default): a partition size (256 .. 16384 keys, a power of two) is chosen
- *   as the largest for which partitions x KV heads reaches this many workgroups.  Unset, it is 1.5 times the keys that each
+ *   "decode_min_workgroups" (default 0): if positive, the partition size is the largest power of two from 256 to 16384
+ *   keys for which partitions x KV heads reaches this many workgroups (256 if none does).  At 0 it is 1.5 times the keys that each
  *   of the chip's workgroup slots gets on average, at least 256.  A decode row with more keys than
  *   that is cut into equal shares of whole 32-key blocks, and the longest shares are launched first.
  *   "overlap_attention" (default 1): prefill and decode attention of a layer share one launch where the prefill part is

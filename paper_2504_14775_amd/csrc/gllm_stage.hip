@@ -423,7 +423,7 @@ gllm_status gllm_stage_set_option(gllm_stage* s, const char* name, int64_t value
         return GLLM_OK;
     }
     if (std::strcmp(name, "decode_min_workgroups") == 0) {
-        if (value < 1) return fail(s, GLLM_E_INVALID, "decode_min_workgroups must be positive");
+        if (value < 0) return fail(s, GLLM_E_INVALID, "decode_min_workgroups must not be negative");
         s->decode_min_workgroups = value;
         return GLLM_OK;
     }
@@ -521,7 +521,9 @@ gllm_status gllm_stage_forward(gllm_stage* s, const gllm_batch* b, const void* h
             // a row is cut only where its share would hold up the launch: where it is more than 1.5 times what each of the
             // workgroup slots gets on average (two per compute unit).  Against partitions of at least 2048 workgroups:
             // 128 rows of 512 .. 4096 keys 2682 -> 2571 us per batch (8 layers), 64 rows of 1500 .. 3500 keys 1735 -> 1699,
-            // 40 rows of 256 .. 8192 keys 606 -> 588 (3 layers); rows never cut: 681 there.
+            // 40 rows of 256 .. 8192 keys 606 -> 588 (3 layers); rows never cut: 681 there.  A few long rows alike (2 layers):
+            // 1 row of 32768 keys 263 -> 247, 2 of 32768 307 -> 285, 4 of 16384 290 -> 283, 8 of 8192 285 -> 277; 4 of 4096
+            // 214 -> 218, the only one of 54 such batches that lost (a third of the slots stays empty where rows are alike).
             int64_t keys = 0;
             for (int i = 0; i < S; ++i)
                 if (b->new_tokens[i] == 1) keys += (int64_t)b->cached_len[i] + 1;

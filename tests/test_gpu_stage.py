@@ -219,6 +219,26 @@ def test_decode_rows_of_very_different_lengths_match_the_oracle():
     assert_output("skew", r, literal=False)
 
 
+def test_decode_partitioning_option_goes_back_to_the_default_rule():
+    """decode_min_workgroups: 1 leaves a long row whole, 0 is the default rule again (which cuts it), less is refused."""
+    print("decode_min_workgroups back to the default", flush=True)
+    one_layer = dataclasses.replace(MID, num_layers=1, name="mid1")
+    batch = synth.build_batch([(1, 3000)] + [(1, 7 + 5 * i) for i in range(30)], 15, spare_blocks=5, label="skew")
+    w = layer_weights_np(one_layer, 15)
+    kp0, vp0 = pool_np(one_layer, 15, batch.num_blocks)
+    x = to_dev_bits(hidden_np(one_layer, 15, batch.num_tokens))
+    stage = GpuStage(one_layer, w, [batch])
+    run = lambda: stage.run(batch, to_dev_bits(kp0), to_dev_bits(vp0), x)[1].clone()
+    default = run()
+    stage.stage.set_option("decode_min_workgroups", 1)
+    whole = run()
+    stage.stage.set_option("decode_min_workgroups", 0)
+    assert torch.equal(run(), default) and not torch.equal(whole[0], default[0])
+    with pytest.raises(B.GllmError):
+        stage.stage.set_option("decode_min_workgroups", -1)
+    assert torch.equal(run(), default)
+
+
 def test_qkv_bias_and_nan_sentinels_in_unused_slots():
     print("qkv bias + NaN sentinel in never-written slots", flush=True)
     shape = dataclasses.replace(synth.SHAPES["tiny"], has_qkv_bias=True, name="tiny_bias")
