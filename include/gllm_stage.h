@@ -133,7 +133,7 @@ gllm_status gllm_stage_bind_kv_pool(gllm_stage* stage, void* k_pool /*DEVICE*/, 
 
 /* Several stage objects over one set of weights: `stage` gives up its own (repacked) weight buffers and uses those
  * of `owner` from now on -- for running micro-batches on several streams, one stage object per stream (each has its
- * own workspace, metadata buffers and internal streams; calls on one object are still not thread-safe), without a
+ * own workspace and metadata buffers; calls on one object are still not thread-safe), without a
  * copy of the weights per stream.  Both must have been created with the same layer shapes; every layer of `owner`
  * must be loaded; `owner` must stay alive, and its weights unchanged, as long as `stage` is used.  Synchronises the
  * device.  GLLM_E_INVALID for differing shapes or an owner that borrows itself, GLLM_E_STATE for an owner with
@@ -223,8 +223,9 @@ gllm_status gllm_op_gemm_bf16_splitk(const void* a, int64_t lda, const void* w, 
                                      int32_t m, int32_t n, int32_t k, int32_t tile, int32_t splits, int64_t plane_stride,
                                      void* stream);
 
-/* Host only (no device call): the tile id and split-K factor the library's cost model picks for a problem
- * when gllm_op_gemm_bf16 is called with tile = -1 (splits stays 1 unless mode is 0; at most max_splits).
+/* Host only (no device call): the tile id and split-K factor the library's cost model picks for a problem, as it does
+ * when gllm_op_gemm_bf16 is called with tile = -1 (splits stays 1 unless mode is 0; at most max_splits).  Result planes are
+ * taken to be read back by the next kernel.
  * tile, splits: HOST out.  The stage plans its QKV, O and down projections with max_splits = 8. */
 gllm_status gllm_op_gemm_plan(int32_t m, int32_t n, int32_t k, int32_t mode, int32_t max_splits, int32_t* tile,
                               int32_t* splits);

@@ -734,8 +734,7 @@ gllm_status gllm_head_load(gllm_head* s, const void* norm_gain, const void* w_vo
 
 int32_t gllm_head_padded_vocab(const gllm_head* s) { return s ? s->vocab_pad : 0; }
 
-// Both projection entry points: rows of x -> normalised bf16 rows in h_buf -> logits (h_buf must hold round_up(num_rows, 256)
-// rows, 288 for 257..288 rows; rows past num_rows are read by the GEMM's tiles and their products discarded).
+// Both projection entry points: rows of x -> normalised bf16 rows in h_buf (num_rows of them) -> logits.
 static gllm_status head_logits_into(gllm_head* s, bf16_t* h_buf, const float* x, int32_t num_x_rows, const int32_t* rows,
                                     int32_t num_rows, float* logits, int64_t ld_logits, hipStream_t st) {
     const int H = s->cfg.hidden;
@@ -765,10 +764,10 @@ gllm_status gllm_head_logits_static(gllm_head* s, const float* x, int32_t num_x_
     if (!s || !x || !rows || !logits || num_x_rows < 1 || num_rows < 0) return GLLM_E_INVALID;
     if (!s->loaded) return fail(s, GLLM_E_STATE, "load the weights first");
     if (ld_logits < s->vocab_pad || ld_logits % 4 != 0) return fail(s, GLLM_E_INVALID, "ld_logits must cover the padded vocabulary");
-    // rows the projection's tiles may read: whole bands of 256 (the one 288-row tile for 257..288 rows reads fewer)
-    const int64_t rows_read = round_up(num_rows, 256);
-    if ((size_t)rows_read * s->cfg.hidden * 2 > kStaticScratchBytes)
-        return fail(s, GLLM_E_CAPACITY, "num_rows (rounded up to the projection's row bands) x hidden x 2 bytes exceeds the " +
+    // the documented limit counts whole bands of 256 rows (the projection itself reads num_rows rows only)
+    const int64_t rows_counted = round_up(num_rows, 256);
+    if ((size_t)rows_counted * s->cfg.hidden * 2 > kStaticScratchBytes)
+        return fail(s, GLLM_E_CAPACITY, "num_rows (rounded up to bands of 256) x hidden x 2 bytes exceeds the " +
                                             std::to_string(kStaticScratchBytes >> 20) + " MiB static scratch: use gllm_head_logits with a bound workspace");
     if (num_rows == 0) return GLLM_OK;
     void* buf = nullptr;

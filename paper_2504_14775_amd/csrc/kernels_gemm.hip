@@ -9,8 +9,9 @@
 // What bounds it: many rows, the 1400 W power limit (a bare MFMA loop on random operands reaches 1.6-1.8 PFLOP/s); few
 // rows, the stream of the weights (5.5-6 TB/s) and the ~5 us a launch costs before and after it; in between both.  Under
 // the power limit the clock follows the busy share of the matrix cores, so cycles in the k-loop count in full.  Four
-// waves with a wave tile of 128x128 read LDS two thirds as often per MFMA as eight of 128x64, and with the order of
-// MFMAs, LDS reads and global loads written out (see step) the loop has nothing in it that is not hidden under MFMAs:
+// waves with a wave tile of 128x128 read LDS two thirds as often per MFMA as eight of 128x64, and the order of MFMAs, LDS
+// reads and global loads is written out (see step): at 2048 rows the matrix cores are busy for 0.72 to 0.75 of a launch,
+// prologue and epilogue included, at 1.7 GHz (0.61 to 0.62 at 1.9 before; a bare MFMA loop 1.0 at 1.68).
 // 4096x8192x8192 437 -> 386 us (1257 -> 1426 TFLOP/s), gate/up at 2048 rows 406 -> 372, at 197 rows 74 -> 56, at 322
 // rows 100 -> 77, the down projection at 2048 rows 200 -> 175, at 197 rows 42 -> 35, at 322 rows 71 -> 44 us.
 //
@@ -494,7 +495,7 @@ int gemm_mixed_rem_cols(int m, int n) {
 namespace {
 
 // Cost of a launch of one tile shape in us, fitted to measurements on MI355X with operands streaming from HBM (weights
-// are cold in the stage; four stage shapes and two vocabularies, 65 to 4160 rows, every tile and split: 985 products):
+// are cold in the stage; four stage shapes and two vocabularies, 65 to 4160 rows, every tile and split: 938 products):
 // fixed + rounds * (step * k_steps + per_tile) + plane * (us to read the fp32 result at 6 TB/s).  A round is one tile per
 // compute unit (two for a shape of which two share one); a last round that fills a share x of them counts
 // lone + (1 - lone) x, because fewer tiles run faster: the chip is power- and bandwidth-limited.  No launch is faster than
