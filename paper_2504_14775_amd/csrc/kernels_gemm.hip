@@ -8,12 +8,13 @@
 //
 // What bounds it: many rows, the 1400 W power limit (a bare MFMA loop on random operands reaches 1.6-1.8 PFLOP/s); few
 // rows, the stream of the weights (5.5-6 TB/s) and the ~5 us a launch costs before and after it; in between both.  Under
-// the power limit the clock follows the busy share of the matrix cores, so cycles in the k-loop count in full.  Four
-// waves with a wave tile of 128x128 read LDS two thirds as often per MFMA as eight of 128x64, and the order of MFMAs, LDS
-// reads and global loads is written out (see step): at 2048 rows the matrix cores are busy for 0.72 to 0.75 of a launch,
-// prologue and epilogue included, at 1.7 GHz (0.61 to 0.62 at 1.9 before; a bare MFMA loop 1.0 at 1.68).
-// 4096x8192x8192 437 -> 386 us (1257 -> 1426 TFLOP/s), gate/up at 2048 rows 406 -> 372, at 197 rows 74 -> 56, at 322
-// rows 100 -> 77, the down projection at 2048 rows 200 -> 175, at 197 rows 42 -> 35, at 322 rows 71 -> 44 us.
+// the power limit the clock follows the busy share of the matrix cores, so cycles in the k-loop count in full, and so does
+// the energy of a product.  16x16x32 MFMAs touch an accumulator half as often per product as 32x32x16 ones: the same tile at
+// the same order of loads took 99.3 -> 90.6 us for gate/up at 512 rows (28672 x 4096), 859 -> 833 at 2048 rows of 55296 x
+// 5120, 387 -> 378 at 4096x8192x8192 (1455 TFLOP/s); where the weights' stream bounds a product there is no difference (64
+// rows).  Four waves with a wave tile of 128x128 read LDS two thirds as often per MFMA as eight of 128x64, and the order of
+// MFMAs, LDS reads and global loads is written out (see step): in the k-loop of a 256x256 tile the matrix cores are busy for
+// 0.92 of the time, at 1.6 to 1.7 GHz (a bare MFMA loop 1.0 at 1.68).
 //
 // LDS stage layout: rows of 64 k-values (128 bytes = eight 16-byte groups), A rows first, then W
 // rows.  Two consecutive rows form a 256-byte line of 16 group positions (the width of the 64 LDS
@@ -36,6 +37,7 @@
 namespace {
 
 constexpr int BK = 64;
+[[maybe_unused]] constexpr int MB = 16, MK = 32;  // v_mfma_f32_16x16x32_bf16: a block of 16x16 results over 32 k values
 constexpr int kMaxTileM = 288;            // tallest tile
 
 // silu(z) = z / (1 + e^-z) with the hardware exp2 and reciprocal (1 ulp each; the result is rounded to bf16)
@@ -73,14 +75,15 @@ __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ A, int64_t 
     constexpr int kBufferFlags = 0x00027000;  // raw buffer of 32-bit words, bounds checked in bytes
     constexpr int NW = WGM * WGN;
     constexpr int WTM = BM / WGM, WTN = BN / WGN;  // wave tile
-    constexpr int TM = WTM / 32, TN = WTN / 32;    // 32x32 blocks per wave
+    constexpr int TM = WTM / MB, TN = WTN / MB;    // MFMA blocks per wave
     constexpr int GA = BM / 8 / NW, GW = BN / 8 / NW;  // 1 KiB load groups per wave and stage: A, W
     constexpr int GPW = GA + GW;
     constexpr int A_STAGE = BM * BK * 2, W_STAGE = BN * BK * 2, W_BASE = NS * A_STAGE;
     constexpr int LDS_BYTES = NS * A_STAGE + NSW * W_STAGE;
     static_assert(NSW == NS || NSW == NS + 1, "the W tile has as many stages as the A tile, or one more");
     static_assert((BM / 8) % NW == 0 && (BN / 8) % NW == 0 && NW % 2 == 0, "load groups must divide among an even number of waves");
-    static_assert(MODE != GEMM_SWIGLU_BF16 || TN % 2 == 0, "SwiGLU needs gate and up blocks in one wave");
+    static_assert(WTM % MB == 0 && WTN % MB == 0, "a wave tile is made of whole MFMA blocks");
+    static_assert(MODE != GEMM_SWIGLU_BF16 || WTN % (2 * kSwigluGroup) == 0, "SwiGLU needs gate and up columns in one wave");
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
 
     // ---- tile assignment: tiles are numbered band by band ----
@@ -145,31 +148,29 @@ __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ A, int64_t 
                                                      (min(kt_w, KT - 1) + kt_base) * kWBlockBytes, 0, W_ONCE ? kAuxNonTemporal : 0);
     };
 
-    f32x16 acc[TM][TN];
+    f32x4 acc[TM][TN];
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+        for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
     {
-        // operand reads: lane supplies row (lane % 32), k-group (lane / 32) of each 16-wide k step
-        constexpr int KK = BK / 16;
+        // operand reads: lane supplies row (lane % 16), k-group (lane / 16) of each 32-wide k-step
+        constexpr int KK = BK / MK;
         constexpr int kReads = TM + TN, kMfma = TM * TN;
         constexpr int kPart = (GPW + KK - 1) / KK;  // global loads issued per k-step
-        const int frow = lane & 31, fgrp = lane >> 5;
+        const int frow = lane & (MB - 1), fgrp = lane / MB;
         const int fsw = (frow >> 1) & 7, fpar = (frow & 1) * 8;
         const int a_off = (wm * WTM + (frow & ~1)) * (BK * 2), w_off = (wn * WTN + (frow & ~1)) * (BK * 2);
         int fg[KK];
 #pragma unroll
-        for (int kk = 0; kk < KK; ++kk) fg[kk] = ((fpar + kk * 2 + fgrp) ^ fsw) * 16;
+        for (int kk = 0; kk < KK; ++kk) fg[kk] = ((fpar + kk * (MK / 8) + fgrp) ^ fsw) * 16;
         bf16x8 fa[2][TM], fw[2][TN];
         // operand read r of k-step kk of the tile in the stages at sa, sw, in the order the MFMAs want them
         auto read_frag = [&](int r, int kk, int sa, int sw, int buf) {
             if (r == 0) fa[buf][0] = *reinterpret_cast<const bf16x8*>(smem + sa + a_off + fg[kk]);
-            else if (r <= TN) fw[buf][r - 1] = *reinterpret_cast<const bf16x8*>(smem + sw + w_off + fg[kk] + (r - 1) * 32 * (BK * 2));
-            else fa[buf][r - TN] = *reinterpret_cast<const bf16x8*>(smem + sa + a_off + fg[kk] + (r - TN) * 32 * (BK * 2));
+            else if (r <= TN) fw[buf][r - 1] = *reinterpret_cast<const bf16x8*>(smem + sw + w_off + fg[kk] + (r - 1) * MB * (BK * 2));
+            else fa[buf][r - TN] = *reinterpret_cast<const bf16x8*>(smem + sa + a_off + fg[kk] + (r - TN) * MB * (BK * 2));
         };
         // One k-step: multiply the fragments in `buf`, fetch those of k-step kk_next of the tile in the stages at ra, rw
         // into the other buffer, issue part q of the global loads.  The order is written out and held by scheduling
@@ -180,7 +181,7 @@ __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ A, int64_t 
             const int loads = q < 0 ? 0 : max(0, min(kPart, GPW - q * kPart));
 #pragma unroll
             for (int r = 0; r < kMfma; ++r) {
-                acc[r / TN][r % TN] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[buf][r / TN], fw[buf][r % TN], acc[r / TN][r % TN], 0, 0, 0);
+                acc[r / TN][r % TN] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[buf][r / TN], fw[buf][r % TN], acc[r / TN][r % TN], 0, 0, 0);
                 __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                 for (int f = 0; f < kReads; ++f)
@@ -240,46 +241,46 @@ __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ A, int64_t 
     }
 
     // ---- epilogue, staged through LDS so that every global access is a 16-byte piece of a long row
-    // segment.  Accumulator element v of a 32x32 block sits at row 8*(v/4) + 4*(lane/32) + v%4, column
-    // lane%32; a wave writes one 32-row slab of its tile to its private LDS area, then reads it back row
+    // segment.  Accumulator element v of a 16x16 block sits at row 4*(lane/16) + v, column
+    // lane%16; a wave writes one 16-row slab of its tile to its private LDS area, then reads it back row
     // by row, 4 consecutive columns per lane.  Only the first barrier is needed (the slabs overlay the tiles).
     constexpr int C = (MODE == GEMM_SWIGLU_BF16) ? WTN / 2 : WTN;  // result columns of a wave slab
     constexpr int CS = C + 8;                                       // padded row stride (floats)
     constexpr int LPR = C / 4;                                      // lanes per row on the way out
     constexpr int RPI = 64 / LPR;                                   // rows per read instruction (lanes >= RPI*LPR idle)
-    static_assert(32 % RPI == 0, "a slab must be a whole number of read instructions");
-    static_assert(NW * 32 * CS * 4 <= LDS_BYTES, "epilogue slab must fit in the tile buffers");
-    float* slab = reinterpret_cast<float*>(smem) + wave * (32 * CS);
-    const int col_in = lane & 31, row_in = (lane >> 5) * 4;
+    static_assert(MB % RPI == 0, "a slab must be a whole number of read instructions");
+    static_assert(NW * MB * CS * 4 <= LDS_BYTES, "epilogue slab must fit in the tile buffers");
+    float* slab = reinterpret_cast<float*>(smem) + wave * (MB * CS);
+    const int col_in = lane & (MB - 1), row_in = lane / MB * 4;
     const int orow = lane / LPR, ocol = (lane % LPR) * 4;
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the redundant tail loads have landed too
     __syncthreads();  // all waves have finished reading the last tile
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
         if (MODE == GEMM_SWIGLU_BF16) {
-            // block columns alternate gate (even j) / up (odd j) for the same 32 outputs
+            // the columns alternate between kSwigluGroup gate and as many up columns of the same outputs
+            constexpr int GB = kSwigluGroup / MB;
 #pragma unroll
-            for (int j = 0; j < TN; j += 2)
+            for (int j = 0; j < TN / 2; ++j) {
+                const int gate = j / GB * (2 * GB) + j % GB;
 #pragma unroll
-                for (int v = 0; v < 16; ++v)
-                    slab[(8 * (v / 4) + row_in + (v % 4)) * CS + (j / 2) * 32 + col_in] =
-                        silu(acc[i][j][v]) * acc[i][j + 1][v];
+                for (int v = 0; v < 4; ++v) slab[(row_in + v) * CS + j * MB + col_in] = silu(acc[i][gate][v]) * acc[i][gate + GB][v];
+            }
         } else {
 #pragma unroll
             for (int j = 0; j < TN; ++j)
 #pragma unroll
-                for (int v = 0; v < 16; ++v)
-                    slab[(8 * (v / 4) + row_in + (v % 4)) * CS + j * 32 + col_in] = acc[i][j][v];
+                for (int v = 0; v < 4; ++v) slab[(row_in + v) * CS + j * MB + col_in] = acc[i][j][v];
         }
         // the slab is private to the wave and LDS executes a wave's instructions in order: no barrier needed
-        const int mrow0 = m0 + wm * WTM + i * 32;
+        const int mrow0 = m0 + wm * WTM + i * MB;
         const bool lane_on = RPI * LPR == 64 || lane < RPI * LPR;
-        f32x4 val[32 / RPI];
+        f32x4 val[MB / RPI];
 #pragma unroll
-        for (int r = 0; r < 32; r += RPI)  // all reads first, so that their latencies overlap
+        for (int r = 0; r < MB; r += RPI)  // all reads first, so that their latencies overlap
             val[r / RPI] = *reinterpret_cast<const f32x4*>(slab + (r + (lane_on ? orow : 0)) * CS + (lane_on ? ocol : 0));
 #pragma unroll
-        for (int r = 0; r < 32; r += RPI) {
+        for (int r = 0; r < MB; r += RPI) {
             const int m = mrow0 + r + orow;
             if (!lane_on || m >= M) continue;
             if (MODE == GEMM_SWIGLU_BF16) {
