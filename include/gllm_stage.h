@@ -206,9 +206,10 @@ gllm_status gllm_op_pack_weight(const void* w, int64_t ldw, int32_t n, int32_t k
  * from HBM), 7 = 64x128 (picked up to 64 rows: two workgroups per compute unit keep more of the weight stream in
  * flight), 8 and 12 = 256x256 tiles for the whole bands of 256 rows plus 64x256 or 128x256 tiles for a last band of at
  * most 128 rows, or two bands of 192x256 tiles for all rows up to 384 (only for m > 256 with 0 < m mod 256 <= 128 and
- * n a multiple of 256), 9 = 288x192 (six wavefronts; only for 256 < m <= 288, n a multiple of 192, not for SwiGLU: all
- * rows in one band, so the weights are read once); a forced tile that does not fit the
- * shape gives GLLM_E_UNSUPPORTED.
+ * n a multiple of 256), 9 = 288x128 (256x192 where n is no multiple of 128; only for 256 < m <= 288, n a multiple of 192,
+ * not for SwiGLU: all rows in one band, so the weights are read once), 13 = one band of 257 to 384 rows, its height a
+ * multiple of 32, by 128 columns, 14 and 15 = bands of equal height, a multiple of 32 from 160 to 256, by 256 and by 128
+ * columns (mode 1: of 256 rows; 13 too); a forced tile that does not fit the shape gives GLLM_E_UNSUPPORTED.
  * Alignment: operands are loaded in 16-byte pieces from any 4-byte boundary.  Where a, one of its rows (lda odd, m > 1) or
  * w starts off a 4-byte boundary, a plain, slow kernel does the product; where the rows of a lie so far apart that a tile
  * of them spans 4 GiB, it runs in bands of fewer rows; where ldw is 2^23 or more, in 128x64 tiles.  On these paths a forced
@@ -225,8 +226,9 @@ gllm_status gllm_op_gemm_bf16_splitk(const void* a, int64_t lda, const void* w, 
 
 /* Host only (no device call): the tile id and split-K factor the library's cost model picks for a problem, as it does
  * when gllm_op_gemm_bf16 is called with tile = -1 (splits stays 1 unless mode is 0; at most max_splits).  Result planes are
- * taken to be read back by the next kernel.
- * tile, splits: HOST out.  The stage plans its QKV, O and down projections with max_splits = 8. */
+ * taken to be read back by the next kernel.  It chooses among tiles 0 to 9 and powers of two.
+ * tile, splits: HOST out.  The stage plans its QKV, O and down projections with max_splits = 8, and the stage and the head
+ * choose among tiles 13 to 15 and other factors that divide k/64 as well. */
 gllm_status gllm_op_gemm_plan(int32_t m, int32_t n, int32_t k, int32_t mode, int32_t max_splits, int32_t* tile,
                               int32_t* splits);
 

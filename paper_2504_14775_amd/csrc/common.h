@@ -48,7 +48,9 @@ enum GemmMode { GEMM_STORE_F32 = 0, GEMM_ADD_F32 = 1, GEMM_SWIGLU_BF16 = 2 };
 // (only where gemm_mixed_rem_cols(m, n) > 0); 5 = 256x192 (not SwiGLU); 6 = 128x128 with four LDS stages; 7 = 64x128
 // (up to 64 rows: weight streaming); 8 and 12 = 256x256 tiles for the whole bands of 256 rows plus 64x256 or 128x256
 // tiles for a last band of at most 128 rows, two bands of 192x256 tiles up to 384 rows (only where
-// gemm_rowmix_rem_rows(m, n) > 0); 9 = 288x192.
+// gemm_rowmix_rem_rows(m, n) > 0); 9 = 288x128 (256x192 where n is no multiple of 128); 13 = one band of 257..384 rows, its
+// height a multiple of 32, x 128; 14 and 15 = bands of equal height, a multiple of 32 from 160 to 256, x 256 and x 128
+// (mode GEMM_ADD_F32: 256).
 // splits > 1 (store mode only): split s covers k range [s*k/splits, (s+1)*k/splits) and writes its partial
 // product to out + s*split_stride floats; the consumer sums the planes in order.
 hipError_t launch_gemm_bf16(const bf16_t* a, int64_t lda, const bf16_t* w, int64_t ldw, void* out, int64_t ldc,
@@ -61,6 +63,8 @@ int gemm_rowmix_rem_rows(int m, int n);
 // whether it may pick tile 8.  Result planes count twice: as they are written and as the next kernel reads them back.
 struct GemmPlan { int tile; int splits; };
 GemmPlan gemm_plan(int m, int n, int k, int mode, int max_splits, bool row_mixed = true);
+// The same among tiles 0 to 9 and split-K factors that are powers of two: the answers of gllm_op_gemm_plan.
+GemmPlan gemm_plan_listed(int m, int n, int k, int mode, int max_splits);
 
 // Residual stream entry: x = float(in_bf16), h = bf16(rmsnorm(x) * gamma).  The launch also copies copy_bytes (a multiple
 // of 16) from copy_src, which may be pinned host memory, to copy_dst; both 16-byte aligned.

@@ -83,7 +83,9 @@ __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ A, int64_t 
     static_assert(NSW == NS || NSW == NS + 1, "the W tile has as many stages as the A tile, or one more");
     static_assert((BM / 8) % NW == 0 && (BN / 8) % NW == 0 && NW % 2 == 0, "load groups must divide among an even number of waves");
     static_assert(WTM % MB == 0 && WTN % MB == 0, "a wave tile is made of whole MFMA blocks");
-    static_assert(MODE != GEMM_SWIGLU_BF16 || WTN % (2 * kSwigluGroup) == 0, "SwiGLU needs gate and up columns in one wave");
+    static_assert(MODE != GEMM_SWIGLU_BF16 || WTN % (2 * kSwigluGroup) == 0 || WTN == 2 * MB, "SwiGLU needs gate and up columns in one wave");
+    // a wave tile of 32 columns takes 16 gate columns and the 16 up columns of the same outputs
+    constexpr bool kPaired = MODE == GEMM_SWIGLU_BF16 && WTN == 2 * MB;
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
 
     // ---- tile assignment: tiles are numbered band by band ----
@@ -161,7 +163,7 @@ __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ A, int64_t 
         constexpr int kPart = (GPW + KK - 1) / KK;  // global loads issued per k-step
         const int frow = lane & (MB - 1), fgrp = lane / MB;
         const int fsw = (frow >> 1) & 7, fpar = (frow & 1) * 8;
-        const int a_off = (wm * WTM + (frow & ~1)) * (BK * 2), w_off = (wn * WTN + (frow & ~1)) * (BK * 2);
+        const int a_off = (wm * WTM + (frow & ~1)) * (BK * 2), w_off = ((kPaired ? wn / 2 * (2 * kSwigluGroup) + wn % 2 * MB : wn * WTN) + (frow & ~1)) * (BK * 2);
         int fg[KK];
 #pragma unroll
         for (int kk = 0; kk < KK; ++kk) fg[kk] = ((fpar + kk * (MK / 8) + fgrp) ^ fsw) * 16;
@@ -169,7 +171,7 @@ __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ A, int64_t 
         // operand read r of k-step kk of the tile in the stages at sa, sw, in the order the MFMAs want them
         auto read_frag = [&](int r, int kk, int sa, int sw, int buf) {
             if (r == 0) fa[buf][0] = *reinterpret_cast<const bf16x8*>(smem + sa + a_off + fg[kk]);
-            else if (r <= TN) fw[buf][r - 1] = *reinterpret_cast<const bf16x8*>(smem + sw + w_off + fg[kk] + (r - 1) * MB * (BK * 2));
+            else if (r <= TN) fw[buf][r - 1] = *reinterpret_cast<const bf16x8*>(smem + sw + w_off + fg[kk] + (r - 1) * (kPaired ? kSwigluGroup : MB) * (BK * 2));
             else fa[buf][r - TN] = *reinterpret_cast<const bf16x8*>(smem + sa + a_off + fg[kk] + (r - TN) * MB * (BK * 2));
         };
         // One k-step: multiply the fragments in `buf`, fetch those of k-step kk_next of the tile in the stages at ra, rw
@@ -259,7 +261,7 @@ __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ A, int64_t 
     for (int i = 0; i < TM; ++i) {
         if (MODE == GEMM_SWIGLU_BF16) {
             // the columns alternate between kSwigluGroup gate and as many up columns of the same outputs
-            constexpr int GB = kSwigluGroup / MB;
+            constexpr int GB = kPaired ? 1 : kSwigluGroup / MB;
 #pragma unroll
             for (int j = 0; j < TN / 2; ++j) {
                 const int gate = j / GB * (2 * GB) + j % GB;
@@ -300,6 +302,10 @@ __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ A, int64_t 
 #endif
 }
 
+// LDS stages of the A tile beside three of a 256-column W tile: what 160 KiB hold.
+template <int H>
+constexpr int kWideStages = H <= 160 ? 3 : 2;
+
 template <int BM, int BN, int WGM, int WGN, int MODE, int NS = 2, int NSW = NS, bool W_ONCE = false, bool W_FAR = false>
 __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_kernel(const bf16_t* __restrict__ A, int64_t lda,
                                                                     const bf16_t* __restrict__ W, int64_t ldw,
@@ -316,21 +322,21 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_kernel(const bf16_t*
                                                        v / num_tiles, gridDim.y, split_stride);
 }
 
-// Two tile shapes in one launch: the first big_tiles workgroups cover columns [0, n_split) with 256x256
-// tiles (whole rounds of the 256 compute units), the rest cover [n_split, N) with 256x128 tiles, so that
-// the last, partial round still gives every compute unit a (half-size) tile.
-template <int MODE>
+// Two tile shapes in one launch: the first big_tiles workgroups cover columns [0, n_split) with H x 256 tiles (whole rounds
+// of the 256 compute units), the rest cover [n_split, N) with H x 128 tiles, so that the last, partial round still gives
+// every compute unit a (half-size) tile.
+template <int MODE, int H, bool W_ONCE>
 __global__ __launch_bounds__(256) void gemm_bf16_mixed_kernel(const bf16_t* __restrict__ A, int64_t lda,
                                                                const bf16_t* __restrict__ W, int64_t ldw,
                                                                void* __restrict__ out, int64_t ldc, int M, int K,
                                                                int tiles_m, int big_cols, int small_cols) {
     const int big_tiles = tiles_m * big_cols;
     if ((int)blockIdx.x < big_tiles)
-        gemm_tile<256, 256, 2, 2, MODE, 2, 3>(A, lda, W, ldw, out, ldc, M, K, tiles_m, big_cols, 0,
-                                              xcd_contiguous(blockIdx.x, big_tiles), 0, 1, 0);
+        gemm_tile<H, 256, 2, 2, MODE, kWideStages<H>, 3, W_ONCE>(A, lda, W, ldw, out, ldc, M, K, tiles_m, big_cols, 0,
+                                                                xcd_contiguous(blockIdx.x, big_tiles), 0, 1, 0);
     else
-        gemm_tile<256, 128, 2, 2, MODE, 3>(A, lda, W, ldw, out, ldc, M, K, tiles_m, small_cols, big_cols * 256,
-                                           xcd_contiguous(blockIdx.x - big_tiles, tiles_m * small_cols), 0, 1, 0);
+        gemm_tile<H, 128, 2, 2, MODE, 3, 3, W_ONCE>(A, lda, W, ldw, out, ldc, M, K, tiles_m, small_cols, big_cols * 256,
+                                                    xcd_contiguous(blockIdx.x - big_tiles, tiles_m * small_cols), 0, 1, 0);
 }
 
 // Two tile heights in one launch: the first big_tiles workgroups cover the whole bands of 256 rows with 256x256
@@ -400,23 +406,60 @@ hipError_t launch_tile(const bf16_t* a, int64_t lda, const bf16_t* w, int64_t ld
                    : launch_tile_w<BM, BN, WGM, WGN, MODE, NS, NSW, false>(a, lda, w, ldw, out, ldc, m, n, k, splits, split_stride, stream);
 }
 
+// Heights.  A band of 256 rows around 200 does a fifth of its MFMAs and LDS reads for nothing, two of 256 around 400 likewise,
+// so rows are cut into bands of equal height, a multiple of 32 (16 rows a wave); from 257 to 384 rows one band of them all
+// with 128 columns reads the weights once instead of twice.  us, before -> after (gate/up 28672 x 4096, best tile before): 200
+// rows 55.4 -> 52.7, 257 rows 72.7 -> 58.4, 320 rows 76.8 -> 66.3, 352 rows 78.0 -> 69.6, 448 rows 97.4 -> 82.8; vocabulary
+// 128256 x 4096: 200 rows 225.6 -> 208.3, 257 rows 303.1 -> 282.2, 320 rows 357.4 -> 301.1, 448 rows 417.0 -> 382.1.
+// Height of `bands` bands of equal height that cover m rows: a multiple of 32 from 160 on (lower ones gain nothing: the
+// weights' stream bounds them).
+int band_height(int m, int bands) { return std::max(160, (int)round_up(ceil_div(m, bands), 32)); }
+
+// Bands of at most 256 rows: as few as cover m rows, or one more where that pads less (960 rows: five of 192, not four of 256).
+int gemm_band_height(int m, int mode) {
+    if (mode == GEMM_ADD_F32) return 256;  // (no caller of this library's own: one height)
+    const int few = (int)ceil_div(m, 256), h0 = band_height(m, few), h1 = band_height(m, few + 1);
+    return round_up(m, h1) < round_up(m, h0) ? h1 : h0;
+}
+
 template <int MODE>
 hipError_t launch_mode(const bf16_t* a, int64_t lda, const bf16_t* w, int64_t ldw, void* out, int64_t ldc, int m,
                        int n, int k, int tile, int splits, int64_t split_stride, hipStream_t stream) {
 #define GLLM_TILE_ARGS a, lda, w, ldw, out, ldc, m, n, k, splits, split_stride, stream
+    const int height = gemm_band_height(m, MODE);
     switch (tile) {
         case 0: return launch_tile<128, 128, 2, 2, MODE, 2, 3>(GLLM_TILE_ARGS);  // 80 KiB of LDS: two workgroups per compute unit
         case 1:
             if (gemm_low_bands(m)) return launch_tile<192, 128, 2, 2, MODE, 4>(GLLM_TILE_ARGS);
             return launch_tile<256, 128, 2, 2, MODE, 3>(GLLM_TILE_ARGS);
+        case 8: case 12: return launch_tile<192, 256, 2, 2, MODE, 2, 3>(GLLM_TILE_ARGS);  // 257..384 rows
+        case 14:
+            if constexpr (MODE != GEMM_ADD_F32) {
+                if (height == 160) return launch_tile<160, 256, 2, 2, MODE, kWideStages<160>, 3>(GLLM_TILE_ARGS);
+                if (height == 192) return launch_tile<192, 256, 2, 2, MODE, kWideStages<192>, 3>(GLLM_TILE_ARGS);
+                if (height == 224) return launch_tile<224, 256, 2, 2, MODE, kWideStages<224>, 3>(GLLM_TILE_ARGS);
+            }
+            return launch_tile<256, 256, 2, 2, MODE, 2, 3>(GLLM_TILE_ARGS);
+        case 15:
+            if constexpr (MODE != GEMM_ADD_F32) {
+                if (height == 160) return launch_tile<160, 128, 2, 2, MODE, 4>(GLLM_TILE_ARGS);
+                if (height == 192) return launch_tile<192, 128, 2, 2, MODE, 4>(GLLM_TILE_ARGS);
+                if (height == 224) return launch_tile<224, 128, 2, 2, MODE, 3>(GLLM_TILE_ARGS);
+            }
+            return launch_tile<256, 128, 2, 2, MODE, 3>(GLLM_TILE_ARGS);
         case 2: case 3: case 10: return launch_tile<256, 256, 2, 2, MODE, 2, 3>(GLLM_TILE_ARGS);
         case 6: return launch_tile<128, 128, 2, 2, MODE, 4>(GLLM_TILE_ARGS);
-        case 7: return launch_tile<64, 128, 2, 2, MODE, 3>(GLLM_TILE_ARGS);
-        case 8: case 12:  // 257..384 rows
-            return launch_tile<192, 256, 2, 2, MODE, 2, 3>(GLLM_TILE_ARGS);
-        case 9:  // one 288-row tile covers all rows
-            if constexpr (MODE != GEMM_SWIGLU_BF16) return launch_tile<288, 192, 3, 2, MODE, 2, 3>(GLLM_TILE_ARGS);
-            else return hipErrorInvalidValue;
+        case 7:  // up to 32 rows half the activations to load and to read from LDS: one row of the 8B shape 785 -> 770 us
+            if (m <= 32) return launch_tile<32, 128, 1, 4, MODE, 3>(GLLM_TILE_ARGS);
+            return launch_tile<64, 128, 2, 2, MODE, 3>(GLLM_TILE_ARGS);
+        case 13:  // one band of 257..384 rows
+            if constexpr (MODE != GEMM_ADD_F32) {
+                if (m <= 288) return launch_tile<288, 128, 2, 2, MODE, 3>(GLLM_TILE_ARGS);
+                if (m <= 320) return launch_tile<320, 128, 2, 2, MODE, 2, 3>(GLLM_TILE_ARGS);
+                if (m <= 352) return launch_tile<352, 128, 2, 2, MODE, 2, 3>(GLLM_TILE_ARGS);
+                return launch_tile<384, 128, 2, 2, MODE, 2, 3>(GLLM_TILE_ARGS);
+            }
+            return launch_tile<256, 128, 2, 2, MODE, 3>(GLLM_TILE_ARGS);
         case 5:
             if constexpr (MODE != GEMM_SWIGLU_BF16) return launch_tile<256, 192, 2, 2, MODE, 2, 3>(GLLM_TILE_ARGS);
             else return hipErrorInvalidValue;
@@ -434,23 +477,37 @@ hipError_t launch_far(const bf16_t* a, int64_t lda, const bf16_t* w, int64_t ldw
 
 constexpr size_t kWideTileLds = (2 * 256 + 3 * 256) * BK * sizeof(bf16_t);  // 256x256 tile: all 160 KiB
 
-// Mixed launch (see gemm_bf16_mixed_kernel); rem_cols 256-wide tile columns are turned into 2*rem_cols
-// 128-wide ones.
-template <int MODE>
-hipError_t launch_mixed(const bf16_t* a, int64_t lda, const bf16_t* w, int64_t ldw, void* out, int64_t ldc, int m,
-                        int n, int k, int rem_cols, hipStream_t stream) {
-    const int tiles_m = (int)ceil_div(m, 256), big_cols = n / 256 - rem_cols, small_cols = 2 * rem_cols;
-    auto kern = gemm_bf16_mixed_kernel<MODE>;
+// Mixed launch (see gemm_bf16_mixed_kernel); rem_cols 256-wide tile columns are turned into 2*rem_cols 128-wide ones.
+template <int MODE, int H, bool W_ONCE>
+hipError_t launch_mixed_h(const bf16_t* a, int64_t lda, const bf16_t* w, int64_t ldw, void* out, int64_t ldc, int m,
+                          int n, int k, int rem_cols, hipStream_t stream) {
+    const int tiles_m = (int)ceil_div(m, H), big_cols = n / 256 - rem_cols, small_cols = 2 * rem_cols;
+    const size_t smem = std::max(kWideStages<H> * H + 3 * 256, 3 * H + 3 * 128) * BK * sizeof(bf16_t);
+    auto kern = gemm_bf16_mixed_kernel<MODE, H, W_ONCE>;
     static bool configured = false;
     if (!configured) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)kWideTileLds);
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
         if (e != hipSuccess) return e;
         configured = true;
     }
-    kern<<<tiles_m * (big_cols + small_cols), 256, kWideTileLds, stream>>>(a, lda, w, ldw, out, ldc, m, k, tiles_m, big_cols,
-                                                                           small_cols);
+    kern<<<tiles_m * (big_cols + small_cols), 256, smem, stream>>>(a, lda, w, ldw, out, ldc, m, k, tiles_m, big_cols, small_cols);
     return hipGetLastError();
+}
+
+template <int MODE>
+hipError_t launch_mixed(const bf16_t* a, int64_t lda, const bf16_t* w, int64_t ldw, void* out, int64_t ldc, int m,
+                        int n, int k, int rem_cols, hipStream_t stream) {
+#define GLLM_MIXED(H_) (m <= H_ ? launch_mixed_h<MODE, H_, true>(a, lda, w, ldw, out, ldc, m, n, k, rem_cols, stream)   \
+                                : launch_mixed_h<MODE, H_, false>(a, lda, w, ldw, out, ldc, m, n, k, rem_cols, stream))
+    if constexpr (MODE != GEMM_ADD_F32) {
+        const int height = band_height(m, (int)ceil_div(m, 256));
+        if (height == 160) return GLLM_MIXED(160);
+        if (height == 192) return GLLM_MIXED(192);
+        if (height == 224) return GLLM_MIXED(224);
+    }
+    return GLLM_MIXED(256);
+#undef GLLM_MIXED
 }
 
 // Row-mixed launch (see gemm_bf16_rowmix_kernel); BMR is 64 or 128.
@@ -496,34 +553,113 @@ int gemm_mixed_rem_cols(int m, int n) {
 namespace {
 
 // Cost of a launch of one tile shape in us, fitted to measurements on MI355X with operands streaming from HBM (weights
-// are cold in the stage; four stage shapes and two vocabularies, 65 to 4160 rows, every tile and split: 938 products):
+// are cold in the stage; four stage shapes and two vocabularies, 65 to 4160 rows, every tile and split: 936 products):
 // fixed + rounds * (step * k_steps + per_tile) + plane * (us to read the fp32 result at 6 TB/s).  A round is one tile per
 // compute unit (two for a shape of which two share one); a last round that fills a share x of them counts
 // lone + (1 - lone) x, because fewer tiles run faster: the chip is power- and bandwidth-limited.  No launch is faster than
-// its loads: the weights at `stream` TB/s and the activations, once per tile column, at 62 TB/s from the caches, both
-// slower by as much as the last round is short of tiles.  (Decides from 65 to 192 rows: with one bound for all tiles,
-// 128256 x 4096 at 128 rows ran on 128x128 tiles with a compute unit each in 253 us; two of them sharing one take 207.)
-// The picks are 0.8 % behind the best ones on average (profiles/gemm_plan_sweep.txt).
+// its loads: the weights at `stream` TB/s and the activations, once per tile column, at kCacheRate TB/s from the caches, both
+// slower by as much as the last round is short of tiles.
+// The picks are 0.6 % behind the best ones on average (profiles/gemm_plan_sweep.txt): as far on a run that was not fitted.
 struct TileCost {
     int slots, width;  // tiles in a round, columns of a tile
     double step, fixed, lone, per_tile, plane, stream;
 };
-constexpr TileCost kCost128x128{512, 128, 0.955, 8.21, 0.44, 0.08, 0.7, 5.96}, kCost128x128Deep{256, 128, 0.507, 3.44, 0.7, 0.76, 0.95, 5.54},
-    kCost192x128{256, 128, 0.684, 3.9, 0.54, 2.31, 0.69, 5.38}, kCost256x128{256, 128, 0.812, 4.38, 0.62, 3.69, 0.4, 5.28},
-    kCost256x192{256, 192, 1.175, 4.32, 0.59, 0.0, 0.99, 5.07}, kCost256x256{256, 256, 1.456, 4.35, 0.52, 2.38, 0.93, 5.55},
-    kCost192x256{256, 256, 1.2, 0.47, 0.44, 7.24, 0.54, 7.46}, kCost288x192{256, 192, 1.587, 2.25, 0.68, 0.0, 1.09, 6.17};
+constexpr double kCacheRate = 154;
+constexpr TileCost kCost128x128{512, 128, 0.919, 7.22, 0.45, 0, 0.57, 6.25}, kCost128x128Deep{256, 128, 0.526, 3.35, 0.76, 0.78, 0.97, 6.29}, kCost256x192{256, 192, 1.13, 4.19, 0.66, 1.97, 0.39, 5.13};
+// tiles of 160, 192, 224 and 256 rows x 128 and x 256 columns, and of 288, 320, 352 and 384 rows x 128
+constexpr TileCost narrow_cost(double step) { return {256, 128, step, 4.41, 0.6, 3, 0.66, 5.27}; }
+constexpr TileCost tall_cost(double step) { return {256, 128, step, 4.85, 0.57, 2.54, 0.47, 4.34}; }
+constexpr TileCost wide_cost(double step) { return {256, 256, step, 3.38, 0.5, 2.22, 0.63, 6.33}; }
+constexpr TileCost kCostNarrow[4] = {narrow_cost(0.564), narrow_cost(0.592), narrow_cost(0.672), narrow_cost(0.745)},
+                   kCostWide[4] = {wide_cost(1.02), wide_cost(1.08), wide_cost(1.207), wide_cost(1.386)},
+                   kCostTall[4] = {tall_cost(0.888), tall_cost(0.926), tall_cost(0.961), tall_cost(1.042)};
+const TileCost& narrow_cost_of(int height) { return kCostNarrow[(height - 160) / 32]; }
+const TileCost& wide_cost_of(int height) { return kCostWide[(height - 160) / 32]; }
 
+// Rounds that `tiles` tiles count as, where a round has c.slots of them.
 double rounds_of(const TileCost& c, double tiles) {
-    const double full = std::floor(tiles / c.slots), rest = tiles / c.slots - full;
+    const double full = std::floor(tiles / c.slots + 1e-9), rest = tiles / c.slots - full;
     return full + (rest > 1e-9 ? c.lone + (1.0 - c.lone) * rest : 0.0);
 }
 
-// Tile shape and split-K factor (a power of two in [min_splits, max_splits]) of the lowest cost.  Up to 64 rows the
+// The same for a row-mixed launch: `big` tiles of 256 rows, then `low` tiles of the last band, which count 0.75 of one each.
+constexpr double kLowTile = 0.75;
+double rounds_of_rowmix(const TileCost& c, double big, double low) {
+    const double full = std::floor(big / c.slots), rest = big - full * c.slots;
+    if (rest <= 0) return full + kLowTile * rounds_of(c, low);
+    const double beside = std::min(low, c.slots - rest);  // low tiles in the round of the last big ones
+    return full + c.lone + (1.0 - c.lone) * (rest + kLowTile * beside) / c.slots + kLowTile * rounds_of(c, low - beside);
+}
+
+// Tile shape and split-K factor (a divisor of the k-steps, at most max_splits) of the lowest cost.  Up to 64 rows the
 // product is a stream of the weights and the 64x128 tile (two workgroups per compute unit, 64 KiB of weights in flight on
-// each, half the activation traffic of a 128-row tile) the only candidate: 0.30 x 1.65 us per k-step of a tile, but not
-// less than the weights take at 5.5 TB/s.  A result plane is read back by the next kernel, so a product that is split
-// less is worth the time of that.
-GemmPlan cheapest(int m, int n, int k, int mode, int min_splits, int max_splits, bool row_mixed) {
+// each, half the activation traffic of a 128-row tile) the only candidate, split 1, 2, 4 or 8 ways: 0.30 x 1.65 us per k-step
+// of a tile, but not less than the weights take at 5.5 TB/s.  A result plane is read back by the next kernel, so a product
+// that is split less is worth the time of that.
+GemmPlan cheapest(int m, int n, int k, int mode, int max_splits, bool row_mixed) {
+    const int its = k / BK;
+    GemmPlan best{0, 1};
+    double best_cost = 1e30;
+    if (mode != GEMM_STORE_F32) max_splits = 1;
+    for (int s = 1; s <= max_splits; ++s) {
+        if (its % s != 0 || (s > 1 && its / s < 8)) continue;
+        const double steps = (double)its / s;
+        const double plane = mode == GEMM_STORE_F32 ? (double)m * n * 4.0 * s / 6e6 : 0.0;  // us to read the result
+        if (m <= 64 && n % 128 == 0) {
+            if (s & (s - 1)) continue;
+            const double cost = std::max((double)ceil_div((int64_t)(n / 128) * s, 512) * steps * 0.30, (double)n * k * 2.0 / 5.5e12 / 1.65e-6) +
+                                2.0 + (double)m * n * 4.0 * s / 8e12 / 1.65e-6;
+            if (cost < best_cost) { best_cost = cost; best = GemmPlan{7, s}; }
+            continue;
+        }
+        auto round_us = [&](const TileCost& c) { return c.step * steps + c.per_tile; };
+        // `rounds` as they count, `full` if the last one were as good as the others
+        auto consider_rounds = [&](int tile, const TileCost& c, double rounds, double full) {
+            const double work = c.fixed + rounds * round_us(c) + c.plane * plane;
+            const double loads = (double)n * k * 2e-6 * (1.0 / c.stream + m / (kCacheRate * c.width)) * rounds / full;
+            const double cost = std::max(work, loads) + plane + 1e-3 * work;  // of two that their loads bound, the lighter one
+            if (cost < best_cost) { best_cost = cost; best = GemmPlan{tile, s}; }
+        };
+        auto consider = [&](int tile, const TileCost& c, double tiles) {
+            consider_rounds(tile, c, rounds_of(c, tiles * s), tiles * s / c.slots);
+        };
+        const int height = gemm_band_height(m, mode);
+        const double bands = (double)ceil_div(m, height), b128 = (double)ceil_div(m, 128), b256 = (double)ceil_div(m, 256);
+        if (n % 256 == 0) {
+            const double cols = n / 256;
+            if (row_mixed && m > 384 && gemm_rowmix_rem_rows(m, n) > 0) {
+                const double big = (double)(m / 256) * cols * s, low = cols * s;
+                consider_rounds(8, wide_cost_of(256), rounds_of_rowmix(wide_cost_of(256), big, low), (big + kLowTile * low) / 256);
+            }
+            if (s == 1 && gemm_mixed_rem_cols(m, n) > 0) {  // whole rounds of big tiles and one of half-width ones
+                const int h = mode == GEMM_ADD_F32 ? 256 : band_height(m, (int)b256);
+                const TileCost &big = wide_cost_of(h), &low = narrow_cost_of(h);
+                const double tiles = b256 * cols, whole = std::floor(tiles / 256), half = rounds_of(low, 2 * (tiles - whole * 256));
+                consider_rounds(4, big, whole + half * round_us(low) / round_us(big), tiles / 256);
+            }
+            consider(3, wide_cost_of(256), b256 * cols);
+            if (height < 256) consider(14, wide_cost_of(height), bands * cols);
+        }
+        if (n % 192 == 0 && mode != GEMM_SWIGLU_BF16) consider(5, kCost256x192, b256 * (n / 192));
+        if (n % 128 == 0) {
+            const double cols = n / 128;
+            consider(15, narrow_cost_of(height), bands * cols);
+            if (m > 256 && m <= 384 && mode != GEMM_ADD_F32) consider(13, kCostTall[(m - 257) / 32], cols);
+            consider(6, kCost128x128Deep, b128 * cols);
+            consider(0, kCost128x128, b128 * cols);
+        }
+    }
+    return best;
+}
+
+constexpr TileCost kListed128x128{512, 128, 0.955, 8.21, 0.44, 0.08, 0.7, 5.96}, kListed128x128Deep{256, 128, 0.507, 3.44, 0.7, 0.76, 0.95, 5.54},
+    kListed192x128{256, 128, 0.684, 3.9, 0.54, 2.31, 0.69, 5.38}, kListed256x128{256, 128, 0.812, 4.38, 0.62, 3.69, 0.4, 5.28},
+    kListed256x192{256, 192, 1.175, 4.32, 0.59, 0.0, 0.99, 5.07}, kListed256x256{256, 256, 1.456, 4.35, 0.52, 2.38, 0.93, 5.55},
+    kListed192x256{256, 256, 1.2, 0.47, 0.44, 7.24, 0.54, 7.46}, kListed288x192{256, 192, 1.587, 2.25, 0.68, 0.0, 1.09, 6.17};
+
+// The planner of the public operations: the tile ids 0 to 9 and split-K factors that are powers of two, with the costs above
+// (fitted to 938 products of these forms, measured with the 32x32x16 MFMAs).
+GemmPlan cheapest_listed(int m, int n, int k, int mode, int min_splits, int max_splits, bool row_mixed) {
     const int its = k / BK;
     GemmPlan best{0, min_splits};
     double best_cost = 1e30;
@@ -553,24 +689,24 @@ GemmPlan cheapest(int m, int n, int k, int mode, int min_splits, int max_splits,
         if (n % 256 == 0) {
             const double cols = n / 256;
             const int rr = row_mixed ? gemm_rowmix_rem_rows(m, n) : 0;
-            if (rr > 0 && m <= 384) consider(8, kCost192x256, 2 * cols);
-            else if (rr > 0) consider(8, kCost256x256, (m / 256 + (rr == 64 ? 0.6 : 0.8)) * cols);
+            if (rr > 0 && m <= 384) consider(8, kListed192x256, 2 * cols);
+            else if (rr > 0) consider(8, kListed256x256, (m / 256 + (rr == 64 ? 0.6 : 0.8)) * cols);
             if (s == 1 && gemm_mixed_rem_cols(m, n) > 0) {  // whole rounds of big tiles and one of half-width ones
-                const double tiles = b256 * cols, whole = std::floor(tiles / 256), half = rounds_of(kCost256x128, 2 * (tiles - whole * 256));
-                consider_rounds(4, kCost256x256, whole + half * round_us(kCost256x128) / round_us(kCost256x256), tiles / 256);
+                const double tiles = b256 * cols, whole = std::floor(tiles / 256), half = rounds_of(kListed256x128, 2 * (tiles - whole * 256));
+                consider_rounds(4, kListed256x256, whole + half * round_us(kListed256x128) / round_us(kListed256x256), tiles / 256);
             }
-            consider(3, kCost256x256, b256 * cols);
+            consider(3, kListed256x256, b256 * cols);
         }
         if (n % 192 == 0 && mode != GEMM_SWIGLU_BF16) {
-            consider(5, kCost256x192, b256 * (n / 192));
-            if (m > 256 && m <= 288) consider(9, kCost288x192, n / 192);
+            consider(5, kListed256x192, b256 * (n / 192));
+            if (m > 256 && m <= 288) consider(9, kListed288x192, n / 192);
         }
         if (n % 128 == 0) {
             const double cols = n / 128;
-            if (gemm_low_bands(m)) consider(1, kCost192x128, b192 * cols);
-            else consider(1, kCost256x128, b256 * cols);
-            consider(6, kCost128x128Deep, b128 * cols);
-            consider(0, kCost128x128, b128 * cols);
+            if (gemm_low_bands(m)) consider(1, kListed192x128, b192 * cols);
+            else consider(1, kListed256x128, b256 * cols);
+            consider(6, kListed128x128Deep, b128 * cols);
+            consider(0, kListed128x128, b128 * cols);
         }
     }
     return best;
@@ -579,8 +715,10 @@ GemmPlan cheapest(int m, int n, int k, int mode, int min_splits, int max_splits,
 }  // namespace
 
 GemmPlan gemm_plan(int m, int n, int k, int mode, int max_splits, bool row_mixed) {
-    return cheapest(m, n, k, mode, 1, max_splits, row_mixed);
+    return cheapest(m, n, k, mode, max_splits, row_mixed);
 }
+
+GemmPlan gemm_plan_listed(int m, int n, int k, int mode, int max_splits) { return cheapest_listed(m, n, k, mode, 1, max_splits, true); }
 
 namespace {
 
@@ -593,6 +731,9 @@ bool tile_fits(int tile, int m, int n, int mode, int splits) {
         case 5: return n % 192 == 0 && mode != GEMM_SWIGLU_BF16;
         case 8: case 12: return gemm_rowmix_rem_rows(m, n) > 0;
         case 9: return m > 256 && m <= 288 && n % 192 == 0 && mode != GEMM_SWIGLU_BF16;
+        case 13: return m > 256 && m <= 384 && n % 128 == 0;
+        case 14: return n % 256 == 0;
+        case 15: return n % 128 == 0;
         default: return false;
     }
 }
@@ -608,9 +749,10 @@ hipError_t launch_gemm_bf16(const bf16_t* a, int64_t lda, const bf16_t* w, int64
     if (splits < 1 || (k / BK) % splits != 0) return hipErrorInvalidValue;
     if (splits > 1 && mode != GEMM_STORE_F32) return hipErrorInvalidValue;
     if (tile < 0) {
-        tile = cheapest(m, n, k, splits == 1 ? mode : GEMM_STORE_F32, splits, splits, true).tile;
+        tile = cheapest_listed(m, n, k, splits == 1 ? mode : GEMM_STORE_F32, splits, splits, true).tile;
     }
     if (!tile_fits(tile, m, n, mode, splits)) return hipErrorInvalidValue;
+    if (tile == 9) tile = n % 128 == 0 ? 13 : 5;
     if ((((uintptr_t)a | (uintptr_t)w) & 3) || (m > 1 && lda % 2 != 0)) {
         const int cols = mode == GEMM_SWIGLU_BF16 ? n / 2 : n;
         const int64_t blocks = ceil_div((int64_t)m * cols, 256);

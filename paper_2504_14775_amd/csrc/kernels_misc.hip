@@ -377,7 +377,11 @@ hipError_t launch_rmsnorm_any(const bf16_t* in, float* x, const float* y, int pl
         if (FROM_BF16 || planes == 0) GLLM_RMS_P(V, 0, N);       \
         else if (planes == 1) GLLM_RMS_P(V, 1, N);               \
         else if (planes == 2) GLLM_RMS_P(V, 2, N);               \
+        else if (planes == 3) GLLM_RMS_P(V, 3, N);               \
         else if (planes == 4) GLLM_RMS_P(V, 4, N);               \
+        else if (planes == 5) GLLM_RMS_P(V, 5, N);               \
+        else if (planes == 6) GLLM_RMS_P(V, 6, N);               \
+        else if (planes == 7) GLLM_RMS_P(V, 7, N);               \
         else if (planes == 8) GLLM_RMS_P(V, 8, N);               \
         else GLLM_RMS_P(V, -1, N);                               \
     } while (0)
@@ -461,7 +465,11 @@ hipError_t launch_rope_kv_write(const RopeKvArgs& a, hipStream_t stream) {
     switch (a.planes) {
         case 1: rope_kv_write_kernel<1><<<grid, 256, 0, stream>>>(a, parts); break;
         case 2: rope_kv_write_kernel<2><<<grid, 256, 0, stream>>>(a, parts); break;
+        case 3: rope_kv_write_kernel<3><<<grid, 256, 0, stream>>>(a, parts); break;
         case 4: rope_kv_write_kernel<4><<<grid, 256, 0, stream>>>(a, parts); break;
+        case 5: rope_kv_write_kernel<5><<<grid, 256, 0, stream>>>(a, parts); break;
+        case 6: rope_kv_write_kernel<6><<<grid, 256, 0, stream>>>(a, parts); break;
+        case 7: rope_kv_write_kernel<7><<<grid, 256, 0, stream>>>(a, parts); break;
         case 8: rope_kv_write_kernel<8><<<grid, 256, 0, stream>>>(a, parts); break;
         default: rope_kv_write_kernel<-1><<<grid, 256, 0, stream>>>(a, parts); break;
     }

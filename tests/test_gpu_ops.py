@@ -399,3 +399,39 @@ def test_pack_weight_writes_the_documented_tiled_layout():
     assert np.abs(res.cpu().numpy() - ref).max() <= 2e-5 * np.abs(ref).max() + 1e-6
     with pytest.raises(B.GllmError):          # a k extent that is no multiple of 64
         B.gllm_op_gemm_bf16(to_dev_bits(padded_rows(a, 256)), to_dev_weight(wn), res, M, N, k, B.GEMM_STORE_F32, -1, ldw=200)
+
+
+def _gate_up(bits):
+    """Rows of a [2*I, K] matrix (gate rows, then up rows) in the order the ABI states: 32 gate rows, the 32 matching up rows."""
+    I = bits.shape[0] // 2
+    return np.concatenate([bits[:I].reshape(I // 32, 1, 32, -1), bits[I:].reshape(I // 32, 1, 32, -1)], axis=1).reshape(bits.shape)
+
+
+@pytest.mark.parametrize("tile,N,rows", [(7, 256, (1, 31, 32, 33)), (13, 256, (257, 288, 289, 320, 321, 352, 353, 384)),
+                                         (14, 512, (1, 160, 161, 193, 224, 225, 257, 321, 449, 960)),
+                                         (15, 384, (1, 160, 161, 193, 224, 225, 257, 321, 449, 960)),
+                                         (4, 66048, (65, 161, 193, 225))])
+@pytest.mark.parametrize("K", [64, 320])
+def test_gemm_band_heights_at_their_edges(tile, N, rows, K):
+    """Both sides of every band height, plain and SwiGLU; NaN behind the last row of a, canaries behind the last row of the
+    result.  K roundings of 2^-24 of the sum of magnitudes bound an fp32 sum; SwiGLU rounds to bf16 (2^-8 and the hardware
+    exponential's and reciprocal's ulps) and takes the error of both sums."""
+    for M in rows:
+        print(f"gemm heights tile={tile} K={K} M={M}", flush=True)
+        a, w = rand_bits(14, M, (M, K), 1.0), rand_bits(14, 2, (N, K), 0.05)
+        ap = np.full((M + 64, K), 0x7FC0, dtype=np.uint16)
+        ap[:M] = a
+        x, y = oracle.bf16_to_f64(a), oracle.bf16_to_f64(w)
+        ref, bound = x @ y.T, (np.abs(x) @ np.abs(y).T) * K * 2.0 ** -24
+        out = torch.full((M + 40, N), 7.0, dtype=torch.float32, device=DEV)
+        B.gllm_op_gemm_bf16(to_dev_bits(ap), to_dev_weight(w), out, M, N, K, B.GEMM_STORE_F32, tile)
+        act = torch.full((M + 40, N // 2), 7.0, dtype=torch.bfloat16, device=DEV)
+        B.gllm_op_gemm_bf16(to_dev_bits(ap), to_dev_weight(_gate_up(w)), act, M, N, K, B.GEMM_SWIGLU_BF16, tile)
+        torch.cuda.synchronize()
+        got = out.cpu().numpy().astype(np.float64)
+        assert np.all(np.abs(got[:M] - ref) <= bound) and np.all(got[M:] == 7.0), (tile, K, M)
+        g, u = ref[:, :N // 2], ref[:, N // 2:]
+        want = g / (1 + np.exp(-g)) * u
+        slack = np.abs(want) * 2.0 ** -8 * 1.01 + 1.1 * np.abs(u) * bound[:, :N // 2] + np.abs(g) * bound[:, N // 2:] + 1e-30
+        got = act.float().cpu().numpy().astype(np.float64)
+        assert np.all(np.abs(got[:M] - want) <= slack) and np.all(got[M:] == 7.0), (tile, K, M)
