@@ -116,6 +116,21 @@ struct RopeKvArgs {
 };
 hipError_t launch_rope_kv_write(const RopeKvArgs& a, hipStream_t stream);
 
+#if defined(__HIPCC__)
+// Rotates four pairs (lo[v], hi[v]) by the angles whose (cos, sin) are c01 = two pairs, c23 = two more.
+__device__ __forceinline__ void rope_rotate(f32x4 lo, f32x4 hi, f32x4 c01, f32x4 c23, bf16x4& out_lo, bf16x4& out_hi) {
+    const f32x4 co = {c01[0], c01[2], c23[0], c23[2]}, si = {c01[1], c01[3], c23[1], c23[3]};
+    f32x4 rlo, rhi;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        rlo[v] = lo[v] * co[v] - hi[v] * si[v];
+        rhi[v] = hi[v] * co[v] + lo[v] * si[v];
+    }
+    out_lo = __builtin_convertvector(rlo, bf16x4);
+    out_hi = __builtin_convertvector(rhi, bf16x4);
+}
+#endif
+
 struct AttnArgs {
     const bf16_t* q;          // [T][ld_q] rotated queries
     int64_t ld_q;

@@ -159,6 +159,7 @@ __global__ __launch_bounds__(256) void pack_gate_up_kernel(const bf16_t* __restr
 // neighbouring columns of the same rows -- and stores them as one 16-byte piece; neighbouring lanes store
 // neighbouring pieces.  Pieces that the run covers only in part are stored slot by slot.  The value of an
 // element is formed exactly as in the token workgroups (planes in order, then the bias).
+template <int PLANES>
 __device__ __forceinline__ void write_v_tile(const RopeKvArgs& a, const VTile vt, int hd) {
     const int v_col0 = (a.n_q + a.n_kv) * a.d;
     const int pieces = a.d * 2;  // (dim, half of the slots) of head hd
@@ -169,18 +170,23 @@ __device__ __forceinline__ void write_v_tile(const RopeKvArgs& a, const VTile vt
         const int col = v_col0 + he;
         const int64_t row_of_slot0 = (int64_t)vt.row0 - vt.slot0;  // row of slot s is row_of_slot0 + s (used for s_lo <= s < s_hi only)
         const float b = a.bias ? (float)a.bias[col] : 0.f;
+        // all planes of all slots are loaded before the first sum: a chain of planes costs a memory latency each (8B shape, 197
+        // prompt rows, 4 planes: the launch 10.5 -> 8.0 us)
+        float part[8][PLANES];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            const int sl = min(max(hf * 8 + k, s_lo), s_hi - 1);  // (slots outside the run repeat one inside)
+            const float* src = a.qkv + (row_of_slot0 + sl) * a.ld_qkv + col;
+#pragma unroll
+            for (int p = 0; p < PLANES; ++p) part[k][p] = src[p * a.plane_stride];
+        }
         f32x8 val;
 #pragma unroll
         for (int k = 0; k < 8; ++k) {
-            const int sl = hf * 8 + k;
-            val[k] = 0.f;
-            if (sl >= s_lo && sl < s_hi) {
-                const float* src = a.qkv + (row_of_slot0 + sl) * a.ld_qkv + col;
-                float v = src[0];
-                for (int p = 1; p < a.planes; ++p) v += src[p * a.plane_stride];
-                if (a.bias) v += b;
-                val[k] = v;
-            }
+            val[k] = part[k][0];
+#pragma unroll
+            for (int p = 1; p < PLANES; ++p) val[k] += part[k][p];
+            if (a.bias) val[k] += b;
         }
         const bf16x8 o = __builtin_convertvector(val, bf16x8);
         bf16_t* vb = a.v_pool + ((int64_t)vt.page * a.n_kv + hd) * (int64_t)(a.d * kPage) + e * kPage + hf * 8;
@@ -199,8 +205,7 @@ __device__ __forceinline__ void write_v_tile(const RopeKvArgs& a, const VTile vt
 // bf16 and stored at (page, slot = pos % 16) in the layer's pool:
 //   K element (head h, dim e) -> ((page*n_kv + h)*d*16) + (e/8)*128 + slot*8 + e%8
 //   V element (head h, dim e) -> ((page*n_kv + h)*d*16) + e*16 + slot
-// PLANES >= 1 fixes the number of split-K planes at compile time (their loads are then issued together), PLANES < 0
-// takes it from the arguments.
+// PLANES is the number of split-K planes (their loads are issued together).
 // With few tokens the kernel is a chain of memory latencies, one per pass of a workgroup over its token's columns; then a
 // token gets as many workgroups as it has passes (64 rows, 4 planes 7.1 -> 4.8 us, one row 5.7 -> 4.4).  From 129 rows on
 // one workgroup per token is as good or better (197 rows 6.2 against 7.2 us): the chip is full, and the lookups of a
@@ -210,7 +215,7 @@ template <int PLANES>
 __global__ __launch_bounds__(256) void rope_kv_write_kernel(RopeKvArgs a, int parts) {
     const int v_wgs = a.n_vtiles * a.n_kv;  // the first workgroups write the V runs, one (run, head) each
     if ((int)blockIdx.x < v_wgs) {
-        write_v_tile(a, a.v_tiles[blockIdx.x / a.n_kv], blockIdx.x % a.n_kv);
+        write_v_tile<PLANES>(a, a.v_tiles[blockIdx.x / a.n_kv], blockIdx.x % a.n_kv);
         return;
     }
     const int t = (blockIdx.x - v_wgs) / parts, first = (blockIdx.x - v_wgs) % parts * 256 + threadIdx.x, step = parts * 256;
@@ -224,15 +229,11 @@ __global__ __launch_bounds__(256) void rope_kv_write_kernel(RopeKvArgs a, int pa
     const int k_col0 = a.n_q * d, v_col0 = k_col0 + a.n_kv * d;
     auto gather = [&](int col) {  // sum of the partial planes (+ bias) of 4 consecutive columns
         f32x4 v = *reinterpret_cast<const f32x4*>(row + col);
-        if constexpr (PLANES >= 1) {
-            f32x4 part[PLANES];
+        f32x4 part[PLANES];
 #pragma unroll
-            for (int p = 1; p < PLANES; ++p) part[p] = *reinterpret_cast<const f32x4*>(row + p * a.plane_stride + col);
+        for (int p = 1; p < PLANES; ++p) part[p] = *reinterpret_cast<const f32x4*>(row + p * a.plane_stride + col);
 #pragma unroll
-            for (int p = 1; p < PLANES; ++p) v += part[p];
-        } else {
-            for (int p = 1; p < a.planes; ++p) v += *reinterpret_cast<const f32x4*>(row + p * a.plane_stride + col);
-        }
+        for (int p = 1; p < PLANES; ++p) v += part[p];
         if (a.bias) v += __builtin_convertvector(*reinterpret_cast<const bf16x4*>(a.bias + col), f32x4);
         return v;
     };
@@ -243,14 +244,8 @@ __global__ __launch_bounds__(256) void rope_kv_write_kernel(RopeKvArgs a, int pa
         const int col = (is_q ? 0 : k_col0) + hd * d + j;
         const f32x4 lo = gather(col), hi = gather(col + half);
         const f32x4 c01 = cs[j / 2], c23 = cs[j / 2 + 1];  // (cos, sin) of pairs j, j+1 | j+2, j+3
-        const f32x4 co = {c01[0], c01[2], c23[0], c23[2]}, si = {c01[1], c01[3], c23[1], c23[3]};
-        f32x4 rlo, rhi;
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            rlo[v] = lo[v] * co[v] - hi[v] * si[v];
-            rhi[v] = hi[v] * co[v] + lo[v] * si[v];
-        }
-        const bf16x4 blo = __builtin_convertvector(rlo, bf16x4), bhi = __builtin_convertvector(rhi, bf16x4);
+        bf16x4 blo, bhi;
+        rope_rotate(lo, hi, c01, c23, blo, bhi);
         if (is_q) {
             bf16_t* q = a.q_out + (int64_t)t * a.ld_q + hd * d;
             *reinterpret_cast<bf16x4*>(q + j) = blo;
@@ -282,7 +277,7 @@ template <int ITERS>
 __global__ __launch_bounds__(256) void rope_kv_write_batched_kernel(RopeKvArgs a) {
     const int v_wgs = a.n_vtiles * a.n_kv;
     if ((int)blockIdx.x < v_wgs) {
-        write_v_tile(a, a.v_tiles[blockIdx.x / a.n_kv], blockIdx.x % a.n_kv);
+        write_v_tile<1>(a, a.v_tiles[blockIdx.x / a.n_kv], blockIdx.x % a.n_kv);
         return;
     }
     const int t = blockIdx.x - v_wgs;
@@ -324,14 +319,8 @@ __global__ __launch_bounds__(256) void rope_kv_write_batched_kernel(RopeKvArgs a
             const bool is_q = i < q_quads;
             const int ii = is_q ? i : i - q_quads;
             const int hd = ii / hq, j = (ii % hq) * 4;
-            const f32x4 co = {c01[it][0], c01[it][2], c23[it][0], c23[it][2]}, si = {c01[it][1], c01[it][3], c23[it][1], c23[it][3]};
-            f32x4 rlo, rhi;
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                rlo[v] = lo[it][v] * co[v] - hi[it][v] * si[v];
-                rhi[v] = hi[it][v] * co[v] + lo[it][v] * si[v];
-            }
-            const bf16x4 blo = __builtin_convertvector(rlo, bf16x4), bhi = __builtin_convertvector(rhi, bf16x4);
+            bf16x4 blo, bhi;
+            rope_rotate(lo[it], hi[it], c01[it], c23[it], blo, bhi);
             if (is_q) {
                 bf16_t* q = a.q_out + (int64_t)t * a.ld_q + hd * d;
                 *reinterpret_cast<bf16x4*>(q + j) = blo;
@@ -445,7 +434,7 @@ hipError_t launch_pack_gate_up(const bf16_t* gate, const bf16_t* up, int inter, 
 
 hipError_t launch_rope_kv_write(const RopeKvArgs& a, hipStream_t stream) {
     if (a.T <= 0) return hipSuccess;
-    if (a.n_vtiles < 0 || (a.n_vtiles > 0 && (!a.v_tiles || !a.tok_own_v))) return hipErrorInvalidValue;
+    if (a.planes < 1 || a.planes > kMaxPlanes || a.n_vtiles < 0 || (a.n_vtiles > 0 && (!a.v_tiles || !a.tok_own_v))) return hipErrorInvalidValue;
     const int units = ((a.n_q + a.n_kv) * (a.d / 8) + a.n_kv * a.d / 4 + 255) / 256;  // passes of 256 four-column units
     const int parts = a.T <= kRopePartsMaxTokens ? units : 1;
     const int grid = a.T * parts + a.n_vtiles * a.n_kv;
@@ -471,7 +460,7 @@ hipError_t launch_rope_kv_write(const RopeKvArgs& a, hipStream_t stream) {
         case 6: rope_kv_write_kernel<6><<<grid, 256, 0, stream>>>(a, parts); break;
         case 7: rope_kv_write_kernel<7><<<grid, 256, 0, stream>>>(a, parts); break;
         case 8: rope_kv_write_kernel<8><<<grid, 256, 0, stream>>>(a, parts); break;
-        default: rope_kv_write_kernel<-1><<<grid, 256, 0, stream>>>(a, parts); break;
+        default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
 }
