@@ -152,6 +152,7 @@ struct DecodeItem {
     int32_t kv_begin;  // first key of this partition (multiple of 32)
     int32_t kv_end;    // one past the last key of this partition
     int32_t single;    // 1: the row's only item; the kernel writes the normalised output itself
+    int32_t pos;       // position of the row's new token, its last key
 };
 struct DecodeRow {
     int32_t row;        // token row
@@ -165,6 +166,10 @@ struct DecodeArgs {
     int num_items;
     float* part_o;         // partials of the items whose row has more than one
     float* part_ml;
+    // from_qkv (every token of the batch is a decode row): queries, new keys and new values are taken from the QKV projection
+    // (`rope`) and the new keys and values written to the pool by the same launch; q and the new slots of the pool are not read.
+    bool from_qkv;
+    RopeKvArgs rope;
 };
 hipError_t launch_decode_attention(const AttnArgs& a, const DecodeArgs& dec, hipStream_t stream);
 hipError_t launch_decode_combine(const AttnArgs& a, const DecodeRow* rows, int num_rows, const float* part_o,

@@ -3,7 +3,8 @@
 // A forward call validates the batch descriptor, builds the per-batch metadata once (it is
 // shared by all layers because every layer uses the same page tables, paper section 3.3),
 // has the first launch copy it from pinned staging, and enqueues, per layer:
-//   RMSNorm -> QKV GEMM -> RoPE + paged KV write -> prefill attention, decode attention (+merge)
+//   RMSNorm -> QKV GEMM -> RoPE + paged KV write -> prefill attention, decode attention (+merge; in a batch of decode rows
+//   RoPE and KV write belong to this launch)
 //   -> O GEMM -> residual add + RMSNorm -> gate/up GEMM (SwiGLU) -> down GEMM -> (residual add fused into the
 //   next layer's RMSNorm)
 // and finally the last residual add with the cast of the fp32 residual stream to bf16.  The O and down
@@ -17,6 +18,7 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <new>
 #include <string>
 #include <vector>
 
@@ -95,6 +97,7 @@ struct gllm_stage {
     int64_t prof_n[PC_COUNT] = {};
     // scratch for validation
     std::vector<int32_t> written_pages;
+    std::vector<uint8_t> page_writers;  // per page of the pool, 0 between calls (see own_pages)
 };
 
 namespace {
@@ -160,6 +163,25 @@ size_t workspace_layout(gllm_stage* s, unsigned char* base) {
     s->part_ml = (float*)take((size_t)s->max_items * c.n_q_heads * 2 * 4);
     s->y = (float*)take((size_t)kMaxSplits * c.max_tokens * c.hidden * 4);
     return off;
+}
+
+// Whether every page that receives a token of a batch of decode rows appears once in the page tables of the batch, as that
+// row's last page.  Then nobody but the row itself reads the new token in this call, and attention need not wait until it is
+// in the pool; where another sequence's cached prefix reaches into such a page all new keys and values are written first.
+bool own_pages(gllm_stage* s, const gllm_batch* b) {
+    std::vector<uint8_t>& w = s->page_writers;
+    if (w.empty()) return false;
+    auto last_page = [&](int i) { return b->block_tables[(int64_t)i * b->block_table_stride + b->cached_len[i] / kPage]; };
+    for (int i = 0; i < b->num_seqs; ++i)
+        if (w[last_page(i)] < 2) ++w[last_page(i)];
+    int64_t seen = 0;
+    for (int i = 0; i < b->num_seqs; ++i) {
+        const int32_t* row = b->block_tables + (int64_t)i * b->block_table_stride;
+        const int64_t pages = (int64_t)b->cached_len[i] / kPage + 1;
+        for (int64_t p = 0; p < pages; ++p) seen += w[row[p]];
+    }
+    for (int i = 0; i < b->num_seqs; ++i) w[last_page(i)] = 0;
+    return seen == b->num_seqs;  // (a page with two writers is seen twice and counts four)
 }
 
 hipEvent_t get_event(gllm_stage* s) {
@@ -391,6 +413,13 @@ gllm_status gllm_stage_bind_kv_pool(gllm_stage* s, void* k_pool, void* v_pool, i
     s->k_pool = (bf16_t*)k_pool;
     s->v_pool = (bf16_t*)v_pool;
     s->num_blocks = num_blocks;
+    if (s->page_writers.size() != (size_t)num_blocks) {
+        try {
+            s->page_writers.assign((size_t)num_blocks, 0);
+        } catch (const std::bad_alloc&) {
+            s->page_writers.clear();  // every batch is then taken as one that shares pages
+        }
+    }
     return GLLM_OK;
 }
 
@@ -597,7 +626,7 @@ gllm_status gllm_stage_forward(gllm_stage* s, const gllm_batch* b, const void* h
             const int share = (int)ceil_div(ceil_div(len, nparts), 32) * 32;
             const int first = n_items;
             for (int k0 = 0; k0 < len; k0 += share)
-                dec_items[n_items++] = DecodeItem{(int32_t)row, (int32_t)bt_off, k0, std::min(k0 + share, len), 0};
+                dec_items[n_items++] = DecodeItem{(int32_t)row, (int32_t)bt_off, k0, std::min(k0 + share, len), 0, cl};
             // a row with a single item is finished by the attention kernel; the others are merged afterwards
             if (n_items - first == 1) dec_items[first].single = 1;
             else dec_rows[n_rows++] = DecodeRow{(int32_t)row, first, n_items - first, 0};
@@ -642,6 +671,7 @@ gllm_status gllm_stage_forward(gllm_stage* s, const gllm_batch* b, const void* h
     const GemmPlan plan_d = gemm_plan(Ti, H, s->inter_pad, GEMM_STORE_F32, kMaxSplits, rm);
     const int split_o = plan_o.splits, split_d = plan_d.splits;
     const int64_t qkv_plane = (int64_t)c.max_tokens * s->n_qkv_pad;
+    bool from_qkv = false;  // decode attention takes queries, new keys and new values from the QKV projection
     int pending = 0;  // planes of y still to be added to the residual stream
     for (int l = s->layer_begin; l < s->layer_end; ++l) {
         const LayerBuffers& L = s->layers[l];
@@ -661,17 +691,19 @@ gllm_status gllm_stage_forward(gllm_stage* s, const gllm_batch* b, const void* h
             HIP_TRY(s, launch_gemm_bf16(s->h, H, L.wqkv, H, s->qkv, s->n_qkv_pad, Ti, s->n_qkv_pad, H, GEMM_STORE_F32, plan_qkv.tile,
                                         plan_qkv.splits, qkv_plane, st));
         }
-        {
+        // (found out here, while the first kernels already run)
+        if (l == s->layer_begin) from_qkv = n_pre == 0 && own_pages(s, b);
+        RopeKvArgs ra{};
+        ra.qkv = s->qkv; ra.ld_qkv = s->n_qkv_pad; ra.planes = plan_qkv.splits; ra.plane_stride = qkv_plane;
+        ra.bias = c.has_qkv_bias ? L.bias : nullptr;
+        ra.rope_cs = s->rope_cs; ra.tok_pos = d_tok_pos; ra.tok_page = d_tok_page;
+        ra.q_out = s->q; ra.ld_q = s->q_dim;
+        ra.k_pool = s->k_pool + (int64_t)l * pool_layer; ra.v_pool = s->v_pool + (int64_t)l * pool_layer;
+        ra.T = Ti; ra.n_q = c.n_q_heads; ra.n_kv = c.n_kv_heads; ra.d = d;
+        ra.v_tiles = d_v_tiles; ra.n_vtiles = n_vt; ra.tok_own_v = d_tok_own_v;
+        if (!from_qkv) {
             ProfScope ps(s, st, PC_ROPE_KV);
-            RopeKvArgs a{};
-            a.qkv = s->qkv; a.ld_qkv = s->n_qkv_pad; a.planes = plan_qkv.splits; a.plane_stride = qkv_plane;
-            a.bias = c.has_qkv_bias ? L.bias : nullptr;
-            a.rope_cs = s->rope_cs; a.tok_pos = d_tok_pos; a.tok_page = d_tok_page;
-            a.q_out = s->q; a.ld_q = s->q_dim;
-            a.k_pool = s->k_pool + (int64_t)l * pool_layer; a.v_pool = s->v_pool + (int64_t)l * pool_layer;
-            a.T = Ti; a.n_q = c.n_q_heads; a.n_kv = c.n_kv_heads; a.d = d;
-            a.v_tiles = d_v_tiles; a.n_vtiles = n_vt; a.tok_own_v = d_tok_own_v;
-            HIP_TRY(s, launch_rope_kv_write(a, st));
+            HIP_TRY(s, launch_rope_kv_write(ra, st));
         }
         AttnArgs aa{};
         aa.q = s->q; aa.ld_q = s->q_dim;
@@ -679,7 +711,7 @@ gllm_status gllm_stage_forward(gllm_stage* s, const gllm_batch* b, const void* h
         aa.bt_flat = d_bt; aa.out = s->attn; aa.ld_o = s->q_dim;
         aa.n_q = c.n_q_heads; aa.n_kv = c.n_kv_heads; aa.d = d;
         aa.scale_log2 = (float)(1.4426950408889634 / std::sqrt((double)d));
-        const DecodeArgs da{d_items, d_order, n_items, s->part_o, s->part_ml};
+        const DecodeArgs da{d_items, d_order, n_items, s->part_o, s->part_ml, from_qkv, ra};
         // both kinds of attention read q and the pool and write disjoint rows of attn
         if (s->overlap_attention && !s->profiling && attention_in_one_launch(aa, n_pre, n_items)) {
             HIP_TRY(s, launch_hybrid_attention(aa, d_pre, n_pre, da, st));

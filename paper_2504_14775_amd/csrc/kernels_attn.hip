@@ -204,13 +204,17 @@ __device__ __forceinline__ void attend_block(AttnState<D, NB>& st, KvFrag<D>& f,
 // Walks key blocks [blk_begin, blk_end) (units of 32 keys) of one sequence.  Page ids are fetched 64
 // at a time, one per lane, and handed out with readlane.  last_page is the last page index of the
 // sequence that may be read (page ids past it are never dereferenced).
-template <int D, int NB>
+// prepare() fills qf; every wave calls it once, when the loads of its first block are on their way.
+template <int D, int NB, typename Prepare>
 __device__ __forceinline__ void attend_range(AttnState<D, NB>& st, const bf16x8 (&qf)[NB][D / 32],
                                              const bf16_t* __restrict__ kp, const bf16_t* __restrict__ vp,
                                              const int32_t* __restrict__ bt, int blk_begin, int blk_end,
                                              int last_page, const int (&limit)[NB], int min_limit, int valid_end,
-                                             int n_kv, int kvh, float scale_log2, int lane) {
-    if (blk_begin >= blk_end) return;
+                                             int n_kv, int kvh, float scale_log2, int lane, Prepare&& prepare) {
+    if (blk_begin >= blk_end) {
+        prepare();
+        return;
+    }
     int ids_base = blk_begin * 2;  // page index held by lane 0
     int ids = bt[min(ids_base + lane, last_page)];
     auto page_of = [&](int pi) -> int64_t {  // pi wave-uniform, within [ids_base, ids_base + 64)
@@ -222,6 +226,7 @@ __device__ __forceinline__ void attend_range(AttnState<D, NB>& st, const bf16x8 
     };
     KvFrag<D> fa, fb;
     load_block(fa, blk_begin);
+    prepare();
     for (int blk = blk_begin; blk < blk_end; blk += 2) {
         // blocks blk and blk+1 use pages 2blk .. 2blk+3; refill the id window when it runs out
         const bool has_b = blk + 1 < blk_end;
@@ -253,15 +258,47 @@ __device__ __forceinline__ void init_state(AttnState<D, NB>& st) {
 // Decode: one workgroup of 4 waves per (item, kv head).  The item's key partition is cut into four runs of
 // 32-key blocks, one per wave; the waves' partial results are merged through LDS and written as
 // one partial (running max, sum, unnormalised output) per query head of the KV head.
-// ------------------------------------------------------------------------------------------
-template <int D>
+//
+// FROM_QKV (batches of decode rows only): the queries and the row's new key and value come straight from the QKV projection.
+// Every workgroup of a row sums the split-K planes of its heads and rotates (a few KiB from the caches, under the latency of
+// the first keys); the one that owns the last position takes the new token as a fifth partial beside those of its waves (its
+// score, weight 1, its value), so nothing waits for the pool.  Workgroups of their own, one per row, write the new keys and
+// values there (write_new_token).  Against a RoPE kernel of its own in front: 64 rows of 1500 .. 3500 keys, eight layers, 1676
+// -> 1656 us, 512 rows of 1024 .. 8192 keys, three layers, 4203 -> 4170.
+constexpr int kMaxGroup = 16;  // query heads per KV head
+template <int D, bool FROM_QKV>
 struct DecodeLds {
     float o[4][16][D + 4];
     float m[4][16], l[4][16];
 };
-
 template <int D>
-__device__ __forceinline__ void decode_workgroup(const AttnArgs& a, const DecodeArgs& dec, int wg, DecodeLds<D>& lds) {
+struct DecodeLds<D, true> : DecodeLds<D, false> {
+    float s_new[16];  // score of the new token per query head
+    __attribute__((aligned(16))) float sum[kMaxGroup + 2][D + 4];  // q heads of the group, k, v: summed planes (rows shifted by a bank group)
+};
+
+// The four columns e .. e+3 of head row h of the group (h = g: the key, g + 1: the value): all planes, not yet summed.
+template <int D>
+__device__ __forceinline__ int64_t qkv_column(const RopeKvArgs& r, int kvh, int g, int i) {
+    const int h = i / (D / 4), e = i % (D / 4) * 4;
+    return (int64_t)(h < g ? kvh * g + h : h == g ? r.n_q + kvh : r.n_q + r.n_kv + kvh) * D + e;
+}
+__device__ __forceinline__ void load_planes(f32x4 (&part)[kMaxPlanes], const RopeKvArgs& r, const float* __restrict__ at) {
+#pragma unroll
+    for (int p = 0; p < kMaxPlanes; ++p)
+        if (p < r.planes) part[p] = *reinterpret_cast<const f32x4*>(at + p * r.plane_stride);
+}
+__device__ __forceinline__ f32x4 sum_planes(const f32x4 (&part)[kMaxPlanes], const RopeKvArgs& r, int64_t col) {
+    f32x4 v = part[0];
+#pragma unroll
+    for (int p = 1; p < kMaxPlanes; ++p)
+        if (p < r.planes) v += part[p];
+    if (r.bias) v += __builtin_convertvector(*reinterpret_cast<const bf16x4*>(r.bias + col), f32x4);
+    return v;
+}
+
+template <int D, bool FROM_QKV>
+__device__ __forceinline__ void decode_workgroup(const AttnArgs& a, const DecodeArgs& dec, int wg, DecodeLds<D, FROM_QKV>& lds) {
     const DecodeItem* __restrict__ items = dec.items;
     float* __restrict__ part_o = dec.part_o;
     float* __restrict__ part_ml = dec.part_ml;
@@ -276,7 +313,21 @@ __device__ __forceinline__ void decode_workgroup(const AttnArgs& a, const Decode
     const int r = lane & 15, G = lane >> 4;
 
     bf16x8 qf[1][D / 32];
-    {
+    f32x4 part[kMaxPlanes], cs[D / 64][4];
+    const int pieces = (g + 2) * (D / 4);  // of four columns: one per thread and pass
+    const RopeKvArgs& rp = dec.rope;
+    const float* qkv_row = nullptr;
+    const f32x4* cs_row = nullptr;
+    if constexpr (FROM_QKV) {
+        qkv_row = rp.qkv + (int64_t)it.row * rp.ld_qkv;
+        cs_row = reinterpret_cast<const f32x4*>(rp.rope_cs + (int64_t)it.pos * D);
+        if ((int)threadIdx.x < pieces) load_planes(part, rp, qkv_row + qkv_column<D>(rp, kvh, g, threadIdx.x));
+#pragma unroll
+        for (int s = 0; s < D / 64; ++s)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) cs[s][i] = cs_row[(s * 4 + G) * 4 + i];
+        __builtin_amdgcn_sched_barrier(0);  // these loads go first: they come from the caches, the keys behind them from HBM
+    } else {
         const bf16_t* qrow = a.q + (int64_t)it.row * a.ld_q + (int64_t)(kvh * g + r) * D;
 #pragma unroll
         for (int s = 0; s < D / 32; ++s) {
@@ -285,16 +336,62 @@ __device__ __forceinline__ void decode_workgroup(const AttnArgs& a, const Decode
             qf[0][s] = __builtin_bit_cast(bf16x8, z);
         }
     }
+    const bool owns_new = FROM_QKV && it.kv_end == it.pos + 1;  // (the same for all threads)
+    const int kv_end = owns_new ? it.pos : it.kv_end;           // keys to be read from the pool
+    auto prepare = [&]() {
+        if constexpr (FROM_QKV) {
+            for (int i = threadIdx.x; i < pieces; i += 256) {
+                const int64_t col = qkv_column<D>(rp, kvh, g, i);
+                if (i >= 256) load_planes(part, rp, qkv_row + col);
+                *reinterpret_cast<f32x4*>(&lds.sum[i / (D / 4)][i % (D / 4) * 4]) = sum_planes(part, rp, col);
+            }
+            __syncthreads();
+            const int h = min(r, g - 1);
+#pragma unroll
+            for (int s = 0; s < D / 64; ++s) {  // dims (s*4+G)*8 .. +7 and their partners D/2 further
+                bf16x4 lo[2], hi[2];
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    const int e = (s * 4 + G) * 8 + i * 4;
+                    rope_rotate(*reinterpret_cast<const f32x4*>(&lds.sum[h][e]), *reinterpret_cast<const f32x4*>(&lds.sum[h][e + D / 2]),
+                                cs[s][2 * i], cs[s][2 * i + 1], lo[i], hi[i]);
+                }
+                bf16x8 ql = __builtin_shufflevector(lo[0], lo[1], 0, 1, 2, 3, 4, 5, 6, 7), qh = __builtin_shufflevector(hi[0], hi[1], 0, 1, 2, 3, 4, 5, 6, 7);
+                const u32x4 zero = {0u, 0u, 0u, 0u};
+                qf[0][s] = r < g ? ql : __builtin_bit_cast(bf16x8, zero);
+                qf[0][s + D / 64] = r < g ? qh : __builtin_bit_cast(bf16x8, zero);
+            }
+            if (owns_new) {  // the score of the new token: this lane's dims of key and queries, then the sum over the lane groups
+                float dot = 0.f;
+#pragma unroll
+                for (int s = 0; s < D / 64; ++s) {
+                    bf16x4 lo[2], hi[2];
+#pragma unroll
+                    for (int i = 0; i < 2; ++i) {
+                        const int e = (s * 4 + G) * 8 + i * 4;
+                        rope_rotate(*reinterpret_cast<const f32x4*>(&lds.sum[g][e]), *reinterpret_cast<const f32x4*>(&lds.sum[g][e + D / 2]),
+                                    cs[s][2 * i], cs[s][2 * i + 1], lo[i], hi[i]);
+#pragma unroll
+                        for (int v = 0; v < 4; ++v)
+                            dot += (float)lo[i][v] * (float)qf[0][s][i * 4 + v] + (float)hi[i][v] * (float)qf[0][s + D / 64][i * 4 + v];
+                    }
+                }
+                dot += __shfl_xor(dot, 16);
+                dot += __shfl_xor(dot, 32);
+                if (wave == 0 && G == 0) lds.s_new[r] = dot * a.scale_log2;
+            }
+        }
+    };
     const int blk0 = it.kv_begin / 32;
-    const int nblk = (it.kv_end - it.kv_begin + 31) / 32;
+    const int nblk = (kv_end - it.kv_begin + 31) / 32;
     const int per_wave = (nblk + 3) / 4;
     const int b_begin = blk0 + min(wave * per_wave, nblk);
     const int b_end = blk0 + min((wave + 1) * per_wave, nblk);
-    const int limit[1] = {it.kv_end - 1};
+    const int limit[1] = {kv_end - 1};
     AttnState<D, 1> st;
     init_state<D, 1>(st);
-    attend_range<D, 1>(st, qf, a.k_pool, a.v_pool, a.bt_flat + it.bt_off, b_begin, b_end, (it.kv_end - 1) / kPage,
-                       limit, it.kv_end - 1, it.kv_end, a.n_kv, kvh, a.scale_log2, lane);
+    attend_range<D, 1>(st, qf, a.k_pool, a.v_pool, a.bt_flat + it.bt_off, b_begin, b_end, (kv_end - 1) / kPage,
+                       limit, kv_end - 1, kv_end, a.n_kv, kvh, a.scale_log2, lane, prepare);
     float l = st.l[0];
     l += __shfl_xor(l, 16);
     l += __shfl_xor(l, 32);
@@ -310,6 +407,9 @@ __device__ __forceinline__ void decode_workgroup(const AttnArgs& a, const Decode
     for (int idx = threadIdx.x; idx < g * (D / 4); idx += 256) {
         const int j = idx / (D / 4), e = (idx % (D / 4)) * 4;
         float mw[4], ms = kNegBig;
+        if constexpr (FROM_QKV) {
+            if (owns_new) ms = lds.s_new[j];
+        }
 #pragma unroll
         for (int w = 0; w < 4; ++w) {
             mw[w] = lds.m[w][j];
@@ -317,6 +417,14 @@ __device__ __forceinline__ void decode_workgroup(const AttnArgs& a, const Decode
         }
         f32x4 acc = {0.f, 0.f, 0.f, 0.f};
         float ls = 0.f;
+        if constexpr (FROM_QKV) {
+            if (owns_new) {
+                ls = __builtin_amdgcn_exp2f(lds.s_new[j] - ms);
+                const bf16x4 v = __builtin_convertvector(*reinterpret_cast<const f32x4*>(&lds.sum[g + 1][e]), bf16x4);
+#pragma unroll
+                for (int u = 0; u < 4; ++u) acc[u] = (float)v[u] * ls;
+            }
+        }
 #pragma unroll
         for (int w = 0; w < 4; ++w) {
             const float sc = __builtin_amdgcn_exp2f(mw[w] - ms);
@@ -342,10 +450,56 @@ __device__ __forceinline__ void decode_workgroup(const AttnArgs& a, const Decode
     }
 }
 
+// New key and value of token row t, all heads, into the pool: the same sums, rotation and rounding as rope_kv_write, a
+// thread per four rotated pairs of K or four dims of V.
 template <int D>
+__device__ __forceinline__ void write_new_token(const RopeKvArgs& r, int t) {
+    const int pos = r.tok_pos[t], slot = pos % kPage;
+    const int64_t page = (int64_t)r.tok_page[t] * r.n_kv * (D * kPage);
+    const float* row = r.qkv + (int64_t)t * r.ld_qkv;
+    const f32x4* cs = reinterpret_cast<const f32x4*>(r.rope_cs + (int64_t)pos * D);
+    const int k_units = r.n_kv * (D / 8), units = k_units + r.n_kv * (D / 4);
+    for (int i = threadIdx.x; i < units; i += 256) {
+        f32x4 part[kMaxPlanes];
+        if (i < k_units) {
+            const int hd = i / (D / 8), e = i % (D / 8) * 4;
+            const int64_t col = (int64_t)(r.n_q + hd) * D + e;
+            f32x4 part_hi[kMaxPlanes];
+            load_planes(part, r, row + col);
+            load_planes(part_hi, r, row + col + D / 2);
+            const f32x4 c01 = cs[e / 2], c23 = cs[e / 2 + 1];
+            bf16x4 lo, hi;
+            rope_rotate(sum_planes(part, r, col), sum_planes(part_hi, r, col + D / 2), c01, c23, lo, hi);
+            bf16_t* kb = r.k_pool + page + hd * (D * kPage) + slot * 8;
+            *reinterpret_cast<bf16x4*>(kb + (e >> 3) * (kPage * 8) + (e & 7)) = lo;
+            *reinterpret_cast<bf16x4*>(kb + ((e + D / 2) >> 3) * (kPage * 8) + (e & 7)) = hi;
+        } else {
+            const int hd = (i - k_units) / (D / 4), e = (i - k_units) % (D / 4) * 4;
+            const int64_t col = (int64_t)(r.n_q + r.n_kv + hd) * D + e;
+            load_planes(part, r, row + col);
+            const bf16x4 v = __builtin_convertvector(sum_planes(part, r, col), bf16x4);
+            bf16_t* vb = r.v_pool + page + hd * (D * kPage) + e * kPage + slot;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) vb[u * kPage] = v[u];
+        }
+    }
+}
+
+// FROM_QKV: the workgroups that write the new tokens come last, into the slots that the shortest rows leave.  512 rows of 1024
+// .. 8192 keys, three layers: 4170 us so, 4265 with them in front (all slots held while the memory idles), 4312 with every
+// attention workgroup writing its own token (4127 without any writes: spread over the launch they break up the stream of
+// reads), 4203 with a RoPE kernel before the launch.
+template <int D, bool FROM_QKV>
 __global__ __launch_bounds__(256, 2) void decode_attention_kernel(AttnArgs a, DecodeArgs dec) {
-    __shared__ DecodeLds<D> lds;
-    decode_workgroup<D>(a, dec, blockIdx.x, lds);
+    __shared__ DecodeLds<D, FROM_QKV> lds;
+    if constexpr (FROM_QKV) {
+        const int t = (int)blockIdx.x - dec.num_items * a.n_kv;
+        if (t >= 0) {
+            write_new_token<D>(dec.rope, t);
+            return;
+        }
+    }
+    decode_workgroup<D, FROM_QKV>(a, dec, blockIdx.x, lds);
 }
 
 // grid (rows, query heads), D/4 threads: merges the partials of a row in partition order.
@@ -582,20 +736,23 @@ __global__ __launch_bounds__(256, 2) void hybrid_attention_kernel(AttnArgs a, co
                                                                    DecodeArgs dec) {
     __shared__ union Lds {
         PrefillLds<D> prefill;
-        DecodeLds<D> decode;
+        DecodeLds<D, false> decode;
     } lds;
     if ((int)blockIdx.x < prefill_wgs) prefill_workgroup<D, HW>(a, items, blockIdx.x, lds.prefill);
-    else decode_workgroup<D>(a, dec, blockIdx.x - prefill_wgs, lds.decode);
+    else decode_workgroup<D, false>(a, dec, blockIdx.x - prefill_wgs, lds.decode);
 }
 
 }  // namespace
 
 hipError_t launch_decode_attention(const AttnArgs& a, const DecodeArgs& dec, hipStream_t stream) {
     if (dec.num_items <= 0) return hipSuccess;
-    dim3 grid(dec.num_items * a.n_kv);
-    if (a.d == 128) decode_attention_kernel<128><<<grid, 256, 0, stream>>>(a, dec);
-    else if (a.d == 64) decode_attention_kernel<64><<<grid, 256, 0, stream>>>(a, dec);
-    else return hipErrorInvalidValue;
+    const dim3 grid(dec.num_items * a.n_kv + (dec.from_qkv ? dec.rope.T : 0));
+    if (a.n_q / a.n_kv > kMaxGroup || (dec.from_qkv && (dec.rope.planes < 1 || dec.rope.planes > kMaxPlanes))) return hipErrorInvalidValue;
+    if (a.d != 128 && a.d != 64) return hipErrorInvalidValue;
+    if (a.d == 128 && dec.from_qkv) decode_attention_kernel<128, true><<<grid, 256, 0, stream>>>(a, dec);
+    else if (a.d == 128) decode_attention_kernel<128, false><<<grid, 256, 0, stream>>>(a, dec);
+    else if (dec.from_qkv) decode_attention_kernel<64, true><<<grid, 256, 0, stream>>>(a, dec);
+    else decode_attention_kernel<64, false><<<grid, 256, 0, stream>>>(a, dec);
     return hipGetLastError();
 }
 
@@ -650,6 +807,7 @@ hipError_t launch_hybrid_attention(const AttnArgs& a, const PrefillItem* items, 
     const int hw = prefill_heads_per_workgroup(a.n_q, a.n_kv);
     const int prefill_wgs = num_items * (a.n_q / hw);
     if (num_items <= 0 || dec.num_items <= 0) return hipErrorInvalidValue;
+    if (dec.from_qkv) return hipErrorInvalidValue;
     const dim3 grid(prefill_wgs + dec.num_items * a.n_kv);
 #define GLLM_HYBRID(D_, HW_) hybrid_attention_kernel<D_, HW_><<<grid, 256, 0, stream>>>(a, items, prefill_wgs, dec)
     if (a.d == 128) GLLM_BY_HEADS(GLLM_HYBRID, 128);

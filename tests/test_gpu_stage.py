@@ -570,3 +570,46 @@ def test_empty_batch_and_batches_at_the_stage_limits():
     torch.cuda.synchronize()
     assert_output("one token", dict(ref=ref1, out=bits_of(o1), out32=o132.cpu().numpy()), literal=True)
     st.destroy()
+
+
+DECODE_EDGES = [0, 1, 14, 15, 16, 17, 30, 31, 32, 33, 63, 64, 127, 128, 255, 256, 300, 511, 700]
+
+
+@pytest.mark.parametrize("n_q,n_kv,d,hidden,bias,min_wgs", [(6, 2, 128, 256, False, 0), (16, 1, 64, 256, True, 0), (16, 1, 128, 1024, True, 10 ** 6),
+                                                            (4, 4, 64, 1024, False, 10 ** 6), (10, 2, 128, 2048, True, 0), (8, 1, 128, 512, False, 64)])
+def test_batches_of_decode_rows_at_page_block_and_partition_edges(n_q, n_kv, d, hidden, bias, min_wgs):
+    """Only decode rows: attention takes queries, new keys and values from the QKV projection (1, 2 and more planes), the new
+    token beside the pool's keys, also where the row has none or is cut.  Unused slots hold NaN patterns."""
+    print(f"decode edges n_q={n_q} n_kv={n_kv} d={d} hidden={hidden} bias={bias} min_wgs={min_wgs}", flush=True)
+    shape = synth.StageShape("dec", 2 if hidden < 1024 else 1, hidden, n_q, n_kv, d, 384, has_qkv_bias=bias)
+    batch = synth.build_batch([(1, c) for c in DECODE_EDGES], 31, spare_blocks=3)
+    w = layer_weights_np(shape, 31)
+    kp0, vp0 = sentinel_pool_with_prefixes(shape, batch, 31)
+    stage = GpuStage(shape, w, [batch])
+    stage.stage.set_option("decode_min_workgroups", min_wgs)
+    r = run_both(shape, w, batch, kp0, vp0, hidden_np(shape, 31, batch.num_tokens), stage)
+    assert_output("decode edges", r, literal=False)
+    mk, mv = written_mask(shape, batch)
+    check_pool("K", r["gk"], kp0, r["kp"], shape.num_layers, mask=mk)
+    check_pool("V", r["gv"], vp0, r["vp"], shape.num_layers, mask=mv)
+
+
+def test_decode_row_whose_new_token_another_sequence_reads():
+    """A page that receives a token of one decode row lies in the cached prefix of another: that row sees the new token, as
+    everywhere (keys and values are read after all of them have been written)."""
+    print("a decode row's page in another sequence's prefix", flush=True)
+    shape = dataclasses.replace(MID, num_layers=1, name="mid1")
+    w = layer_weights_np(shape, 33)
+    batch = synth.build_batch([(1, 20), (1, 40), (1, 100), (1, 5)], 33, spare_blocks=3)
+    batch.block_tables[1, 1] = batch.block_tables[0, 1]       # positions 16 .. 31 of sequence 1: the new one of sequence 0 among them
+    kp0, vp0 = pool_np(shape, 33, batch.num_blocks)
+    r = run_both(shape, w, batch, kp0, vp0, hidden_np(shape, 33, batch.num_tokens))
+    assert_output("shared page", r, literal=False)
+    # the test sees the difference: with the row's slot as it was before the call, the other row comes out elsewhere
+    old = batch.block_tables.copy()
+    old[1, 1] = next(p for p in range(batch.num_blocks) if p not in batch.block_tables)
+    kp1, vp1 = kp0.copy().reshape(batch.num_blocks, -1), vp0.copy().reshape(batch.num_blocks, -1)
+    kp1[old[1, 1]], vp1[old[1, 1]] = kp1[batch.block_tables[0, 1]], vp1[batch.block_tables[0, 1]]
+    ref, _ = oracle.stage_forward(shape, w, batch.new_tokens, batch.cached_len, old, batch.num_blocks, kp1.reshape(-1), vp1.reshape(-1),
+                                  hidden_np(shape, 33, batch.num_tokens))
+    assert np.abs(ref[1] - r["ref"][1]).max() > 4 * np.abs(r["out32"][1] - r["ref"][1]).max()
