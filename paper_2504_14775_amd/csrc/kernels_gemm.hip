@@ -422,6 +422,22 @@ int gemm_band_height(int m, int mode) {
     return round_up(m, h1) < round_up(m, h0) ? h1 : h0;
 }
 
+// Tiles of H rows (32 or 64) x 128, three LDS stages of both operands, or two of A and three of W where the tiles run in
+// several rounds of which the last is nearly full: with more loads in flight some compute units run ahead of others and the
+// last round is a long tail (128256 x 4096, 64 rows: the first tiles end between 62 and 91 us, so between 77 and 82).
+// 128256 x 4096: one row 157 -> 153 us, 32 rows 178 -> 170, 64 rows 199 -> 179; 128256 x 8192, 64 rows 355 -> 338.  Where the
+// last round is short the tiles had better end at different times (152064 x 8192, 0.3 of a round left, 64 rows: 433 and 453).
+constexpr int kSkinnySlots = 512;  // tiles that run at one time, two per compute unit
+template <int MODE, int H>
+hipError_t launch_skinny(const bf16_t* a, int64_t lda, const bf16_t* w, int64_t ldw, void* out, int64_t ldc, int m,
+                         int n, int k, int splits, int64_t split_stride, hipStream_t stream) {
+    constexpr int WM = H == 32 ? 1 : 2;  // waves along the rows
+    const int64_t tiles = (int64_t)(n / 128) * splits, last = tiles % kSkinnySlots;
+    if (tiles > kSkinnySlots && (last == 0 || last >= kSkinnySlots * 3 / 4))
+        return launch_tile_w<H, 128, WM, 4 / WM, MODE, 2, 3, true>(a, lda, w, ldw, out, ldc, m, n, k, splits, split_stride, stream);
+    return launch_tile_w<H, 128, WM, 4 / WM, MODE, 3, 3, true>(a, lda, w, ldw, out, ldc, m, n, k, splits, split_stride, stream);
+}
+
 template <int MODE>
 hipError_t launch_mode(const bf16_t* a, int64_t lda, const bf16_t* w, int64_t ldw, void* out, int64_t ldc, int m,
                        int n, int k, int tile, int splits, int64_t split_stride, hipStream_t stream) {
@@ -449,9 +465,10 @@ hipError_t launch_mode(const bf16_t* a, int64_t lda, const bf16_t* w, int64_t ld
             return launch_tile<256, 128, 2, 2, MODE, 3>(GLLM_TILE_ARGS);
         case 2: case 3: case 10: return launch_tile<256, 256, 2, 2, MODE, 2, 3>(GLLM_TILE_ARGS);
         case 6: return launch_tile<128, 128, 2, 2, MODE, 4>(GLLM_TILE_ARGS);
-        case 7:  // up to 32 rows half the activations to load and to read from LDS: one row of the 8B shape 785 -> 770 us
-            if (m <= 32) return launch_tile<32, 128, 1, 4, MODE, 3>(GLLM_TILE_ARGS);
-            return launch_tile<64, 128, 2, 2, MODE, 3>(GLLM_TILE_ARGS);
+        case 7:  // (up to 32 rows half the activations to load and to read from LDS: one row of the 8B shape 785 -> 770 us)
+            if (m <= 32) return launch_skinny<MODE, 32>(GLLM_TILE_ARGS);
+            if (m <= 64) return launch_skinny<MODE, 64>(GLLM_TILE_ARGS);
+            return launch_tile_w<64, 128, 2, 2, MODE, 3, 3, false>(GLLM_TILE_ARGS);
         case 13:  // one band of 257..384 rows
             if constexpr (MODE != GEMM_ADD_F32) {
                 if (m <= 288) return launch_tile<288, 128, 2, 2, MODE, 3>(GLLM_TILE_ARGS);

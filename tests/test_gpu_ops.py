@@ -407,7 +407,7 @@ def _gate_up(bits):
     return np.concatenate([bits[:I].reshape(I // 32, 1, 32, -1), bits[I:].reshape(I // 32, 1, 32, -1)], axis=1).reshape(bits.shape)
 
 
-@pytest.mark.parametrize("tile,N,rows", [(7, 256, (1, 31, 32, 33)), (13, 256, (257, 288, 289, 320, 321, 352, 353, 384)),
+@pytest.mark.parametrize("tile,N,rows", [(7, 256, (1, 31, 32, 33)), (7, 131072, (32, 33)), (13, 256, (257, 288, 289, 320, 321, 352, 353, 384)),
                                          (14, 512, (1, 160, 161, 193, 224, 225, 257, 321, 449, 960)),
                                          (15, 384, (1, 160, 161, 193, 224, 225, 257, 321, 449, 960)),
                                          (4, 66048, (65, 161, 193, 225))])
