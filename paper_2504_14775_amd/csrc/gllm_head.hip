@@ -80,10 +80,13 @@ __global__ __launch_bounds__(256) void pad_rows_kernel(const bf16_t* __restrict_
 // Where the list overflows or the guess fails, a second pass takes a tighter bound from the maxima of the 1024 threads
 // over the whole row; where that fails too (nearly flat distributions, very large k, masses of ties), the selection
 // runs over the row, one pass per digit, and the draw takes a pass that sums masses per 4096 consecutive tokens.
-// Measured at a vocabulary of 128256 (before: four to ten passes per row, one row per compute unit; both in us):
-//   top-k 50 + nucleus 0.95   1 row 160 -> 28, 256 rows 171 -> 39, 257 rows 320 -> 48
-//   nucleus 0.95 (logits of standard deviation 4.3)   1 row 780 -> 30, 64 rows 880 -> 35, 257 rows 1740 -> 49
-//   nucleus 0.95 of a nearly flat row (the selection runs over the row)   1 row 750 -> 166
+// Measured at a vocabulary of 128256 (first: four to ten passes per row, one row per compute unit; then one pass with the last
+// blocks of a row loaded one by one; now these together, and where every row has a compute unit the next four blocks while
+// four are worked on; us):
+//   top-k 50 + nucleus 0.95   1 row 160 -> 30.7 -> 28.2, 64 rows 37.7 -> 33.0, 256 rows 171 -> 45.6 -> 43.5, 257 rows 320 -> 58.0 -> 56.9
+//   nucleus 0.95 (logits of standard deviation 4.3)   1 row 780 -> 33.8 -> 31.7, 64 rows 880 -> 39.7 -> 35.9, 257 rows 1740 -> 56.6 -> 55.5
+//   nucleus 0.95 of nearly flat rows (the selection runs over the row)   64 rows 189 -> 183
+//   greedy   1 row 9.5 -> 9.1
 constexpr int kSampleThreads = 1024;
 constexpr int kSampleWaves = kSampleThreads / 64;
 constexpr int kDigitBits = 12, kBins = 1 << kDigitBits;
@@ -97,9 +100,22 @@ __device__ __forceinline__ uint32_t float_key(float f) {
 }
 __device__ __forceinline__ float key_float(uint32_t k) { return __uint_as_float((k & 0x80000000u) ? k ^ 0x80000000u : ~k); }
 
+// The thread's pieces of blocks first .. first + U - 1, as far as the row reaches.
+template <int U>
+__device__ __forceinline__ void load_tail(f32x4 (&v)[U], const float* __restrict__ lg, int first, int vocab) {
+#pragma unroll
+    for (int q = 0; q < U; ++q) {
+        const int i = ((first + q) << 12) + 4 * (int)threadIdx.x;
+        if (i + 4 <= vocab) v[q] = *reinterpret_cast<const f32x4*>(lg + i);
+        else if (i < vocab)
+            for (int e = 0; e < 4; ++e) v[q][e] = lg[min(i + e, vocab - 1)];
+    }
+}
+
 // Calls f(block, index, logit, valid) for the elements of a row that this thread owns, in increasing index order, the
 // whole workgroup walking blocks of 4096 consecutive logits (block = index / 4096): 16-byte loads, `U` blocks in flight,
-// when the row starts on a 16-byte boundary, single ones otherwise.  block_end(block) follows the four calls of a block.
+// when the row starts on a 16-byte boundary, single ones otherwise.  block_end(block) follows the four calls of a block.  The
+// last blocks are loaded together like the others: one by one they cost a memory latency each.
 template <int U, class F, class E>
 __device__ __forceinline__ void for_row(const float* __restrict__ lg, int vocab, F&& f, E&& block_end) {
     const int tid = threadIdx.x;
@@ -117,17 +133,20 @@ __device__ __forceinline__ void for_row(const float* __restrict__ lg, int vocab,
                 block_end(b + q);
             }
         }
-        for (; b < blocks; ++b) {
-            const int i = (b << 12) + 4 * tid;
-            if (i + 4 <= vocab) {
-                const f32x4 v = *reinterpret_cast<const f32x4*>(lg + i);
+        if (b < blocks) {  // at most U: fewer than U whole ones and the one that ends the row
+            f32x4 v[U];
+            load_tail(v, lg, b, vocab);
 #pragma unroll
-                for (int e = 0; e < 4; ++e) f(i + e, v[e]);
-            } else {
-                for (int e = 0; e < 4; ++e)
-                    if (i + e < vocab) f(i + e, lg[i + e]);
+            for (int q = 0; q < U; ++q) {
+                if (b + q >= blocks) continue;
+                const int i = ((b + q) << 12) + 4 * tid;
+                if (i < vocab) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (i + e < vocab) f(i + e, v[q][e]);
+                }
+                block_end(b + q);
             }
-            block_end(b);
         }
     } else {
         for (int b = 0; b < blocks; ++b) {
@@ -383,17 +402,21 @@ __device__ __forceinline__ int row_argmax(SampleShared& sh, const float* __restr
     return best_i == INT_MAX ? 0 : best_i;
 }
 
+constexpr int kRoomyMaxRows = 256;   // up to here every row has a compute unit
 constexpr int kFirstList = 1400;     // first bound of a nucleus: taken so that the list comes to 1.5 - 2 times this many
 constexpr int kMaxFirstK = 256;      // largest k for which the list taken with the first bound is expected to fit
 constexpr int kSecondKeys = 960;     // second bound of a nucleus: 960 of the thread maxima of the whole row, about 2800 logits
 
-__global__ __launch_bounds__(kSampleThreads, 8) void sample_kernel(const float* __restrict__ logits, int64_t ld, int vocab,
+// ROOMY: a row has a compute unit to itself, so twice the registers, and twice the loads in flight in the pass over the row.
+template <bool ROOMY>
+__global__ __launch_bounds__(kSampleThreads, ROOMY ? 4 : 8) void sample_kernel(const float* __restrict__ logits, int64_t ld, int vocab,
                                                                    float mass_one, const float* __restrict__ temperature,
                                                                    const int32_t* __restrict__ top_k,
                                                                    const float* __restrict__ top_p,
                                                                    const float* __restrict__ uniform,
                                                                    int32_t* __restrict__ out) {
     __shared__ SampleShared sh;
+    constexpr int U = ROOMY ? 8 : 4;
     const int tid = threadIdx.x, lane = tid & 63, row = blockIdx.x;
     const float* lg = logits + (int64_t)row * ld;
     const float temp = temperature[row];
@@ -409,7 +432,7 @@ __global__ __launch_bounds__(kSampleThreads, 8) void sample_kernel(const float* 
     const auto no_end = [](int) {};
 
     // ---- the pass over the row: maxima of the threads, and, where it is likely to work, the list ----
-    const int blocks = (vocab + 4095) >> 12, quarter = vocab >> 14;
+    const int quarter = vocab >> 14;
     const bool first_list = quarter > 0 && (reinterpret_cast<uintptr_t>(lg) & 15) == 0 && (by_k ? k <= kMaxFirstK : by_p);
     if (tid == 0) sh.count = 0;
     float bound = -INFINITY, ref = 0.f;
@@ -443,22 +466,42 @@ __global__ __launch_bounds__(kSampleThreads, 8) void sample_kernel(const float* 
             for (int e = 0; e < 4; ++e) own_max = fmaxf(own_max, v[q][e]);
         bound = bound_of(kth_of_threads<false>(sh, float_key(own_max), by_k ? k : kSampleWaves * min(40, max(4, kFirstList * 1024 / vocab))));
         if (!by_k) ref = block_max(sh, own_max);
-        for (int i = 0;;) {
+        auto load = [&](f32x4 (&to)[4], int i) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) to[q] = *reinterpret_cast<const f32x4*>(lg + ((q * quarter + i) << 12) + 4 * tid);
+        };
+        auto take_all = [&](const f32x4 (&from)[4], int i) {
 #pragma unroll
             for (int q = 0; q < 4; ++q)
 #pragma unroll
-                for (int e = 0; e < 4; ++e) take(((q * quarter + i) << 12) + 4 * tid + e, v[q][e]);
-            if (++i >= quarter) break;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) v[q] = *reinterpret_cast<const f32x4*>(lg + ((q * quarter + i) << 12) + 4 * tid);
+                for (int e = 0; e < 4; ++e) take(((q * quarter + i) << 12) + 4 * tid + e, from[q][e]);
+        };
+        if constexpr (ROOMY) {
+            f32x4 w[4];
+            for (int i = 0; i < quarter; i += 2) {
+                if (i + 1 < quarter) load(w, i + 1);
+                take_all(v, i);
+                if (i + 2 < quarter) load(v, i + 2);
+                if (i + 1 < quarter) take_all(w, i + 1);
+            }
+        } else {
+            for (int i = 0;;) {
+                take_all(v, i);
+                if (++i >= quarter) break;
+                load(v, i);
+            }
         }
-        for (int b = 4 * quarter; b < blocks; ++b) {
-            const int i = (b << 12) + 4 * tid;
+        load_tail(v, lg, 4 * quarter, vocab);  // (at most four blocks are left)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int i = ((4 * quarter + q) << 12) + 4 * tid;
+            if (i >= vocab) continue;
+#pragma unroll
             for (int e = 0; e < 4; ++e)
-                if (i + e < vocab) take(i + e, lg[i + e]);
+                if (i + e < vocab) take(i + e, v[q][e]);
         }
     } else {
-        for_row<4>(lg, vocab, [&](int, float v) { own_max = fmaxf(own_max, v); }, no_end);
+        for_row<U>(lg, vocab, [&](int, float v) { own_max = fmaxf(own_max, v); }, no_end);
     }
     const float best = block_max(sh, own_max);
     // probability of a token relative to the most probable one (0 for a logit that is no number); a mass is that in units
@@ -537,7 +580,7 @@ __global__ __launch_bounds__(kSampleThreads, 8) void sample_kernel(const float* 
             __syncthreads();
             ref = best;
             rest = 0.f;
-            for_row<4>(lg, vocab, take, no_end);
+            for_row<U>(lg, vocab, take, no_end);
             __syncthreads();
         }
         const int n = sh.count;
@@ -786,8 +829,9 @@ gllm_status gllm_op_sample(const float* logits, int64_t ld_logits, int32_t num_r
     // unit of the fixed-point masses: the sum of a whole row stays below 2^63
     int log_vocab = 0;
     while ((1 << log_vocab) < vocab) ++log_vocab;
-    sample_kernel<<<num_rows, kSampleThreads, 0, (hipStream_t)stream>>>(logits, ld_logits, vocab, ldexpf(1.f, 62 - log_vocab),
-                                                                        temperature, top_k, top_p, u, out_ids);
+    auto kernel = num_rows <= kRoomyMaxRows ? sample_kernel<true> : sample_kernel<false>;
+    kernel<<<num_rows, kSampleThreads, 0, (hipStream_t)stream>>>(logits, ld_logits, vocab, ldexpf(1.f, 62 - log_vocab), temperature,
+                                                                 top_k, top_p, u, out_ids);
     return hipGetLastError() == hipSuccess ? GLLM_OK : GLLM_E_HIP;
 }
 

@@ -225,3 +225,19 @@ def test_rows_without_a_finite_softmax_go_to_their_largest_logit(V, k, p):
         masked = torch.nan_to_num(holes, nan=-float("inf"))
         a, b = (run_sampler(x.to(DEV), V, [0.8], [k], [p], [u])[0] for x in (holes, masked))
         assert a == b and not np.isnan(holes[0, int(a)].item()), (u, a, b)
+
+
+@pytest.mark.parametrize("V", [4096, 16384, 16388, 28672, 32772, 36864 + 4092, 65536 - 4, 65536 + 12292])
+def test_sampler_reads_every_block_of_a_row(V):
+    """Vocabularies around multiples of the blocks that are loaded together, few rows (a compute unit each) and many (two share
+    one): the largest logit is found in each of the last places, and the k largest tokens are drawn wherever they lie."""
+    print(f"sampler: blocks, V={V}", flush=True)
+    places = sorted({0, V // 2, *[max(0, V - 1 - d) for d in (0, 3, 4, 4095, 4096, 8192, 16384)]})
+    for M in (len(places), 260):
+        lg = torch.randn(M, V, generator=torch.Generator().manual_seed(V)) * 0.5
+        at = np.array([places[i % len(places)] for i in range(M)])
+        lg[torch.arange(M), torch.from_numpy(at)] = 40.0
+        d = lg.to(DEV)
+        u = np.linspace(0.0, 0.999, M).tolist()
+        for temp, k, p in ((0.0, 0, 1.0), (0.8, 5, 1.0), (0.8, 0, 0.95), (1.0, 50, 0.9)):   # all mass on one token (weight of the rest < 1e-12)
+            assert np.array_equal(run_sampler(d, V, [temp] * M, [k] * M, [p] * M, u), at), (V, M, temp, k, p)
