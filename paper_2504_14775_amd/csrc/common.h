@@ -175,18 +175,19 @@ hipError_t launch_decode_attention(const AttnArgs& a, const DecodeArgs& dec, hip
 hipError_t launch_decode_combine(const AttnArgs& a, const DecodeRow* rows, int num_rows, const float* part_o,
                                  const float* part_ml, hipStream_t stream);
 
-// Prefill chunks: one work item per prefill_item_rows() consecutive query rows of a chunk.
-int prefill_item_rows(int n_q, int n_kv);
+// Prefill chunks: one work item per prefill_item_rows() consecutive query rows of a chunk; `half`: items of half the rows.
+int prefill_item_rows(int n_q, int n_kv, bool half);
+int prefill_heads_per_workgroup(int n_q, int n_kv, bool half);
 struct PrefillItem {
     int32_t row0;      // first token row of the tile
     int32_t n_rows;    // valid query rows in the tile (1 .. prefill_item_rows)
     int32_t pos0;      // position of the first query row
     int32_t bt_off;    // offset of the sequence's first page id in bt_flat
 };
-hipError_t launch_prefill_attention(const AttnArgs& a, const PrefillItem* items, int num_items, hipStream_t stream);
+hipError_t launch_prefill_attention(const AttnArgs& a, const PrefillItem* items, int num_items, bool half, hipStream_t stream);
 // Prefill and decode items of one batch in one launch, and whether that pays.
-bool attention_in_one_launch(const AttnArgs& a, int num_items, int num_decode_items);
-hipError_t launch_hybrid_attention(const AttnArgs& a, const PrefillItem* items, int num_items, const DecodeArgs& dec, hipStream_t stream);
+bool attention_in_one_launch(const AttnArgs& a, int num_items, bool half, int num_decode_items);
+hipError_t launch_hybrid_attention(const AttnArgs& a, const PrefillItem* items, int num_items, bool half, const DecodeArgs& dec, hipStream_t stream);
 
 // Ceiling probes (see kernels_peak.hip).  peak_mfma: workgroups x 4 waves x iters x 16 MFMAs of
 // 2*32*32*16 flop each.  peak_read: reads `bytes` once.

@@ -40,6 +40,7 @@ struct LayerBuffers {
 };
 
 constexpr int kStagingSlots = 4;
+constexpr int kHalfItemsMax = 256;  // workgroups of whole prefill items
 constexpr int kDecodeSlots = 512;  // decode attention workgroups that run at one time
 constexpr int kMaxSplits = kMaxPlanes;
 
@@ -56,7 +57,7 @@ struct gllm_stage {
     // derived sizes
     int q_dim = 0, kv_dim = 0, n_qkv = 0, n_qkv_pad = 0, inter_pad = 0, hidden_pad_n = 0;
     int64_t m_pad = 0;
-    int max_items = 0, max_pre_items = 0, max_v_tiles = 0, pre_rows = 64;
+    int max_items = 0, max_pre_items = 0, max_v_tiles = 0;
     std::vector<LayerBuffers> layers;
     bool borrowed_weights = false;  // the layer buffers belong to another stage (gllm_stage_share_weights)
     float* rope_cs = nullptr;  // device [max_position][d/2][2]
@@ -275,8 +276,7 @@ gllm_status gllm_stage_create(const gllm_stage_config* cfg, gllm_stage** out) {
     s->hidden_pad_n = (int)round_up(c.hidden, kGemmPadN);
     s->m_pad = round_up(c.max_tokens, kGemmPadM);
     s->max_items = 4 * c.max_seqs + 1024;
-    s->pre_rows = prefill_item_rows(c.n_q_heads, c.n_kv_heads);
-    s->max_pre_items = c.max_tokens / s->pre_rows + c.max_seqs + 1;
+    s->max_pre_items = c.max_tokens / prefill_item_rows(c.n_q_heads, c.n_kv_heads, true) + c.max_seqs + 1;
     s->max_v_tiles = c.max_tokens / kPage + 2 * c.max_seqs + 1;
     s->layers.resize(c.num_layers);
     s->layer_end = c.num_layers;
@@ -568,10 +568,21 @@ gllm_status gllm_stage_forward(gllm_stage* s, const gllm_batch* b, const void* h
     unsigned char* st_base = s->staging[slot];
     // compact layout for this batch: only what is used travels to the device
     int64_t cnt_items = 0, cnt_pre = 0, cnt_vt = 0;
+    // Items of half the rows where whole ones would not give every compute unit a second workgroup: an item's time is then the
+    // chain of its key blocks, shorter with one column group per wave than with two.  8B shape, eight layers: 197 prompt rows
+    // 1268 -> 1249 us, 100 rows behind 3000 cached ones 1450 -> 1298, 500 rows 1916 -> 1908; 300 rows behind 1000 (14B, three
+    // layers) 743 -> 714.  With 256 workgroups of whole items there is no difference (1000 rows), with 448 they are better (the
+    // keys and values pass through LDS once per item: 2048 rows 8975, halves 9047).
+    int64_t whole_wgs = 0;
+    for (int i = 0; i < S; ++i)
+        if (b->new_tokens[i] > 1) whole_wgs += ceil_div(b->new_tokens[i], prefill_item_rows(c.n_q_heads, c.n_kv_heads, false));
+    whole_wgs *= c.n_q_heads / prefill_heads_per_workgroup(c.n_q_heads, c.n_kv_heads, false);
+    const bool half_items = whole_wgs <= kHalfItemsMax;
+    const int pre_rows = prefill_item_rows(c.n_q_heads, c.n_kv_heads, half_items);
     for (int i = 0; i < S; ++i) {
         if (b->new_tokens[i] == 1) cnt_items += ceil_div((int64_t)b->cached_len[i] + 1, part);
         else {
-            cnt_pre += ceil_div(b->new_tokens[i], s->pre_rows);
+            cnt_pre += ceil_div(b->new_tokens[i], pre_rows);
             cnt_vt += ((int64_t)b->cached_len[i] + b->new_tokens[i] - 1) / kPage - b->cached_len[i] / kPage + 1;
         }
     }
@@ -631,8 +642,8 @@ gllm_status gllm_stage_forward(gllm_stage* s, const gllm_batch* b, const void* h
             if (n_items - first == 1) dec_items[first].single = 1;
             else dec_rows[n_rows++] = DecodeRow{(int32_t)row, first, n_items - first, 0};
         } else {
-            for (int t0 = 0; t0 < n; t0 += s->pre_rows)
-                pre_items[n_pre++] = PrefillItem{(int32_t)(row + t0), std::min(s->pre_rows, n - t0), cl + t0,
+            for (int t0 = 0; t0 < n; t0 += pre_rows)
+                pre_items[n_pre++] = PrefillItem{(int32_t)(row + t0), std::min(pre_rows, n - t0), cl + t0,
                                                  (int32_t)bt_off};
         }
         bt_off += pages;
@@ -713,12 +724,12 @@ gllm_status gllm_stage_forward(gllm_stage* s, const gllm_batch* b, const void* h
         aa.scale_log2 = (float)(1.4426950408889634 / std::sqrt((double)d));
         const DecodeArgs da{d_items, d_order, n_items, s->part_o, s->part_ml, from_qkv, ra};
         // both kinds of attention read q and the pool and write disjoint rows of attn
-        if (s->overlap_attention && !s->profiling && attention_in_one_launch(aa, n_pre, n_items)) {
-            HIP_TRY(s, launch_hybrid_attention(aa, d_pre, n_pre, da, st));
+        if (s->overlap_attention && !s->profiling && attention_in_one_launch(aa, n_pre, half_items, n_items)) {
+            HIP_TRY(s, launch_hybrid_attention(aa, d_pre, n_pre, half_items, da, st));
         } else {
             if (n_pre > 0) {
                 ProfScope ps(s, st, PC_ATTN_PREFILL);
-                HIP_TRY(s, launch_prefill_attention(aa, d_pre, n_pre, st));
+                HIP_TRY(s, launch_prefill_attention(aa, d_pre, n_pre, half_items, st));
             }
             if (n_items > 0) {
                 ProfScope ps(s, st, PC_ATTN_DECODE);

@@ -572,14 +572,14 @@ __device__ __forceinline__ void await_lds(u32x4 (&v)[N]) {
 
 // ------------------------------------------------------------------------------------------
 // Prefill: one workgroup of 4 waves per (item, group of HW query heads of one KV head).  An item is up
-// to 128/HW consecutive query rows of a chunk, so the workgroup owns 8 column groups of 16 (2 per wave)
+// to 64*NB/HW consecutive query rows of a chunk, so the workgroup owns 4*NB column groups of 16 (NB per wave)
 // that all share the same K/V: every 32-key block is brought into LDS once (global_load_lds into a ring
 // of 3 stages, two blocks in flight while one is processed: a block is only ~0.5 us of work, far less
 // than the memory latency) and read by all 4 waves.
 // A lane owns 8 consecutive keys of the block (the K operand rows are permuted accordingly),
 // so a V operand is one 16-byte LDS read of 8 slots of one page; LDS holds the pages as the pool does, except
 // that the second K page is shifted by four slots (see issue_block).
-// Column group cb = 2*wave + c covers head (cb % HW) and query rows 16*(cb / HW) .. +15 of the item.
+// Column group cb = NB*wave + c covers head (cb % HW) and query rows 16*(cb / HW) .. +15 of the item.
 // ------------------------------------------------------------------------------------------
 typedef const __attribute__((address_space(1))) void* gptr_t;
 typedef __attribute__((address_space(3))) void* lptr_t;
@@ -590,9 +590,8 @@ struct PrefillLds {
     __attribute__((aligned(1024))) unsigned char stage[kPrefillStages][4][D * kPage * 2];  // [stage][K0,K1,V0,V1]
 };
 
-template <int D, int HW>
+template <int D, int HW, int NB>
 __device__ __forceinline__ void prefill_workgroup(const AttnArgs& a, const PrefillItem* __restrict__ items, int wg, PrefillLds<D>& shared) {
-    constexpr int NB = 2;
     constexpr int PAGE_BYTES = D * kPage * 2;  // one (page, head) of K or of V
     constexpr int NS = kPrefillStages;
     constexpr int IPB = PAGE_BYTES / 1024;     // load instructions per wave and block
@@ -723,22 +722,22 @@ __device__ __forceinline__ void prefill_workgroup(const AttnArgs& a, const Prefi
     }
 }
 
-template <int D, int HW>
+template <int D, int HW, int NB>
 __global__ __launch_bounds__(256, 3) void prefill_attention_kernel(AttnArgs a, const PrefillItem* __restrict__ items) {
     __shared__ PrefillLds<D> lds;
-    prefill_workgroup<D, HW>(a, items, blockIdx.x, lds);
+    prefill_workgroup<D, HW, NB>(a, items, blockIdx.x, lds);
 }
 
 // Both kinds in one launch: the first workgroups take the prefill items, the others the decode items.  For batches with so
 // few prefill workgroups that they would run on a nearly empty chip (kHybridPrefillMax).
-template <int D, int HW>
+template <int D, int HW, int NB>
 __global__ __launch_bounds__(256, 2) void hybrid_attention_kernel(AttnArgs a, const PrefillItem* __restrict__ items, int prefill_wgs,
                                                                    DecodeArgs dec) {
     __shared__ union Lds {
         PrefillLds<D> prefill;
         DecodeLds<D, false> decode;
     } lds;
-    if ((int)blockIdx.x < prefill_wgs) prefill_workgroup<D, HW>(a, items, blockIdx.x, lds.prefill);
+    if ((int)blockIdx.x < prefill_wgs) prefill_workgroup<D, HW, NB>(a, items, blockIdx.x, lds.prefill);
     else decode_workgroup<D, false>(a, dec, blockIdx.x - prefill_wgs, lds.decode);
 }
 
@@ -766,23 +765,30 @@ hipError_t launch_decode_combine(const AttnArgs& a, const DecodeRow* rows, int n
     return hipGetLastError();
 }
 
-int prefill_heads_per_workgroup(int n_q, int n_kv) {
+// Query heads of a KV head that share a workgroup, and rows of an item: a workgroup has four waves of NB column groups of 16
+// (16 rows of one head), eight groups, or four (`half`).
+int prefill_heads_per_workgroup(int n_q, int n_kv, bool half) {
     const int g = n_q / n_kv;
+    if (g == 8 && half) return 4;
     return (g == 1 || g == 2 || g == 4 || g == 8) ? g : 1;
 }
 
-int prefill_item_rows(int n_q, int n_kv) { return 128 / prefill_heads_per_workgroup(n_q, n_kv); }
+int prefill_item_rows(int n_q, int n_kv, bool half) { return (half ? 64 : 128) / prefill_heads_per_workgroup(n_q, n_kv, half); }
 
-#define GLLM_BY_HEADS(LAUNCH, D_)                                                                        \
-    do {                                                                                                  \
-        if (hw == 8) LAUNCH(D_, 8); else if (hw == 4) LAUNCH(D_, 4); else if (hw == 2) LAUNCH(D_, 2); else LAUNCH(D_, 1); \
+#define GLLM_BY_HEADS(LAUNCH, D_)                                       \
+    do {                                                                \
+        if (half) {                                                     \
+            if (hw == 4) LAUNCH(D_, 4, 1); else if (hw == 2) LAUNCH(D_, 2, 1); else LAUNCH(D_, 1, 1);                               \
+        } else {                                                        \
+            if (hw == 8) LAUNCH(D_, 8, 2); else if (hw == 4) LAUNCH(D_, 4, 2); else if (hw == 2) LAUNCH(D_, 2, 2); else LAUNCH(D_, 1, 2); \
+        }                                                               \
     } while (0)
 
-hipError_t launch_prefill_attention(const AttnArgs& a, const PrefillItem* items, int num_items, hipStream_t stream) {
+hipError_t launch_prefill_attention(const AttnArgs& a, const PrefillItem* items, int num_items, bool half, hipStream_t stream) {
     if (num_items <= 0) return hipSuccess;
-    const int hw = prefill_heads_per_workgroup(a.n_q, a.n_kv);
+    const int hw = prefill_heads_per_workgroup(a.n_q, a.n_kv, half);
     const dim3 grid(num_items * (a.n_q / hw));
-#define GLLM_PREFILL(D_, HW_) prefill_attention_kernel<D_, HW_><<<grid, 256, 0, stream>>>(a, items)
+#define GLLM_PREFILL(D_, HW_, NB_) prefill_attention_kernel<D_, HW_, NB_><<<grid, 256, 0, stream>>>(a, items)
     if (a.d == 128) GLLM_BY_HEADS(GLLM_PREFILL, 128);
     else if (a.d == 64) GLLM_BY_HEADS(GLLM_PREFILL, 64);
     else return hipErrorInvalidValue;
@@ -790,7 +796,7 @@ hipError_t launch_prefill_attention(const AttnArgs& a, const PrefillItem* items,
     return hipGetLastError();
 }
 
-// Up to 64 prefill workgroups (a quarter of the compute units) share the launch of the decode items: with 4 of them (52
+// Up to 64 prefill workgroups (a quarter of the compute units; twice as many of half the rows) share the launch of the decode items: with 4 of them (52
 // rows, one layer) a batch takes 43 instead of 46 us, with 32 (71 prompt rows beside 251 decode rows, eight layers) 2220
 // instead of 2306 us, against two launches one after the other.
 // More of them gain nothing beside the key stream of the decode items (160: +0.5 % of the batch, 448: +0.5 %): their own
@@ -798,18 +804,18 @@ hipError_t launch_prefill_attention(const AttnArgs& a, const PrefillItem* items,
 // comes out -- from one launch, in either order or interleaved, and from two streams (whose events cost 13 us on top).
 constexpr int kHybridPrefillMax = 64;
 
-bool attention_in_one_launch(const AttnArgs& a, int num_items, int num_decode_items) {
+bool attention_in_one_launch(const AttnArgs& a, int num_items, bool half, int num_decode_items) {
     return num_items > 0 && num_decode_items > 0 &&
-           num_items * (a.n_q / prefill_heads_per_workgroup(a.n_q, a.n_kv)) <= kHybridPrefillMax;
+           num_items * (a.n_q / prefill_heads_per_workgroup(a.n_q, a.n_kv, half)) <= (half ? 2 : 1) * kHybridPrefillMax;
 }
 
-hipError_t launch_hybrid_attention(const AttnArgs& a, const PrefillItem* items, int num_items, const DecodeArgs& dec, hipStream_t stream) {
-    const int hw = prefill_heads_per_workgroup(a.n_q, a.n_kv);
+hipError_t launch_hybrid_attention(const AttnArgs& a, const PrefillItem* items, int num_items, bool half, const DecodeArgs& dec, hipStream_t stream) {
+    const int hw = prefill_heads_per_workgroup(a.n_q, a.n_kv, half);
     const int prefill_wgs = num_items * (a.n_q / hw);
     if (num_items <= 0 || dec.num_items <= 0) return hipErrorInvalidValue;
     if (dec.from_qkv) return hipErrorInvalidValue;
     const dim3 grid(prefill_wgs + dec.num_items * a.n_kv);
-#define GLLM_HYBRID(D_, HW_) hybrid_attention_kernel<D_, HW_><<<grid, 256, 0, stream>>>(a, items, prefill_wgs, dec)
+#define GLLM_HYBRID(D_, HW_, NB_) hybrid_attention_kernel<D_, HW_, NB_><<<grid, 256, 0, stream>>>(a, items, prefill_wgs, dec)
     if (a.d == 128) GLLM_BY_HEADS(GLLM_HYBRID, 128);
     else if (a.d == 64) GLLM_BY_HEADS(GLLM_HYBRID, 64);
     else return hipErrorInvalidValue;

@@ -613,3 +613,16 @@ def test_decode_row_whose_new_token_another_sequence_reads():
     ref, _ = oracle.stage_forward(shape, w, batch.new_tokens, batch.cached_len, old, batch.num_blocks, kp1.reshape(-1), vp1.reshape(-1),
                                   hidden_np(shape, 33, batch.num_tokens))
     assert np.abs(ref[1] - r["ref"][1]).max() > 4 * np.abs(r["out32"][1] - r["ref"][1]).max()
+
+
+@pytest.mark.parametrize("n_kv,d", [(16, 64), (8, 128), (4, 64), (2, 128)])
+def test_chunks_of_many_workgroups_match_the_oracle(n_kv, d):
+    """More prefill workgroups than compute units: items of 128 rows x heads instead of the halves that smaller batches take, for
+    1, 2, 4 and 8 query heads per KV head."""
+    print(f"many prefill workgroups n_kv={n_kv} d={d}", flush=True)
+    shape = synth.StageShape("many", 1, 256, 16, n_kv, d, 384)
+    batch = synth.build_batch([(1500, 37), (620, 0), (1, 99)], 41, spare_blocks=5)
+    w = layer_weights_np(shape, 41)
+    kp0, vp0 = pool_np(shape, 41, batch.num_blocks)
+    r = run_both(shape, w, batch, kp0, vp0, hidden_np(shape, 41, batch.num_tokens))
+    assert_output(f"many/{n_kv}/{d}", r, literal=False)
