@@ -38,7 +38,7 @@ namespace {
 
 constexpr int BK = 64;
 [[maybe_unused]] constexpr int MB = 16, MK = 32;  // v_mfma_f32_16x16x32_bf16: a block of 16x16 results over 32 k values
-constexpr int kMaxTileM = 288;            // tallest tile
+constexpr int kMaxTileM = 384;            // tallest tile
 
 // silu(z) = z / (1 + e^-z) with the hardware exp2 and reciprocal (1 ulp each; the result is rounded to bf16)
 __device__ __forceinline__ float silu(float z) {

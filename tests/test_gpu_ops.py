@@ -337,6 +337,21 @@ def test_gemm_rows_farther_apart_than_32_bit_offsets_reach():
     assert np.all(np.abs(out.cpu().numpy() - x @ y.T) <= (np.abs(x) @ np.abs(y).T) * K * 2.0 ** -24)
 
 
+@pytest.mark.parametrize("M,ld", [(329, 6520000), (330, 6520000), (384, 5592404), (384, 5592406)])
+def test_gemm_far_rows_under_the_tallest_tile(M, ld):
+    """One band of 257..384 rows whose rows lie so far apart that just all of them, or not all, are within 32-bit offsets."""
+    N, K = 256, 64
+    print(f"gemm far rows M={M} ld={ld}", flush=True)
+    a, w = rand_bits(15, 1, (M, K), 1.0), rand_bits(15, 2, (N, K), 0.05)
+    far = torch.empty((M - 1) * ld + K, dtype=torch.bfloat16, device=DEV).as_strided((M, K), (ld, 1))
+    far.copy_(to_dev_bits(a).view(torch.bfloat16))
+    out = torch.zeros((M, N), dtype=torch.float32, device=DEV)
+    B.gllm_op_gemm_bf16(far, to_dev_weight(w), out, M, N, K, B.GEMM_STORE_F32, 13)
+    torch.cuda.synchronize()
+    x, y = oracle.bf16_to_f64(a), oracle.bf16_to_f64(w)
+    assert np.all(np.abs(out.cpu().numpy() - x @ y.T) <= (np.abs(x) @ np.abs(y).T) * K * 2.0 ** -24)
+
+
 @pytest.mark.parametrize("ldw,N,whole", [(1 << 23, 128, False), (1 << 23, 192, False), (1 << 25, 128, False), (1 << 25, 128, True)])
 def test_gemm_weights_with_a_k_extent_beyond_32_bit_offsets(ldw, N, whole):
     """Row blocks of W that lie 1 and 4 GiB apart: the product over a leading part of k, and over all of it with values in the
