@@ -36,12 +36,11 @@ struct CopyIn {
 // as the fp32 residual stream; the workgroups in front of the rows' bring the batch's metadata from pinned host memory to
 // the device (see CopyIn), beside the rows and without a launch or a copy engine of its own.  Otherwise the row is the fp32 residual stream plus `planes` partial
 // GEMM outputs (summed in plane order and written back), so the residual add costs no extra pass.
-// The row is kept in registers between the two phases (MAXV 16-byte pieces per thread).  PLANES >= 0 fixes the
-// number of planes at compile time (the loop unrolls and all loads of a piece are issued together: with a few
-// hundred rows the kernel is all latency); PLANES < 0 takes it from the argument.
+// The row is kept in registers between the two phases (MAXV 16-byte pieces per thread).  PLANES is the number of planes (the
+// loop unrolls and all loads of a piece are issued together: with a few hundred rows the kernel is all latency).
 template <bool FROM_BF16, int MAXV, int PLANES, int THREADS>
 __global__ __launch_bounds__(THREADS) void rmsnorm_kernel(const bf16_t* __restrict__ in, float* __restrict__ x,
-                                                       const float* __restrict__ y, int planes, int64_t plane_stride,
+                                                       const float* __restrict__ y, int64_t plane_stride,
                                                        const bf16_t* __restrict__ gamma, bf16_t* __restrict__ h,
                                                        int64_t ldh, int hidden, float eps, CopyIn copy) {
     __shared__ float red[THREADS / 64];
@@ -73,18 +72,13 @@ __global__ __launch_bounds__(THREADS) void rmsnorm_kernel(const bf16_t* __restri
                 *reinterpret_cast<f32x4*>(xr + j) = v;
             } else {
                 v = *reinterpret_cast<const f32x4*>(xr + j);
-                if constexpr (PLANES >= 0) {
-                    f32x4 part[PLANES > 0 ? PLANES : 1];
+                f32x4 part[PLANES > 0 ? PLANES : 1];
 #pragma unroll
-                    for (int p = 0; p < PLANES; ++p)
-                        part[p] = *reinterpret_cast<const f32x4*>(y + p * plane_stride + row * hidden + j);
+                for (int p = 0; p < PLANES; ++p)
+                    part[p] = *reinterpret_cast<const f32x4*>(y + p * plane_stride + row * hidden + j);
 #pragma unroll
-                    for (int p = 0; p < PLANES; ++p) v += part[p];
-                } else {
-                    for (int p = 0; p < planes; ++p)
-                        v += *reinterpret_cast<const f32x4*>(y + p * plane_stride + row * hidden + j);
-                }
-                if (planes > 0) *reinterpret_cast<f32x4*>(xr + j) = v;
+                for (int p = 0; p < PLANES; ++p) v += part[p];
+                if constexpr (PLANES > 0) *reinterpret_cast<f32x4*>(xr + j) = v;
             }
         }
         keep[i] = v;
@@ -359,7 +353,7 @@ hipError_t launch_rmsnorm_any(const bf16_t* in, float* x, const float* y, int pl
         const int copy_wgs = (int)ceil_div(copy.vecs, N * kCopyVecs);                                                      \
         CopyIn c = copy;                                                                                                 \
         c.workgroups = copy_wgs;                                                                                         \
-        rmsnorm_kernel<FROM_BF16, V, P, N><<<rows + copy_wgs, N, 0, stream>>>(in, x, y, planes, plane_stride, gamma, h, ldh, hidden, eps, c); \
+        rmsnorm_kernel<FROM_BF16, V, P, N><<<rows + copy_wgs, N, 0, stream>>>(in, x, y, plane_stride, gamma, h, ldh, hidden, eps, c); \
     } while (0)
 #define GLLM_RMS(V, N)                                           \
     do {                                                         \
@@ -371,8 +365,7 @@ hipError_t launch_rmsnorm_any(const bf16_t* in, float* x, const float* y, int pl
         else if (planes == 5) GLLM_RMS_P(V, 5, N);               \
         else if (planes == 6) GLLM_RMS_P(V, 6, N);               \
         else if (planes == 7) GLLM_RMS_P(V, 7, N);               \
-        else if (planes == 8) GLLM_RMS_P(V, 8, N);               \
-        else GLLM_RMS_P(V, -1, N);                               \
+        else GLLM_RMS_P(V, 8, N);                                \
     } while (0)
     if (rows <= kWideRmsMaxRows && hidden > 1024) {
         const int vecs = (int)ceil_div(hidden, 4096);
