@@ -206,8 +206,8 @@ gllm_status gllm_op_pack_weight(const void* w, int64_t ldw, int32_t n, int32_t k
  * from HBM), 7 = 64x128, up to 32 rows 32x128 (picked up to 64 rows: two workgroups per compute unit keep more of the weight stream in
  * flight), 8 and 12 = 256x256 tiles for the whole bands of 256 rows plus 64x256 or 128x256 tiles for a last band of at
  * most 128 rows, or two bands of 192x256 tiles for all rows up to 384 (only for m > 256 with 0 < m mod 256 <= 128 and
- * n a multiple of 256), 9 = 288x128 (256x192 where n is no multiple of 128; only for 256 < m <= 288, n a multiple of 192,
- * not for SwiGLU: all rows in one band, so the weights are read once), 13 = one band of 257 to 384 rows, its height a
+ * n a multiple of 256), 9 = 288x128, or 288x192 (six wavefronts) where n is no multiple of 128 and in mode 1 (only for
+ * 256 < m <= 288, n a multiple of 192, not for SwiGLU: all rows in one band, so the weights are read once), 13 = one band of 257 to 384 rows, its height a
  * multiple of 32, by 128 columns, 14 and 15 = bands of equal height, a multiple of 32 from 160 to 256, by 256 and by 128
  * columns (mode 1: of 256 rows; 13 too); a forced tile that does not fit the shape gives GLLM_E_UNSUPPORTED.
  * Alignment: operands are loaded in 16-byte pieces from any 4-byte boundary.  Where a, one of its rows (lda odd, m > 1) or

@@ -480,6 +480,10 @@ hipError_t launch_mode(const bf16_t* a, int64_t lda, const bf16_t* w, int64_t ld
         case 5:
             if constexpr (MODE != GEMM_SWIGLU_BF16) return launch_tile<256, 192, 2, 2, MODE, 2, 3>(GLLM_TILE_ARGS);
             else return hipErrorInvalidValue;
+        case 9:  // 257..288 rows in one band where 128 columns do not divide n (and to add): six waves on four SIMDs, but the weights
+                 // are read once.  Against two bands of 256x192, 257 rows: 24768 x 4096 118 -> 85 us, 74304 x 4096 260 -> 190
+            if constexpr (MODE != GEMM_SWIGLU_BF16) return launch_tile_w<288, 192, 3, 2, MODE, 2, 3, true>(GLLM_TILE_ARGS);
+            else return hipErrorInvalidValue;
         default: return hipErrorInvalidValue;
     }
 #undef GLLM_TILE_ARGS
@@ -769,7 +773,7 @@ hipError_t launch_gemm_bf16(const bf16_t* a, int64_t lda, const bf16_t* w, int64
         tile = cheapest_listed(m, n, k, splits == 1 ? mode : GEMM_STORE_F32, splits, splits, true).tile;
     }
     if (!tile_fits(tile, m, n, mode, splits)) return hipErrorInvalidValue;
-    if (tile == 9) tile = n % 128 == 0 ? 13 : 5;
+    if (tile == 9 && n % 128 == 0 && mode != GEMM_ADD_F32) tile = 13;
     if ((((uintptr_t)a | (uintptr_t)w) & 3) || (m > 1 && lda % 2 != 0)) {
         const int cols = mode == GEMM_SWIGLU_BF16 ? n / 2 : n;
         const int64_t blocks = ceil_div((int64_t)m * cols, 256);

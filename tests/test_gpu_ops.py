@@ -139,12 +139,13 @@ def test_gemm_row_mixed_launch(M, rowmix=8):
     assert np.all(err <= np.abs(ref_s) * 2.0 ** -7 + 1e-4), float(err.max())
 
 
+@pytest.mark.parametrize("N", [576, 768])
 @pytest.mark.parametrize("M", [257, 270, 288])
-def test_gemm_288_row_tile(M):
-    """All of 257..288 rows in one band of 288x192 tiles (six waves): store, add and split-K planes; refused outside
-    that row range, for other column counts and for SwiGLU."""
-    N, K = 576, 384
-    print(f"gemm 288x192 tile M={M}", flush=True)
+def test_gemm_288_row_tile(M, N):
+    """All of 257..288 rows in one band, 288x192 tiles (six waves) for 576 columns, 288x128 for 768 (to add 288x192): store, add
+    and split-K planes; refused outside that row range, for other column counts and for SwiGLU."""
+    K = 384
+    print(f"gemm 288-row tile M={M} N={N}", flush=True)
     a = rand_bits(10, 1, (M, K), 1.0)
     w = rand_bits(10, 2, (N, K), 0.05)
     ref = oracle.linear(oracle.bf16_to_f64(a), w)
@@ -162,6 +163,27 @@ def test_gemm_288_row_tile(M):
         with pytest.raises(B.GllmError) as e:
             B.gllm_op_gemm_bf16(da, to_dev_weight(rand_bits(10, 3, (768, K), 0.05)), torch.empty(512, 768, device=DEV), m, n, K, mode, 9)
         assert e.value.status == -7          # GLLM_E_UNSUPPORTED
+
+
+def test_gemm_288_row_tile_reads_the_weights_once():
+    """24768 columns are 129 tiles of 288x192, one round of the compute units, and 258 of 256x192, two: 85 and 118 us measured."""
+    M, N, K = 257, 24768, 4096
+    a = torch.randn(M, K, device=DEV).to(torch.bfloat16)
+    w = [(torch.randn(N, K, device=DEV) * 0.02).to(torch.bfloat16) for _ in range(3)]
+    out = torch.empty(M, N, device=DEV)
+    us = {9: [], 5: []}
+    for _ in range(12):
+        for tile in us:
+            e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            e0.record()
+            for i in range(9):
+                B.gllm_op_gemm_bf16(a, w[i % 3], out, M, N, K, B.GEMM_STORE_F32, tile)
+            e1.record()
+            e1.synchronize()
+            us[tile].append(e0.elapsed_time(e1) * 1e3 / 9)
+    one, two = (float(np.median(us[t][2:])) for t in (9, 5))
+    print(f"gemm 288-row tile: one band {one:.1f} us, two bands {two:.1f} us", flush=True)
+    assert one < 0.9 * two
 
 
 def test_gemm_row_mixed_launch_refuses_shapes_without_a_short_last_band():
