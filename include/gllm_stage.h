@@ -224,11 +224,10 @@ gllm_status gllm_op_gemm_bf16_splitk(const void* a, int64_t lda, const void* w, 
                                      int32_t m, int32_t n, int32_t k, int32_t tile, int32_t splits, int64_t plane_stride,
                                      void* stream);
 
-/* Host only (no device call): the tile id and split-K factor the library's cost model picks for a problem, as it does
- * when gllm_op_gemm_bf16 is called with tile = -1 (splits stays 1 unless mode is 0; at most max_splits).  Result planes are
- * taken to be read back by the next kernel.  It chooses among tiles 0 to 9 and powers of two.
- * tile, splits: HOST out.  The stage plans its QKV, O and down projections with max_splits = 8, and the stage and the head
- * choose among tiles 13 to 15 and other factors that divide k/64 as well. */
+/* Host only (no device call): the tile id and split-K factor the library's cost model picks for a problem: what the stage
+ * (option gemm_row_mixed on) and the head run, and gllm_op_gemm_bf16 when it is called with tile = -1 (splits stays 1 unless mode is 0; at most
+ * max_splits, a factor that divides k/64).  Result planes are taken to be read back by the next kernel.
+ * tile, splits: HOST out.  The stage plans its QKV, O and down projections with max_splits = 8. */
 gllm_status gllm_op_gemm_plan(int32_t m, int32_t n, int32_t k, int32_t mode, int32_t max_splits, int32_t* tile,
                               int32_t* splits);
 

@@ -63,8 +63,6 @@ int gemm_rowmix_rem_rows(int m, int n);
 // whether it may pick tile 8.  Result planes count twice: as they are written and as the next kernel reads them back.
 struct GemmPlan { int tile; int splits; };
 GemmPlan gemm_plan(int m, int n, int k, int mode, int max_splits, bool row_mixed = true);
-// The same among tiles 0 to 9 and split-K factors that are powers of two: the answers of gllm_op_gemm_plan.
-GemmPlan gemm_plan_listed(int m, int n, int k, int mode, int max_splits);
 
 // Residual stream entry: x = float(in_bf16), h = bf16(rmsnorm(x) * gamma).  The launch also copies copy_bytes (a multiple
 // of 16) from copy_src, which may be pinned host memory, to copy_dst; both 16-byte aligned.

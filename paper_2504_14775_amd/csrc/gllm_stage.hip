@@ -795,7 +795,7 @@ gllm_status gllm_op_gemm_plan(int32_t m, int32_t n, int32_t k, int32_t mode, int
     if (!tile || !splits || m < 1 || n < 1 || k < 1 || n % 64 != 0 || k % 64 != 0 || max_splits < 1 || mode < 0 ||
         mode > GEMM_SWIGLU_BF16)
         return GLLM_E_INVALID;
-    const GemmPlan p = gemm_plan_listed(m, n, k, mode, max_splits);
+    const GemmPlan p = gemm_plan(m, n, k, mode, max_splits);
     *tile = p.tile;
     *splits = p.splits;
     return GLLM_OK;

@@ -586,7 +586,8 @@ struct TileCost {
     double step, fixed, lone, per_tile, plane, stream;
 };
 constexpr double kCacheRate = 154;
-constexpr TileCost kCost128x128{512, 128, 0.919, 7.22, 0.45, 0, 0.57, 6.25}, kCost128x128Deep{256, 128, 0.526, 3.35, 0.76, 0.78, 0.97, 6.29}, kCost256x192{256, 192, 1.13, 4.19, 0.66, 1.97, 0.39, 5.13};
+constexpr TileCost kCost128x128{512, 128, 0.919, 7.22, 0.45, 0, 0.57, 6.25}, kCost128x128Deep{256, 128, 0.526, 3.35, 0.76, 0.78, 0.97, 6.29}, kCost256x192{256, 192, 1.13, 4.19, 0.66, 1.97, 0.39, 5.13},
+    kCost288x192{256, 192, 1.27, 2.6, 0.92, 2.65, 1.8, 6.2};
 // tiles of 160, 192, 224 and 256 rows x 128 and x 256 columns, and of 288, 320, 352 and 384 rows x 128
 constexpr TileCost narrow_cost(double step) { return {256, 128, step, 4.41, 0.6, 3, 0.66, 5.27}; }
 constexpr TileCost tall_cost(double step) { return {256, 128, step, 4.85, 0.57, 2.54, 0.47, 4.34}; }
@@ -612,22 +613,22 @@ double rounds_of_rowmix(const TileCost& c, double big, double low) {
     return full + c.lone + (1.0 - c.lone) * (rest + kLowTile * beside) / c.slots + kLowTile * rounds_of(c, low - beside);
 }
 
-// Tile shape and split-K factor (a divisor of the k-steps, at most max_splits) of the lowest cost.  Up to 64 rows the
-// product is a stream of the weights and the 64x128 tile (two workgroups per compute unit, 64 KiB of weights in flight on
-// each, half the activation traffic of a 128-row tile) the only candidate, split 1, 2, 4 or 8 ways: 0.30 x 1.65 us per k-step
-// of a tile, but not less than the weights take at 5.5 TB/s.  A result plane is read back by the next kernel, so a product
-// that is split less is worth the time of that.
-GemmPlan cheapest(int m, int n, int k, int mode, int max_splits, bool row_mixed) {
+// Tile shape and split-K factor (a divisor of the k-steps from min_splits to max_splits) of the lowest cost.  Up to 64 rows the
+// product is a stream of the weights and tile 7 (64x128, up to 32 rows 32x128: two workgroups per compute unit, 64 KiB of
+// weights in flight on each, half the activation traffic of a 128-row tile) the only candidate, split 1, 2, 4 or 8 ways unless
+// the factor is given: 0.30 x 1.65 us per k-step of a tile, but not less than the weights take at 5.5 TB/s.  A result plane is
+// read back by the next kernel, so a product that is split less is worth the time of that.
+GemmPlan cheapest(int m, int n, int k, int mode, int min_splits, int max_splits, bool row_mixed) {
     const int its = k / BK;
-    GemmPlan best{0, 1};
+    GemmPlan best{0, min_splits};
     double best_cost = 1e30;
     if (mode != GEMM_STORE_F32) max_splits = 1;
-    for (int s = 1; s <= max_splits; ++s) {
-        if (its % s != 0 || (s > 1 && its / s < 8)) continue;
+    for (int s = min_splits; s <= std::min(max_splits, its); ++s) {
+        if (its % s != 0 || (s > min_splits && its / s < 8)) continue;
         const double steps = (double)its / s;
         const double plane = mode == GEMM_STORE_F32 ? (double)m * n * 4.0 * s / 6e6 : 0.0;  // us to read the result
         if (m <= 64 && n % 128 == 0) {
-            if (s & (s - 1)) continue;
+            if (s > min_splits && (s & (s - 1))) continue;
             const double cost = std::max((double)ceil_div((int64_t)(n / 128) * s, 512) * steps * 0.30, (double)n * k * 2.0 / 5.5e12 / 1.65e-6) +
                                 2.0 + (double)m * n * 4.0 * s / 8e12 / 1.65e-6;
             if (cost < best_cost) { best_cost = cost; best = GemmPlan{7, s}; }
@@ -661,7 +662,10 @@ GemmPlan cheapest(int m, int n, int k, int mode, int max_splits, bool row_mixed)
             consider(3, wide_cost_of(256), b256 * cols);
             if (height < 256) consider(14, wide_cost_of(height), bands * cols);
         }
-        if (n % 192 == 0 && mode != GEMM_SWIGLU_BF16) consider(5, kCost256x192, b256 * (n / 192));
+        if (n % 192 == 0 && mode != GEMM_SWIGLU_BF16) {
+            consider(5, kCost256x192, b256 * (n / 192));
+            if (m > 256 && m <= 288 && n % 128 != 0) consider(9, kCost288x192, n / 192);
+        }
         if (n % 128 == 0) {
             const double cols = n / 128;
             consider(15, narrow_cost_of(height), bands * cols);
@@ -673,73 +677,11 @@ GemmPlan cheapest(int m, int n, int k, int mode, int max_splits, bool row_mixed)
     return best;
 }
 
-constexpr TileCost kListed128x128{512, 128, 0.955, 8.21, 0.44, 0.08, 0.7, 5.96}, kListed128x128Deep{256, 128, 0.507, 3.44, 0.7, 0.76, 0.95, 5.54},
-    kListed192x128{256, 128, 0.684, 3.9, 0.54, 2.31, 0.69, 5.38}, kListed256x128{256, 128, 0.812, 4.38, 0.62, 3.69, 0.4, 5.28},
-    kListed256x192{256, 192, 1.175, 4.32, 0.59, 0.0, 0.99, 5.07}, kListed256x256{256, 256, 1.456, 4.35, 0.52, 2.38, 0.93, 5.55},
-    kListed192x256{256, 256, 1.2, 0.47, 0.44, 7.24, 0.54, 7.46}, kListed288x192{256, 192, 1.587, 2.25, 0.68, 0.0, 1.09, 6.17};
-
-// The planner of the public operations: the tile ids 0 to 9 and split-K factors that are powers of two, with the costs above
-// (fitted to 938 products of these forms, measured with the 32x32x16 MFMAs).
-GemmPlan cheapest_listed(int m, int n, int k, int mode, int min_splits, int max_splits, bool row_mixed) {
-    const int its = k / BK;
-    GemmPlan best{0, min_splits};
-    double best_cost = 1e30;
-    if (mode != GEMM_STORE_F32) max_splits = 1;
-    for (int s = min_splits; s <= max_splits; s *= 2) {
-        if (its % s != 0 || (s > 1 && s > min_splits && its / s < 8)) continue;
-        const double steps = (double)its / s;
-        const double plane = mode == GEMM_STORE_F32 ? (double)m * n * 4.0 * s / 6e6 : 0.0;  // us to read the result
-        auto round_us = [&](const TileCost& c) { return c.step * steps + c.per_tile; };
-        // `rounds` as they count, `full` if the last one were as good as the others
-        auto consider_rounds = [&](int tile, const TileCost& c, double rounds, double full) {
-            const double work = c.fixed + rounds * round_us(c) + c.plane * plane;
-            const double loads = (double)n * k * 2e-6 * (1.0 / c.stream + 0.016 * m / c.width) * rounds / full;
-            const double cost = std::max(work, loads) + plane + 1e-3 * work;  // of two that their loads bound, the lighter one
-            if (cost < best_cost) { best_cost = cost; best = GemmPlan{tile, s}; }
-        };
-        auto consider = [&](int tile, const TileCost& c, double tiles) {
-            consider_rounds(tile, c, rounds_of(c, tiles * s), tiles * s / c.slots);
-        };
-        if (m <= 64 && n % 128 == 0) {
-            const double cost = std::max((double)ceil_div((int64_t)(n / 128) * s, 512) * steps * 0.30, (double)n * k * 2.0 / 5.5e12 / 1.65e-6) +
-                                2.0 + (double)m * n * 4.0 * s / 8e12 / 1.65e-6;
-            if (cost < best_cost) { best_cost = cost; best = GemmPlan{7, s}; }
-            continue;
-        }
-        const double b128 = (double)ceil_div(m, 128), b192 = (double)ceil_div(m, 192), b256 = (double)ceil_div(m, 256);
-        if (n % 256 == 0) {
-            const double cols = n / 256;
-            const int rr = row_mixed ? gemm_rowmix_rem_rows(m, n) : 0;
-            if (rr > 0 && m <= 384) consider(8, kListed192x256, 2 * cols);
-            else if (rr > 0) consider(8, kListed256x256, (m / 256 + (rr == 64 ? 0.6 : 0.8)) * cols);
-            if (s == 1 && gemm_mixed_rem_cols(m, n) > 0) {  // whole rounds of big tiles and one of half-width ones
-                const double tiles = b256 * cols, whole = std::floor(tiles / 256), half = rounds_of(kListed256x128, 2 * (tiles - whole * 256));
-                consider_rounds(4, kListed256x256, whole + half * round_us(kListed256x128) / round_us(kListed256x256), tiles / 256);
-            }
-            consider(3, kListed256x256, b256 * cols);
-        }
-        if (n % 192 == 0 && mode != GEMM_SWIGLU_BF16) {
-            consider(5, kListed256x192, b256 * (n / 192));
-            if (m > 256 && m <= 288) consider(9, kListed288x192, n / 192);
-        }
-        if (n % 128 == 0) {
-            const double cols = n / 128;
-            if (gemm_low_bands(m)) consider(1, kListed192x128, b192 * cols);
-            else consider(1, kListed256x128, b256 * cols);
-            consider(6, kListed128x128Deep, b128 * cols);
-            consider(0, kListed128x128, b128 * cols);
-        }
-    }
-    return best;
-}
-
 }  // namespace
 
 GemmPlan gemm_plan(int m, int n, int k, int mode, int max_splits, bool row_mixed) {
-    return cheapest(m, n, k, mode, max_splits, row_mixed);
+    return cheapest(m, n, k, mode, 1, max_splits, row_mixed);
 }
-
-GemmPlan gemm_plan_listed(int m, int n, int k, int mode, int max_splits) { return cheapest_listed(m, n, k, mode, 1, max_splits, true); }
 
 namespace {
 
@@ -770,7 +712,7 @@ hipError_t launch_gemm_bf16(const bf16_t* a, int64_t lda, const bf16_t* w, int64
     if (splits < 1 || (k / BK) % splits != 0) return hipErrorInvalidValue;
     if (splits > 1 && mode != GEMM_STORE_F32) return hipErrorInvalidValue;
     if (tile < 0) {
-        tile = cheapest_listed(m, n, k, splits == 1 ? mode : GEMM_STORE_F32, splits, splits, true).tile;
+        tile = cheapest(m, n, k, splits == 1 ? mode : GEMM_STORE_F32, splits, splits, true).tile;
     }
     if (!tile_fits(tile, m, n, mode, splits)) return hipErrorInvalidValue;
     if (tile == 9 && n % 128 == 0 && mode != GEMM_ADD_F32) tile = 13;
