@@ -574,43 +574,62 @@ int gemm_mixed_rem_cols(int m, int n) {
 namespace {
 
 // Cost of a launch of one tile shape in us, fitted to measurements on MI355X with operands streaming from HBM (weights
-// are cold in the stage; four stage shapes and two vocabularies, 65 to 4160 rows, every tile and split: 936 products):
-// fixed + rounds * (step * k_steps + per_tile) + plane * (us to read the fp32 result at 6 TB/s).  A round is one tile per
-// compute unit (two for a shape of which two share one); a last round that fills a share x of them counts
-// lone + (1 - lone) x, because fewer tiles run faster: the chip is power- and bandwidth-limited.  No launch is faster than
-// its loads: the weights at `stream` TB/s and the activations, once per tile column, at kCacheRate TB/s from the caches, both
-// slower by as much as the last round is short of tiles.
-// The picks are 0.6 % behind the best ones on average (profiles/gemm_plan_sweep.txt): as far on a run that was not fitted.
+// are cold in the stage; four stage shapes and two vocabularies, 65 to 4160 rows, every tile and split: 3036 products, forms in
+// random order, median of three runs): fixed + rounds * (step * k_steps + per_tile) + plane * (us to read the fp32 result at
+// 6 TB/s).  A round is one tile per compute unit (two for a shape of which two share one).  Rounds count between the work (tiles
+// / tiles in a round) and the span (when the last tile ends), the span with the weight `lone`: a last round that is not full
+// takes less than a whole one, because fewer tiles run faster -- the chip is power- and bandwidth-limited -- but how much less
+// depends on whether whole rounds run in front of it.  No launch is faster than its loads: the weights at `stream` TB/s and
+// the activations, once per tile column, at kCacheRate TB/s from the caches, both slower by as much as the last round is short
+// of tiles.
+// The picks are 0.37 % behind the fastest forms on average, at most 10 % (profiles/gemm_plan_sweep.txt); fitted to three quarters
+// of the products, 0.44 % and 14 % on the rest, of other row counts.  Before, with one `lone` for all and the low tiles of a
+// row-mixed launch in a round of their own: 1.2 %, at most 28 % (28672 x 4096 at 1050 rows 240 -> 192 us, 4096 x 4096 at 800
+// rows 41 -> 35).
 struct TileCost {
     int slots, width;  // tiles in a round, columns of a tile
-    double step, fixed, lone, per_tile, plane, stream;
+    double step, fixed, lone[3];  // lone: no whole round in front of the last one, one, more
+    double per_tile, plane, stream;
 };
-constexpr double kCacheRate = 154;
-constexpr TileCost kCost128x128{512, 128, 0.919, 7.22, 0.45, 0, 0.57, 6.25}, kCost128x128Deep{256, 128, 0.526, 3.35, 0.76, 0.78, 0.97, 6.29}, kCost256x192{256, 192, 1.13, 4.19, 0.66, 1.97, 0.39, 5.13},
-    kCost288x192{256, 192, 1.27, 2.6, 0.92, 2.65, 1.8, 6.2};
+constexpr double kCacheRate = 121;
+constexpr TileCost kCost128x128{512, 128, 0.867, 7.42, {0.3, 0.77, 0.26}, 2.05, 0.24, 4.61}, kCost128x128Deep{256, 128, 0.454, 3.05, {0.99, 1, 1}, 1.15, 1.55, 6.72},
+    kCost256x192{256, 192, 0.996, 6.74, {0.34, 0.82, 0.92}, 0, 1.09, 6.87}, kCost288x192{256, 192, 1.27, 2.6, {0.89, 0.94, 0.95}, 2.65, 1.8, 6.2};
 // tiles of 160, 192, 224 and 256 rows x 128 and x 256 columns, and of 288, 320, 352 and 384 rows x 128
-constexpr TileCost narrow_cost(double step) { return {256, 128, step, 4.41, 0.6, 3, 0.66, 5.27}; }
-constexpr TileCost tall_cost(double step) { return {256, 128, step, 4.85, 0.57, 2.54, 0.47, 4.34}; }
-constexpr TileCost wide_cost(double step) { return {256, 256, step, 3.38, 0.5, 2.22, 0.63, 6.33}; }
-constexpr TileCost kCostNarrow[4] = {narrow_cost(0.564), narrow_cost(0.592), narrow_cost(0.672), narrow_cost(0.745)},
-                   kCostWide[4] = {wide_cost(1.02), wide_cost(1.08), wide_cost(1.207), wide_cost(1.386)},
-                   kCostTall[4] = {tall_cost(0.888), tall_cost(0.926), tall_cost(0.961), tall_cost(1.042)};
+constexpr TileCost narrow_cost(double step) { return {256, 128, step, 3.5, {0.67, 0.86, 0.66}, 2.89, 0.58, 6.15}; }
+constexpr TileCost tall_cost(double step) { return {256, 128, step, 4.89, {0.87, 0.63, 0.17}, 1.34, 0.61, 5.73}; }
+constexpr TileCost wide_cost(double step) { return {256, 256, step, 3.5, {0.66, 0.62, 0.59}, 2.14, 0.62, 6.74}; }
+constexpr TileCost kCostNarrow[4] = {narrow_cost(0.594), narrow_cost(0.641), narrow_cost(0.746), narrow_cost(0.759)},
+                   kCostWide[4] = {wide_cost(1.021), wide_cost(1.117), wide_cost(1.296), wide_cost(1.37)},
+                   kCostTall[4] = {tall_cost(0.874), tall_cost(0.902), tall_cost(0.943), tall_cost(1.113)};
 const TileCost& narrow_cost_of(int height) { return kCostNarrow[(height - 160) / 32]; }
 const TileCost& wide_cost_of(int height) { return kCostWide[(height - 160) / 32]; }
 
-// Rounds that `tiles` tiles count as, where a round has c.slots of them.
-double rounds_of(const TileCost& c, double tiles) {
-    const double full = std::floor(tiles / c.slots + 1e-9), rest = tiles / c.slots - full;
-    return full + (rest > 1e-9 ? c.lone + (1.0 - c.lone) * rest : 0.0);
+// Rounds that a launch counts as: `work` of them are filled, its last tile ends after `span`.
+double counted_rounds(const TileCost& c, double span, double work) {
+    const double lone = c.lone[std::min((int)(work + 1e-9), 2)];
+    return lone * span + (1.0 - lone) * work;
 }
+double rounds_of(const TileCost& c, double tiles) { return counted_rounds(c, std::ceil(tiles / c.slots - 1e-9), tiles / c.slots); }
 
-// The same for a row-mixed launch: `big` tiles of 256 rows, then `low` tiles of the last band, which count 0.75 of one each.
-constexpr double kLowTile = 0.75;
-double rounds_of_rowmix(const TileCost& c, double big, double low) {
-    const double full = std::floor(big / c.slots), rest = big - full * c.slots;
-    if (rest <= 0) return full + kLowTile * rounds_of(c, low);
-    const double beside = std::min(low, c.slots - rest);  // low tiles in the round of the last big ones
-    return full + c.lone + (1.0 - c.lone) * (rest + kLowTile * beside) / c.slots + kLowTile * rounds_of(c, low - beside);
+// The same for a row-mixed launch: `big` tiles of 256 rows, then `low` tiles of the last band, which take kLowShare of a big
+// one's time each (of 64 and of 128 rows alike: fitted one by one 0.78 and 0.75) and start as compute units become free.
+constexpr double kLowShare = 0.75;
+double rowmix_span(double big, double low) {
+    const double full = std::floor(big / 256), rest = big - full * 256, free = 256 - rest;  // compute units free after `full` rounds
+    double early = 0, late = 1;  // since then: when the free units end their next tile, and the others
+    double end = rest > 0 ? 1 : 0;
+    while (low > 0) {
+        if (rest == 0 || early <= late) {
+            early += kLowShare;
+            low -= free;
+            end = std::max(end, early);
+        } else {
+            late += kLowShare;
+            low -= rest;
+            end = std::max(end, late);
+        }
+    }
+    return full + end;
 }
 
 // Tile shape and split-K factor (a divisor of the k-steps from min_splits to max_splits) of the lowest cost.  Up to 64 rows the
@@ -650,8 +669,9 @@ GemmPlan cheapest(int m, int n, int k, int mode, int min_splits, int max_splits,
         if (n % 256 == 0) {
             const double cols = n / 256;
             if (row_mixed && m > 384 && gemm_rowmix_rem_rows(m, n) > 0) {
-                const double big = (double)(m / 256) * cols * s, low = cols * s;
-                consider_rounds(8, wide_cost_of(256), rounds_of_rowmix(wide_cost_of(256), big, low), (big + kLowTile * low) / 256);
+                const TileCost& c = wide_cost_of(256);
+                const double big = (double)(m / 256) * cols * s, low = cols * s, work = (big + kLowShare * low) / c.slots;
+                consider_rounds(8, c, counted_rounds(c, rowmix_span(big, low), work), work);
             }
             if (s == 1 && gemm_mixed_rem_cols(m, n) > 0) {  // whole rounds of big tiles and one of half-width ones
                 const int h = mode == GEMM_ADD_F32 ? 256 : band_height(m, (int)b256);
@@ -669,6 +689,9 @@ GemmPlan cheapest(int m, int n, int k, int mode, int min_splits, int max_splits,
         if (n % 128 == 0) {
             const double cols = n / 128;
             consider(15, narrow_cost_of(height), bands * cols);
+            // as few bands as cover the rows, where those of equal height are one more (600 rows of 5120 x 5120: 47 -> 41 us)
+            const int h1 = gemm_low_bands(m) ? 192 : 256;
+            if (h1 != height) consider(1, narrow_cost_of(h1), (double)ceil_div(m, h1) * cols);
             if (m > 256 && m <= 384 && mode != GEMM_ADD_F32) consider(13, kCostTall[(m - 257) / 32], cols);
             consider(6, kCost128x128Deep, b128 * cols);
             consider(0, kCost128x128, b128 * cols);
