@@ -185,6 +185,18 @@ bool own_pages(gllm_stage* s, const gllm_batch* b) {
     return seen == b->num_seqs;  // (a page with two writers is seen twice and counts four)
 }
 
+// Whether own_pages is worth its time on the host, 0.24 ns a page table entry: the first RMSNorm and QKV product hide 12 us of
+// it and as long as that product streams its weights or multiplies, and RoPE and KV write inside attention save 5 us a layer
+// and the passes over the QKV result.  Calls that are waited for, us, RoPE in front / inside: one KV head of 64, 512 rows of
+// 1024 keys, two layers (33k entries) 179 / 170, of 4096 keys (131k) 356 / 361, of 8191 keys, one layer (262k) 366 / 405; 14B
+// shape, of 4096 keys, two layers 3448 / 3378, of 8191 keys, one layer 3110 / 3094.
+bool worth_looking_through(const gllm_stage* s, int64_t entries, int64_t tokens) {
+    const double nk = (double)s->n_qkv_pad * s->cfg.hidden;
+    const double hidden_us = 12.0 + std::max(2.0 * nk / 6e6, 2.0 * nk * tokens / 1e9);
+    const double saved_us = (5.0 + 8.0 * s->n_qkv_pad * tokens / 5e6) * (s->layer_end - s->layer_begin);
+    return entries * 0.24e-3 <= hidden_us + saved_us;
+}
+
 hipEvent_t get_event(gllm_stage* s) {
     if (!s->ev_pool.empty()) {
         hipEvent_t e = s->ev_pool.back();
@@ -703,7 +715,8 @@ gllm_status gllm_stage_forward(gllm_stage* s, const gllm_batch* b, const void* h
                                         plan_qkv.splits, qkv_plane, st));
         }
         // (found out here, while the first kernels already run)
-        if (l == s->layer_begin) from_qkv = n_pre == 0 && own_pages(s, b);
+        if (l == s->layer_begin)
+            from_qkv = n_pre == 0 && worth_looking_through(s, total_pages, T) && own_pages(s, b);
         RopeKvArgs ra{};
         ra.qkv = s->qkv; ra.ld_qkv = s->n_qkv_pad; ra.planes = plan_qkv.splits; ra.plane_stride = qkv_plane;
         ra.bias = c.has_qkv_bias ? L.bias : nullptr;

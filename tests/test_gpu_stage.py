@@ -615,6 +615,32 @@ def test_decode_row_whose_new_token_another_sequence_reads():
     assert np.abs(ref[1] - r["ref"][1]).max() > 4 * np.abs(r["out32"][1] - r["ref"][1]).max()
 
 
+@pytest.mark.parametrize("pages,inside", [(780, True), (790, False)])
+def test_decode_batches_with_many_page_table_entries(pages, inside):
+    """91 decode rows that share all pages but their last: at 780 pages a row RoPE and KV write are part of the attention launch,
+    with ten pages more the entries are too many to look through on the host and the two come first.  Same results."""
+    print(f"decode rows with {91 * pages} page table entries", flush=True)
+    rows, shape = 91, synth.StageShape("entries", 1, 256, 4, 1, 64, 384)
+    bt = np.empty((rows, pages), dtype=np.int32)
+    bt[:, :-1] = np.random.default_rng(3).permutation(pages - 1)
+    bt[:, -1] = pages - 1 + np.arange(rows)
+    cached = (pages - 1) * 16 + np.arange(rows, dtype=np.int32) % 16
+    batch = synth.Batch(np.ones(rows, dtype=np.int32), cached.astype(np.int32), bt, pages + rows)
+    w = layer_weights_np(shape, 35)
+    kp0, vp0 = pool_np(shape, 35, batch.num_blocks)
+    r = run_both(shape, w, batch, kp0, vp0, hidden_np(shape, 35, rows))
+    assert_output(f"{91 * pages} entries", r, literal=False)
+    mk, mv = written_mask(shape, batch)
+    check_pool("K", r["gk"], kp0, r["kp"], mask=mk)
+    check_pool("V", r["gv"], vp0, r["vp"], mask=mv)
+    stage = r["stage"].stage
+    stage.set_profiling(True)
+    r["stage"].run(batch, to_dev_bits(kp0), to_dev_bits(vp0), to_dev_bits(hidden_np(shape, 35, rows)))
+    launches = {k: n for k, (_, n) in stage.read_profile().items()}
+    stage.set_profiling(False)
+    assert launches["rope_kv_write"] == (0 if inside else 1) and launches["attn_decode"] == 1, launches
+
+
 @pytest.mark.parametrize("n_kv,d", [(16, 64), (8, 128), (4, 64), (2, 128)])
 def test_chunks_of_many_workgroups_match_the_oracle(n_kv, d):
     """More prefill workgroups than compute units: items of 128 rows x heads instead of the halves that smaller batches take, for
