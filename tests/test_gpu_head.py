@@ -117,9 +117,14 @@ def test_greedy_and_its_equivalents_are_exact():
 
 def check_against_oracle(lg, temp, k, p, u, label, slack=2):
     """lg: float32 [M, V] on the host.  Every GPU token must be a kept token whose interval of the running sum
-    contains u within 1e-4; all but `slack` must equal the oracle's."""
+    contains u within 1e-4; all but `slack` must equal the oracle's.  The rows repeated until they are more than there are
+    compute units (two share one then, with half the registers and loads) give the same tokens."""
     M, V = lg.shape
-    got = run_sampler(lg.to(DEV), V, temp.tolist(), k.tolist(), p.tolist(), u.tolist())
+    d = lg.to(DEV)
+    got = run_sampler(d, V, temp.tolist(), k.tolist(), p.tolist(), u.tolist())
+    times = 256 // M + 1
+    many = run_sampler(d.repeat(times, 1), V, *(np.tile(x, times).tolist() for x in (temp, k, p, u)))
+    assert np.array_equal(many, np.tile(got, times)), np.argwhere(many != np.tile(got, times))[:5]
     same = 0
     for i in range(M):
         row = lg[i].numpy()
@@ -230,7 +235,8 @@ def test_rows_without_a_finite_softmax_go_to_their_largest_logit(V, k, p):
 @pytest.mark.parametrize("V", [4096, 16384, 16388, 28672, 32772, 36864 + 4092, 65536 - 4, 65536 + 12292])
 def test_sampler_reads_every_block_of_a_row(V):
     """Vocabularies around multiples of the blocks that are loaded together, few rows (a compute unit each) and many (two share
-    one): the largest logit is found in each of the last places, and the k largest tokens are drawn wherever they lie."""
+    one): the largest logit is found in each of the last places, and of equal masses in all these places each is drawn by its
+    share of u, so that none is dropped or counted twice."""
     print(f"sampler: blocks, V={V}", flush=True)
     places = sorted({0, V // 2, *[max(0, V - 1 - d) for d in (0, 3, 4, 4095, 4096, 8192, 16384)]})
     for M in (len(places), 260):
@@ -240,4 +246,10 @@ def test_sampler_reads_every_block_of_a_row(V):
         d = lg.to(DEV)
         u = np.linspace(0.0, 0.999, M).tolist()
         for temp, k, p in ((0.0, 0, 1.0), (0.8, 5, 1.0), (0.8, 0, 0.95), (1.0, 50, 0.9)):   # all mass on one token (weight of the rest < 1e-12)
+            assert np.array_equal(run_sampler(d, V, [temp] * M, [k] * M, [p] * M, u), at), (V, M, temp, k, p)
+        n = len(places)
+        lg[:, torch.tensor(places)] = 40.0
+        d = lg.to(DEV)
+        u = [(i % n + 0.5) / n for i in range(M)]                                          # the middle of each place's share
+        for temp, k, p in ((0.8, n, 1.0), (0.8, 0, 1.0), (0.8, 0, 0.95), (1.0, 50, 0.9)):  # (equal masses stay together in a nucleus)
             assert np.array_equal(run_sampler(d, V, [temp] * M, [k] * M, [p] * M, u), at), (V, M, temp, k, p)

@@ -472,3 +472,23 @@ def test_gemm_band_heights_at_their_edges(tile, N, rows, K):
         slack = np.abs(want) * 2.0 ** -8 * 1.01 + 1.1 * np.abs(u) * bound[:, :N // 2] + np.abs(g) * bound[:, N // 2:] + 1e-30
         got = act.float().cpu().numpy().astype(np.float64)
         assert np.all(np.abs(got[:M] - want) <= slack) and np.all(got[M:] == 7.0), (tile, K, M)
+
+
+@pytest.mark.parametrize("splits,K", [(3, 384), (5, 640), (6, 1152), (7, 448)])
+def test_gemm_splits_that_are_no_powers_of_two(splits, K):
+    """Every plane of a split product holds the product over its share of k, in bands of equal height, one band of 257..384 rows
+    and the 128-row tiles: K/splits roundings of 2^-24 of the sum of magnitudes."""
+    N, part = 512, K // splits
+    w = rand_bits(16, 2, (N, K), 0.05)
+    y, dw = oracle.bf16_to_f64(w), to_dev_weight(w)
+    for M, tiles in ((193, (0, 6, 14, 15)), (289, (13, 14, 15)), (600, (8, 14, 15))):
+        a = rand_bits(16, M, (M, K), 1.0)
+        x, da = oracle.bf16_to_f64(a), to_dev_bits(padded_rows(a, M + 64))
+        for tile in tiles:
+            print(f"gemm splits={splits} M={M} tile={tile}", flush=True)
+            out = torch.full((splits, M, N), 7.0, dtype=torch.float32, device=DEV)
+            B.gllm_op_gemm_bf16_splitk(da, dw, out, M, N, K, tile, splits)
+            torch.cuda.synchronize()
+            for s in range(splits):
+                xs, ys = x[:, s * part:(s + 1) * part], y[:, s * part:(s + 1) * part]
+                assert np.all(np.abs(out[s].cpu().numpy() - xs @ ys.T) <= (np.abs(xs) @ np.abs(ys).T) * part * 2.0 ** -24), (splits, M, tile, s)

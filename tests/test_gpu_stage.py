@@ -594,6 +594,27 @@ def test_batches_of_decode_rows_at_page_block_and_partition_edges(n_q, n_kv, d, 
     check_pool("V", r["gv"], vp0, r["vp"], shape.num_layers, mask=mv)
 
 
+@pytest.mark.parametrize("hidden,planes", [(1536, 3), (2560, 5), (3072, 6), (3584, 7)])
+def test_plane_counts_that_are_no_powers_of_two(hidden, planes):
+    """QKV and down projections split 3, 5, 6 and 7 ways: the planes are summed by RoPE and KV write (with bias; V runs at page
+    edges), by decode attention in a batch of decode rows, by RMSNorm of the second layer and by the last cast."""
+    print(f"{planes} planes: hidden {hidden}", flush=True)
+    shape = synth.StageShape("planes", 2, hidden, 4, 1, 128, hidden, has_qkv_bias=True)
+    chunks = [(2, 15), (16, 16), (17, 32), (18, 15), (5, 3), (1, 15), (1, 16), (1, 0), (33, 0), (31, 17)]
+    batches = [synth.build_batch(chunks, 51, spare_blocks=3), synth.build_batch([(1, c) for c in 4 * DECODE_EDGES], 52, spare_blocks=3)]
+    w = layer_weights_np(shape, 51)
+    stage = GpuStage(shape, w, batches)
+    for batch in batches:
+        T = batch.num_tokens
+        assert B.gllm_op_gemm_plan(T, 768, hidden, 0, 8)[1] == planes and B.gllm_op_gemm_plan(T, hidden, hidden, 0, 8)[1] == planes
+        kp0, vp0 = sentinel_pool_with_prefixes(shape, batch, 51)
+        r = run_both(shape, w, batch, kp0, vp0, hidden_np(shape, 51, T), stage)
+        assert_output(f"{planes} planes, {T} rows", r, literal=False)
+        mk, mv = written_mask(shape, batch)
+        check_pool("K", r["gk"], kp0, r["kp"], shape.num_layers, mask=mk)
+        check_pool("V", r["gv"], vp0, r["vp"], shape.num_layers, mask=mv)
+
+
 def test_decode_row_whose_new_token_another_sequence_reads():
     """A page that receives a token of one decode row lies in the cached prefix of another: that row sees the new token, as
     everywhere (keys and values are read after all of them have been written)."""
