@@ -13,8 +13,9 @@
 // the same order of loads took 99.3 -> 90.6 us for gate/up at 512 rows (28672 x 4096), 859 -> 833 at 2048 rows of 55296 x
 // 5120, 387 -> 378 at 4096x8192x8192 (1455 TFLOP/s); where the weights' stream bounds a product there is no difference (64
 // rows).  Four waves with a wave tile of 128x128 read LDS two thirds as often per MFMA as eight of 128x64, and the order of
-// MFMAs, LDS reads and global loads is written out (see step): in the k-loop of a 256x256 tile the matrix cores are busy for
-// 0.92 of the time, at 1.6 to 1.7 GHz (a bare MFMA loop 1.0 at 1.68).
+// MFMAs, LDS reads and global loads is written out (see step): over whole launches of 256x256 tiles the matrix cores are busy
+// for 0.67 to 0.74 of the time at 1.8 to 2.0 GHz (profiles/stage_*_mfma_counters.txt; a bare MFMA loop 1.0 at 1.68).  Where
+// tiles fill a part of the chip, power is no limit and the smaller MFMAs cost up to 5 % (5184 x 4096, 257 rows 56.4 -> 59.2).
 //
 // LDS stage layout: rows of 64 k-values (128 bytes = eight 16-byte groups), A rows first, then W
 // rows.  Two consecutive rows form a 256-byte line of 16 group positions (the width of the 64 LDS
@@ -199,7 +200,7 @@ __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ A, int64_t 
         // multiplied.  LDS -> registers: the fragments of k-step kk+1 are fetched while k-step kk is multiplied, also
         // across the tile boundary: the barrier sits before the last k-step of a tile, after which the next tile's
         // first fragments are fetched under the MFMAs of that last k-step.  The loads into the stages vacated at that
-        // barrier are issued in four parts, one per k-step from there on (part 0 behind the barrier, part q + 1 in
+        // barrier are issued in KK parts, one per k-step from there on (part 0 behind the barrier, part q + 1 in
         // k-step q of the next tile), A before W: a load instruction keeps the address unit busy for 16 cycles, and all
         // of them at once stall every wave behind the barrier for longer than the MFMAs of one k-step last.
         // Every iteration issues the same number of loads (see issue), so the wait counts are compile-time constants.
@@ -427,6 +428,8 @@ int gemm_band_height(int m, int mode) {
 // last round is a long tail (128256 x 4096, 64 rows: the first tiles end between 62 and 91 us, so between 77 and 82).
 // 128256 x 4096: one row 157 -> 153 us, 32 rows 178 -> 170, 64 rows 199 -> 179; 128256 x 8192, 64 rows 355 -> 338.  Where the
 // last round is short the tiles had better end at different times (152064 x 8192, 0.3 of a round left, 64 rows: 433 and 453).
+// Two against three stages of A at 1.06 to 4 rounds, k of 4096, 5120 and 8192, one to 64 rows: a full last round takes 0.96 to
+// 1.0 of the time, 0.75 and 0.88 of one 0.85 to 1.0, 0.62 of one 0.95 to 0.99, half of one 0.98 to 1.12, a quarter 0.95 to 1.15.
 constexpr int kSkinnySlots = 512;  // tiles that run at one time, two per compute unit
 template <int MODE, int H>
 hipError_t launch_skinny(const bf16_t* a, int64_t lda, const bf16_t* w, int64_t ldw, void* out, int64_t ldc, int m,
