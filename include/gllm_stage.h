@@ -174,7 +174,8 @@ gllm_status gllm_stage_forward(gllm_stage* stage, const gllm_batch* batch /*HOST
 /* Per-kernel timing.  With profiling on, forward() brackets every kernel with HIP events on
  * the caller's stream; gllm_stage_read_profile() synchronises those events and adds their
  * durations to per-class totals.  Classes are listed by gllm_profile_class_name(i) for
- * i in [0, gllm_profile_num_classes()).  ms and launches are HOST arrays of that length. */
+ * i in [0, gllm_profile_num_classes()).  ms and launches are HOST arrays of that length.  In a batch of decode rows RoPE and
+ * KV write may be part of the attention launch: attn_decode then counts both, rope_kv_write none. */
 gllm_status gllm_stage_set_profiling(gllm_stage* stage, int32_t on);
 gllm_status gllm_stage_read_profile(gllm_stage* stage, double* ms /*HOST*/, int64_t* launches /*HOST*/, int32_t reset);
 int32_t gllm_profile_num_classes(void);

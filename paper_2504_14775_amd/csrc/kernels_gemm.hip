@@ -609,7 +609,7 @@ const TileCost& wide_cost_of(int height) { return kCostWide[(height - 160) / 32]
 
 // Rounds that a launch counts as: `work` of them are filled, its last tile ends after `span`.
 double counted_rounds(const TileCost& c, double span, double work) {
-    const double lone = c.lone[std::min((int)(work + 1e-9), 2)];
+    const double lone = c.lone[(int)std::min(work + 1e-9, 2.0)];
     return lone * span + (1.0 - lone) * work;
 }
 double rounds_of(const TileCost& c, double tiles) { return counted_rounds(c, std::ceil(tiles / c.slots - 1e-9), tiles / c.slots); }
@@ -621,6 +621,8 @@ double rowmix_span(double big, double low) {
     const double full = std::floor(big / 256), rest = big - full * 256, free = 256 - rest;  // compute units free after `full` rounds
     double early = 0, late = 1;  // since then: when the free units end their next tile, and the others
     double end = rest > 0 ? 1 : 0;
+    const double later = std::max(0.0, std::floor(low / 256) - 2);  // once all units take low tiles, 256 of them end every kLowShare
+    low -= later * 256;
     while (low > 0) {
         if (rest == 0 || early <= late) {
             early += kLowShare;
@@ -632,7 +634,7 @@ double rowmix_span(double big, double low) {
             end = std::max(end, late);
         }
     }
-    return full + end;
+    return full + end + later * kLowShare;
 }
 
 // Tile shape and split-K factor (a divisor of the k-steps from min_splits to max_splits) of the lowest cost.  Up to 64 rows the
@@ -645,8 +647,8 @@ GemmPlan cheapest(int m, int n, int k, int mode, int min_splits, int max_splits,
     GemmPlan best{0, min_splits};
     double best_cost = 1e30;
     if (mode != GEMM_STORE_F32) max_splits = 1;
-    for (int s = min_splits; s <= std::min(max_splits, its); ++s) {
-        if (its % s != 0 || (s > min_splits && its / s < 8)) continue;
+    for (int s = min_splits; s <= std::max(min_splits, std::min(max_splits, its / 8)); ++s) {  // (at least 8 k-steps a share)
+        if (its % s != 0) continue;
         const double steps = (double)its / s;
         const double plane = mode == GEMM_STORE_F32 ? (double)m * n * 4.0 * s / 6e6 : 0.0;  // us to read the result
         if (m <= 64 && n % 128 == 0) {

@@ -1,6 +1,7 @@
 """The C-ABI library loads and exports every function include/gllm_stage.h declares (no GPU needed)."""
 import os
 import re
+import time
 
 import pytest
 
@@ -107,6 +108,16 @@ def test_gemm_planner_choices_are_launchable():
     assert B.gllm_op_gemm_plan(257, 20160, 4096, 0, 1) == (5, 1) and B.gllm_op_gemm_plan(257, 24768, 4096, 0, 1) == (9, 1)
     with pytest.raises(B.GllmError):
         B.gllm_op_gemm_plan(128, 100, 4096, 0, 8)
+
+
+def test_gemm_planner_ends_on_the_largest_problems():
+    """Tiles are counted, not walked through, whatever the sizes: a short last band (row-mixed launch) over millions of columns,
+    any number of splits allowed."""
+    t = time.perf_counter()
+    for m, n, k in ((2 ** 20 + 1, 2 ** 30, 2 ** 20), (513, 2 ** 31 - 256, 2 ** 31 - 64), (2 ** 31 - 1, 256, 64)):
+        tile, splits = B.gllm_op_gemm_plan(m, n, k, 0, 2 ** 31 - 1)
+        assert tile >= 0 and (k // 64) % splits == 0, (m, n, k)
+    assert time.perf_counter() - t < 5.0
 
 
 # us per product on MI355X with cold weights (median of three runs, forms in random order), of the (tile, splits) that come
