@@ -15,7 +15,7 @@ pytestmark = pytest.mark.gpu
 
 
 def test_static_scratch_projection_equals_the_workspace_one_on_consecutive_calls():
-    H, V, T = 4096, 32256, 700          # 32256 = 42 * 768: the 288 x 192 tile applies at 270 rows
+    H, V, T = 4096, 32256, 700          # 252 columns of 128: one band of 288 rows at 270 rows
     print(f"no-alloc logits H={H} V={V}", flush=True)
     gain = synth.bf16_bits(synth.normal_bf16(7, 1, 0, H, 0.1, 1.0))
     w = synth.normal_bf16(7, 2, 0, V * H, 0.02, 0.0, device=DEV).view(V, H)
@@ -26,7 +26,7 @@ def test_static_scratch_projection_equals_the_workspace_one_on_consecutive_calls
     ref_head.load(to_dev_bits(gain), w)
     head.load(to_dev_bits(gain), w)
     assert int(head.lib.gllm_head_static_scratch_bytes()) == 8 << 20
-    for M in (600, 37, 270):                                      # a big call, a smaller one after it, the 288-row tile
+    for M in (600, 37, 270):                                      # a big call, a smaller one after it, one band of 288 rows
         rows = torch.from_numpy(rng.integers(0, T, size=M).astype(np.int32)).to(DEV)
         want = torch.full((M, ref_head.padded_vocab), float("nan"), dtype=torch.float32, device=DEV)
         got = torch.full((M, head.padded_vocab), float("nan"), dtype=torch.float32, device=DEV)
