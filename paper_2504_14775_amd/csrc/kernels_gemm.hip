@@ -423,23 +423,35 @@ int gemm_band_height(int m, int mode) {
     return round_up(m, h1) < round_up(m, h0) ? h1 : h0;
 }
 
-// Tiles of H rows (32 or 64) x 128, three LDS stages of both operands, or two of A and three of W where the tiles run in
-// several rounds of which the last is nearly full: with more loads in flight some compute units run ahead of others and the
+// Up to 64 rows: tiles of H rows (32 or 64) x COLS columns (128 or 64, see skinny_columns).  Up to 256 of them have a compute
+// unit each and keep more loads in flight (four LDS stages, six of 32x64; 128-column tiles against three: 0.97 of the time at
+// up to 32 rows, 0.97 at 33 to 64); from there two tiles or more share a compute unit, and three stages (four of 64 columns) let
+// as many in (deeper 128-column tiles at 432 and 448 tiles 1.02, 64-column ones 1.01 to 1.04).  In several rounds of which
+// the last is nearly full two stages of A and three of W: with more loads in flight some compute units run ahead of others and the
 // last round is a long tail (128256 x 4096, 64 rows: the first tiles end between 62 and 91 us, so between 77 and 82).
 // 128256 x 4096: one row 157 -> 153 us, 32 rows 178 -> 170, 64 rows 199 -> 179; 128256 x 8192, 64 rows 355 -> 338.  Where the
 // last round is short the tiles had better end at different times (152064 x 8192, 0.3 of a round left, 64 rows: 433 and 453).
 // Two against three stages of A at 1.06 to 4 rounds, k of 4096, 5120 and 8192, one to 64 rows: a full last round takes 0.96 to
 // 1.0 of the time, 0.75 and 0.88 of one 0.85 to 1.0, 0.62 of one 0.95 to 0.99, half of one 0.98 to 1.12, a quarter 0.95 to 1.15.
-constexpr int kSkinnySlots = 512;  // tiles that run at one time, two per compute unit
-template <int MODE, int H>
+constexpr int kSkinnySlots = 512;  // 128-column tiles of three stages that run at one time, two per compute unit
+template <int MODE, int H, int COLS>
 hipError_t launch_skinny(const bf16_t* a, int64_t lda, const bf16_t* w, int64_t ldw, void* out, int64_t ldc, int m,
                          int n, int k, int splits, int64_t split_stride, hipStream_t stream) {
-    constexpr int WM = H == 32 ? 1 : 2;  // waves along the rows
-    const int64_t tiles = (int64_t)(n / 128) * splits, last = tiles % kSkinnySlots;
-    if (tiles > kSkinnySlots && (last == 0 || last >= kSkinnySlots * 3 / 4))
-        return launch_tile_w<H, 128, WM, 4 / WM, MODE, 2, 3, true>(a, lda, w, ldw, out, ldc, m, n, k, splits, split_stride, stream);
-    return launch_tile_w<H, 128, WM, 4 / WM, MODE, 3, 3, true>(a, lda, w, ldw, out, ldc, m, n, k, splits, split_stride, stream);
+    constexpr int WM = H == 32 && COLS == 128 ? 1 : 2;  // waves along the rows
+    const int64_t tiles = (int64_t)(n / COLS) * splits, last = tiles % kSkinnySlots;
+    if constexpr (COLS == 64) {
+        if constexpr (H == 32) {
+            if (tiles <= 256) return launch_tile_w<H, COLS, WM, 4 / WM, MODE, 6, 6, true>(a, lda, w, ldw, out, ldc, m, n, k, splits, split_stride, stream);
+        }
+        return launch_tile_w<H, COLS, WM, 4 / WM, MODE, 4, 4, true>(a, lda, w, ldw, out, ldc, m, n, k, splits, split_stride, stream);
+    } else {
+        if (tiles <= 256) return launch_tile_w<H, COLS, WM, 4 / WM, MODE, 4, 4, true>(a, lda, w, ldw, out, ldc, m, n, k, splits, split_stride, stream);
+        if (tiles > kSkinnySlots && (last == 0 || last >= kSkinnySlots * 3 / 4))
+            return launch_tile_w<H, COLS, WM, 4 / WM, MODE, 2, 3, true>(a, lda, w, ldw, out, ldc, m, n, k, splits, split_stride, stream);
+        return launch_tile_w<H, COLS, WM, 4 / WM, MODE, 3, 3, true>(a, lda, w, ldw, out, ldc, m, n, k, splits, split_stride, stream);
+    }
 }
+int skinny_columns(int m, int n, int k, int mode, int splits);
 
 template <int MODE>
 hipError_t launch_mode(const bf16_t* a, int64_t lda, const bf16_t* w, int64_t ldw, void* out, int64_t ldc, int m,
@@ -469,8 +481,12 @@ hipError_t launch_mode(const bf16_t* a, int64_t lda, const bf16_t* w, int64_t ld
         case 2: case 3: case 10: return launch_tile<256, 256, 2, 2, MODE, 2, 3>(GLLM_TILE_ARGS);
         case 6: return launch_tile<128, 128, 2, 2, MODE, 4>(GLLM_TILE_ARGS);
         case 7:  // (up to 32 rows half the activations to load and to read from LDS: one row of the 8B shape 785 -> 770 us)
-            if (m <= 32) return launch_skinny<MODE, 32>(GLLM_TILE_ARGS);
-            if (m <= 64) return launch_skinny<MODE, 64>(GLLM_TILE_ARGS);
+            if constexpr (MODE == GEMM_STORE_F32) {
+                if (m <= 64 && skinny_columns(m, n, k, MODE, splits) == 64)
+                    return m <= 32 ? launch_skinny<MODE, 32, 64>(GLLM_TILE_ARGS) : launch_skinny<MODE, 64, 64>(GLLM_TILE_ARGS);
+            }
+            if (m <= 32) return launch_skinny<MODE, 32, 128>(GLLM_TILE_ARGS);
+            if (m <= 64) return launch_skinny<MODE, 64, 128>(GLLM_TILE_ARGS);
             return launch_tile_w<64, 128, 2, 2, MODE, 3, 3, false>(GLLM_TILE_ARGS);
         case 13:  // one band of 257..384 rows
             if constexpr (MODE != GEMM_ADD_F32) {
@@ -637,11 +653,36 @@ double rowmix_span(double big, double low) {
     return full + end + later * kLowShare;
 }
 
+// us of a launch whose rounds count as `rounds` and would be `full` if the last one were as good as the others.
+double launch_us(const TileCost& c, int m, int n, int k, double steps, double plane, double rounds, double full) {
+    const double work = c.fixed + rounds * (c.step * steps + c.per_tile) + c.plane * plane;
+    const double loads = (double)n * k * 2e-6 * (1.0 / c.stream + m / (kCacheRate * c.width)) * rounds / full;
+    return std::max(work, loads) + plane + 1e-3 * work;  // of two that their loads bound, the lighter one
+}
+double plane_us(int m, int n, int mode, int splits) { return mode == GEMM_STORE_F32 ? (double)m * n * 4.0 * splits / 6e6 : 0.0; }
+
+// Up to 64 rows: tiles of 128 or 64 columns, a round of one per compute unit (a second one on it halves the pace of both), so
+// that the tiles should come to just under a multiple of 256: 40 x 6 for 5120 x 27648, not 40 x 8 (64 rows 62.3 -> 46.1 us), 64
+// x 4 of half the width for 4096 x 4096, not 32 x 8 (64 rows 11.1 -> 9.2, one row 8.0 -> 7.1: half the planes too).  Fitted to
+// products of 1024 to 12288 columns and k of 1024 to 28672, and the vocabularies, at 1 to 64 rows (721, every factor and width):
+// 0.44 % behind the fastest form on average, more than 5 % in 18, 14 % at most (12288 x 8192, one row); fitted to three quarters
+// 0.53 % on the rest.  Factors of 1, 2, 4 and 8 and 128 columns alone took 1.095 times as long.
+constexpr TileCost kCostSkinny128[2] = {{256, 128, 0.544, 2.756, {0.374, 0.449, 1}, 0.646, 2.319, 7.97}, {256, 128, 0.556, 3.181, {0.536, 0.648, 1}, 0.091, 1.997, 7.789}},
+                   kCostSkinny64[2] = {{256, 64, 0.29, 2.625, {0.467, 0.414, 0.618}, 0.166, 3.244, 9}, {256, 64, 0.319, 2.257, {0.856, 0.629, 0.616}, 0, 3.343, 9}};
+double skinny_us(const TileCost& c, int m, int n, int k, int mode, int splits) {
+    const double tiles = (double)(n / c.width) * splits;
+    return launch_us(c, m, n, k, (double)(k / BK) / splits, plane_us(m, n, mode, splits), rounds_of(c, tiles), tiles / c.slots);
+}
+
+// 64 or 128: the columns of tile 7 up to 64 rows (n a multiple of 128).
+int skinny_columns(int m, int n, int k, int mode, int splits) {
+    const int h = m > 32;
+    return mode == GEMM_STORE_F32 && skinny_us(kCostSkinny64[h], m, n, k, mode, splits) < skinny_us(kCostSkinny128[h], m, n, k, mode, splits) ? 64 : 128;
+}
+
 // Tile shape and split-K factor (a divisor of the k-steps from min_splits to max_splits) of the lowest cost.  Up to 64 rows the
-// product is a stream of the weights and tile 7 (64x128, up to 32 rows 32x128: two workgroups per compute unit, 64 KiB of
-// weights in flight on each, half the activation traffic of a 128-row tile) the only candidate, split 1, 2, 4 or 8 ways unless
-// the factor is given: 0.30 x 1.65 us per k-step of a tile, but not less than the weights take at 5.5 TB/s.  A result plane is
-// read back by the next kernel, so a product that is split less is worth the time of that.
+// product is a stream of the weights and tile 7 the only candidate.  A result plane is read back by the next kernel, so a product that is
+// split less is worth the time of that.
 GemmPlan cheapest(int m, int n, int k, int mode, int min_splits, int max_splits, bool row_mixed) {
     const int its = k / BK;
     GemmPlan best{0, min_splits};
@@ -650,20 +691,16 @@ GemmPlan cheapest(int m, int n, int k, int mode, int min_splits, int max_splits,
     for (int s = min_splits; s <= std::max(min_splits, std::min(max_splits, its / 8)); ++s) {  // (at least 8 k-steps a share)
         if (its % s != 0) continue;
         const double steps = (double)its / s;
-        const double plane = mode == GEMM_STORE_F32 ? (double)m * n * 4.0 * s / 6e6 : 0.0;  // us to read the result
+        const double plane = plane_us(m, n, mode, s);
         if (m <= 64 && n % 128 == 0) {
-            if (s > min_splits && (s & (s - 1))) continue;
-            const double cost = std::max((double)ceil_div((int64_t)(n / 128) * s, 512) * steps * 0.30, (double)n * k * 2.0 / 5.5e12 / 1.65e-6) +
-                                2.0 + (double)m * n * 4.0 * s / 8e12 / 1.65e-6;
+            const double cost = skinny_us(skinny_columns(m, n, k, mode, s) == 64 ? kCostSkinny64[m > 32] : kCostSkinny128[m > 32], m, n, k, mode, s);
             if (cost < best_cost) { best_cost = cost; best = GemmPlan{7, s}; }
             continue;
         }
         auto round_us = [&](const TileCost& c) { return c.step * steps + c.per_tile; };
         // `rounds` as they count, `full` if the last one were as good as the others
         auto consider_rounds = [&](int tile, const TileCost& c, double rounds, double full) {
-            const double work = c.fixed + rounds * round_us(c) + c.plane * plane;
-            const double loads = (double)n * k * 2e-6 * (1.0 / c.stream + m / (kCacheRate * c.width)) * rounds / full;
-            const double cost = std::max(work, loads) + plane + 1e-3 * work;  // of two that their loads bound, the lighter one
+            const double cost = launch_us(c, m, n, k, steps, plane, rounds, full);
             if (cost < best_cost) { best_cost = cost; best = GemmPlan{tile, s}; }
         };
         auto consider = [&](int tile, const TileCost& c, double tiles) {

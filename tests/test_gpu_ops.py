@@ -267,6 +267,27 @@ def test_gemm_tile_ids_of_one_launch_and_few_k_steps():
         assert np.all(err <= (np.abs(x) @ np.abs(y).T) * K * 2.0 ** -24), (M, N, K, ids, splits)
 
 
+@pytest.mark.parametrize("N,K,splits", [(128, 64, 1), (640, 1152, 3), (4096, 384, 6), (8192, 128, 2), (16512, 128, 1), (33024, 128, 1), (65664, 128, 1)])
+def test_gemm_up_to_64_rows(N, K, splits):
+    """Tile 7 takes 128 or 64 columns and three to six LDS stages, by the number of tiles: from two tiles to more than 512, shares
+    of one k-step and more, both sides of 32 rows.  The rows behind the last one hold NaN and canaries; K roundings of 2^-24 of
+    the sum of magnitudes bound the error."""
+    w = rand_bits(13, 2, (N, K), 0.05)
+    dw, y = to_dev_weight(w), oracle.bf16_to_f64(w)
+    for M in (1, 32, 33, 64):
+        print(f"gemm up to 64 rows M={M} N={N} K={K} splits={splits}", flush=True)
+        a = rand_bits(13, M, (M, K), 1.0)
+        ap = np.full((256, K + 64), 0x7FC0, dtype=np.uint16)
+        ap[:M, :K] = a
+        planes = torch.full((splits, M + 8, N), 7.0, dtype=torch.float32, device=DEV)
+        B.gllm_op_gemm_bf16_splitk(to_dev_bits(ap), dw, planes[:, :M], M, N, K, 7, splits)
+        torch.cuda.synchronize()
+        x = oracle.bf16_to_f64(a)
+        got = planes.cpu().numpy().astype(np.float64)
+        assert np.all(np.abs(got[:, :M].sum(axis=0) - x @ y.T) <= (np.abs(x) @ np.abs(y).T) * K * 2.0 ** -24), M
+        assert np.all(got[:, M:] == 7.0)
+
+
 @pytest.mark.parametrize("tile", [0, 1, 3, 5, 6, 7, 8])
 @pytest.mark.parametrize("K", [64, 128, 448])
 def test_gemm_tiles_at_their_edges(tile, K):
