@@ -45,7 +45,8 @@ enum GemmMode { GEMM_STORE_F32 = 0, GEMM_ADD_F32 = 1, GEMM_SWIGLU_BF16 = 2 };
 // extent (a multiple of 64, >= k).
 // tile: -1 picks a tile shape from m, n and k; 0 = 128x128 (two workgroups share a compute unit); 1 = 256x128, or 192x128
 // where bands of 192 rows cover m with less padding; 2, 3 and 10 = 256x256; 4 and 11 = the mixed 256x256 + 256x128 launch
-// (only where gemm_mixed_rem_cols(m, n) > 0); 5 = 256x192 (not SwiGLU); 6 = 128x128 with four LDS stages; 7 = 64x128,
+// (only where gemm_mixed_rem_cols(m, n) > 0); 5 = 256x192 (not SwiGLU); 6 = 128x128 with four LDS stages, up to 96 rows 96x128, up to
+// 128 rows 64 columns where there are few tiles; 7 = 64x128,
 // up to 32 rows 32x128, up to 64 rows 64 columns where that balances better (up to 64 rows: weight streaming); 8 and 12 = 256x256 tiles for the whole bands of 256 rows plus 64x256 or 128x256
 // tiles for a last band of at most 128 rows, two bands of 192x256 tiles up to 384 rows (only where
 // gemm_rowmix_rem_rows(m, n) > 0); 9 = 288x128, or 288x192 where n is no multiple of 128 and for GEMM_ADD_F32; 13 = one band of 257..384 rows, its

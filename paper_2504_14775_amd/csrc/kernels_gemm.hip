@@ -453,6 +453,10 @@ hipError_t launch_skinny(const bf16_t* a, int64_t lda, const bf16_t* w, int64_t 
 }
 int skinny_columns(int m, int n, int k, int mode, int splits);
 
+// Tile 6 up to 128 rows: 64 columns where half of the compute units would be without a tile of 128 (4096 x 4096 in four shares
+// of k instead of eight, half the planes: 72 rows 12.1 -> 9.9 us, 128 rows 14.7 -> 12.6).
+bool half_width_deep(int m, int n, int splits) { return m <= 128 && (int64_t)(n / 128) * splits <= 128; }
+
 template <int MODE>
 hipError_t launch_mode(const bf16_t* a, int64_t lda, const bf16_t* w, int64_t ldw, void* out, int64_t ldc, int m,
                        int n, int k, int tile, int splits, int64_t split_stride, hipStream_t stream) {
@@ -479,7 +483,13 @@ hipError_t launch_mode(const bf16_t* a, int64_t lda, const bf16_t* w, int64_t ld
             }
             return launch_tile<256, 128, 2, 2, MODE, 3>(GLLM_TILE_ARGS);
         case 2: case 3: case 10: return launch_tile<256, 256, 2, 2, MODE, 2, 3>(GLLM_TILE_ARGS);
-        case 6: return launch_tile<128, 128, 2, 2, MODE, 4>(GLLM_TILE_ARGS);
+        case 6:
+            if constexpr (MODE == GEMM_STORE_F32) {
+                if (half_width_deep(m, n, splits)) return m <= 96 ? launch_tile_w<96, 64, 2, 2, MODE, 4, 4, true>(GLLM_TILE_ARGS) : launch_tile_w<128, 64, 2, 2, MODE, 4, 4, true>(GLLM_TILE_ARGS);
+            }
+            // (a quarter of the rows less to load, read and multiply, us: 96 rows of 6144 x 4096 14.4 -> 13.8, 8192 x 28672 76.5 -> 75.2)
+            if (m <= 96) return launch_tile_w<96, 128, 2, 2, MODE, 3, 3, true>(GLLM_TILE_ARGS);
+            return launch_tile<128, 128, 2, 2, MODE, 4>(GLLM_TILE_ARGS);
         case 7:  // (up to 32 rows half the activations to load and to read from LDS: one row of the 8B shape 785 -> 770 us)
             if constexpr (MODE == GEMM_STORE_F32) {
                 if (m <= 64 && skinny_columns(m, n, k, MODE, splits) == 64)
@@ -611,7 +621,7 @@ struct TileCost {
     double per_tile, plane, stream;
 };
 constexpr double kCacheRate = 121;
-constexpr TileCost kCost128x128{512, 128, 0.867, 7.42, {0.3, 0.77, 0.26}, 2.05, 0.24, 4.61}, kCost128x128Deep{256, 128, 0.454, 3.05, {0.99, 1, 1}, 1.15, 1.55, 6.72},
+constexpr TileCost kCost128x128{512, 128, 0.867, 7.42, {0.3, 0.77, 0.26}, 2.05, 0.24, 4.61}, kCost128x128Deep{256, 128, 0.454, 3.05, {0.99, 1, 1}, 1.15, 1.55, 6.72}, kCost128x64Deep{256, 64, 0.37, 2.9, {0.99, 1, 1}, 0.9, 0.5, 6.72},
     kCost256x192{256, 192, 0.996, 6.74, {0.34, 0.82, 0.92}, 0, 1.09, 6.87}, kCost288x192{256, 192, 1.27, 2.6, {0.89, 0.94, 0.95}, 2.65, 1.8, 6.2};
 // tiles of 160, 192, 224 and 256 rows x 128 and x 256 columns, and of 288, 320, 352 and 384 rows x 128
 constexpr TileCost narrow_cost(double step) { return {256, 128, step, 3.5, {0.67, 0.86, 0.66}, 2.89, 0.58, 6.15}; }
@@ -735,7 +745,8 @@ GemmPlan cheapest(int m, int n, int k, int mode, int min_splits, int max_splits,
             const int h1 = gemm_low_bands(m) ? 192 : 256;
             if (h1 != height) consider(1, narrow_cost_of(h1), (double)ceil_div(m, h1) * cols);
             if (m > 256 && m <= 384 && mode != GEMM_ADD_F32) consider(13, kCostTall[(m - 257) / 32], cols);
-            consider(6, kCost128x128Deep, b128 * cols);
+            if (mode == GEMM_STORE_F32 && half_width_deep(m, n, s)) consider(6, kCost128x64Deep, 2 * cols);
+            else consider(6, kCost128x128Deep, b128 * cols);
             consider(0, kCost128x128, b128 * cols);
         }
     }

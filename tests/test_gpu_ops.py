@@ -268,19 +268,19 @@ def test_gemm_tile_ids_of_one_launch_and_few_k_steps():
 
 
 @pytest.mark.parametrize("N,K,splits", [(128, 64, 1), (640, 1152, 3), (4096, 384, 6), (8192, 128, 2), (16512, 128, 1), (33024, 128, 1), (65664, 128, 1)])
-def test_gemm_up_to_64_rows(N, K, splits):
-    """Tile 7 takes 128 or 64 columns and three to six LDS stages, by the number of tiles: from two tiles to more than 512, shares
-    of one k-step and more, both sides of 32 rows.  The rows behind the last one hold NaN and canaries; K roundings of 2^-24 of
-    the sum of magnitudes bound the error."""
+def test_gemm_up_to_128_rows(N, K, splits):
+    """Tile 7 (up to 64 rows) takes 128 or 64 columns and three to six LDS stages by the number of tiles, tile 6 (up to 128 rows) 128
+    or 64 columns and 96 or 128 rows: from two tiles to more than 512, shares of one k-step and more, both sides of 32, 64 and 96
+    rows.  The rows behind the last one hold NaN and canaries; K roundings of 2^-24 of the sum of magnitudes bound the error."""
     w = rand_bits(13, 2, (N, K), 0.05)
     dw, y = to_dev_weight(w), oracle.bf16_to_f64(w)
-    for M in (1, 32, 33, 64):
-        print(f"gemm up to 64 rows M={M} N={N} K={K} splits={splits}", flush=True)
+    for M, tile in ((1, 7), (32, 7), (33, 7), (64, 7), (65, 6), (96, 6), (97, 6), (128, 6)):
+        print(f"gemm up to 128 rows M={M} tile={tile} N={N} K={K} splits={splits}", flush=True)
         a = rand_bits(13, M, (M, K), 1.0)
         ap = np.full((256, K + 64), 0x7FC0, dtype=np.uint16)
         ap[:M, :K] = a
         planes = torch.full((splits, M + 8, N), 7.0, dtype=torch.float32, device=DEV)
-        B.gllm_op_gemm_bf16_splitk(to_dev_bits(ap), dw, planes[:, :M], M, N, K, 7, splits)
+        B.gllm_op_gemm_bf16_splitk(to_dev_bits(ap), dw, planes[:, :M], M, N, K, tile, splits)
         torch.cuda.synchronize()
         x = oracle.bf16_to_f64(a)
         got = planes.cpu().numpy().astype(np.float64)
