@@ -204,7 +204,7 @@ gllm_status gllm_op_pack_weight(const void* w, int64_t ldw, int32_t n, int32_t k
  * (192x128 where bands of 192 rows cover m with less padding), 2, 3 and 10 = 256x256, 4 and 11 = 256x256 tiles for whole
  * rounds of the compute units plus 256x128 tiles for the remainder (only for shapes with such a remainder), 5 = 256x192
  * (n a multiple of 192, not for SwiGLU), 6 = 128x128 with four LDS stages (for few rows, where the weights stream
- * from HBM; up to 96 rows 96x128, in mode 0 up to 128 rows by 64 columns where tiles of 128 would leave half of the compute units without one), 7 = 64x128, up to 32 rows 32x128, in mode 0 up to 64 rows by 64 columns where that gives the compute units more
+ * from HBM; up to 96 rows 96x128, in mode 0 up to 128 rows by 64 columns where tiles of 128 would leave half of the compute units without one and those of 64 few), 7 = 64x128, up to 32 rows 32x128, in mode 0 up to 64 rows by 64 columns where that gives the compute units more
  * equal shares (picked up to 64 rows: the product is a stream of the weights), 8 and 12 = 256x256 tiles for the whole bands of 256 rows plus 64x256 or 128x256 tiles for a last band of at
  * most 128 rows, or two bands of 192x256 tiles for all rows up to 384 (only for m > 256 with 0 < m mod 256 <= 128 and
  * n a multiple of 256), 9 = 288x128, or 288x192 (six wavefronts) where n is no multiple of 128 and in mode 1 (only for

@@ -453,9 +453,12 @@ hipError_t launch_skinny(const bf16_t* a, int64_t lda, const bf16_t* w, int64_t 
 }
 int skinny_columns(int m, int n, int k, int mode, int splits);
 
-// Tile 6 up to 128 rows: 64 columns where half of the compute units would be without a tile of 128 (4096 x 4096 in four shares
-// of k instead of eight, half the planes: 72 rows 12.1 -> 9.9 us, 128 rows 14.7 -> 12.6).
-bool half_width_deep(int m, int n, int splits) { return m <= 128 && (int64_t)(n / 128) * splits <= 128; }
+// Tile 6 up to 128 rows: 64 columns where half of the compute units would be without a tile of 128 and nearly all have one of 64
+// (4096 x 4096 in four shares of k instead of eight, half the planes: 72 rows 12.1 -> 9.9 us, 128 rows 14.7 -> 12.6).
+bool half_width_deep(int m, int n, int splits) {
+    const int64_t tiles = (int64_t)(n / 128) * splits;
+    return m <= 128 && tiles > 112 && tiles <= 128;
+}
 
 template <int MODE>
 hipError_t launch_mode(const bf16_t* a, int64_t lda, const bf16_t* w, int64_t ldw, void* out, int64_t ldc, int m,

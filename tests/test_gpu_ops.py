@@ -267,7 +267,7 @@ def test_gemm_tile_ids_of_one_launch_and_few_k_steps():
         assert np.all(err <= (np.abs(x) @ np.abs(y).T) * K * 2.0 ** -24), (M, N, K, ids, splits)
 
 
-@pytest.mark.parametrize("N,K,splits", [(128, 64, 1), (640, 1152, 3), (4096, 384, 6), (8192, 128, 2), (16512, 128, 1), (33024, 128, 1), (65664, 128, 1)])
+@pytest.mark.parametrize("N,K,splits", [(128, 64, 1), (640, 1152, 3), (4096, 256, 4), (4096, 384, 6), (8192, 128, 2), (16512, 128, 1), (33024, 128, 1), (65664, 128, 1)])
 def test_gemm_up_to_128_rows(N, K, splits):
     """Tile 7 (up to 64 rows) takes 128 or 64 columns and three to six LDS stages by the number of tiles, tile 6 (up to 128 rows) 128
     or 64 columns and 96 or 128 rows: from two tiles to more than 512, shares of one k-step and more, both sides of 32, 64 and 96
