@@ -145,6 +145,7 @@ struct AttnArgs {
 // Decode rows (one new token per sequence).  Work items split the keys of a row into
 // partitions; every item writes one partial per query head, then a second kernel merges the rows
 // that have more than one item (DecodeRow lists only those).
+constexpr int kDecodeWaves = 4;
 struct DecodeItem {
     int32_t row;       // token row
     int32_t bt_off;    // offset of the sequence's first page id in bt_flat
@@ -152,7 +153,18 @@ struct DecodeItem {
     int32_t kv_end;    // one past the last key of this partition
     int32_t single;    // 1: the row's only item; the kernel writes the normalised output itself
     int32_t pos;       // position of the row's new token, its last key
+    int32_t slot;      // place of its partial results
+    int32_t pad;
+    // page ids of the block (32 keys, two pages) that each wave starts with (decode_wave_first), so that its keys are asked for
+    // as soon as the item is there
+    int32_t first_pages[kDecodeWaves][2];
 };
+static_assert(sizeof(DecodeItem) == 64, "one scalar load");
+// First 32-key block, counted from the item's, of wave w (0 .. kDecodeWaves: where the run of wave w - 1 ends).
+__host__ __device__ static inline int decode_wave_first(const DecodeItem& it, int w) {
+    const int blocks = (it.kv_end - it.kv_begin + 31) / 32, per_wave = (blocks + kDecodeWaves - 1) / kDecodeWaves;
+    return w * per_wave < blocks ? w * per_wave : blocks;
+}
 struct DecodeRow {
     int32_t row;        // token row
     int32_t first_item; // first partial of this row
@@ -160,8 +172,7 @@ struct DecodeRow {
     int32_t pad;
 };
 struct DecodeArgs {
-    const DecodeItem* items;
-    const int32_t* order;  // order[i] = index of the item that workgroup group i works on (a permutation of 0 .. num_items-1)
+    const DecodeItem* items;  // in launch order
     int num_items;
     float* part_o;         // partials of the items whose row has more than one
     float* part_ml;

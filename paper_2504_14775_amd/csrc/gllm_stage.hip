@@ -45,7 +45,7 @@ constexpr int kDecodeSlots = 512;  // decode attention workgroups that run at on
 constexpr int kMaxSplits = kMaxPlanes;
 
 struct MetaLayout {  // offsets in bytes inside the metadata block (host staging and device copy alike)
-    size_t tok_pos, tok_page, tok_own_v, bt_flat, dec_items, dec_order, dec_rows, pre_items, v_tiles, total;
+    size_t tok_pos, tok_page, tok_own_v, bt_flat, dec_items, dec_rows, pre_items, v_tiles, total;
 };
 
 }  // namespace
@@ -98,6 +98,9 @@ struct gllm_stage {
     int64_t prof_n[PC_COUNT] = {};
     // scratch for validation
     std::vector<int32_t> written_pages;
+    // scratch for the decode work items, max_items each: as they come, and the order they are launched in
+    std::vector<DecodeItem> item_list;
+    std::vector<int32_t> item_order;
     std::vector<uint8_t> page_writers;  // per page of the pool, 0 between calls (see own_pages)
 };
 
@@ -288,6 +291,8 @@ gllm_status gllm_stage_create(const gllm_stage_config* cfg, gllm_stage** out) {
     s->hidden_pad_n = (int)round_up(c.hidden, kGemmPadN);
     s->m_pad = round_up(c.max_tokens, kGemmPadM);
     s->max_items = 4 * c.max_seqs + 1024;
+    s->item_list.resize((size_t)s->max_items);
+    s->item_order.resize((size_t)s->max_items);
     s->max_pre_items = c.max_tokens / prefill_item_rows(c.n_q_heads, c.n_kv_heads, true) + c.max_seqs + 1;
     s->max_v_tiles = c.max_tokens / kPage + 2 * c.max_seqs + 1;
     s->layers.resize(c.num_layers);
@@ -323,7 +328,6 @@ gllm_status gllm_stage_create(const gllm_stage_config* cfg, gllm_stage** out) {
         m.tok_own_v = take((size_t)c.max_tokens * 4);
         m.bt_flat = take((size_t)c.max_seqs * c.max_blocks_per_seq * 4);
         m.dec_items = take((size_t)s->max_items * sizeof(DecodeItem));
-        m.dec_order = take((size_t)s->max_items * 4);
         m.dec_rows = take((size_t)c.max_seqs * sizeof(DecodeRow));
         m.pre_items = take((size_t)s->max_pre_items * sizeof(PrefillItem));
         m.v_tiles = take((size_t)s->max_v_tiles * sizeof(VTile));
@@ -609,7 +613,6 @@ gllm_status gllm_stage_forward(gllm_stage* s, const gllm_batch* b, const void* h
         ml.tok_own_v = take((size_t)T * 4);
         ml.bt_flat = take((size_t)total_pages * 4);
         ml.dec_items = take((size_t)cnt_items * sizeof(DecodeItem));
-        ml.dec_order = take((size_t)cnt_items * 4);
         ml.dec_rows = take((size_t)n_dec * sizeof(DecodeRow));
         ml.pre_items = take((size_t)cnt_pre * sizeof(PrefillItem));
         ml.v_tiles = take((size_t)cnt_vt * sizeof(VTile));
@@ -621,7 +624,6 @@ gllm_status gllm_stage_forward(gllm_stage* s, const gllm_batch* b, const void* h
     VTile* v_tiles = (VTile*)(st_base + ml.v_tiles);
     int32_t* bt_flat = (int32_t*)(st_base + ml.bt_flat);
     DecodeItem* dec_items = (DecodeItem*)(st_base + ml.dec_items);
-    int32_t* dec_order = (int32_t*)(st_base + ml.dec_order);
     DecodeRow* dec_rows = (DecodeRow*)(st_base + ml.dec_rows);
     PrefillItem* pre_items = (PrefillItem*)(st_base + ml.pre_items);
     int n_items = 0, n_rows = 0, n_pre = 0, n_vt = 0;
@@ -648,10 +650,15 @@ gllm_status gllm_stage_forward(gllm_stage* s, const gllm_batch* b, const void* h
             const int nparts = (int)ceil_div(len, part);
             const int share = (int)ceil_div(ceil_div(len, nparts), 32) * 32;
             const int first = n_items;
-            for (int k0 = 0; k0 < len; k0 += share)
-                dec_items[n_items++] = DecodeItem{(int32_t)row, (int32_t)bt_off, k0, std::min(k0 + share, len), 0, cl};
+            for (int k0 = 0; k0 < len; k0 += share) {
+                DecodeItem it{(int32_t)row, (int32_t)bt_off, k0, std::min(k0 + share, len), 0, cl, n_items, 0, {}};
+                for (int w = 0; w < kDecodeWaves; ++w)
+                    for (int p = 0; p < 2; ++p)
+                        it.first_pages[w][p] = tab[std::min((k0 / 32 + decode_wave_first(it, w)) * 2 + p, cl / kPage)];
+                s->item_list[n_items++] = it;
+            }
             // a row with a single item is finished by the attention kernel; the others are merged afterwards
-            if (n_items - first == 1) dec_items[first].single = 1;
+            if (n_items - first == 1) s->item_list[first].single = 1;
             else dec_rows[n_rows++] = DecodeRow{(int32_t)row, first, n_items - first, 0};
         } else {
             for (int t0 = 0; t0 < n; t0 += pre_rows)
@@ -666,10 +673,11 @@ gllm_status gllm_stage_forward(gllm_stage* s, const gllm_batch* b, const void* h
     std::stable_sort(pre_items, pre_items + n_pre, [](const PrefillItem& x, const PrefillItem& y) {
         return x.pos0 + x.n_rows > y.pos0 + y.n_rows;
     });
-    for (int i = 0; i < n_items; ++i) dec_order[i] = i;
-    std::stable_sort(dec_order, dec_order + n_items, [&](int32_t x, int32_t y) {
-        return dec_items[x].kv_end - dec_items[x].kv_begin > dec_items[y].kv_end - dec_items[y].kv_begin;
+    for (int i = 0; i < n_items; ++i) s->item_order[i] = i;
+    std::stable_sort(s->item_order.begin(), s->item_order.begin() + n_items, [&](int32_t x, int32_t y) {
+        return s->item_list[x].kv_end - s->item_list[x].kv_begin > s->item_list[y].kv_end - s->item_list[y].kv_begin;
     });
+    for (int i = 0; i < n_items; ++i) dec_items[i] = s->item_list[s->item_order[i]];
     hipStream_t st = (hipStream_t)stream_;
 
     const int32_t* d_tok_pos = (const int32_t*)(s->meta_dev + ml.tok_pos);
@@ -678,7 +686,6 @@ gllm_status gllm_stage_forward(gllm_stage* s, const gllm_batch* b, const void* h
     const VTile* d_v_tiles = (const VTile*)(s->meta_dev + ml.v_tiles);
     const int32_t* d_bt = (const int32_t*)(s->meta_dev + ml.bt_flat);
     const DecodeItem* d_items = (const DecodeItem*)(s->meta_dev + ml.dec_items);
-    const int32_t* d_order = (const int32_t*)(s->meta_dev + ml.dec_order);
     const DecodeRow* d_rows = (const DecodeRow*)(s->meta_dev + ml.dec_rows);
     const PrefillItem* d_pre = (const PrefillItem*)(s->meta_dev + ml.pre_items);
 
@@ -735,7 +742,7 @@ gllm_status gllm_stage_forward(gllm_stage* s, const gllm_batch* b, const void* h
         aa.bt_flat = d_bt; aa.out = s->attn; aa.ld_o = s->q_dim;
         aa.n_q = c.n_q_heads; aa.n_kv = c.n_kv_heads; aa.d = d;
         aa.scale_log2 = (float)(1.4426950408889634 / std::sqrt((double)d));
-        const DecodeArgs da{d_items, d_order, n_items, s->part_o, s->part_ml, from_qkv, ra};
+        const DecodeArgs da{d_items, n_items, s->part_o, s->part_ml, from_qkv, ra};
         // both kinds of attention read q and the pool and write disjoint rows of attn
         if (s->overlap_attention && !s->profiling && attention_in_one_launch(aa, n_pre, half_items, n_items)) {
             HIP_TRY(s, launch_hybrid_attention(aa, d_pre, n_pre, half_items, da, st));

@@ -203,12 +203,13 @@ __device__ __forceinline__ void attend_block(AttnState<D, NB>& st, KvFrag<D>& f,
 
 // Walks key blocks [blk_begin, blk_end) (units of 32 keys) of one sequence.  Page ids are fetched 64
 // at a time, one per lane, and handed out with readlane.  last_page is the last page index of the
-// sequence that may be read (page ids past it are never dereferenced).
+// sequence that may be read (page ids past it are never dereferenced); page0 and page1 are the ids of the first block's pages, so
+// that its loads need not wait for the table.
 // prepare() fills qf; every wave calls it once, when the loads of its first block are on their way.
 template <int D, int NB, typename Prepare>
 __device__ __forceinline__ void attend_range(AttnState<D, NB>& st, const bf16x8 (&qf)[NB][D / 32],
                                              const bf16_t* __restrict__ kp, const bf16_t* __restrict__ vp,
-                                             const int32_t* __restrict__ bt, int blk_begin, int blk_end,
+                                             const int32_t* __restrict__ bt, int blk_begin, int blk_end, int page0, int page1,
                                              int last_page, const int (&limit)[NB], int min_limit, int valid_end,
                                              int n_kv, int kvh, float scale_log2, int lane, Prepare&& prepare) {
     if (blk_begin >= blk_end) {
@@ -225,7 +226,7 @@ __device__ __forceinline__ void attend_range(AttnState<D, NB>& st, const bf16x8 
         load_kv<D>(f, kp, vp, page_of(p0), page_of(p1), n_kv, kvh, lane);
     };
     KvFrag<D> fa, fb;
-    load_block(fa, blk_begin);
+    load_kv<D>(fa, kp, vp, page0, page1, n_kv, kvh, lane);
     prepare();
     for (int blk = blk_begin; blk < blk_end; blk += 2) {
         // blocks blk and blk+1 use pages 2blk .. 2blk+3; refill the id window when it runs out
@@ -304,13 +305,17 @@ __device__ __forceinline__ void decode_workgroup(const AttnArgs& a, const Decode
     float* __restrict__ part_ml = dec.part_ml;
     // the KV heads of one item are neighbouring workgroups: they run at the same time and read
     // neighbouring 4 KiB pieces of the same pages
-    const int item_idx = dec.order[wg / a.n_kv];
     const int kvh = wg % a.n_kv;
-    const DecodeItem it = items[item_idx];
+    // (the items lie in launch order and name the pages of each wave's first block: keys are asked for after one trip to memory, not
+    // three -- order, item, page table.  200 rows of 16 .. 600 keys, eight layers 1600 -> 1581 us, 251 rows beside two chunks 2112 -> 2098,
+    // 256 rows beside a chunk 9296 -> 9244, one row 740 -> 738)
+    const DecodeItem& item = items[wg / a.n_kv];
+    const DecodeItem it = item;
     const int g = a.n_q / a.n_kv;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int r = lane & 15, G = lane >> 4;
+    const int page0 = item.first_pages[wave][0], page1 = item.first_pages[wave][1];
 
     bf16x8 qf[1][D / 32];
     f32x4 part[kMaxPlanes], cs[D / 64][4];
@@ -383,14 +388,13 @@ __device__ __forceinline__ void decode_workgroup(const AttnArgs& a, const Decode
         }
     };
     const int blk0 = it.kv_begin / 32;
-    const int nblk = (kv_end - it.kv_begin + 31) / 32;
-    const int per_wave = (nblk + 3) / 4;
-    const int b_begin = blk0 + min(wave * per_wave, nblk);
-    const int b_end = blk0 + min((wave + 1) * per_wave, nblk);
+    const int nblk = (kv_end - it.kv_begin + 31) / 32;  // (one less than the item's where the new token starts a block)
+    const int b_begin = blk0 + decode_wave_first(it, wave);
+    const int b_end = blk0 + min(decode_wave_first(it, wave + 1), nblk);
     const int limit[1] = {kv_end - 1};
     AttnState<D, 1> st;
     init_state<D, 1>(st);
-    attend_range<D, 1>(st, qf, a.k_pool, a.v_pool, a.bt_flat + it.bt_off, b_begin, b_end, (kv_end - 1) / kPage,
+    attend_range<D, 1>(st, qf, a.k_pool, a.v_pool, a.bt_flat + it.bt_off, b_begin, b_end, page0, page1, (kv_end - 1) / kPage,
                        limit, kv_end - 1, kv_end, a.n_kv, kvh, a.scale_log2, lane, prepare);
     float l = st.l[0];
     l += __shfl_xor(l, 16);
@@ -441,7 +445,7 @@ __device__ __forceinline__ void decode_workgroup(const AttnArgs& a, const Decode
                 __builtin_convertvector(acc, bf16x4);
             continue;
         }
-        const int64_t slot = ((int64_t)item_idx * a.n_q + kvh * g + j);
+        const int64_t slot = ((int64_t)it.slot * a.n_q + kvh * g + j);
         *reinterpret_cast<f32x4*>(part_o + slot * D + e) = acc;
         if (e == 0) {
             part_ml[slot * 2] = ms;
