@@ -169,12 +169,17 @@ struct SampleShared {
         } list;
         uint32_t keys[kSampleThreads];
     };
+    struct __attribute__((aligned(16))) Few {
+        uint32_t key;
+        int id;
+        uint64_t weight;
+    } few[64];                      // what top-k leaves, where that is little; the others weigh nothing
     uint64_t wave_sum[kSampleWaves];
     uint64_t above;
     float wave_f[kSampleWaves];
     int wave_i[kSampleWaves];
     uint32_t digit;
-    int count;
+    int count, few_count;
 };
 
 // Lane l receives v of lane l - N of its row of 16 (row_shr), or of the last lane of the row(s) before it (row_bcast),
@@ -402,6 +407,7 @@ __device__ __forceinline__ int row_argmax(SampleShared& sh, const float* __restr
     return best_i == INT_MAX ? 0 : best_i;
 }
 
+constexpr int kFewStep = 8;          // entries that finish_on_few reads from LDS at one time
 constexpr int kRoomyMaxRows = 256;   // up to here every row has a compute unit
 constexpr int kFirstList = 1400;     // first bound of a nucleus: taken so that the list comes to 1.5 - 2 times this many
 constexpr int kMaxFirstK = 256;      // largest k for which the list taken with the first bound is expected to fit
@@ -518,8 +524,44 @@ __global__ __launch_bounds__(kSampleThreads, ROOMY ? 4 : 8) void sample_kernel(c
         return;
     }
 
+    // Nucleus and draw among the n <= 64 entries of sh.few, by one wave: an entry compares itself with all others.  (A key is in
+    // the nucleus when the keys above it do not reach the mass by themselves; the token drawn is the one in whose interval of the
+    // running sum `need` falls.)
+    auto finish_on_few = [&](int n) {
+        const uint32_t key = lane < n ? sh.few[lane].key : 0;
+        const int id = lane < n ? sh.few[lane].id : 0;
+        uint64_t weight = lane < n ? sh.few[lane].weight : 0;
+        uint64_t total = lane_value(wave_scan(weight), 63);
+        if (by_p) {
+            uint64_t above = 0;
+            for (int i = 0; i < n; i += kFewStep) {
+                SampleShared::Few f[kFewStep];
+#pragma unroll
+                for (int j = 0; j < kFewStep; ++j) f[j] = sh.few[i + j];
+#pragma unroll
+                for (int j = 0; j < kFewStep; ++j) above += f[j].key > key ? f[j].weight : 0;
+            }
+            if (above >= nucleus_need(p, total)) weight = 0;
+            total = lane_value(wave_scan(weight), 63);
+        }
+        sh.few[lane].weight = weight;  // (read back by this wave only, which LDS serves in order)
+        const uint64_t need = draw_need(u, total);
+        uint64_t before = 0;
+        for (int i = 0; i < n; i += kFewStep) {
+            SampleShared::Few f[kFewStep];
+#pragma unroll
+            for (int j = 0; j < kFewStep; ++j) f[j] = sh.few[i + j];
+#pragma unroll
+            for (int j = 0; j < kFewStep; ++j) before += f[j].id < id ? f[j].weight : 0;
+        }
+        if (total == 0 ? lane == 0 : before < need && before + weight >= need) out[row] = total ? id : 0;
+    };
+
     // Finishes the row on the list of n candidates; false when the guess of a nucleus does not hold.
     auto finish_on_list = [&](int n, float others) -> bool {
+        // keys relative to that of the bound, below which nothing is listed: 24 or 25 bits, two digits instead of three
+        const uint32_t key_lo = float_key(bound / temp), key_span = float_key(best / temp) - key_lo;
+        const int key_bits = 32 - __clz((int)key_span);  // (0 bits: all keys are equal)
         uint32_t key[kPerThread], ikey[kPerThread];
         uint64_t weight[kPerThread];
         uint64_t own = 0;
@@ -530,7 +572,7 @@ __global__ __launch_bounds__(kSampleThreads, ROOMY ? 4 : 8) void sample_kernel(c
             weight[j] = 0;
             if (s < n) {
                 const float v = sh.list.v[s];
-                key[j] = float_key(v / temp);
+                key[j] = float_key(v / temp) - key_lo;
                 ikey[j] = 0xFFFFFFu - (uint32_t)sh.list.id[s];  // larger for tokens that come first
                 weight[j] = mass(v);
                 own += weight[j];
@@ -542,12 +584,33 @@ __global__ __launch_bounds__(kSampleThreads, ROOMY ? 4 : 8) void sample_kernel(c
             uint64_t one[kPerThread];
 #pragma unroll
             for (int j = 0; j < kPerThread; ++j) one[j] = j * kSampleThreads + tid < n ? 1 : 0;
-            const uint32_t floor_key = select_key(sh, key, one, 32, (uint64_t)k);
+            const uint32_t floor_key = select_key(sh, key, one, key_bits, (uint64_t)k);
             own = 0;
 #pragma unroll
             for (int j = 0; j < kPerThread; ++j) {
                 if (key[j] < floor_key) weight[j] = 0;
                 own += weight[j];
+            }
+            if (k <= 64) {  // (more than 64 are left where many are equal to the k-th largest)
+                if (tid == 0) sh.few_count = 0;
+                if (tid < 64) sh.few[tid].weight = 0;
+                __syncthreads();
+#pragma unroll
+                for (int j = 0; j < kPerThread; ++j)
+                    if (weight[j]) {
+                        const int at = atomicAdd(&sh.few_count, 1);
+                        if (at < 64) {
+                            sh.few[at].key = key[j];
+                            sh.few[at].id = (int)(0xFFFFFFu - ikey[j]);
+                            sh.few[at].weight = weight[j];
+                        }
+                    }
+                __syncthreads();
+                const int few = sh.few_count;
+                if (few <= 64) {
+                    if (tid < 64) finish_on_few(few);
+                    return true;
+                }
             }
             total = block_sum(sh, own);
         } else {
@@ -556,7 +619,7 @@ __global__ __launch_bounds__(kSampleThreads, ROOMY ? 4 : 8) void sample_kernel(c
             if (listed < nucleus_need(p, total)) return false;
         }
         if (by_p) {
-            const uint32_t t = select_key(sh, key, weight, 32, nucleus_need(p, total));
+            const uint32_t t = select_key(sh, key, weight, key_bits, nucleus_need(p, total));
             own = 0;
 #pragma unroll
             for (int j = 0; j < kPerThread; ++j) {
