@@ -67,7 +67,7 @@ __global__ __launch_bounds__(256) void pad_rows_kernel(const bf16_t* __restrict_
 // What bounds it: a row of logits (0.5 MB at a 128k vocabulary) does not fit on chip, so the cost is the number of
 // passes over it (6 to 8 us each for a compute unit of its own, 24 us for 256 rows: 5.5 TB/s) and the chains of barriers
 // behind them.  One workgroup per row, because a call has one row per sequence and the rows are independent; 64 registers
-// per thread and 34 KiB of LDS let two rows share a compute unit, so 257 rows are not two rounds.
+// per thread and 43 KiB of LDS let two rows share a compute unit, so 257 rows are not two rounds.
 //
 // The row is read once.  Its first 16384 logits to be read (four blocks from all over it) stay in registers while a
 // bound is taken from them, and from there on every logit at or above the bound goes into a list in LDS:
@@ -90,7 +90,9 @@ __global__ __launch_bounds__(256) void pad_rows_kernel(const bf16_t* __restrict_
 constexpr int kSampleThreads = 1024;
 constexpr int kSampleWaves = kSampleThreads / 64;
 constexpr int kDigitBits = 12, kBins = 1 << kDigitBits;
-constexpr int kList = 4096, kPerThread = kList / kSampleThreads;  // candidates held in LDS, then in registers
+// Candidates held in LDS, then in registers.  A nucleus lists 2450 logits on average and up to 4400 in 256 rows; with room for 4096
+// one such row took a second pass and the launch 59 us instead of 37.
+constexpr int kList = 5120, kPerThread = kList / kSampleThreads;
 static_assert(kBins == 4 * kSampleThreads, "find_bin gives every thread four bins; a block of for_row is one bin of the draw");
 
 // order-preserving map from float to unsigned: a < b  <=>  key(a) < key(b) (for non-NaN values), and back
@@ -407,7 +409,6 @@ __device__ __forceinline__ int row_argmax(SampleShared& sh, const float* __restr
     return best_i == INT_MAX ? 0 : best_i;
 }
 
-constexpr int kFewStep = 8;          // entries that finish_on_few reads from LDS at one time
 constexpr int kRoomyMaxRows = 256;   // up to here every row has a compute unit
 constexpr int kFirstList = 1400;     // first bound of a nucleus: taken so that the list comes to 1.5 - 2 times this many
 constexpr int kMaxFirstK = 256;      // largest k for which the list taken with the first bound is expected to fit
@@ -423,6 +424,7 @@ __global__ __launch_bounds__(kSampleThreads, ROOMY ? 4 : 8) void sample_kernel(c
                                                                    int32_t* __restrict__ out) {
     __shared__ SampleShared sh;
     constexpr int U = ROOMY ? 8 : 4;
+    constexpr int kFewStep = ROOMY ? 8 : 1;  // entries that finish_on_few reads from LDS at one time (64 registers hold no more)
     const int tid = threadIdx.x, lane = tid & 63, row = blockIdx.x;
     const float* lg = logits + (int64_t)row * ld;
     const float temp = temperature[row];

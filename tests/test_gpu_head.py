@@ -199,6 +199,26 @@ def test_sampler_at_the_edges_of_its_paths(V, sigma, k, p):
     check_against_oracle(lg, full(0.9, np.float32), full(k, np.int32), full(p, np.float32), u, f"edges V={V} k={k} p={p}", slack=1)
 
 
+@pytest.mark.parametrize("rows", [20, 260])                          # a compute unit per row, and two rows on one
+@pytest.mark.parametrize("k", [1, 2, 63, 64, 65])
+def test_sampler_around_64_candidates(k, rows):
+    """Up to 64 tokens that top-k leaves are finished by one wave, more (a larger k, or ties at the k-th largest) by the
+    workgroup: distinct logits, ties that make 64 and 65 of the k kept, all of the mass on one token, negative logits only."""
+    print(f"sampler: k={k} rows={rows}", flush=True)
+    V = 20000
+    g = torch.Generator().manual_seed(k)
+    lg = (torch.randn(rows, V, generator=g) * 4).to(torch.float32)
+    order = torch.argsort(lg, dim=1, descending=True)
+    for r in range(0, rows, 5):
+        lg[r, order[r, k - 1:64 + r % 2]] = lg[r, order[r, k - 1]].item()      # 64 or 65 kept, where k is smaller
+    lg[1::5] -= 100.0
+    lg[2::5, 7] = 200.0
+    rng = np.random.default_rng(k)
+    temp = rng.choice([0.7, 1.0, 1.3], size=rows).astype(np.float32)
+    p = rng.choice([1.0, 0.95, 0.5, 1e-6], size=rows).astype(np.float32)
+    check_against_oracle(lg, temp, np.full(rows, k, np.int32), p, rng.random(rows).astype(np.float32), f"k={k}")
+
+
 def largest(row):
     """Lowest index of the largest logit, NaN left out; 0 when no logit lies above -infinity."""
     return int(np.argmax(np.where(np.isnan(row), -np.inf, row)))
