@@ -140,6 +140,8 @@ struct AttnArgs {
     int64_t ld_o;
     int n_q, n_kv, d;
     float scale_log2;         // log2(e) / sqrt(d)
+    float* part_o;            // partial results of rows whose keys are cut: [slot][n_q][d], not normalised,
+    float* part_ml;           // and [slot][n_q][2]: reference exponent and sum
 };
 
 // Decode rows (one new token per sequence).  Work items split the keys of a row into
@@ -174,18 +176,16 @@ struct DecodeRow {
 struct DecodeArgs {
     const DecodeItem* items;  // in launch order
     int num_items;
-    float* part_o;         // partials of the items whose row has more than one
-    float* part_ml;
     // from_qkv (every token of the batch is a decode row): queries, new keys and new values are taken from the QKV projection
     // (`rope`) and the new keys and values written to the pool by the same launch; q and the new slots of the pool are not read.
     bool from_qkv;
     RopeKvArgs rope;
 };
 hipError_t launch_decode_attention(const AttnArgs& a, const DecodeArgs& dec, hipStream_t stream);
-hipError_t launch_decode_combine(const AttnArgs& a, const DecodeRow* rows, int num_rows, const float* part_o,
-                                 const float* part_ml, hipStream_t stream);
+hipError_t launch_decode_combine(const AttnArgs& a, const DecodeRow* rows, int num_rows, hipStream_t stream);
 
-// Prefill chunks: one work item per prefill_item_rows() consecutive query rows of a chunk; `half`: items of half the rows.
+// Prefill chunks: one work item per prefill_item_rows() consecutive query rows of a chunk, or several, each with a part of the
+// keys; `half`: items of half the rows.
 int prefill_item_rows(int n_q, int n_kv, bool half);
 int prefill_heads_per_workgroup(int n_q, int n_kv, bool half);
 struct PrefillItem {
@@ -193,10 +193,13 @@ struct PrefillItem {
     int32_t n_rows;    // valid query rows in the tile (1 .. prefill_item_rows)
     int32_t pos0;      // position of the first query row
     int32_t bt_off;    // offset of the sequence's first page id in bt_flat
+    int32_t blk_begin, blk_end;  // key blocks (of 32) of this part; all of the tile's but in the last part visible to every row
+    int32_t parts;     // 1: the kernel writes the normalised output itself
+    int32_t slot0;     // partial results of row i of the tile: slot0 + i * parts
 };
 hipError_t launch_prefill_attention(const AttnArgs& a, const PrefillItem* items, int num_items, bool half, hipStream_t stream);
 // Prefill and decode items of one batch in one launch, and whether that pays.
-bool attention_in_one_launch(const AttnArgs& a, int num_items, bool half, int num_decode_items);
+bool attention_in_one_launch(const AttnArgs& a, int num_tiles, bool half, int num_decode_items);
 hipError_t launch_hybrid_attention(const AttnArgs& a, const PrefillItem* items, int num_items, bool half, const DecodeArgs& dec, hipStream_t stream);
 
 // Ceiling probes (see kernels_peak.hip).  peak_mfma: workgroups x 4 waves x iters x 16 MFMAs of

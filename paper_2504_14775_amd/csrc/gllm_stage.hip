@@ -41,6 +41,8 @@ struct LayerBuffers {
 
 constexpr int kStagingSlots = 4;
 constexpr int kHalfItemsMax = 256;  // workgroups of whole prefill items
+constexpr int kPrefillSlots = 640;  // workgroups that the prefill items are cut into where there are fewer
+constexpr int kPrefillMinBlocks = 16;  // fewest key blocks (of 32) in a part of a prefill item
 constexpr int kDecodeSlots = 512;  // decode attention workgroups that run at one time
 constexpr int kMaxSplits = kMaxPlanes;
 
@@ -290,10 +292,10 @@ gllm_status gllm_stage_create(const gllm_stage_config* cfg, gllm_stage** out) {
     s->inter_pad = (int)round_up(c.intermediate, kGemmPadN / 2);
     s->hidden_pad_n = (int)round_up(c.hidden, kGemmPadN);
     s->m_pad = round_up(c.max_tokens, kGemmPadM);
-    s->max_items = 4 * c.max_seqs + 1024;
+    s->max_items = 4 * c.max_seqs + 1024 + std::min(4 * c.max_tokens, 2048);
     s->item_list.resize((size_t)s->max_items);
     s->item_order.resize((size_t)s->max_items);
-    s->max_pre_items = c.max_tokens / prefill_item_rows(c.n_q_heads, c.n_kv_heads, true) + c.max_seqs + 1;
+    s->max_pre_items = c.max_tokens / prefill_item_rows(c.n_q_heads, c.n_kv_heads, true) + c.max_seqs + 1 + kPrefillSlots;
     s->max_v_tiles = c.max_tokens / kPage + 2 * c.max_seqs + 1;
     s->layers.resize(c.num_layers);
     s->layer_end = c.num_layers;
@@ -328,7 +330,7 @@ gllm_status gllm_stage_create(const gllm_stage_config* cfg, gllm_stage** out) {
         m.tok_own_v = take((size_t)c.max_tokens * 4);
         m.bt_flat = take((size_t)c.max_seqs * c.max_blocks_per_seq * 4);
         m.dec_items = take((size_t)s->max_items * sizeof(DecodeItem));
-        m.dec_rows = take((size_t)c.max_seqs * sizeof(DecodeRow));
+        m.dec_rows = take(((size_t)c.max_seqs + s->max_items / 2) * sizeof(DecodeRow));
         m.pre_items = take((size_t)s->max_pre_items * sizeof(PrefillItem));
         m.v_tiles = take((size_t)s->max_v_tiles * sizeof(VTile));
         m.total = off;
@@ -595,10 +597,45 @@ gllm_status gllm_stage_forward(gllm_stage* s, const gllm_batch* b, const void* h
     whole_wgs *= c.n_q_heads / prefill_heads_per_workgroup(c.n_q_heads, c.n_kv_heads, false);
     const bool half_items = whole_wgs <= kHalfItemsMax;
     const int pre_rows = prefill_item_rows(c.n_q_heads, c.n_kv_heads, half_items);
+    // f(first row, rows, key blocks, those of them that every row of it sees) for each prefill tile of sequence i
+    auto for_tiles = [&](int i, auto&& f) {
+        const int n = b->new_tokens[i], cl = b->cached_len[i];
+        for (int t0 = 0; t0 < n; t0 += pre_rows) {
+            const int rows = std::min(pre_rows, n - t0);
+            f(t0, rows, (cl + t0 + rows - 1) / 32 + 1, (cl + t0 + 1) / 32);
+        }
+    };
+    // parts of a tile's keys, at most `len` blocks each but for the last, which also takes those at the causal edge
+    auto parts_of = [&](int full, int64_t len) { return (int)std::max<int64_t>(1, std::min<int64_t>(ceil_div(full, len), full / kPrefillMinBlocks)); };
+    // Few tiles with many keys behind them leave most of the chip idle for as long as one workgroup takes to walk all of the
+    // keys (0.6 us per block of 32); then the keys are cut, as those of decode rows are, where the partial results have room: into
+    // about 640 workgroups, two to three per compute unit.  us per batch, uncut -> cut (8B shape, eight layers): 32 rows behind 6000
+    // cached keys 1388 -> 859, 100 behind 3000 1269 -> 1087, 300 behind 6000 2526 -> 1883, 600 behind 4000 3127 -> 2989, two chunks of
+    // 32 beside 20 decode rows 1768 -> 1089; 300 rows of the 14B shape, three layers, 1029 -> 787; 200 behind 3000 of the 70B shape 869
+    // either way.  512 and 1024 workgroups are 0 to 3 % slower at 300 rows and 1 % faster at 600; parts of at least 8 blocks 0 to 3 %
+    // slower, of 24 1 to 2 %.
+    int64_t part_blocks = INT32_MAX, cut_slots = 0, cut_rows = 0;
+    if (half_items && whole_wgs > 0) {
+        const int groups = c.n_q_heads / prefill_heads_per_workgroup(c.n_q_heads, c.n_kv_heads, true);
+        int64_t blocks = 0, room = s->max_items;
+        for (int i = 0; i < S; ++i)
+            if (b->new_tokens[i] == 1) room -= ceil_div((int64_t)b->cached_len[i] + 1, part);
+            else for_tiles(i, [&](int, int, int all, int) { blocks += all; });
+        for (part_blocks = std::max<int64_t>(kPrefillMinBlocks, ceil_div(blocks * groups, kPrefillSlots));; part_blocks *= 2) {
+            cut_slots = cut_rows = 0;
+            for (int i = 0; i < S; ++i)
+                if (b->new_tokens[i] > 1) for_tiles(i, [&](int, int rows, int, int full) {
+                    const int parts = parts_of(full, part_blocks);
+                    cut_slots += parts > 1 ? (int64_t)rows * parts : 0;
+                    cut_rows += parts > 1 ? rows : 0;
+                });
+            if (cut_slots <= room) break;
+        }
+    }
     for (int i = 0; i < S; ++i) {
         if (b->new_tokens[i] == 1) cnt_items += ceil_div((int64_t)b->cached_len[i] + 1, part);
         else {
-            cnt_pre += ceil_div(b->new_tokens[i], pre_rows);
+            for_tiles(i, [&](int, int, int, int full) { cnt_pre += parts_of(full, part_blocks); });
             cnt_vt += ((int64_t)b->cached_len[i] + b->new_tokens[i] - 1) / kPage - b->cached_len[i] / kPage + 1;
         }
     }
@@ -613,7 +650,7 @@ gllm_status gllm_stage_forward(gllm_stage* s, const gllm_batch* b, const void* h
         ml.tok_own_v = take((size_t)T * 4);
         ml.bt_flat = take((size_t)total_pages * 4);
         ml.dec_items = take((size_t)cnt_items * sizeof(DecodeItem));
-        ml.dec_rows = take((size_t)n_dec * sizeof(DecodeRow));
+        ml.dec_rows = take((size_t)(n_dec + cut_rows) * sizeof(DecodeRow));
         ml.pre_items = take((size_t)cnt_pre * sizeof(PrefillItem));
         ml.v_tiles = take((size_t)cnt_vt * sizeof(VTile));
         ml.total = off;
@@ -626,8 +663,8 @@ gllm_status gllm_stage_forward(gllm_stage* s, const gllm_batch* b, const void* h
     DecodeItem* dec_items = (DecodeItem*)(st_base + ml.dec_items);
     DecodeRow* dec_rows = (DecodeRow*)(st_base + ml.dec_rows);
     PrefillItem* pre_items = (PrefillItem*)(st_base + ml.pre_items);
-    int n_items = 0, n_rows = 0, n_pre = 0, n_vt = 0;
-    int64_t bt_off = 0, row = 0;
+    int n_items = 0, n_rows = 0, n_pre = 0, n_tiles = 0, n_vt = 0;
+    int64_t bt_off = 0, row = 0, cut_at = 0;
     for (int i = 0; i < S; ++i) {
         const int n = b->new_tokens[i], cl = b->cached_len[i];
         const int32_t* tab = b->block_tables + (int64_t)i * b->block_table_stride;
@@ -661,9 +698,17 @@ gllm_status gllm_stage_forward(gllm_stage* s, const gllm_batch* b, const void* h
             if (n_items - first == 1) s->item_list[first].single = 1;
             else dec_rows[n_rows++] = DecodeRow{(int32_t)row, first, n_items - first, 0};
         } else {
-            for (int t0 = 0; t0 < n; t0 += pre_rows)
-                pre_items[n_pre++] = PrefillItem{(int32_t)(row + t0), std::min(pre_rows, n - t0), cl + t0,
-                                                 (int32_t)bt_off};
+            for_tiles(i, [&](int t0, int rows, int all, int full) {
+                const int parts = parts_of(full, part_blocks);
+                ++n_tiles;
+                for (int p = 0; p < parts; ++p)
+                    pre_items[n_pre++] = PrefillItem{(int32_t)(row + t0), rows, cl + t0, (int32_t)bt_off, full * p / parts,
+                                                     p + 1 < parts ? full * (p + 1) / parts : all, parts, (int32_t)(cnt_items + cut_at + p)};
+                if (parts == 1) return;
+                for (int t = 0; t < rows; ++t)
+                    dec_rows[n_rows++] = DecodeRow{(int32_t)(row + t0 + t), (int32_t)(cnt_items + cut_at + (int64_t)t * parts), parts, 0};
+                cut_at += (int64_t)rows * parts;
+            });
         }
         bt_off += pages;
         row += n;
@@ -671,7 +716,7 @@ gllm_status gllm_stage_forward(gllm_stage* s, const gllm_batch* b, const void* h
     // launch order, both kinds of attention: longest first, so that the last workgroups to start are the shortest
     // (a chunk deep in a long prompt attends to many times the keys of a chunk that starts one)
     std::stable_sort(pre_items, pre_items + n_pre, [](const PrefillItem& x, const PrefillItem& y) {
-        return x.pos0 + x.n_rows > y.pos0 + y.n_rows;
+        return x.blk_end - x.blk_begin > y.blk_end - y.blk_begin;
     });
     for (int i = 0; i < n_items; ++i) s->item_order[i] = i;
     std::stable_sort(s->item_order.begin(), s->item_order.begin() + n_items, [&](int32_t x, int32_t y) {
@@ -742,9 +787,10 @@ gllm_status gllm_stage_forward(gllm_stage* s, const gllm_batch* b, const void* h
         aa.bt_flat = d_bt; aa.out = s->attn; aa.ld_o = s->q_dim;
         aa.n_q = c.n_q_heads; aa.n_kv = c.n_kv_heads; aa.d = d;
         aa.scale_log2 = (float)(1.4426950408889634 / std::sqrt((double)d));
-        const DecodeArgs da{d_items, n_items, s->part_o, s->part_ml, from_qkv, ra};
+        aa.part_o = s->part_o; aa.part_ml = s->part_ml;
+        const DecodeArgs da{d_items, n_items, from_qkv, ra};
         // both kinds of attention read q and the pool and write disjoint rows of attn
-        if (s->overlap_attention && !s->profiling && attention_in_one_launch(aa, n_pre, half_items, n_items)) {
+        if (s->overlap_attention && !s->profiling && attention_in_one_launch(aa, n_tiles, half_items, n_items)) {
             HIP_TRY(s, launch_hybrid_attention(aa, d_pre, n_pre, half_items, da, st));
         } else {
             if (n_pre > 0) {
@@ -756,9 +802,9 @@ gllm_status gllm_stage_forward(gllm_stage* s, const gllm_batch* b, const void* h
                 HIP_TRY(s, launch_decode_attention(aa, da, st));
             }
         }
-        if (n_items > 0) {
+        if (n_items > 0 || n_rows > 0) {
             ProfScope ps(s, st, PC_ATTN_MERGE);
-            HIP_TRY(s, launch_decode_combine(aa, d_rows, n_rows, s->part_o, s->part_ml, st));
+            HIP_TRY(s, launch_decode_combine(aa, d_rows, n_rows, st));
         }
         {
             // the projection writes split_o partial products; the next RMSNorm adds them to the residual stream

@@ -301,8 +301,8 @@ __device__ __forceinline__ f32x4 sum_planes(const f32x4 (&part)[kMaxPlanes], con
 template <int D, bool FROM_QKV>
 __device__ __forceinline__ void decode_workgroup(const AttnArgs& a, const DecodeArgs& dec, int wg, DecodeLds<D, FROM_QKV>& lds) {
     const DecodeItem* __restrict__ items = dec.items;
-    float* __restrict__ part_o = dec.part_o;
-    float* __restrict__ part_ml = dec.part_ml;
+    float* __restrict__ part_o = a.part_o;
+    float* __restrict__ part_ml = a.part_ml;
     // the KV heads of one item are neighbouring workgroups: they run at the same time and read
     // neighbouring 4 KiB pieces of the same pages
     const int kvh = wg % a.n_kv;
@@ -508,8 +508,9 @@ __global__ __launch_bounds__(256, 2) void decode_attention_kernel(AttnArgs a, De
 
 // grid (rows, query heads), D/4 threads: merges the partials of a row in partition order.
 template <int D>
-__global__ void decode_combine_kernel(AttnArgs a, const DecodeRow* __restrict__ rows, const float* __restrict__ part_o,
-                                      const float* __restrict__ part_ml) {
+__global__ void decode_combine_kernel(AttnArgs a, const DecodeRow* __restrict__ rows) {
+    const float* __restrict__ part_o = a.part_o;
+    const float* __restrict__ part_ml = a.part_ml;
     const DecodeRow rw = rows[blockIdx.x];
     const int hq = blockIdx.y, e = threadIdx.x * 4;
     // the partials are read eight at a time (all loads of a batch are issued before the first use: a row has a
@@ -584,6 +585,9 @@ __device__ __forceinline__ void await_lds(u32x4 (&v)[N]) {
 // so a V operand is one 16-byte LDS read of 8 slots of one page; LDS holds the pages as the pool does, except
 // that the second K page is shifted by four slots (see issue_block).
 // Column group cb = NB*wave + c covers head (cb % HW) and query rows 16*(cb / HW) .. +15 of the item.
+// The keys of a tile may be cut into parts, an item each: what the waves hold at the end then goes out as partial results, which
+// decode_combine_kernel merges like those of decode rows.  The cuts lie where every row of the tile sees all keys, so that no
+// part is wholly masked for any of them.
 // ------------------------------------------------------------------------------------------
 typedef const __attribute__((address_space(1))) void* gptr_t;
 typedef __attribute__((address_space(3))) void* lptr_t;
@@ -623,7 +627,7 @@ __device__ __forceinline__ void prefill_workgroup(const AttnArgs& a, const Prefi
             qf[c][s] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(qrow + (s * 4 + G) * 8));
     }
     const int last_pos = it.pos0 + it.n_rows - 1;
-    const int nblk = last_pos / 32 + 1, last_page = last_pos / kPage;
+    const int blk0 = it.blk_begin, blk1 = it.blk_end, last_page = last_pos / kPage;
     const int32_t* bt = a.bt_flat + it.bt_off;
     // wave w brings in piece w of a block: K page 0, K page 1, V page 0, V page 1 (4 x 1 KiB per page at d=128)
     const bf16_t* pool = (wave < 2) ? a.k_pool : a.v_pool;
@@ -683,26 +687,26 @@ __device__ __forceinline__ void prefill_workgroup(const AttnArgs& a, const Prefi
     // every wave always issues its piece (indices past the end re-read the last page into a stage nobody
     // reads), so the count of outstanding loads is the same in every iteration
 #pragma unroll
-    for (int i = 0; i < NS - 1; ++i) issue_block(page_id(i), i);
-    int pid_next = page_id(NS - 1);  // page of block blk + NS - 1, fetched one iteration ahead
+    for (int i = 0; i < NS - 1; ++i) issue_block(page_id(blk0 + i), i);
+    int pid_next = page_id(blk0 + NS - 1);  // page of block blk + NS - 1, fetched one iteration ahead
     auto ring_advance = [&](int blk) {
         // blocks blk+1 .. blk+NS-2 may still be in flight
         asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NS - 2) * IPB) : "memory");
         __syncthreads();  // block blk has landed; nobody reads stage (blk-1) % NS any more
-        issue_block(pid_next, (blk + NS - 1) % NS);
+        issue_block(pid_next, (blk - blk0 + NS - 1) % NS);
         pid_next = page_id(blk + NS);
     };
-    // Two loops with one barrier per block each (every wave passes nblk barriers in total): first the
+    // Two loops with one barrier per block each (every wave passes the same number of barriers in total): first the
     // blocks wholly visible to every row of this wave -- no masks at all, the common case -- then the
     // blocks at the causal edge / the end of the written keys (masked) and the wholly invisible ones (skipped).
-    const int n_full = min((wave_min + 1) / 32, nblk);
-    for (int blk = 0; blk < n_full; ++blk) {
+    const int full1 = max(blk0, min((wave_min + 1) / 32, blk1));
+    for (int blk = blk0; blk < full1; ++blk) {
         ring_advance(blk);
-        block_step(blk % NS, blk * 32, std::false_type{});
+        block_step((blk - blk0) % NS, blk * 32, std::false_type{});
     }
-    for (int blk = n_full; blk < nblk; ++blk) {
+    for (int blk = full1; blk < blk1; ++blk) {
         ring_advance(blk);
-        if (blk * 32 <= wave_max) block_step(blk % NS, blk * 32, std::true_type{});
+        if (blk * 32 <= wave_max) block_step((blk - blk0) % NS, blk * 32, std::true_type{});
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // no LDS fill may outlive the workgroup
 #pragma unroll
@@ -710,10 +714,18 @@ __device__ __forceinline__ void prefill_workgroup(const AttnArgs& a, const Prefi
         float l = st.l[c];
         l += __shfl_xor(l, 16);
         l += __shfl_xor(l, 32);
-        const float inv = 1.0f / l;
         const int cb = wave * NB + c;
         const int qi = (cb / HW) * 16 + r;
-        if (qi < it.n_rows) {
+        if (qi < it.n_rows && it.parts > 1) {
+            const int64_t slot = (int64_t)(it.slot0 + qi * it.parts) * a.n_q + head0 + cb % HW;
+#pragma unroll
+            for (int b = 0; b < D / 16; ++b) *reinterpret_cast<f32x4*>(a.part_o + slot * D + b * 16 + G * 4) = st.o[c][b];
+            if (G == 0) {
+                a.part_ml[slot * 2] = st.m[c];
+                a.part_ml[slot * 2 + 1] = l;
+            }
+        } else if (qi < it.n_rows) {
+            const float inv = 1.0f / l;
             bf16_t* orow = a.out + (int64_t)(it.row0 + qi) * a.ld_o + (int64_t)(head0 + cb % HW) * D;
 #pragma unroll
             for (int b = 0; b < D / 16; ++b) {
@@ -759,12 +771,11 @@ hipError_t launch_decode_attention(const AttnArgs& a, const DecodeArgs& dec, hip
     return hipGetLastError();
 }
 
-hipError_t launch_decode_combine(const AttnArgs& a, const DecodeRow* rows, int num_rows, const float* part_o,
-                                 const float* part_ml, hipStream_t stream) {
+hipError_t launch_decode_combine(const AttnArgs& a, const DecodeRow* rows, int num_rows, hipStream_t stream) {
     if (num_rows <= 0) return hipSuccess;
     dim3 grid(num_rows, a.n_q);
-    if (a.d == 128) decode_combine_kernel<128><<<grid, 32, 0, stream>>>(a, rows, part_o, part_ml);
-    else if (a.d == 64) decode_combine_kernel<64><<<grid, 16, 0, stream>>>(a, rows, part_o, part_ml);
+    if (a.d == 128) decode_combine_kernel<128><<<grid, 32, 0, stream>>>(a, rows);
+    else if (a.d == 64) decode_combine_kernel<64><<<grid, 16, 0, stream>>>(a, rows);
     else return hipErrorInvalidValue;
     return hipGetLastError();
 }
@@ -808,9 +819,9 @@ hipError_t launch_prefill_attention(const AttnArgs& a, const PrefillItem* items,
 // comes out -- from one launch, in either order or interleaved, and from two streams (whose events cost 13 us on top).
 constexpr int kHybridPrefillMax = 64;
 
-bool attention_in_one_launch(const AttnArgs& a, int num_items, bool half, int num_decode_items) {
-    return num_items > 0 && num_decode_items > 0 &&
-           num_items * (a.n_q / prefill_heads_per_workgroup(a.n_q, a.n_kv, half)) <= (half ? 2 : 1) * kHybridPrefillMax;
+bool attention_in_one_launch(const AttnArgs& a, int num_tiles, bool half, int num_decode_items) {
+    return num_tiles > 0 && num_decode_items > 0 &&
+           num_tiles * (a.n_q / prefill_heads_per_workgroup(a.n_q, a.n_kv, half)) <= (half ? 2 : 1) * kHybridPrefillMax;
 }
 
 hipError_t launch_hybrid_attention(const AttnArgs& a, const PrefillItem* items, int num_items, bool half, const DecodeArgs& dec, hipStream_t stream) {

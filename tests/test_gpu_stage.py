@@ -594,6 +594,29 @@ def test_batches_of_decode_rows_at_page_block_and_partition_edges(n_q, n_kv, d, 
     check_pool("V", r["gv"], vp0, r["vp"], shape.num_layers, mask=mv)
 
 
+LONG_PREFIXES = [(20, 1100), (1, 700), (5, 1500), (33, 1023), (16, 2047), (2, 1007), (64, 991), (17, 0), (1, 0)]
+
+
+@pytest.mark.parametrize("n_q,n_kv,d,hidden,seqs", [
+    (2, 2, 128, 256, LONG_PREFIXES), (6, 2, 64, 256, LONG_PREFIXES), (4, 2, 128, 256, LONG_PREFIXES), (8, 2, 64, 512, LONG_PREFIXES), (8, 1, 128, 256, LONG_PREFIXES),
+    (8, 1, 64, 256, [(3, 3001), (130, 1200)]),                     # chunks alone
+    (2, 1, 128, 256, [(900, 1100), (40, 1600)]),                   # more parts than the partial results have room for
+])
+def test_chunks_behind_long_prefixes(n_q, n_kv, d, hidden, seqs):
+    """The keys of a few chunk rows are cut into parts, from two (1024 keys that all rows of a tile see) to many, beside decode rows
+    that are cut too, at every head grouping; tiles of one row and of all, prefixes that end at and inside pages and blocks."""
+    print(f"long prefixes n_q={n_q} n_kv={n_kv} d={d} rows={sum(n for n, _ in seqs)}", flush=True)
+    shape = synth.StageShape("long", 1, hidden, n_q, n_kv, d, 384)
+    batch = synth.build_batch(seqs, 61, spare_blocks=3)
+    w = layer_weights_np(shape, 61)
+    kp0, vp0 = sentinel_pool_with_prefixes(shape, batch, 61)
+    r = run_both(shape, w, batch, kp0, vp0, hidden_np(shape, 61, batch.num_tokens))
+    assert_output("long prefixes", r, literal=False)
+    mk, mv = written_mask(shape, batch)
+    check_pool("K", r["gk"], kp0, r["kp"], shape.num_layers, mask=mk)
+    check_pool("V", r["gv"], vp0, r["vp"], shape.num_layers, mask=mv)
+
+
 @pytest.mark.parametrize("hidden,planes", [(1536, 3), (2560, 5), (3072, 6), (3584, 7)])
 def test_plane_counts_that_are_no_powers_of_two(hidden, planes):
     """QKV and down projections split 3, 5, 6 and 7 ways: the planes are summed by RoPE and KV write (with bias; V runs at page
