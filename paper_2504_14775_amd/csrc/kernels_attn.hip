@@ -627,7 +627,9 @@ __device__ __forceinline__ void prefill_workgroup(const AttnArgs& a, const Prefi
             qf[c][s] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(qrow + (s * 4 + G) * 8));
     }
     const int last_pos = it.pos0 + it.n_rows - 1;
-    const int blk0 = it.blk_begin, blk1 = it.blk_end, last_page = last_pos / kPage;
+    // (only items of half the rows are cut; whole ones, which fill the chip, have no registers to spare for it)
+    constexpr bool CUT = NB == 1;
+    const int blk0 = CUT ? it.blk_begin : 0, blk1 = CUT ? it.blk_end : last_pos / 32 + 1, last_page = last_pos / kPage;
     const int32_t* bt = a.bt_flat + it.bt_off;
     // wave w brings in piece w of a block: K page 0, K page 1, V page 0, V page 1 (4 x 1 KiB per page at d=128)
     const bf16_t* pool = (wave < 2) ? a.k_pool : a.v_pool;
@@ -716,7 +718,7 @@ __device__ __forceinline__ void prefill_workgroup(const AttnArgs& a, const Prefi
         l += __shfl_xor(l, 32);
         const int cb = wave * NB + c;
         const int qi = (cb / HW) * 16 + r;
-        if (qi < it.n_rows && it.parts > 1) {
+        if (CUT && qi < it.n_rows && it.parts > 1) {
             const int64_t slot = (int64_t)(it.slot0 + qi * it.parts) * a.n_q + head0 + cb % HW;
 #pragma unroll
             for (int b = 0; b < D / 16; ++b) *reinterpret_cast<f32x4*>(a.part_o + slot * D + b * 16 + G * 4) = st.o[c][b];
