@@ -677,9 +677,9 @@ double plane_us(int m, int n, int mode, int splits) { return mode == GEMM_STORE_
 // Up to 64 rows: tiles of 128 or 64 columns, a round of one per compute unit (a second one on it halves the pace of both), so
 // that the tiles should come to just under a multiple of 256: 40 x 6 for 5120 x 27648, not 40 x 8 (64 rows 62.3 -> 46.1 us), 64
 // x 4 of half the width for 4096 x 4096, not 32 x 8 (64 rows 11.1 -> 9.2, one row 8.0 -> 7.1: half the planes too).  Fitted to
-// products of 1024 to 12288 columns and k of 1024 to 28672, and the vocabularies, at 1 to 64 rows (721, every factor and width):
-// 0.44 % behind the fastest form on average, more than 5 % in 18, 14 % at most (12288 x 8192, one row); fitted to three quarters
-// 0.53 % on the rest.  Factors of 1, 2, 4 and 8 and 128 columns alone took 1.095 times as long.
+// products of 1024 to 12288 columns and k of 1024 to 28672, and the vocabularies, at 1 to 64 rows (700, every factor and width,
+// profiles/gemm_plan_up_to_64_rows.txt): 0.45 % behind the fastest form on average, more than 5 % in 18, 14 % at most (12288 x
+// 8192, one row); fitted to three quarters 0.53 % on the rest.  Factors of 1, 2, 4 and 8 and 128 columns alone: 9.5 % behind.
 constexpr TileCost kCostSkinny128[2] = {{256, 128, 0.544, 2.756, {0.374, 0.449, 1}, 0.646, 2.319, 7.97}, {256, 128, 0.556, 3.181, {0.536, 0.648, 1}, 0.091, 1.997, 7.789}},
                    kCostSkinny64[2] = {{256, 64, 0.29, 2.625, {0.467, 0.414, 0.618}, 0.166, 3.244, 9}, {256, 64, 0.319, 2.257, {0.856, 0.629, 0.616}, 0, 3.343, 9}};
 double skinny_us(const TileCost& c, int m, int n, int k, int mode, int splits) {
