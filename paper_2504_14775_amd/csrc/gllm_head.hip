@@ -561,8 +561,13 @@ __global__ __launch_bounds__(kSampleThreads, ROOMY ? 4 : 8) void sample_kernel(c
 
     // Finishes the row on the list of n candidates; false when the guess of a nucleus does not hold.
     auto finish_on_list = [&](int n, float others) -> bool {
-        // keys relative to that of the bound, below which nothing is listed: 24 or 25 bits, two digits instead of three
-        const uint32_t key_lo = float_key(bound / temp), key_span = float_key(best / temp) - key_lo;
+        // Keys relative to that of the bound, below which nothing is listed: 24 bits, and so two digits instead of three, where
+        // the largest logit is less than about four times the bound (wider ranges take the three of whole keys).  Zeros compare
+        // equal, so both are listed with a bound that is one, and either may be the largest logit: the range holds the keys of
+        // both.  (A bound of -infinity over an infinite temperature is no number.)
+        const float z_lo = bound / temp, z_hi = best / temp;
+        const uint32_t key_lo = z_lo == 0.f ? float_key(-0.f) : z_lo == z_lo ? float_key(z_lo) : 0u;
+        const uint32_t key_span = float_key(z_hi == 0.f ? 0.f : z_hi) - key_lo;
         const int key_bits = 32 - __clz((int)key_span);  // (0 bits: all keys are equal)
         uint32_t key[kPerThread], ikey[kPerThread];
         uint64_t weight[kPerThread];

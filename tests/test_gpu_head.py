@@ -219,6 +219,33 @@ def test_sampler_around_64_candidates(k, rows):
     check_against_oracle(lg, temp, np.full(rows, k, np.int32), p, rng.random(rows).astype(np.float32), f"k={k}")
 
 
+@pytest.mark.parametrize("k,p", [(5, 1.0), (5, 0.9), (4, 1.0), (6, 1.0), (300, 1.0), (0, 0.9)])
+@pytest.mark.parametrize("V", [1000, 5003, 20000, 20001])             # both sides of the 16384 of the first list, rows off the 16-byte grid
+def test_sampler_with_signed_zeros(V, k, p):
+    """Five positive logits in different threads, the others -0 (what multiplying negative logits by a mask of zeros leaves), or
+    -0 with some +0 where the k-th largest is positive: a zero of either sign is neither above the positive logits nor outside
+    the range of the keys, at temperatures at which the first bound on the logits is +0, at others, and at an infinite one."""
+    print(f"sampler: signed zeros V={V} k={k} p={p}", flush=True)
+    M = 24
+    g = torch.Generator().manual_seed(V + k)
+    rng = np.random.default_rng(V + k)
+    lg = torch.full((M, V), -0.0)
+    for r in range(M):
+        at = torch.arange(5) * 90 + 3 + torch.randint(0, 100, (1,), generator=g)
+        lg[r, at] = 0.10 + 0.01 * torch.randperm(5, generator=g)
+        if r % 3 == 1: lg[r, V // 2:] = -torch.rand(V - V // 2, generator=g) - 1.0
+        if r % 3 == 2 and 0 < k <= 5: lg[r, 600::2] = 0.0
+    temp = rng.choice([0.005, 0.02, 0.1, 0.25, 1.0], size=M).astype(np.float32)
+    if k not in (4, 5): temp[3::8] = np.inf                           # (all of a row as probable as the largest)
+    if p == 1.0 and k > 5:
+        lg[:3] = -0.0                                                  # nothing but zeros, and the largest at either sign
+        lg[1, V // 3] = 0.0
+        lg[2, :V // 2] = -1.0
+    u = rng.random(M).astype(np.float32)
+    u[0], u[1] = 0.0, np.float32(1.0 - 2 ** -24)
+    check_against_oracle(lg, temp, np.full(M, k, np.int32), np.full(M, p, np.float32), u, f"signed zeros V={V} k={k} p={p}")
+
+
 def largest(row):
     """Lowest index of the largest logit, NaN left out; 0 when no logit lies above -infinity."""
     return int(np.argmax(np.where(np.isnan(row), -np.inf, row)))
