@@ -546,7 +546,9 @@ __global__ __launch_bounds__(kSampleThreads, ROOMY ? 4 : 8) void sample_kernel(c
             if (above >= nucleus_need(p, total)) weight = 0;
             total = lane_value(wave_scan(weight), 63);
         }
-        sh.few[lane].weight = weight;  // (read back by this wave only, which LDS serves in order)
+        sh.few[lane].weight = weight;  // read back by other lanes of this wave, which LDS serves in order; the fence keeps
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // the compiler from using what it read above (no instruction)
+        __builtin_amdgcn_wave_barrier();
         const uint64_t need = draw_need(u, total);
         uint64_t before = 0;
         for (int i = 0; i < n; i += kFewStep) {
