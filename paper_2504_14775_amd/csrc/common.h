@@ -198,8 +198,8 @@ struct PrefillItem {
     int32_t slot0;     // partial results of row i of the tile: slot0 + i * parts
 };
 hipError_t launch_prefill_attention(const AttnArgs& a, const PrefillItem* items, int num_items, bool half, hipStream_t stream);
-// Prefill and decode items of one batch in one launch, and whether that pays.
-bool attention_in_one_launch(const AttnArgs& a, int num_tiles, bool half, int num_decode_items);
+// Prefill and decode items of one batch in one launch, and whether that pays (num_tiles: prefill items with their keys in one part).
+bool attention_in_one_launch(int n_q, int n_kv, int64_t num_tiles, bool half, int num_decode_rows);
 hipError_t launch_hybrid_attention(const AttnArgs& a, const PrefillItem* items, int num_items, bool half, const DecodeArgs& dec, hipStream_t stream);
 
 // Ceiling probes (see kernels_peak.hip).  peak_mfma: workgroups x 4 waves x iters x 16 MFMAs of

@@ -43,6 +43,7 @@ constexpr int kStagingSlots = 4;
 constexpr int kHalfItemsMax = 256;  // workgroups of whole prefill items
 constexpr int kPrefillSlots = 640;  // workgroups that the prefill items are cut into where there are fewer
 constexpr int kPrefillMinBlocks = 16;  // fewest key blocks (of 32) in a part of a prefill item
+constexpr int64_t kHidingBytes = 9400000;  // keys and values of decode rows that are read while a workgroup beside them takes a block
 constexpr int kDecodeSlots = 512;  // decode attention workgroups that run at one time
 constexpr int kMaxSplits = kMaxPlanes;
 
@@ -597,6 +598,10 @@ gllm_status gllm_stage_forward(gllm_stage* s, const gllm_batch* b, const void* h
     whole_wgs *= c.n_q_heads / prefill_heads_per_workgroup(c.n_q_heads, c.n_kv_heads, false);
     const bool half_items = whole_wgs <= kHalfItemsMax;
     const int pre_rows = prefill_item_rows(c.n_q_heads, c.n_kv_heads, half_items);
+    int64_t n_tiles = 0;
+    for (int i = 0; i < S; ++i)
+        if (b->new_tokens[i] > 1) n_tiles += ceil_div(b->new_tokens[i], pre_rows);
+    const bool one_launch = attention_in_one_launch(c.n_q_heads, c.n_kv_heads, n_tiles, half_items, n_dec);
     // f(first row, rows, key blocks, those of them that every row of it sees) for each prefill tile of sequence i
     auto for_tiles = [&](int i, auto&& f) {
         const int n = b->new_tokens[i], cl = b->cached_len[i];
@@ -605,23 +610,32 @@ gllm_status gllm_stage_forward(gllm_stage* s, const gllm_batch* b, const void* h
             f(t0, rows, (cl + t0 + rows - 1) / 32 + 1, (cl + t0 + 1) / 32);
         }
     };
-    // parts of a tile's keys, at most `len` blocks each but for the last, which also takes those at the causal edge
+    // parts of a tile's keys, of at most `len` blocks each (up to 31 where more would be shorter than kPrefillMinBlocks); the last also
+    // takes the blocks at the causal edge
     auto parts_of = [&](int full, int64_t len) { return (int)std::max<int64_t>(1, std::min<int64_t>(ceil_div(full, len), full / kPrefillMinBlocks)); };
     // Few tiles with many keys behind them leave most of the chip idle for as long as one workgroup takes to walk all of the
     // keys (0.6 us per block of 32); then the keys are cut, as those of decode rows are, where the partial results have room: into
-    // about 640 workgroups, two to three per compute unit.  us per batch, uncut -> cut (8B shape, eight layers): 32 rows behind 6000
+    // 640 workgroups, two to three per compute unit, and up to one more for every tile and group of heads.  us per batch, uncut -> cut (8B shape, eight layers): 32 rows behind 6000
     // cached keys 1388 -> 859, 100 behind 3000 1269 -> 1087, 300 behind 6000 2526 -> 1883, 600 behind 4000 3127 -> 2989, two chunks of
     // 32 beside 20 decode rows 1768 -> 1089; 300 rows of the 14B shape, three layers, 1029 -> 787; 200 behind 3000 of the 70B shape 869
     // either way.  512 and 1024 workgroups are 0 to 3 % slower at 300 rows and 1 % faster at 600; parts of at least 8 blocks 0 to 3 %
     // slower, of 24 1 to 2 %.
+    // In one launch with decode rows a tile hides behind the stream of their keys, where a block takes about 1.45 us; a part need
+    // not be shorter than that stream (6.5 TB/s): more workgroups would only wait in the same queues, and their results are to be
+    // merged.  us per batch, 8B shape, two layers, uncut / cut to 640 workgroups / to this length: 32 rows behind 6000 keys beside 20
+    // rows of 2300 keys 408 / 285 / 285, beside 128 731 / 703 / 686, beside 256 1139 / 1178 / 1138; 128 rows behind 6000 beside 64
+    // 614 / 575 / 521, beside 256 1197 / 1292 / 1197; 128 behind 1200 beside 64 497 / 516 / 497.
     int64_t part_blocks = INT32_MAX, cut_slots = 0, cut_rows = 0;
     if (half_items && whole_wgs > 0) {
         const int groups = c.n_q_heads / prefill_heads_per_workgroup(c.n_q_heads, c.n_kv_heads, true);
-        int64_t blocks = 0, room = s->max_items;
+        int64_t blocks = 0, room = s->max_items, dec_keys = 0;
         for (int i = 0; i < S; ++i)
-            if (b->new_tokens[i] == 1) room -= ceil_div((int64_t)b->cached_len[i] + 1, part);
-            else for_tiles(i, [&](int, int, int all, int) { blocks += all; });
-        for (part_blocks = std::max<int64_t>(kPrefillMinBlocks, ceil_div(blocks * groups, kPrefillSlots));; part_blocks *= 2) {
+            if (b->new_tokens[i] == 1) {
+                room -= ceil_div((int64_t)b->cached_len[i] + 1, part);
+                dec_keys += (int64_t)b->cached_len[i] + 1;
+            } else for_tiles(i, [&](int, int, int all, int) { blocks += all; });
+        const int64_t hidden = one_launch ? dec_keys * s->kv_dim * 4 / kHidingBytes : 0;
+        for (part_blocks = std::max({(int64_t)kPrefillMinBlocks, hidden, ceil_div(blocks * groups, kPrefillSlots)});; part_blocks *= 2) {
             cut_slots = cut_rows = 0;
             for (int i = 0; i < S; ++i)
                 if (b->new_tokens[i] > 1) for_tiles(i, [&](int, int rows, int, int full) {
@@ -663,7 +677,7 @@ gllm_status gllm_stage_forward(gllm_stage* s, const gllm_batch* b, const void* h
     DecodeItem* dec_items = (DecodeItem*)(st_base + ml.dec_items);
     DecodeRow* dec_rows = (DecodeRow*)(st_base + ml.dec_rows);
     PrefillItem* pre_items = (PrefillItem*)(st_base + ml.pre_items);
-    int n_items = 0, n_rows = 0, n_pre = 0, n_tiles = 0, n_vt = 0;
+    int n_items = 0, n_rows = 0, n_pre = 0, n_vt = 0;
     int64_t bt_off = 0, row = 0, cut_at = 0;
     for (int i = 0; i < S; ++i) {
         const int n = b->new_tokens[i], cl = b->cached_len[i];
@@ -700,10 +714,9 @@ gllm_status gllm_stage_forward(gllm_stage* s, const gllm_batch* b, const void* h
         } else {
             for_tiles(i, [&](int t0, int rows, int all, int full) {
                 const int parts = parts_of(full, part_blocks);
-                ++n_tiles;
                 for (int p = 0; p < parts; ++p)
-                    pre_items[n_pre++] = PrefillItem{(int32_t)(row + t0), rows, cl + t0, (int32_t)bt_off, full * p / parts,
-                                                     p + 1 < parts ? full * (p + 1) / parts : all, parts, (int32_t)(cnt_items + cut_at + p)};
+                    pre_items[n_pre++] = PrefillItem{(int32_t)(row + t0), rows, cl + t0, (int32_t)bt_off, (int32_t)((int64_t)full * p / parts),
+                                                     p + 1 < parts ? (int32_t)((int64_t)full * (p + 1) / parts) : all, parts, (int32_t)(cnt_items + cut_at + p)};
                 if (parts == 1) return;
                 for (int t = 0; t < rows; ++t)
                     dec_rows[n_rows++] = DecodeRow{(int32_t)(row + t0 + t), (int32_t)(cnt_items + cut_at + (int64_t)t * parts), parts, 0};
@@ -790,7 +803,7 @@ gllm_status gllm_stage_forward(gllm_stage* s, const gllm_batch* b, const void* h
         aa.part_o = s->part_o; aa.part_ml = s->part_ml;
         const DecodeArgs da{d_items, n_items, from_qkv, ra};
         // both kinds of attention read q and the pool and write disjoint rows of attn
-        if (s->overlap_attention && !s->profiling && attention_in_one_launch(aa, n_tiles, half_items, n_items)) {
+        if (s->overlap_attention && !s->profiling && one_launch) {
             HIP_TRY(s, launch_hybrid_attention(aa, d_pre, n_pre, half_items, da, st));
         } else {
             if (n_pre > 0) {
