@@ -41,7 +41,7 @@ struct LayerBuffers {
 
 constexpr int kStagingSlots = 4;
 constexpr int kHalfItemsMax = 256;  // workgroups of whole prefill items
-constexpr int kPrefillSlots = 640;  // workgroups that the prefill items are cut into where there are fewer
+constexpr int kPrefillSlots = 768;  // prefill attention workgroups that run at one time, three per compute unit
 constexpr int kPrefillMinBlocks = 16;  // fewest key blocks (of 32) in a part of a prefill item
 constexpr int64_t kHidingBytes = 9400000;  // keys and values of decode rows that are read while a workgroup beside them takes a block
 constexpr int kDecodeSlots = 512;  // decode attention workgroups that run at one time
@@ -504,6 +504,17 @@ gllm_status gllm_stage_read_profile(gllm_stage* s, double* ms, int64_t* launches
     return GLLM_OK;
 }
 
+// Whether prefill attention is done clearly earlier with its keys in parts, from `wg_blocks` key blocks of all workgroups, those of
+// the longest one with and without parts, and the partial results.  us at 128 dims, at 64 about 0.8 of it: a workgroup walks a block
+// in 0.42 to 0.49 up to 288 chunk rows, in 0.56 to 0.69 from 300 (on four shapes, with 64 to 504 workgroups and the same clock; why
+// there is not known); all of them together take no less than 0.95e-3 and 1.5e-3 a block.  The merge is a launch, and the partial
+// results are written and read at 4 TB/s.
+static bool worth_cutting(const gllm_stage_config& c, int64_t rows, int64_t wg_blocks, int64_t longest, int64_t longest_part, int64_t slots) {
+    const double scale = c.head_dim == 128 ? 1.0 : 0.8, block = rows > 288 ? 0.68 : 0.42, block_of_all = rows > 288 ? 1.5e-3 : 0.95e-3;
+    const double merge = 4.0 + (double)slots * c.n_q_heads * c.head_dim * 8.0 / 4e6;
+    return scale * std::max(block * longest_part, block_of_all * wg_blocks) + merge < 0.9 * scale * block * longest;
+}
+
 gllm_status gllm_stage_forward(gllm_stage* s, const gllm_batch* b, const void* hidden_in, void* hidden_out,
                                float* hidden_out_f32, void* stream_) {
     if (!s) return GLLM_E_INVALID;
@@ -614,37 +625,48 @@ gllm_status gllm_stage_forward(gllm_stage* s, const gllm_batch* b, const void* h
     // takes the blocks at the causal edge
     auto parts_of = [&](int full, int64_t len) { return (int)std::max<int64_t>(1, std::min<int64_t>(ceil_div(full, len), full / kPrefillMinBlocks)); };
     // Few tiles with many keys behind them leave most of the chip idle for as long as one workgroup takes to walk all of the
-    // keys (0.6 us per block of 32); then the keys are cut, as those of decode rows are, where the partial results have room: into
-    // 640 workgroups, two to three per compute unit, and up to one more for every tile and group of heads.  us per batch, uncut -> cut (8B shape, eight layers): 32 rows behind 6000
-    // cached keys 1388 -> 859, 100 behind 3000 1269 -> 1087, 300 behind 6000 2526 -> 1883, 600 behind 4000 3127 -> 2989, two chunks of
-    // 32 beside 20 decode rows 1768 -> 1089; 300 rows of the 14B shape, three layers, 1029 -> 787; 200 behind 3000 of the 70B shape 869
-    // either way.  512 and 1024 workgroups are 0 to 3 % slower at 300 rows and 1 % faster at 600; parts of at least 8 blocks 0 to 3 %
-    // slower, of 24 1 to 2 %.
+    // keys; then the keys are cut, as those of decode rows are, where the partial results have room: into no more workgroups than
+    // run at one time, and only where that saves more than the merge costs (see worth_cutting).  us per batch, 8B shape, two
+    // layers, uncut / cut into 640 workgroups and up to one more for every tile / now: 32 rows behind 6000 cached keys 365 / 228 / 228,
+    // 300 behind 6000 611 / 457 / 456, 600 behind 3000 723 / 709 / 693, 1000 behind 1300 899 / 917 / 902; 70B, one layer, 200 behind
+    // 6000 478 / 463 / 466, 500 behind 3000 818 / 855 / 828; 14B, one layer, 600 behind 1300 394 / 413 / 397.  Parts of at least 8
+    // blocks are 0 to 3 % slower, of 24 1 to 2 %.
     // In one launch with decode rows a tile hides behind the stream of their keys, where a block takes about 1.45 us; a part need
     // not be shorter than that stream (6.5 TB/s): more workgroups would only wait in the same queues, and their results are to be
     // merged.  us per batch, 8B shape, two layers, uncut / cut to 640 workgroups / to this length: 32 rows behind 6000 keys beside 20
     // rows of 2300 keys 408 / 285 / 285, beside 128 731 / 703 / 686, beside 256 1139 / 1178 / 1138; 128 rows behind 6000 beside 64
     // 614 / 575 / 521, beside 256 1197 / 1292 / 1197; 128 behind 1200 beside 64 497 / 516 / 497.
     int64_t part_blocks = INT32_MAX, cut_slots = 0, cut_rows = 0;
-    if (half_items && whole_wgs > 0) {
+    if (half_items && n_tiles > 0) {
         const int groups = c.n_q_heads / prefill_heads_per_workgroup(c.n_q_heads, c.n_kv_heads, true);
-        int64_t blocks = 0, room = s->max_items, dec_keys = 0;
+        int64_t blocks = 0, longest = 0, most_full = 0, room = s->max_items, dec_keys = 0;
         for (int i = 0; i < S; ++i)
             if (b->new_tokens[i] == 1) {
                 room -= ceil_div((int64_t)b->cached_len[i] + 1, part);
                 dec_keys += (int64_t)b->cached_len[i] + 1;
-            } else for_tiles(i, [&](int, int, int all, int) { blocks += all; });
+            } else for_tiles(i, [&](int, int, int all, int full) {
+                blocks += all;
+                longest = std::max<int64_t>(longest, all);
+                most_full = std::max<int64_t>(most_full, full);
+            });
         const int64_t hidden = one_launch ? dec_keys * s->kv_dim * 4 / kHidingBytes : 0;
-        for (part_blocks = std::max({(int64_t)kPrefillMinBlocks, hidden, ceil_div(blocks * groups, kPrefillSlots)});; part_blocks *= 2) {
+        int64_t len = std::max({(int64_t)kPrefillMinBlocks, hidden, ceil_div(blocks * groups, kPrefillSlots)});
+        for (; parts_of((int)most_full, len) > 1; len += ceil_div(len, 8)) {
+            int64_t items = 0, longest_part = 0;
             cut_slots = cut_rows = 0;
             for (int i = 0; i < S; ++i)
-                if (b->new_tokens[i] > 1) for_tiles(i, [&](int, int rows, int, int full) {
-                    const int parts = parts_of(full, part_blocks);
+                if (b->new_tokens[i] > 1) for_tiles(i, [&](int, int rows, int all, int full) {
+                    const int parts = parts_of(full, len);
+                    items += parts;
+                    longest_part = std::max<int64_t>(longest_part, all - full + ceil_div(full, parts));
                     cut_slots += parts > 1 ? (int64_t)rows * parts : 0;
                     cut_rows += parts > 1 ? rows : 0;
                 });
-            if (cut_slots <= room) break;
+            if (items * groups > kPrefillSlots || cut_slots > room) continue;
+            if (worth_cutting(c, T - n_dec, blocks * groups, longest, longest_part, cut_slots)) part_blocks = len;
+            break;
         }
+        if (part_blocks == INT32_MAX) cut_slots = cut_rows = 0;
     }
     for (int i = 0; i < S; ++i) {
         if (b->new_tokens[i] == 1) cnt_items += ceil_div((int64_t)b->cached_len[i] + 1, part);
