@@ -597,24 +597,65 @@ def test_batches_of_decode_rows_at_page_block_and_partition_edges(n_q, n_kv, d, 
 LONG_PREFIXES = [(20, 1100), (1, 700), (5, 1500), (33, 1023), (16, 2047), (2, 1007), (64, 991), (17, 0), (1, 0)]
 
 
-@pytest.mark.parametrize("n_q,n_kv,d,hidden,seqs", [
-    (2, 2, 128, 256, LONG_PREFIXES), (6, 2, 64, 256, LONG_PREFIXES), (4, 2, 128, 256, LONG_PREFIXES), (8, 2, 64, 512, LONG_PREFIXES), (8, 1, 128, 256, LONG_PREFIXES),
-    (8, 1, 64, 256, [(3, 3001), (130, 1200)]),                     # chunks alone
-    (2, 1, 128, 256, [(900, 1100), (40, 1600)]),                   # more parts than the partial results have room for
+def cuts_of_chunk_keys(shape, seqs, min_wgs):
+    """What the stage's host code does with the keys of chunks (half-row tiles, a stage sized for this batch): parts per tile at the
+    first length tried and at the one taken, partial results of the first and the room for them."""
+    n_q, n_kv, d = shape.n_q_heads, shape.n_kv_heads, shape.head_dim
+    hw = {1: 1, 2: 2, 4: 4, 8: 4}.get(n_q // n_kv, 1)
+    step, groups = 64 // hw, n_q // hw
+    tiles = [(min(step, n - t), (c + t + min(step, n - t) - 1) // 32 + 1, (c + t + 1) // 32) for n, c in seqs if n > 1 for t in range(0, n, step)]
+    keys = [c + 1 for n, c in seqs if n == 1]
+    rows = sum(n for n, _ in seqs if n > 1)
+    partition = 256 if min_wgs else max(256, -(-(-(-sum(keys) * n_kv * 3 // 1024)) // 32) * 32)
+    room = 4 * len(seqs) + 1024 + min(4 * (rows + len(keys)), 2048) - sum(-(-k // partition) for k in keys)
+    blocks = groups * sum(a for _, a, _ in tiles)
+    hidden = sum(keys) * n_kv * d * 4 // 9400000 if keys and len(tiles) * groups <= 128 else 0
+    length, first, taken = max(16, hidden, -(-blocks // 768)), None, [1] * len(tiles)
+    while True:
+        parts = [max(1, min(-(-full // length), full // 16)) for _, _, full in tiles]
+        slots = sum(r * p for (r, _, _), p in zip(tiles, parts) if p > 1)
+        first = first or (parts, slots)
+        if max(parts) == 1: break
+        if sum(parts) * groups <= 768 and slots <= room:
+            block, of_all, scale = (0.68, 1.5e-3, 1 if d == 128 else 0.8) if rows > 288 else (0.42, 0.95e-3, 1 if d == 128 else 0.8)
+            longest = max(a - full + -(-full // p) for (_, a, full), p in zip(tiles, parts))
+            if scale * max(block * longest, of_all * blocks) + 4 + slots * n_q * d * 2e-6 < 0.9 * scale * block * max(a for _, a, _ in tiles):
+                taken = parts
+            break
+        length += -(-length // 8)
+    return first[0], taken, first[1], room
+
+
+@pytest.mark.parametrize("n_q,n_kv,d,hidden,seqs,min_wgs", [
+    (2, 2, 128, 256, LONG_PREFIXES, 0), (6, 2, 64, 256, LONG_PREFIXES, 0), (4, 2, 128, 256, LONG_PREFIXES, 0), (8, 2, 64, 512, LONG_PREFIXES, 0),
+    (8, 1, 128, 256, LONG_PREFIXES, 0),
+    (8, 1, 64, 256, [(3, 3001), (130, 1200)], 0),                  # chunks alone
+    (2, 1, 128, 256, [(900, 1100), (40, 1600)], 0),
+    (2, 1, 128, 256, [(1400, 1600)], 0),                           # more parts than the partial results have room for
+    (2, 1, 64, 256, [(200, 6000)] + [(1, 2000)] * 64, 10 ** 6),    # the same because decode rows take room: 512 work items
 ])
-def test_chunks_behind_long_prefixes(n_q, n_kv, d, hidden, seqs):
+def test_chunks_behind_long_prefixes(n_q, n_kv, d, hidden, seqs, min_wgs):
     """The keys of a few chunk rows are cut into parts, from two (1024 keys that all rows of a tile see) to many, beside decode rows
-    that are cut too, at every head grouping; tiles of one row and of all, prefixes that end at and inside pages and blocks."""
+    that are cut too, at every head grouping; tiles of one row and of all, prefixes that end at and inside pages and blocks.  In a
+    batch without decode rows the merge is launched for the cut rows alone."""
     print(f"long prefixes n_q={n_q} n_kv={n_kv} d={d} rows={sum(n for n, _ in seqs)}", flush=True)
     shape = synth.StageShape("long", 1, hidden, n_q, n_kv, d, 384)
+    first, parts, slots, room = cuts_of_chunk_keys(shape, seqs, min_wgs)
+    assert max(parts) > 1 and (slots > room) == (seqs[0][0] in (200, 1400)), (parts, slots, room)
     batch = synth.build_batch(seqs, 61, spare_blocks=3)
     w = layer_weights_np(shape, 61)
     kp0, vp0 = sentinel_pool_with_prefixes(shape, batch, 61)
-    r = run_both(shape, w, batch, kp0, vp0, hidden_np(shape, 61, batch.num_tokens))
+    stage = GpuStage(shape, w, [batch])
+    stage.stage.set_option("decode_min_workgroups", min_wgs)
+    r = run_both(shape, w, batch, kp0, vp0, hidden_np(shape, 61, batch.num_tokens), stage)
     assert_output("long prefixes", r, literal=False)
     mk, mv = written_mask(shape, batch)
     check_pool("K", r["gk"], kp0, r["kp"], shape.num_layers, mask=mk)
     check_pool("V", r["gv"], vp0, r["vp"], shape.num_layers, mask=mv)
+    if all(n > 1 for n, _ in seqs):
+        stage.stage.set_profiling(True)
+        stage.run(batch, to_dev_bits(kp0), to_dev_bits(vp0), to_dev_bits(hidden_np(shape, 61, batch.num_tokens)))
+        assert stage.stage.read_profile()["attn_decode_merge"][1] == 1
 
 
 @pytest.mark.parametrize("hidden,planes", [(1536, 3), (2560, 5), (3072, 6), (3584, 7)])
