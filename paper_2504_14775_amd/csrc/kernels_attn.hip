@@ -612,25 +612,29 @@ __device__ __forceinline__ void prefill_workgroup(const AttnArgs& a, const Prefi
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int r = lane & 15, G = lane >> 4;
 
+    // (only items of half the rows are cut; whole ones, which fill the chip, have no registers to spare for it)
+    constexpr bool CUT = NB == 1;
+    // Keys, pages and positions are counted from the first key of the part, so that the loop is the same as without parts (counted
+    // from that of the sequence, with the first block subtracted for the ring's stage, it took 172 instead of 155 us at 512 workgroups
+    // of uncut tiles).
+    const int blk0 = CUT ? it.blk_begin : 0, pos0 = it.pos0 - 32 * blk0;
     bf16x8 qf[NB][D / 32];
     int limit[NB], wave_min = 0x7FFFFFFF, wave_max = -1;
 #pragma unroll
     for (int c = 0; c < NB; ++c) {
         const int cb = wave * NB + c, qb = cb / HW;
         const int qi = min(qb * 16 + r, it.n_rows - 1);  // rows past the item repeat its last row (never stored)
-        limit[c] = it.pos0 + qi;
-        wave_min = min(wave_min, it.pos0 + min(qb * 16, it.n_rows - 1));
-        wave_max = max(wave_max, it.pos0 + min(qb * 16 + 15, it.n_rows - 1));
+        limit[c] = pos0 + qi;
+        wave_min = min(wave_min, pos0 + min(qb * 16, it.n_rows - 1));
+        wave_max = max(wave_max, pos0 + min(qb * 16 + 15, it.n_rows - 1));
         const bf16_t* qrow = a.q + (int64_t)(it.row0 + qi) * a.ld_q + (int64_t)(head0 + cb % HW) * D;
 #pragma unroll
         for (int s = 0; s < D / 32; ++s)
             qf[c][s] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(qrow + (s * 4 + G) * 8));
     }
-    const int last_pos = it.pos0 + it.n_rows - 1;
-    // (only items of half the rows are cut; whole ones, which fill the chip, have no registers to spare for it)
-    constexpr bool CUT = NB == 1;
-    const int blk0 = CUT ? it.blk_begin : 0, blk1 = CUT ? it.blk_end : last_pos / 32 + 1, last_page = last_pos / kPage;
-    const int32_t* bt = a.bt_flat + it.bt_off;
+    const int last_pos = pos0 + it.n_rows - 1;
+    const int nblk = CUT ? it.blk_end - blk0 : last_pos / 32 + 1, last_page = last_pos / kPage;
+    const int32_t* bt = a.bt_flat + it.bt_off + 2 * blk0;
     // wave w brings in piece w of a block: K page 0, K page 1, V page 0, V page 1 (4 x 1 KiB per page at d=128)
     const bf16_t* pool = (wave < 2) ? a.k_pool : a.v_pool;
     auto page_id = [&](int blk) -> int { return bt[min(blk * 2 + (wave & 1), last_page)]; };
@@ -689,26 +693,26 @@ __device__ __forceinline__ void prefill_workgroup(const AttnArgs& a, const Prefi
     // every wave always issues its piece (indices past the end re-read the last page into a stage nobody
     // reads), so the count of outstanding loads is the same in every iteration
 #pragma unroll
-    for (int i = 0; i < NS - 1; ++i) issue_block(page_id(blk0 + i), i);
-    int pid_next = page_id(blk0 + NS - 1);  // page of block blk + NS - 1, fetched one iteration ahead
+    for (int i = 0; i < NS - 1; ++i) issue_block(page_id(i), i);
+    int pid_next = page_id(NS - 1);  // page of block blk + NS - 1, fetched one iteration ahead
     auto ring_advance = [&](int blk) {
         // blocks blk+1 .. blk+NS-2 may still be in flight
         asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NS - 2) * IPB) : "memory");
         __syncthreads();  // block blk has landed; nobody reads stage (blk-1) % NS any more
-        issue_block(pid_next, (blk - blk0 + NS - 1) % NS);
+        issue_block(pid_next, (blk + NS - 1) % NS);
         pid_next = page_id(blk + NS);
     };
     // Two loops with one barrier per block each (every wave passes the same number of barriers in total): first the
     // blocks wholly visible to every row of this wave -- no masks at all, the common case -- then the
     // blocks at the causal edge / the end of the written keys (masked) and the wholly invisible ones (skipped).
-    const int full1 = max(blk0, min((wave_min + 1) / 32, blk1));
-    for (int blk = blk0; blk < full1; ++blk) {
+    const int n_full = min((wave_min + 1) / 32, nblk);
+    for (int blk = 0; blk < n_full; ++blk) {
         ring_advance(blk);
-        block_step((blk - blk0) % NS, blk * 32, std::false_type{});
+        block_step(blk % NS, blk * 32, std::false_type{});
     }
-    for (int blk = full1; blk < blk1; ++blk) {
+    for (int blk = n_full; blk < nblk; ++blk) {
         ring_advance(blk);
-        if (blk * 32 <= wave_max) block_step((blk - blk0) % NS, blk * 32, std::true_type{});
+        if (blk * 32 <= wave_max) block_step(blk % NS, blk * 32, std::true_type{});
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // no LDS fill may outlive the workgroup
 #pragma unroll
