@@ -80,13 +80,14 @@ __global__ __launch_bounds__(256) void pad_rows_kernel(const bf16_t* __restrict_
 // Where the list overflows or the guess fails, a second pass takes a tighter bound from the maxima of the 1024 threads
 // over the whole row; where that fails too (nearly flat distributions, very large k, masses of ties), the selection
 // runs over the row, one pass per digit, and the draw takes a pass that sums masses per 4096 consecutive tokens.
-// Measured at a vocabulary of 128256 (first: four to ten passes per row, one row per compute unit; then one pass with the last
-// blocks of a row loaded one by one; now these together, and where every row has a compute unit the next four blocks while
-// four are worked on; us):
-//   top-k 50 + nucleus 0.95   1 row 160 -> 30.7 -> 28.2, 64 rows 37.7 -> 33.0, 256 rows 171 -> 45.6 -> 43.5, 257 rows 320 -> 58.0 -> 56.9
-//   nucleus 0.95 (logits of standard deviation 4.3)   1 row 780 -> 33.8 -> 31.7, 64 rows 880 -> 39.7 -> 35.9, 257 rows 1740 -> 56.6 -> 55.5
-//   nucleus 0.95 of nearly flat rows (the selection runs over the row)   64 rows 189 -> 183
-//   greedy   1 row 9.5 -> 9.1
+// Measured at a vocabulary of 128256 (first: four to ten passes per row, one row per compute unit; then: one pass, a list of 4096 with
+// whole keys; now: keys relative to the bound, a list of 5120 of which only the entries in use are walked, a top-k of up to 64
+// finished by one wave; us):
+//   top-k 50 + nucleus 0.95   1 row 160 -> 27.5 -> 22.0, 64 rows 31.2 -> 25.2, 256 rows 171 -> 42.6 -> 36.7, 257 rows 320 -> 56.0 -> 47.8
+//   top-k 300 + nucleus 0.95   1 row 32.1 -> 29.9, 256 rows 60.5 -> 58.1, 257 rows 71.1 -> 68.5 (75.3 with ten more registers spilled)
+//   nucleus 0.95 (logits of standard deviation 4.3)   1 row 780 -> 30.5 -> 29.1, 64 rows 880 -> 35.0 -> 33.1, 257 rows 1740 -> 57.0 -> 54.4
+//   nucleus 0.95 of nearly flat rows (the selection runs over the row)   64 rows 183
+//   greedy   1 row 8.6, 257 rows 33
 constexpr int kSampleThreads = 1024;
 constexpr int kSampleWaves = kSampleThreads / 64;
 constexpr int kDigitBits = 12, kBins = 1 << kDigitBits;
@@ -262,10 +263,10 @@ __device__ __forceinline__ uint32_t find_bin(SampleShared& sh, uint64_t need, ui
     return sh.digit;
 }
 
-// The largest key t with weight(entries with key >= t) >= need, over the workgroup's list (kPerThread entries per
-// thread, weight 0 where there is none); `bits` (at most 32) is the width of the keys.  The bins must be clear.
-__device__ __forceinline__ uint32_t select_key(SampleShared& sh, const uint32_t (&key)[kPerThread],
-                                               const uint64_t (&weight)[kPerThread], int bits, uint64_t need) {
+// The largest key t with weight(entries with key >= t) >= need, over the workgroup's list (entry j of a thread weighs weight(j), 0
+// where there is none; the list ends within entries `per` - 1); `bits` (at most 32) is the width of the keys.  The bins must be clear.
+template <class W>
+__device__ __forceinline__ uint32_t select_key(SampleShared& sh, const uint32_t (&key)[kPerThread], int per, W&& weight, int bits, uint64_t need) {
     uint32_t prefix = 0;
     int low = bits;  // bits below `low` are still open
     while (low > 0) {
@@ -273,8 +274,10 @@ __device__ __forceinline__ uint32_t select_key(SampleShared& sh, const uint32_t 
         const uint32_t digit_mask = (1u << step) - 1u;
 #pragma unroll
         for (int j = 0; j < kPerThread; ++j) {
+            if (j >= per) break;
             const bool same = low == 32 || (key[j] >> low) == (prefix >> low);
-            if (same && weight[j]) add_to_bin(sh, (key[j] >> shift) & digit_mask, weight[j]);
+            const uint64_t w = weight(j);
+            if (same && w) add_to_bin(sh, (key[j] >> shift) & digit_mask, w);
         }
         uint64_t above;
         const uint32_t d = find_bin(sh, need, above);
@@ -285,22 +288,39 @@ __device__ __forceinline__ uint32_t select_key(SampleShared& sh, const uint32_t 
     return prefix;
 }
 
+// A butterfly over the wave without addresses: by __shfl_xor its six lane addresses were kept in registers, or in scratch memory,
+// from one to the next.  (The swap of halves gives every lane both its own value and that of lane ^ 32.)
+template <int O>
+__device__ __forceinline__ float lane_xor(float v) {
+    return __int_as_float(__builtin_amdgcn_ds_swizzle(__float_as_int(v), O << 10 | 0x1F));
+}
+template <class F>
+__device__ __forceinline__ float wave_reduce(float v, F&& f) {
+    const auto halves = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = f(__uint_as_float(halves[0]), __uint_as_float(halves[1]));
+    v = f(v, lane_xor<16>(v));
+    v = f(v, lane_xor<8>(v));
+    v = f(v, lane_xor<4>(v));
+    v = f(v, lane_xor<2>(v));
+    return f(v, lane_xor<1>(v));
+}
+__device__ __forceinline__ int wave_id() { return __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); }
+__device__ __forceinline__ float first_lane(float v) { return __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(v))); }
 // Sum over the workgroup with a fixed association (lanes by butterfly, then the wave sums in order).
 __device__ __forceinline__ float block_sum(SampleShared& sh, float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+    v = wave_reduce(v, [](float a, float b) { return a + b; });
     __syncthreads();
-    if ((threadIdx.x & 63) == 0) sh.wave_f[threadIdx.x >> 6] = v;
+    if ((threadIdx.x & 63) == 0) sh.wave_f[wave_id()] = v;
     __syncthreads();
     float s = 0.f;
 #pragma unroll
     for (int w = 0; w < kSampleWaves; ++w) s += sh.wave_f[w];
-    return s;
+    return first_lane(s);
 }
 __device__ __forceinline__ uint64_t block_sum(SampleShared& sh, uint64_t v) {
     v = wave_scan(v);
     __syncthreads();
-    if ((threadIdx.x & 63) == 63) sh.wave_sum[threadIdx.x >> 6] = v;
+    if ((threadIdx.x & 63) == 63) sh.wave_sum[wave_id()] = v;
     __syncthreads();
     return lane_value(row_scan(sh.wave_sum[threadIdx.x & (kSampleWaves - 1)]), kSampleWaves - 1);
 }
@@ -341,28 +361,32 @@ __device__ __forceinline__ uint32_t kth_of_threads(SampleShared& sh, uint32_t ke
     } else {
         const uint32_t mine[1] = {key};
         const uint32_t own = wave_kth(mine, (k + kSampleWaves - 1) / kSampleWaves);
-        if ((threadIdx.x & 63) == 0) sh.wave_i[threadIdx.x >> 6] = (int)own;
+        if ((threadIdx.x & 63) == 0) sh.wave_i[wave_id()] = (int)own;
         __syncthreads();
 #pragma unroll
         for (int q = 0; q < kSampleWaves; ++q) t = min(t, (uint32_t)sh.wave_i[q]);
     }
-    return t;
+    return __builtin_amdgcn_readfirstlane(t);
 }
 // Largest value of the workgroup.
 __device__ __forceinline__ float block_max(SampleShared& sh, float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
+    v = wave_reduce(v, [](float a, float b) { return fmaxf(a, b); });
     __syncthreads();
-    if ((threadIdx.x & 63) == 0) sh.wave_f[threadIdx.x >> 6] = v;
+    if ((threadIdx.x & 63) == 0) sh.wave_f[wave_id()] = v;
     __syncthreads();
 #pragma unroll
     for (int w = 0; w < kSampleWaves; ++w) v = fmaxf(v, sh.wave_f[w]);
-    return v;
+    return first_lane(v);
 }
 
+// (double)v, made where it stands: hoisted out of the passes over a row the widened constants took scratch memory instead
+__device__ __forceinline__ double widened(float v) {
+    asm volatile("" : "+s"(v));
+    return (double)v;
+}
 // nucleus: the weight that has to be reached, of `total`
 __device__ __forceinline__ uint64_t nucleus_need(float p, uint64_t total) {
-    const double need = ceil((double)p * (double)total);
+    const double need = ceil(widened(p) * (double)total);
     return need >= 1.0 ? (uint64_t)need : 1;
 }
 // draw: the first token whose running sum exceeds u * total
@@ -424,7 +448,7 @@ __global__ __launch_bounds__(kSampleThreads, ROOMY ? 4 : 8) void sample_kernel(c
                                                                    int32_t* __restrict__ out) {
     __shared__ SampleShared sh;
     constexpr int U = ROOMY ? 8 : 4;
-    constexpr int kFewStep = ROOMY ? 8 : 1;  // entries that finish_on_few reads from LDS at one time (64 registers hold no more)
+    constexpr int kFewStep = ROOMY ? 8 : 1;  // entries that finish_on_few reads from LDS at one time (with 64 registers four at a time spill 29 more)
     const int tid = threadIdx.x, lane = tid & 63, row = blockIdx.x;
     const float* lg = logits + (int64_t)row * ld;
     const float temp = temperature[row];
@@ -571,8 +595,10 @@ __global__ __launch_bounds__(kSampleThreads, ROOMY ? 4 : 8) void sample_kernel(c
         const uint32_t key_lo = z_lo == 0.f ? float_key(-0.f) : z_lo == z_lo ? float_key(z_lo) : 0u;
         const uint32_t key_span = float_key(z_hi == 0.f ? 0.f : z_hi) - key_lo;
         const int key_bits = 32 - __clz((int)key_span);  // (0 bits: all keys are equal)
+        const int per = __builtin_amdgcn_readfirstlane((n + kSampleThreads - 1) / kSampleThreads);  // entries that threads hold
         uint32_t key[kPerThread], ikey[kPerThread];
         uint64_t weight[kPerThread];
+        const auto weight_of = [&](int j) { return weight[j]; };
         uint64_t own = 0;
 #pragma unroll
         for (int j = 0; j < kPerThread; ++j) {
@@ -590,10 +616,8 @@ __global__ __launch_bounds__(kSampleThreads, ROOMY ? 4 : 8) void sample_kernel(c
         clear_bins(sh);
         uint64_t total;
         if (by_k) {
-            uint64_t one[kPerThread];
-#pragma unroll
-            for (int j = 0; j < kPerThread; ++j) one[j] = j * kSampleThreads + tid < n ? 1 : 0;
-            const uint32_t floor_key = select_key(sh, key, one, key_bits, (uint64_t)k);
+            const uint32_t floor_key =
+                select_key(sh, key, per, [&](int j) -> uint64_t { return j * kSampleThreads + tid < n ? 1 : 0; }, key_bits, (uint64_t)k);
             own = 0;
 #pragma unroll
             for (int j = 0; j < kPerThread; ++j) {
@@ -624,11 +648,11 @@ __global__ __launch_bounds__(kSampleThreads, ROOMY ? 4 : 8) void sample_kernel(c
             total = block_sum(sh, own);
         } else {
             const uint64_t listed = block_sum(sh, own);
-            total = listed + (uint64_t)((double)block_sum(sh, others) * (double)mass_one);
+            total = listed + (uint64_t)((double)block_sum(sh, others) * widened(mass_one));
             if (listed < nucleus_need(p, total)) return false;
         }
         if (by_p) {
-            const uint32_t t = select_key(sh, key, weight, key_bits, nucleus_need(p, total));
+            const uint32_t t = select_key(sh, key, per, weight_of, key_bits, nucleus_need(p, total));
             own = 0;
 #pragma unroll
             for (int j = 0; j < kPerThread; ++j) {
@@ -637,7 +661,7 @@ __global__ __launch_bounds__(kSampleThreads, ROOMY ? 4 : 8) void sample_kernel(c
             }
             total = block_sum(sh, own);
         }
-        const uint32_t first = select_key(sh, ikey, weight, 24, draw_need(u, total));
+        const uint32_t first = select_key(sh, ikey, per, weight_of, 24, draw_need(u, total));
         if (tid == 0) out[row] = total ? (int)(0xFFFFFFu - first) : 0;
         return true;
     };
@@ -704,7 +728,7 @@ __global__ __launch_bounds__(kSampleThreads, ROOMY ? 4 : 8) void sample_kernel(c
             if (edge == edge) skip = edge - fabsf(edge) * 0x1p-20f;
             if (skip > -INFINITY) floor_key = float_key(skip / temp);
         }
-        floor_key = select_row(floor_key, skip, nucleus_need(p, (uint64_t)((double)row_mass * (double)mass_one)), mass);
+        floor_key = select_row(floor_key, skip, nucleus_need(p, (uint64_t)((double)row_mass * widened(mass_one))), mass);
     }
     // the draw: masses of 4096 consecutive tokens each, then the tokens of the block it falls into
     const bool all = !by_k && !by_p;
