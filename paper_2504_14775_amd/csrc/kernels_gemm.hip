@@ -453,8 +453,12 @@ hipError_t launch_skinny(const bf16_t* a, int64_t lda, const bf16_t* w, int64_t 
 }
 int skinny_columns(int m, int n, int k, int mode, int splits);
 
-// Tile 6 up to 128 rows: 64 columns where half of the compute units would be without a tile of 128 and nearly all have one of 64
-// (4096 x 4096 in four shares of k instead of eight, half the planes: 72 rows 12.1 -> 9.9 us, 128 rows 14.7 -> 12.6).
+// Tile 6 up to 128 rows: 64 columns where half of the compute units would be without a tile of 128 and nearly all have one of 64.
+// 360 products of 65 to 128 rows (profiles/gemm_65_to_128_rows.txt), planes read included: where it is picked, 0.91 of the best form
+// without it on average, 0.78 to 1.00 (4096 x 4096 in four shares of k instead of eight: 80 rows 12.8 -> 10.8 us, 128 rows 14.9 ->
+// 13.1).  Above 128 tiles two share a compute unit and 64 columns are always slower (1.03 to 1.43).  Below 113 they are faster in the
+// same shares (0.7 to 0.8), but the fewer shares that the plan would then take are not always (0.77 to 1.25 of the best, 3584 x 5120 at 65 rows
+// 12.2 -> 11.9); there the forms are as they were, unmeasured in a stage: no shape here has such a product at these rows.
 bool half_width_deep(int m, int n, int splits) {
     const int64_t tiles = (int64_t)(n / 128) * splits;
     return m <= 128 && tiles > 112 && tiles <= 128;
@@ -490,7 +494,7 @@ hipError_t launch_mode(const bf16_t* a, int64_t lda, const bf16_t* w, int64_t ld
             if constexpr (MODE == GEMM_STORE_F32) {
                 if (half_width_deep(m, n, splits)) return m <= 96 ? launch_tile_w<96, 64, 2, 2, MODE, 4, 4, true>(GLLM_TILE_ARGS) : launch_tile_w<128, 64, 2, 2, MODE, 4, 4, true>(GLLM_TILE_ARGS);
             }
-            // (a quarter of the rows less to load, read and multiply, us: 96 rows of 6144 x 4096 14.4 -> 13.8, 8192 x 28672 76.5 -> 75.2)
+            // (a quarter of the rows less to load, read and multiply: 0.99 of the time on average, 0.94 to 1.05)
             if (m <= 96) return launch_tile_w<96, 128, 2, 2, MODE, 3, 3, true>(GLLM_TILE_ARGS);
             return launch_tile<128, 128, 2, 2, MODE, 4>(GLLM_TILE_ARGS);
         case 7:  // (up to 32 rows half the activations to load and to read from LDS: one row of the 8B shape 785 -> 770 us)
@@ -617,7 +621,9 @@ namespace {
 // The picks are 0.37 % behind the fastest forms on average, at most 10 % (profiles/gemm_plan_sweep.txt); fitted to three quarters
 // of the products, 0.44 % and 14 % on the rest, of other row counts.  Before, with one `lone` for all and the low tiles of a
 // row-mixed launch in a round of their own: 1.2 %, at most 28 % (28672 x 4096 at 1050 rows 240 -> 192 us, 4096 x 4096 at 800
-// rows 41 -> 35).
+// rows 41 -> 35).  Tile 6 of 96 rows goes by the costs of 128 rows (0.99 of the time), that of 64 columns by costs set by hand: of
+// the products where it is in question 4.6 % behind the fastest form on average, 2.5 % from 2048 columns on (360 products of 65 to 128
+// rows, profiles/gemm_65_to_128_rows.txt).
 struct TileCost {
     int slots, width;  // tiles in a round, columns of a tile
     double step, fixed, lone[3];  // lone: no whole round in front of the last one, one, more
