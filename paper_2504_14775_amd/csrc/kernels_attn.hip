@@ -203,8 +203,9 @@ __device__ __forceinline__ void attend_block(AttnState<D, NB>& st, KvFrag<D>& f,
 
 // Walks key blocks [blk_begin, blk_end) (units of 32 keys) of one sequence.  Page ids are fetched 64
 // at a time, one per lane, and handed out with readlane.  last_page is the last page index of the
-// sequence that may be read (page ids past it are never dereferenced); page0 and page1 are the ids of the first block's pages, so
-// that its loads need not wait for the table.
+// sequence that holds keys to be read, and no page id past it is taken from the table; page0 and page1 are the ids of the first
+// block's pages, so that its loads need not wait for the table.  (page1 may be the page behind last_page that the new token starts,
+// which the same launch then writes: what is read there is masked, like all keys from valid_end on.)
 // prepare() fills qf; every wave calls it once, when the loads of its first block are on their way.
 template <int D, int NB, typename Prepare>
 __device__ __forceinline__ void attend_range(AttnState<D, NB>& st, const bf16x8 (&qf)[NB][D / 32],
