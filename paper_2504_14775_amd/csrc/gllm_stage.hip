@@ -294,8 +294,6 @@ gllm_status gllm_stage_create(const gllm_stage_config* cfg, gllm_stage** out) {
     s->hidden_pad_n = (int)round_up(c.hidden, kGemmPadN);
     s->m_pad = round_up(c.max_tokens, kGemmPadM);
     s->max_items = 4 * c.max_seqs + 1024 + std::min(4 * c.max_tokens, 2048);
-    s->item_list.resize((size_t)s->max_items);
-    s->item_order.resize((size_t)s->max_items);
     s->max_pre_items = c.max_tokens / prefill_item_rows(c.n_q_heads, c.n_kv_heads, true) + c.max_seqs + 1 + kPrefillSlots;
     s->max_v_tiles = c.max_tokens / kPage + 2 * c.max_seqs + 1;
     s->layers.resize(c.num_layers);
@@ -306,6 +304,12 @@ gllm_status gllm_stage_create(const gllm_stage_config* cfg, gllm_stage** out) {
         gllm_stage_destroy(s);
         return st;
     };
+    try {
+        s->item_list.resize((size_t)s->max_items);
+        s->item_order.resize((size_t)s->max_items);
+    } catch (const std::exception&) {
+        return bail(hipErrorOutOfMemory, "decode work items");
+    }
     // (the weight buffers of a layer are allocated when the layer is first loaded)
     // RoPE table: angle = pos * theta^(-2j/d), formed in double
     {
