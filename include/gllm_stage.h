@@ -109,7 +109,10 @@ const char* gllm_status_name(gllm_status s);
 
 /* Activation workspace: the caller allocates workspace_bytes() of device memory (256-byte
  * aligned) and binds it; the library never frees it.  Contents need not survive between
- * forward calls. */
+ * forward calls.  Besides the activations it holds the partial attention results of rows whose keys
+ * are cut into parts: n_q_heads * (head_dim + 2) floats each, 4 * max_seqs + 1024 of them for decode
+ * rows and min(4 * max_tokens, 2048) more for chunk rows (34 MB with 32 heads of 128); where a batch
+ * would need more, its keys are cut into fewer parts. */
 size_t gllm_stage_workspace_bytes(const gllm_stage* stage);
 gllm_status gllm_stage_bind_workspace(gllm_stage* stage, void* workspace /*DEVICE*/, size_t bytes);
 
