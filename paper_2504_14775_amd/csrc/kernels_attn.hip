@@ -308,8 +308,8 @@ __device__ __forceinline__ void decode_workgroup(const AttnArgs& a, const Decode
     // neighbouring 4 KiB pieces of the same pages
     const int kvh = wg % a.n_kv;
     // (the items lie in launch order and name the pages of each wave's first block: keys are asked for after one trip to memory, not
-    // three -- order, item, page table.  200 rows of 16 .. 600 keys, eight layers 1600 -> 1581 us, 251 rows beside two chunks 2112 -> 2098,
-    // 256 rows beside a chunk 9296 -> 9244, one row 740 -> 738)
+    // three -- order, item, page table.  Share of the batch's time, five runs of each side: 200 rows of 16 .. 600 keys 0.991 to 0.995, 500
+    // of 16 .. 100 0.993, long rows 0.998 to 0.999, 32 rows of 100 .. 300 1.004)
     const DecodeItem& item = items[wg / a.n_kv];
     const DecodeItem it = item;
     const int g = a.n_q / a.n_kv;
