@@ -633,7 +633,7 @@ gllm_status gllm_stage_forward(gllm_stage* s, const gllm_batch* b, const void* h
     // run at one time, and only where that saves more than the merge costs (see worth_cutting).  us per batch, 8B shape, two
     // layers, uncut / cut into 640 workgroups and up to one more for every tile / now: 32 rows behind 6000 cached keys 365 / 228 / 228,
     // 300 behind 6000 611 / 457 / 456, 600 behind 3000 723 / 709 / 693, 1000 behind 1300 899 / 917 / 902; 70B, one layer, 200 behind
-    // 6000 478 / 463 / 466, 500 behind 3000 818 / 855 / 828; 14B, one layer, 600 behind 1300 394 / 413 / 397.  Parts of at least 8
+    // 6000 478 / 463 / 466, 500 behind 3000 822 / 855 / 824; 14B, one layer, 600 behind 1300 394 / 413 / 397.  Parts of at least 8
     // blocks are 0 to 3 % slower, of 24 1 to 2 %.
     // In one launch with decode rows a tile hides behind the stream of their keys, where a block takes about 1.45 us; a part need
     // not be shorter than that stream (6.5 TB/s): more workgroups would only wait in the same queues, and their results are to be

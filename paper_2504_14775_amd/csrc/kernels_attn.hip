@@ -821,7 +821,7 @@ hipError_t launch_prefill_attention(const AttnArgs& a, const PrefillItem* items,
 // Up to 64 prefill workgroups (a quarter of the compute units; twice as many of half the rows) share the launch of the decode items: with 4 of them (52
 // rows, one layer) a batch takes 43 instead of 46 us, with 32 (71 prompt rows beside 251 decode rows, eight layers) 2220
 // instead of 2306 us, against two launches one after the other.  Counted are whole tiles: where the decode rows are too few to hide
-// a tile's keys these are cut (see the stage), into up to 640 workgroups and one per tile.
+// a tile's keys these are cut (see the stage), into up to 768 workgroups.
 // More tiles gain nothing beside the key stream of the decode items (160: +0.5 % of the batch, 448: +0.5 %): their own
 // loads then wait in the same queues, they hold their slots five times as long, and the sum of the two times is what
 // comes out -- from one launch, in either order or interleaved, and from two streams (whose events cost 13 us on top).
