@@ -64,15 +64,22 @@ __device__ __forceinline__ int xcd_contiguous(int wg, int count) {
 // HBM, the activations are re-read from the caches by every tile column, so where LDS cannot hold one more stage of both
 // (256x256: two of each fill 128 of the 160 KiB) the W tile alone gets the third: its loads then have two k-steps
 // to land instead of one.
+// THROUGH: the results are written through the L2 (see kAuxWriteThrough).
 // W_FAR: 32-bit offsets do not reach over the row blocks of W in a tile or along its k range, so each block of each k-step
 // gets a buffer of its own (two scalar additions per load).
-template <int BM, int BN, int WGM, int WGN, int MODE, int NS = 2, int NSW = NS, bool W_ONCE = false, bool W_FAR = false>
+template <int BM, int BN, int WGM, int WGN, int MODE, int NS = 2, int NSW = NS, bool W_ONCE = false, bool W_FAR = false, bool THROUGH = false>
 __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ A, int64_t lda, const bf16_t* __restrict__ W,
                                           int64_t ldw, void* __restrict__ out, int64_t ldc, int M, int K,
                                           int tiles_m, int tiles_n, int n_base, int tile_idx, int split, int num_splits,
                                           int64_t split_stride, int m_base = 0) {
 #if defined(__HIP_DEVICE_COMPILE__)  // (the buffer resource type exists in device code only)
     constexpr int kAuxNonTemporal = 2;        // cache-policy operand of a buffer load: the nt bit
+    // ... and of a buffer store: the sc1 bit.  Results that stay in the L2 are written back when the stream of the weights
+    // displaces them, in pieces, and the reads wait for those writes all along; written through they are on their way at once.
+    // Logits of 64 rows: 152064 x 5120 296 -> 255 us (5.3 -> 6.1 TB/s of weights, 6.6 without any stores; with the nt hint 262),
+    // 128256 x 4096 181 -> 162 (165); 257 rows 328 -> 308.  In a single round all results are stored when the stream has ended, and the
+    // next kernel reads them: there they are left to the L2 (197 rows, eight layers 1243 us, written through 1257).
+    constexpr int kAuxWriteThrough = 16;
     constexpr int kBufferFlags = 0x00027000;  // raw buffer of 32-bit words, bounds checked in bytes
     constexpr int NW = WGM * WGN;
     constexpr int WTM = BM / WGM, WTN = BN / WGN;  // wave tile
@@ -277,6 +284,8 @@ __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ A, int64_t 
         }
         // the slab is private to the wave and LDS executes a wave's instructions in order: no barrier needed
         const int mrow0 = m0 + wm * WTM + i * MB;
+        const auto slab_out = __builtin_amdgcn_make_buffer_rsrc((void*)(reinterpret_cast<float*>(out) + split_off + (int64_t)mrow0 * ldc + n0 + wn * WTN),
+                                                                0, -1, kBufferFlags);  // (THROUGH)
         const bool lane_on = RPI * LPR == 64 || lane < RPI * LPR;
         f32x4 val[MB / RPI];
 #pragma unroll
@@ -294,6 +303,9 @@ __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ A, int64_t 
                 if (MODE == GEMM_ADD_F32) {
                     f32x4 old = *reinterpret_cast<const f32x4*>(p);
                     *reinterpret_cast<f32x4*>(p) = old + val[r / RPI];
+                } else if (THROUGH) {  // (offsets count from the first row of the slab: 32 bits reach over its 16 rows, see kThroughMaxLd)
+                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, val[r / RPI]), slab_out,
+                                                           (int)(((uint32_t)(r + orow) * (uint32_t)ldc + (uint32_t)ocol) * 4u), 0, kAuxWriteThrough);
                 } else {
                     *reinterpret_cast<f32x4*>(p) = val[r / RPI];
                 }
@@ -307,7 +319,7 @@ __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ A, int64_t 
 template <int H>
 constexpr int kWideStages = H <= 160 ? 3 : 2;
 
-template <int BM, int BN, int WGM, int WGN, int MODE, int NS = 2, int NSW = NS, bool W_ONCE = false, bool W_FAR = false>
+template <int BM, int BN, int WGM, int WGN, int MODE, int NS = 2, int NSW = NS, bool W_ONCE = false, bool W_FAR = false, bool THROUGH = false>
 __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_kernel(const bf16_t* __restrict__ A, int64_t lda,
                                                                     const bf16_t* __restrict__ W, int64_t ldw,
                                                                     void* __restrict__ out, int64_t ldc, int M,
@@ -319,7 +331,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_kernel(const bf16_t*
     // as the plain per-share numbering would place them, the L2 sees half as many tiles per panel).
     const int num_tiles = tiles_m * tiles_n;
     const int v = xcd_contiguous(blockIdx.x + blockIdx.y * num_tiles, num_tiles * (int)gridDim.y);
-    gemm_tile<BM, BN, WGM, WGN, MODE, NS, NSW, W_ONCE, W_FAR>(A, lda, W, ldw, out, ldc, M, K, tiles_m, tiles_n, 0, v % num_tiles,
+    gemm_tile<BM, BN, WGM, WGN, MODE, NS, NSW, W_ONCE, W_FAR, THROUGH>(A, lda, W, ldw, out, ldc, M, K, tiles_m, tiles_n, 0, v % num_tiles,
                                                        v / num_tiles, gridDim.y, split_stride);
 }
 
@@ -381,12 +393,21 @@ __global__ __launch_bounds__(256) void gemm_any_address_kernel(const bf16_t* __r
     else *f = sum;
 }
 
-template <int BM, int BN, int WGM, int WGN, int MODE, int NS, int NSW, bool W_ONCE, bool W_FAR = false>
+// Results are written through the L2 where one band of rows takes more than a round, a tile per compute unit (see kAuxWriteThrough;
+// with several bands there is no difference, 4160 rows), and their rows are near enough for 32-bit offsets over 16 of them.
+constexpr int kThroughMinTiles = 257;
+constexpr int64_t kThroughMaxLd = ((int64_t)1 << 26) - 1;
+
+template <int BM, int BN, int WGM, int WGN, int MODE, int NS, int NSW, bool W_ONCE, bool W_FAR = false, bool THROUGH = false>
 hipError_t launch_tile_w(const bf16_t* a, int64_t lda, const bf16_t* w, int64_t ldw, void* out, int64_t ldc, int m,
                          int n, int k, int splits, int64_t split_stride, hipStream_t stream) {
+    if constexpr (MODE == GEMM_STORE_F32 && W_ONCE && !THROUGH) {
+        if ((int64_t)(n / BN) * splits >= kThroughMinTiles && m <= BM && ldc <= kThroughMaxLd)
+            return launch_tile_w<BM, BN, WGM, WGN, MODE, NS, NSW, W_ONCE, W_FAR, true>(a, lda, w, ldw, out, ldc, m, n, k, splits, split_stride, stream);
+    }
     const int tiles_m = (int)ceil_div(m, BM), tiles_n = n / BN;
     const size_t smem = (NS * BM + NSW * BN) * BK * sizeof(bf16_t);
-    auto kern = gemm_bf16_kernel<BM, BN, WGM, WGN, MODE, NS, NSW, W_ONCE, W_FAR>;
+    auto kern = gemm_bf16_kernel<BM, BN, WGM, WGN, MODE, NS, NSW, W_ONCE, W_FAR, THROUGH>;
     static bool configured = false;
     if (!configured) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),

@@ -513,3 +513,21 @@ def test_gemm_splits_that_are_no_powers_of_two(splits, K):
             for s in range(splits):
                 xs, ys = x[:, s * part:(s + 1) * part], y[:, s * part:(s + 1) * part]
                 assert np.all(np.abs(out[s].cpu().numpy() - xs @ ys.T) <= (np.abs(xs) @ np.abs(ys).T) * part * 2.0 ** -24), (splits, M, tile, s)
+
+
+@pytest.mark.parametrize("M,N,ldc,tile", [(17, 49152, 49152, 5), (17, 49344, 49350, 5), (17, 128 * 257, 128 * 257, 7), (2, 49344, (1 << 26) - 4, 5), (2, 49344, 1 << 26, 5)])
+def test_gemm_fp32_results_of_one_round_and_of_more(M, N, ldc, tile):
+    """Results of 256 tiles and of 257, which are stored in another way, packed and with rows as far apart as the 32-bit byte
+    offsets of that way reach and one step farther; nothing between the rows changes."""
+    K = 64
+    print(f"gemm results M={M} N={N} ldc={ldc} tile={tile}", flush=True)
+    a, w = rand_bits(31, 1, (M, K), 1.0), rand_bits(31, 2, (N, K), 0.05)
+    ref = oracle.linear(oracle.bf16_to_f64(a), w)
+    flat = torch.full(((M - 1) * ldc + N + 64,), 7.0, dtype=torch.float32, device=DEV)
+    out = torch.as_strided(flat, (M, N), (ldc, 1))
+    B.gllm_op_gemm_bf16(to_dev_bits(padded_rows(a, 256)), to_dev_weight(w), out, M, N, K, B.GEMM_STORE_F32, tile)
+    torch.cuda.synchronize()
+    got = out.contiguous().cpu().numpy().astype(np.float64)
+    assert np.abs(got - ref).max() <= 2e-5 * np.abs(ref).max() + 1e-6
+    for r in range(M):
+        assert bool((flat[r * ldc + N: min((r + 1) * ldc, flat.numel())] == 7.0).all()), r
