@@ -210,9 +210,10 @@ gllm_status gllm_op_pack_weight(const void* w, int64_t ldw, int32_t n, int32_t k
  * from HBM; up to 96 rows 96x128, in mode 0 up to 128 rows by 64 columns where tiles of 128 would leave half of the compute units without one and those of 64 few), 7 = 64x128, up to 32 rows 32x128, in mode 0 up to 64 rows by 64 columns where that gives the compute units more
  * equal shares (picked up to 64 rows: the product is a stream of the weights), 8 and 12 = 256x256 tiles for the whole bands of 256 rows plus 64x256 or 128x256 tiles for a last band of at
  * most 128 rows, or two bands of 192x256 tiles for all rows up to 384 (only for m > 256 with 0 < m mod 256 <= 128 and
- * n a multiple of 256), 9 = 288x128, or 288x192 (six wavefronts) where n is no multiple of 128 and in mode 1 (only for
+ * n a multiple of 256), 9 = as 13, or 288x192 where n is no multiple of 128 and in mode 1 (only for
  * 256 < m <= 288, n a multiple of 192, not for SwiGLU: all rows in one band, so the weights are read once), 13 = one band of 257 to 384 rows, its height a
- * multiple of 32, by 128 columns, 14 and 15 = bands of equal height, a multiple of 32 from 160 to 256, by 256 and by 128
+ * multiple of 32, by 128 columns (in mode 0 up to 288 rows by 192, or whole rounds of 192 and a last one of 128, where that
+ * balances better), 14 and 15 = bands of equal height, a multiple of 32 from 160 to 256, by 256 and by 128
  * columns (mode 1: of 256 rows; 13 too); a forced tile that does not fit the shape gives GLLM_E_UNSUPPORTED.
  * Alignment: operands are loaded in 16-byte pieces from any 4-byte boundary.  Where a, one of its rows (lda odd, m > 1) or
  * w starts off a 4-byte boundary, a plain, slow kernel does the product; where the rows of a lie so far apart that a tile

@@ -49,8 +49,8 @@ enum GemmMode { GEMM_STORE_F32 = 0, GEMM_ADD_F32 = 1, GEMM_SWIGLU_BF16 = 2 };
 // 128 rows 64 columns where there are few tiles; 7 = 64x128,
 // up to 32 rows 32x128, up to 64 rows 64 columns where that balances better (up to 64 rows: weight streaming); 8 and 12 = 256x256 tiles for the whole bands of 256 rows plus 64x256 or 128x256
 // tiles for a last band of at most 128 rows, two bands of 192x256 tiles up to 384 rows (only where
-// gemm_rowmix_rem_rows(m, n) > 0); 9 = 288x128, or 288x192 where n is no multiple of 128 and for GEMM_ADD_F32; 13 = one band of 257..384 rows, its
-// height a multiple of 32, x 128; 14 and 15 = bands of equal height, a multiple of 32 from 160 to 256, x 256 and x 128
+// gemm_rowmix_rem_rows(m, n) > 0); 9 = as 13, or 288x192 where n is no multiple of 128 and for GEMM_ADD_F32; 13 = one band of 257..384 rows, its
+// height a multiple of 32, x 128, up to 288 rows in store mode x 192, or both widths, where that balances better; 14 and 15 = bands of equal height, a multiple of 32 from 160 to 256, x 256 and x 128
 // (mode GEMM_ADD_F32: 256).
 // splits > 1 (store mode only): split s covers k range [s*k/splits, (s+1)*k/splits) and writes its partial
 // product to out + s*split_stride floats; the consumer sums the planes in order.

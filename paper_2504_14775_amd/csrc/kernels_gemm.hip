@@ -352,6 +352,19 @@ __global__ __launch_bounds__(256) void gemm_bf16_mixed_kernel(const bf16_t* __re
                                                     xcd_contiguous(blockIdx.x - big_tiles, tiles_m * small_cols), 0, 1, 0);
 }
 
+// One band of 257..288 rows, two widths in one launch: whole rounds of 288x192 tiles, then 288x128 ones for a last round.
+template <bool THROUGH>
+__global__ __launch_bounds__(256) void gemm_bf16_tall_mixed_kernel(const bf16_t* __restrict__ A, int64_t lda, const bf16_t* __restrict__ W,
+                                                                   int64_t ldw, void* __restrict__ out, int64_t ldc, int M, int K,
+                                                                   int big_cols, int small_cols) {
+    if ((int)blockIdx.x < big_cols)
+        gemm_tile<288, 192, 2, 2, GEMM_STORE_F32, 2, 3, true, false, THROUGH>(A, lda, W, ldw, out, ldc, M, K, 1, big_cols, 0,
+                                                                              xcd_contiguous(blockIdx.x, big_cols), 0, 1, 0);
+    else
+        gemm_tile<288, 128, 2, 2, GEMM_STORE_F32, 3, 3, true, false, THROUGH>(A, lda, W, ldw, out, ldc, M, K, 1, small_cols, big_cols * 192,
+                                                                              xcd_contiguous(blockIdx.x - big_cols, small_cols), 0, 1, 0);
+}
+
 // Two tile heights in one launch: the first big_tiles workgroups cover the whole bands of 256 rows with 256x256
 // tiles, the rest cover the last band -- at most BMR rows are left -- with BMR x 256 tiles, so a row count just above a
 // multiple of 256 does not pay for a whole band of padding.  blockIdx.y is the split-K share.
@@ -473,6 +486,10 @@ hipError_t launch_skinny(const bf16_t* a, int64_t lda, const bf16_t* w, int64_t 
     }
 }
 int skinny_columns(int m, int n, int k, int mode, int splits);
+// One band of 257..288 rows in store mode: tiles of 128 or of 192 columns, or whole rounds of 192 and a last one of 128.
+enum class Tall { k128, k192, kMixed };
+Tall tall_form(int m, int n, int k, int splits, double* us = nullptr);
+int tall_mixed_cols(int n);
 
 // Tile 6 up to 128 rows: 64 columns where half of the compute units would be without a tile of 128 and nearly all have one of 64.
 // 360 products of 65 to 128 rows (profiles/gemm_65_to_128_rows.txt), planes read included: where it is picked, 0.91 of the best form
@@ -483,6 +500,24 @@ int skinny_columns(int m, int n, int k, int mode, int splits);
 bool half_width_deep(int m, int n, int splits) {
     const int64_t tiles = (int64_t)(n / 128) * splits;
     return m <= 128 && tiles > 112 && tiles <= 128;
+}
+
+// See gemm_bf16_tall_mixed_kernel.
+template <bool THROUGH>
+hipError_t launch_tall_mixed(const bf16_t* a, int64_t lda, const bf16_t* w, int64_t ldw, void* out, int64_t ldc, int m, int n, int k,
+                             hipStream_t stream) {
+    const int big_cols = tall_mixed_cols(n), small_cols = (n - big_cols * 192) / 128;
+    constexpr size_t smem = 3 * (288 + 128) * BK * sizeof(bf16_t);  // (more than the 2 x 288 + 3 x 192 rows of the other width)
+    auto kern = gemm_bf16_tall_mixed_kernel<THROUGH>;
+    static bool configured = false;
+    if (!configured) {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+        if (e != hipSuccess) return e;
+        configured = true;
+    }
+    kern<<<big_cols + small_cols, 256, smem, stream>>>(a, lda, w, ldw, out, ldc, m, k, big_cols, small_cols);
+    return hipGetLastError();
 }
 
 template <int MODE>
@@ -527,6 +562,13 @@ hipError_t launch_mode(const bf16_t* a, int64_t lda, const bf16_t* w, int64_t ld
             if (m <= 64) return launch_skinny<MODE, 64, 128>(GLLM_TILE_ARGS);
             return launch_tile_w<64, 128, 2, 2, MODE, 3, 3, false>(GLLM_TILE_ARGS);
         case 13:  // one band of 257..384 rows
+            if constexpr (MODE == GEMM_STORE_F32) {
+                const Tall form = tall_form(m, n, k, splits);
+                if (form == Tall::k192) return launch_tile_w<288, 192, 2, 2, MODE, 2, 3, true>(GLLM_TILE_ARGS);
+                if (form == Tall::kMixed)
+                    return ldc <= kThroughMaxLd ? launch_tall_mixed<true>(a, lda, w, ldw, out, ldc, m, n, k, stream)
+                                                : launch_tall_mixed<false>(a, lda, w, ldw, out, ldc, m, n, k, stream);
+            }
             if constexpr (MODE != GEMM_ADD_F32) {
                 if (m <= 288) return launch_tile<288, 128, 2, 2, MODE, 3>(GLLM_TILE_ARGS);
                 if (m <= 320) return launch_tile<320, 128, 2, 2, MODE, 2, 3>(GLLM_TILE_ARGS);
@@ -537,9 +579,8 @@ hipError_t launch_mode(const bf16_t* a, int64_t lda, const bf16_t* w, int64_t ld
         case 5:
             if constexpr (MODE != GEMM_SWIGLU_BF16) return launch_tile<256, 192, 2, 2, MODE, 2, 3>(GLLM_TILE_ARGS);
             else return hipErrorInvalidValue;
-        case 9:  // 257..288 rows in one band where 128 columns do not divide n (and to add): six waves on four SIMDs, but the weights
-                 // are read once.  Against two bands of 256x192, 257 rows: 24768 x 4096 118 -> 85 us, 74304 x 4096 260 -> 190
-            if constexpr (MODE != GEMM_SWIGLU_BF16) return launch_tile_w<288, 192, 3, 2, MODE, 2, 3, true>(GLLM_TILE_ARGS);
+        case 9:  // (six waves on four SIMDs, before: 24768 x 4096 at 264 rows 90 -> 74 us, 74304 x 4096 188 -> 163)
+            if constexpr (MODE != GEMM_SWIGLU_BF16) return launch_tile_w<288, 192, 2, 2, MODE, 2, 3, true>(GLLM_TILE_ARGS);
             else return hipErrorInvalidValue;
         default: return hipErrorInvalidValue;
     }
@@ -652,7 +693,7 @@ struct TileCost {
 };
 constexpr double kCacheRate = 121;
 constexpr TileCost kCost128x128{512, 128, 0.867, 7.42, {0.3, 0.77, 0.26}, 2.05, 0.24, 4.61}, kCost128x128Deep{256, 128, 0.454, 3.05, {0.99, 1, 1}, 1.15, 1.55, 6.72}, kCost128x64Deep{256, 64, 0.37, 2.9, {0.99, 1, 1}, 0.9, 0.5, 6.72},
-    kCost256x192{256, 192, 0.996, 6.74, {0.34, 0.82, 0.92}, 0, 1.09, 6.87}, kCost288x192{256, 192, 1.27, 2.6, {0.89, 0.94, 0.95}, 2.65, 1.8, 6.2};
+    kCost256x192{256, 192, 0.996, 6.74, {0.34, 0.82, 0.92}, 0, 1.09, 6.87}, kCost288x192{256, 192, 1.134, 3, {0.6, 0.58, 0.58}, 7.1, 0.4, 6.5};
 // tiles of 160, 192, 224 and 256 rows x 128 and x 256 columns, and of 288, 320, 352 and 384 rows x 128
 constexpr TileCost narrow_cost(double step) { return {256, 128, step, 3.5, {0.67, 0.86, 0.66}, 2.89, 0.58, 6.15}; }
 constexpr TileCost tall_cost(double step) { return {256, 128, step, 4.89, {0.87, 0.63, 0.17}, 1.34, 0.61, 5.73}; }
@@ -720,6 +761,39 @@ int skinny_columns(int m, int n, int k, int mode, int splits) {
     return mode == GEMM_STORE_F32 && skinny_us(kCostSkinny64[h], m, n, k, mode, splits) < skinny_us(kCostSkinny128[h], m, n, k, mode, splits) ? 64 : 128;
 }
 
+// 288x192 tiles in the whole rounds of a launch of both widths (as many as leave whole 288x128 ones), or 0 where there is none.
+int tall_mixed_cols(int n) {
+    for (int big = n / (256 * 192) * 256; big > 0; big -= 256)
+        if (n > big * 192 && (n - big * 192) % 128 == 0) return big;
+    return 0;
+}
+
+// 257..288 rows (n a multiple of 128).  A wider tile loads a fifth less for a result, and has the better of it where it fills the
+// rounds (264 rows, 128 columns -> 192: 49152 x 4096 123 -> 91 us, 89856 x 8192 358 -> 330, 128256 x 4096 the same, 152064 x 5120
+// 379 -> 397, 6144 x 4096 in four shares 26 -> 31); its costs are fitted to 14 products of one to four shares of k.  In loops of one
+// product the costs of both widths come out 11 % too low from two rounds on (the power limit).
+Tall tall_form(int m, int n, int k, int splits, double* us) {
+    if (m <= 256 || m > 288) return Tall::k128;
+    const TileCost &c128 = kCostTall[0], &c192 = kCost288x192;
+    const double steps = (double)(k / BK) / splits, plane = plane_us(m, n, GEMM_STORE_F32, splits);
+    auto cost_of = [&](const TileCost& c, double rounds, double full) { return launch_us(c, m, n, k, steps, plane, rounds, full); };
+    const double tiles = (double)(n / 128) * splits;
+    double best = cost_of(c128, rounds_of(c128, tiles), tiles / 256);
+    Tall form = Tall::k128;
+    auto consider = [&](Tall f, double cost) {
+        if (cost < best) { best = cost; form = f; }
+    };
+    if (splits == 1) {
+        if (n % 192 == 0) consider(Tall::k192, cost_of(c192, rounds_of(c192, n / 192), n / 192 / 256.0));
+        if (const int big = tall_mixed_cols(n); big > 0) {
+            const double whole = big / 256, low = rounds_of(c128, (n - big * 192) / 128) * (c128.step * steps + c128.per_tile) / (c192.step * steps + c192.per_tile);
+            consider(Tall::kMixed, cost_of(c192, whole + low, n / 192.0 / 256.0));
+        }
+    }
+    if (us) *us = best;
+    return form;
+}
+
 // Tile shape and split-K factor (a divisor of the k-steps from min_splits to max_splits) of the lowest cost.  Up to 64 rows the
 // product is a stream of the weights and tile 7 the only candidate.  A result plane is read back by the next kernel, so a product that is
 // split less is worth the time of that.
@@ -774,7 +848,11 @@ GemmPlan cheapest(int m, int n, int k, int mode, int min_splits, int max_splits,
             // as few bands as cover the rows, where those of equal height are one more (600 rows of 5120 x 5120: 47 -> 41 us)
             const int h1 = gemm_low_bands(m) ? 192 : 256;
             if (h1 != height) consider(1, narrow_cost_of(h1), (double)ceil_div(m, h1) * cols);
-            if (m > 256 && m <= 384 && mode != GEMM_ADD_F32) consider(13, kCostTall[(m - 257) / 32], cols);
+            if (m > 256 && m <= 288 && mode == GEMM_STORE_F32) {
+                double us;
+                tall_form(m, n, k, s, &us);
+                if (us < best_cost) { best_cost = us; best = GemmPlan{13, s}; }
+            } else if (m > 256 && m <= 384 && mode != GEMM_ADD_F32) consider(13, kCostTall[(m - 257) / 32], cols);
             if (mode == GEMM_STORE_F32 && half_width_deep(m, n, s)) consider(6, kCost128x64Deep, 2 * cols);
             else consider(6, kCost128x128Deep, b128 * cols);
             consider(0, kCost128x128, b128 * cols);

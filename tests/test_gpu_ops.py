@@ -142,7 +142,7 @@ def test_gemm_row_mixed_launch(M, rowmix=8):
 @pytest.mark.parametrize("N", [576, 768])
 @pytest.mark.parametrize("M", [257, 270, 288])
 def test_gemm_288_row_tile(M, N):
-    """All of 257..288 rows in one band, 288x192 tiles (six waves) for 576 columns, 288x128 for 768 (to add 288x192): store, add
+    """All of 257..288 rows in one band, 288x192 tiles for 576 columns, 288x128 for 768 (to add 288x192): store, add
     and split-K planes; refused outside that row range, for other column counts and for SwiGLU."""
     K = 384
     print(f"gemm 288-row tile M={M} N={N}", flush=True)
@@ -531,3 +531,27 @@ def test_gemm_fp32_results_of_one_round_and_of_more(M, N, ldc, tile):
     assert np.abs(got - ref).max() <= 2e-5 * np.abs(ref).max() + 1e-6
     for r in range(M):
         assert bool((flat[r * ldc + N: min((r + 1) * ldc, flat.numel())] == 7.0).all()), r
+
+
+@pytest.mark.parametrize("M", [257, 288])
+@pytest.mark.parametrize("N", [32896, 49152, 79104])
+def test_gemm_one_band_of_288_rows_by_either_width(M, N):
+    """128-column tiles (32896), one round of 192-column ones (49152), a round of those and one of 128 columns (79104); rows past
+    the last one and the padding of a row stay as they are."""
+    K = 4096
+    print(f"gemm one band M={M} N={N}", flush=True)
+    torch.manual_seed(5)
+    a = torch.randn(M, K, device=DEV).to(torch.bfloat16)
+    w = (torch.randn(N, K, device=DEV) * 0.02).to(torch.bfloat16)
+    packed = torch.empty_like(w)
+    B.gllm_op_pack_weight(w, packed)
+    out = torch.full((M + 1, N + 8), 7.0, dtype=torch.float32, device=DEV)
+    for tile in (13, -1):
+        out.fill_(7.0)
+        B.gllm_op_gemm_bf16(a, packed, out, M, N, K, B.GEMM_STORE_F32, tile)
+        torch.cuda.synchronize()
+        assert bool((out[M] == 7.0).all()) and bool((out[:, N:] == 7.0).all())
+        for c in range(0, N, 8192):
+            x, y = a.double(), w[c:c + 8192].double()
+            err = (out[:M, c:min(c + 8192, N)].double() - x @ y.T).abs()
+            assert bool((err <= (x.abs() @ y.abs().T) * K * 2.0 ** -24).all()), (tile, c)
