@@ -514,39 +514,68 @@ __global__ void decode_combine_kernel(AttnArgs a, const DecodeRow* __restrict__ 
     const float* __restrict__ part_ml = a.part_ml;
     const DecodeRow rw = rows[blockIdx.x];
     const int hq = blockIdx.y, e = threadIdx.x * 4;
-    // the partials are read eight at a time (all loads of a batch are issued before the first use: a row has a
-    // handful of partials and the kernel is all latency), and combined in partition order
-    constexpr int U = 8;
+    // The kernel is all latency.  Up to kFewParts partials, a row's usual number, are asked for at one time, references and sums
+    // beside the outputs; of more the references are read first and then all of them, eight at a time.  Partition order either way.
+    // Few against that order: one row of 2500 keys (ten partials), eight layers 736 -> 726 us, 32 chunk rows behind 6000 keys
+    // 887 -> 874, 300 rows of the 14B shape behind 3000, three layers 772 -> 759; 118 partials are 1 % slower in sixteens.
+    constexpr int kFewParts = 16;
     const int64_t slot0 = (int64_t)rw.first_item * a.n_q + hq, slot_step = a.n_q;
-    float ms = kNegBig;
-    for (int i0 = 0; i0 < rw.num_items; i0 += U) {
-        float m[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) m[u] = i0 + u < rw.num_items ? part_ml[(slot0 + (i0 + u) * slot_step) * 2] : kNegBig;
-#pragma unroll
-        for (int u = 0; u < U; ++u) ms = fmaxf(ms, m[u]);
-    }
+    float ms = kNegBig, ls = 0.f;
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    float ls = 0.f;
-    for (int i0 = 0; i0 < rw.num_items; i0 += U) {
-        float m[U], l[U];
-        f32x4 ov[U];
+    if (rw.num_items <= kFewParts) {
+        float m[kFewParts], l[kFewParts];
+        f32x4 ov[kFewParts];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            if (i0 + u < rw.num_items) {
-                const int64_t slot = slot0 + (i0 + u) * slot_step;
-                m[u] = part_ml[slot * 2];
-                l[u] = part_ml[slot * 2 + 1];
+        for (int u = 0; u < kFewParts; ++u) {
+            m[u] = kNegBig;
+            if (u < rw.num_items) {
+                const int64_t slot = slot0 + u * slot_step;
+                const f32x2 ml = *reinterpret_cast<const f32x2*>(part_ml + slot * 2);
+                m[u] = ml[0];
+                l[u] = ml[1];
                 ov[u] = *reinterpret_cast<const f32x4*>(part_o + slot * D + e);
             }
         }
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            if (i0 + u < rw.num_items) {
+        for (int u = 0; u < kFewParts; ++u) ms = fmaxf(ms, m[u]);
+#pragma unroll
+        for (int u = 0; u < kFewParts; ++u) {
+            if (u < rw.num_items) {
                 const float sc = __builtin_amdgcn_exp2f(m[u] - ms);
 #pragma unroll
                 for (int v = 0; v < 4; ++v) acc[v] += ov[u][v] * sc;
                 ls += l[u] * sc;
+            }
+        }
+    } else {
+        constexpr int U = 8;
+        for (int i0 = 0; i0 < rw.num_items; i0 += U) {
+            float m[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) m[u] = i0 + u < rw.num_items ? part_ml[(slot0 + (i0 + u) * slot_step) * 2] : kNegBig;
+#pragma unroll
+            for (int u = 0; u < U; ++u) ms = fmaxf(ms, m[u]);
+        }
+        for (int i0 = 0; i0 < rw.num_items; i0 += U) {
+            float m[U], l[U];
+            f32x4 ov[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (i0 + u < rw.num_items) {
+                    const int64_t slot = slot0 + (i0 + u) * slot_step;
+                    m[u] = part_ml[slot * 2];
+                    l[u] = part_ml[slot * 2 + 1];
+                    ov[u] = *reinterpret_cast<const f32x4*>(part_o + slot * D + e);
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (i0 + u < rw.num_items) {
+                    const float sc = __builtin_amdgcn_exp2f(m[u] - ms);
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) acc[v] += ov[u][v] * sc;
+                    ls += l[u] * sc;
+                }
             }
         }
     }

@@ -737,3 +737,17 @@ def test_chunks_of_many_workgroups_match_the_oracle(n_kv, d):
     kp0, vp0 = pool_np(shape, 41, batch.num_blocks)
     r = run_both(shape, w, batch, kp0, vp0, hidden_np(shape, 41, batch.num_tokens))
     assert_output(f"many/{n_kv}/{d}", r, literal=False)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_decode_rows_of_as_many_partials_as_are_merged_at_once(d):
+    """Rows of two, sixteen, seventeen and twenty-five partials of 256 keys beside a whole one: sixteen are read at one time."""
+    print(f"partials of decode rows d={d}", flush=True)
+    shape = synth.StageShape("parts", 1, 256, 4, 2, d, 128)
+    batch = synth.build_batch([(1, 511), (1, 4095), (1, 4096), (1, 6200), (1, 100)], 23, spare_blocks=3)
+    w = layer_weights_np(shape, 23)
+    kp0, vp0 = pool_np(shape, 23, batch.num_blocks)
+    stage = GpuStage(shape, w, [batch])
+    stage.stage.set_option("decode_min_workgroups", 10 ** 6)
+    r = run_both(shape, w, batch, kp0, vp0, hidden_np(shape, 23, batch.num_tokens), stage)
+    assert_output("partials", r, literal=False)
