@@ -338,17 +338,17 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_kernel(const bf16_t*
 // Two tile shapes in one launch: the first big_tiles workgroups cover columns [0, n_split) with H x 256 tiles (whole rounds
 // of the 256 compute units), the rest cover [n_split, N) with H x 128 tiles, so that the last, partial round still gives
 // every compute unit a (half-size) tile.
-template <int MODE, int H, bool W_ONCE>
+template <int MODE, int H, bool W_ONCE, bool THROUGH>
 __global__ __launch_bounds__(256) void gemm_bf16_mixed_kernel(const bf16_t* __restrict__ A, int64_t lda,
                                                                const bf16_t* __restrict__ W, int64_t ldw,
                                                                void* __restrict__ out, int64_t ldc, int M, int K,
                                                                int tiles_m, int big_cols, int small_cols) {
     const int big_tiles = tiles_m * big_cols;
     if ((int)blockIdx.x < big_tiles)
-        gemm_tile<H, 256, 2, 2, MODE, kWideStages<H>, 3, W_ONCE>(A, lda, W, ldw, out, ldc, M, K, tiles_m, big_cols, 0,
+        gemm_tile<H, 256, 2, 2, MODE, kWideStages<H>, 3, W_ONCE, false, THROUGH>(A, lda, W, ldw, out, ldc, M, K, tiles_m, big_cols, 0,
                                                                 xcd_contiguous(blockIdx.x, big_tiles), 0, 1, 0);
     else
-        gemm_tile<H, 128, 2, 2, MODE, 3, 3, W_ONCE>(A, lda, W, ldw, out, ldc, M, K, tiles_m, small_cols, big_cols * 256,
+        gemm_tile<H, 128, 2, 2, MODE, 3, 3, W_ONCE, false, THROUGH>(A, lda, W, ldw, out, ldc, M, K, tiles_m, small_cols, big_cols * 256,
                                                     xcd_contiguous(blockIdx.x - big_tiles, tiles_m * small_cols), 0, 1, 0);
 }
 
@@ -406,16 +406,21 @@ __global__ __launch_bounds__(256) void gemm_any_address_kernel(const bf16_t* __r
     else *f = sum;
 }
 
-// Results are written through the L2 where one band of rows takes more than a round, a tile per compute unit (see kAuxWriteThrough;
-// with several bands there is no difference, 4160 rows), and their rows are near enough for 32-bit offsets over 16 of them.
-constexpr int kThroughMinTiles = 257;
-constexpr int64_t kThroughMaxLd = ((int64_t)1 << 26) - 1;
+// Whether results are written through the L2 (see kAuxWriteThrough): where one band of rows takes more than a round, a tile per compute
+// unit, and the results are more than the L2s keep until the launch ends.  us, left in the L2 / written through: 128256 x 4096, 8 rows (4
+// MB) 160 / 158, 16 rows (8 MB) 164 / 161, 32 rows 172 / 160, 128 rows 197 / 175; 152064 x 5120, 16 rows (10 MB) 245 / 247, 32 rows 264 / 249;
+// 49152 x 4096, 16 rows (3 MB) 64 / 65, 64 rows (13 MB) 80 / 75; 10240 x 8192, 17 rows in eight planes (6 MB) 29 / 31 (a workgroup ends
+// when its stores have arrived).  With several bands there is no difference (4160 rows).  Rows must be near enough for 32-bit offsets over 16.
+constexpr int64_t kThroughMinTiles = 257, kThroughMinBytes = 12000000, kThroughMaxLd = ((int64_t)1 << 26) - 1;
+bool write_through(int64_t tiles, int m, int n, int splits, int64_t ldc) {
+    return tiles >= kThroughMinTiles && (int64_t)m * n * splits * 4 >= kThroughMinBytes && ldc <= kThroughMaxLd;
+}
 
 template <int BM, int BN, int WGM, int WGN, int MODE, int NS, int NSW, bool W_ONCE, bool W_FAR = false, bool THROUGH = false>
 hipError_t launch_tile_w(const bf16_t* a, int64_t lda, const bf16_t* w, int64_t ldw, void* out, int64_t ldc, int m,
                          int n, int k, int splits, int64_t split_stride, hipStream_t stream) {
     if constexpr (MODE == GEMM_STORE_F32 && W_ONCE && !THROUGH) {
-        if ((int64_t)(n / BN) * splits >= kThroughMinTiles && m <= BM && ldc <= kThroughMaxLd)
+        if (m <= BM && write_through((int64_t)(n / BN) * splits, m, n, splits, ldc))
             return launch_tile_w<BM, BN, WGM, WGN, MODE, NS, NSW, W_ONCE, W_FAR, true>(a, lda, w, ldw, out, ldc, m, n, k, splits, split_stride, stream);
     }
     const int tiles_m = (int)ceil_div(m, BM), tiles_n = n / BN;
@@ -566,8 +571,8 @@ hipError_t launch_mode(const bf16_t* a, int64_t lda, const bf16_t* w, int64_t ld
                 const Tall form = tall_form(m, n, k, splits);
                 if (form == Tall::k192) return launch_tile_w<288, 192, 2, 2, MODE, 2, 3, true>(GLLM_TILE_ARGS);
                 if (form == Tall::kMixed)
-                    return ldc <= kThroughMaxLd ? launch_tall_mixed<true>(a, lda, w, ldw, out, ldc, m, n, k, stream)
-                                                : launch_tall_mixed<false>(a, lda, w, ldw, out, ldc, m, n, k, stream);
+                    return write_through(kThroughMinTiles, m, n, 1, ldc) ? launch_tall_mixed<true>(a, lda, w, ldw, out, ldc, m, n, k, stream)
+                                                                         : launch_tall_mixed<false>(a, lda, w, ldw, out, ldc, m, n, k, stream);
             }
             if constexpr (MODE != GEMM_ADD_F32) {
                 if (m <= 288) return launch_tile<288, 128, 2, 2, MODE, 3>(GLLM_TILE_ARGS);
@@ -597,12 +602,16 @@ hipError_t launch_far(const bf16_t* a, int64_t lda, const bf16_t* w, int64_t ldw
 constexpr size_t kWideTileLds = (2 * 256 + 3 * 256) * BK * sizeof(bf16_t);  // 256x256 tile: all 160 KiB
 
 // Mixed launch (see gemm_bf16_mixed_kernel); rem_cols 256-wide tile columns are turned into 2*rem_cols 128-wide ones.
-template <int MODE, int H, bool W_ONCE>
+template <int MODE, int H, bool W_ONCE, bool THROUGH = false>
 hipError_t launch_mixed_h(const bf16_t* a, int64_t lda, const bf16_t* w, int64_t ldw, void* out, int64_t ldc, int m,
                           int n, int k, int rem_cols, hipStream_t stream) {
+    if constexpr (MODE == GEMM_STORE_F32 && W_ONCE && !THROUGH) {
+        if (write_through(kThroughMinTiles, m, n, 1, ldc))
+            return launch_mixed_h<MODE, H, W_ONCE, true>(a, lda, w, ldw, out, ldc, m, n, k, rem_cols, stream);
+    }
     const int tiles_m = (int)ceil_div(m, H), big_cols = n / 256 - rem_cols, small_cols = 2 * rem_cols;
     const size_t smem = std::max(kWideStages<H> * H + 3 * 256, 3 * H + 3 * 128) * BK * sizeof(bf16_t);
-    auto kern = gemm_bf16_mixed_kernel<MODE, H, W_ONCE>;
+    auto kern = gemm_bf16_mixed_kernel<MODE, H, W_ONCE, THROUGH>;
     static bool configured = false;
     if (!configured) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),

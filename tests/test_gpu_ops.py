@@ -515,10 +515,11 @@ def test_gemm_splits_that_are_no_powers_of_two(splits, K):
                 assert np.all(np.abs(out[s].cpu().numpy() - xs @ ys.T) <= (np.abs(xs) @ np.abs(ys).T) * part * 2.0 ** -24), (splits, M, tile, s)
 
 
-@pytest.mark.parametrize("M,N,ldc,tile", [(17, 49152, 49152, 5), (17, 49344, 49350, 5), (17, 128 * 257, 128 * 257, 7), (2, 49344, (1 << 26) - 4, 5), (2, 49344, 1 << 26, 5)])
+@pytest.mark.parametrize("M,N,ldc,tile", [(62, 49152, 49152, 5), (60, 49344, 49350, 5), (61, 49344, 49350, 5), (64, 128 * 512, 128 * 512, 7), (92, 32896, 32896, 6),
+                                          (70, 65792, 65800, 4), (15, 192 * 1372, (1 << 26) - 4, 5), (15, 192 * 1372, 1 << 26, 5)])
 def test_gemm_fp32_results_of_one_round_and_of_more(M, N, ldc, tile):
-    """Results of 256 tiles and of 257, which are stored in another way, packed and with rows as far apart as the 32-bit byte
-    offsets of that way reach and one step farther; nothing between the rows changes."""
+    """Results of one round of tiles and of more, of less than 12 MB and of more, which are stored in another way, packed and with
+    rows as far apart as the 32-bit byte offsets of that way reach and one step farther; nothing between the rows changes."""
     K = 64
     print(f"gemm results M={M} N={N} ldc={ldc} tile={tile}", flush=True)
     a, w = rand_bits(31, 1, (M, K), 1.0), rand_bits(31, 2, (N, K), 0.05)
