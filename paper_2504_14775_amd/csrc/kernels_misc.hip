@@ -5,10 +5,19 @@
 
 namespace {
 
+// Sum over the wave, every lane receives it: v += (v of lane ^ o) for o = 32, 16, 8, 4, 2, 1 without a trip through LDS for each.  (A
+// swap of halves or of rows of 16 gives a lane its own value and the other's; behind the step of 8 the values of a row repeat
+// after 8 lanes, and a rotation by 4 is lane ^ 4, and so on.)
+template <int N>
+__device__ __forceinline__ float add_rotated(float v) {  // by N lanes within rows of 16
+    return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x120 + N, 0xF, 0xF, true));
+}
 __device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o);
-    return v;
+    const auto halves = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = __uint_as_float(halves[0]) + __uint_as_float(halves[1]);
+    const auto rows = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = __uint_as_float(rows[0]) + __uint_as_float(rows[1]);
+    return add_rotated<1>(add_rotated<2>(add_rotated<4>(add_rotated<8>(v))));
 }
 
 // Sum over the THREADS threads of a workgroup; every thread receives the total.
