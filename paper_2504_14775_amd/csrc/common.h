@@ -71,9 +71,11 @@ hipError_t launch_rmsnorm_from_bf16(const bf16_t* in, float* x, const bf16_t* ga
                                     int rows, int hidden, float eps, const void* copy_src, void* copy_dst, size_t copy_bytes,
                                     hipStream_t stream);
 // x += y[0] + ... + y[planes-1] (planes may be 0; plane p at y + p*plane_stride), then
-// h = bf16(rmsnorm(x) * gamma).  x is updated in place when planes > 0.
+// h = bf16(rmsnorm(x) * gamma).  x is updated in place when planes > 0.  Where done is not null (pinned host memory as the device
+// addresses it) the launch stores done_value there: the launches before it on the stream have ended.
 hipError_t launch_add_rmsnorm(float* x, const float* y, int planes, int64_t plane_stride, const bf16_t* gamma,
-                              bf16_t* h, int64_t ldh, int rows, int hidden, float eps, hipStream_t stream);
+                              bf16_t* h, int64_t ldh, int rows, int hidden, float eps, hipStream_t stream,
+                              uint32_t* done = nullptr, uint32_t done_value = 0);
 // out_bf16 = RNE(x + y planes), and optionally out_f32 = that sum.
 hipError_t launch_add_cast_out(const float* x, const float* y, int planes, int64_t plane_stride, bf16_t* out,
                                float* out_f32, int64_t count, hipStream_t stream);

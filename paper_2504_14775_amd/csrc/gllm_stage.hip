@@ -15,11 +15,14 @@
 #include "common.h"
 
 #include <algorithm>
+#include <atomic>
+#include <chrono>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
 #include <new>
 #include <string>
+#include <thread>
 #include <vector>
 
 namespace {
@@ -40,6 +43,7 @@ struct LayerBuffers {
 };
 
 constexpr int kStagingSlots = 4;
+constexpr int kFlagStride = 16;  // words: flags in cache lines of their own
 constexpr int kHalfItemsMax = 256;  // workgroups of whole prefill items
 constexpr int kPrefillSlots = 768;  // prefill attention workgroups that run at one time, three per compute unit
 constexpr int kPrefillMinBlocks = 16;  // fewest key blocks (of 32) in a part of a prefill item
@@ -84,8 +88,13 @@ struct gllm_stage {
     unsigned char* meta_dev = nullptr;
     unsigned char* staging[kStagingSlots] = {};      // pinned host memory
     unsigned char* staging_dev[kStagingSlots] = {};  // the same, as the device addresses it
-    hipEvent_t staging_ev[kStagingSlots] = {};
-    bool staging_used[kStagingSlots] = {};
+    // A slot may be written again once the launch that copies it to the device has ended.  A later launch of the batch says so:
+    // it stores the batch's number in the slot's flag.
+    enum class Slot { kFree, kCopied, kFlagged };  // kCopied: no such launch was enqueued (an error came before it)
+    Slot slot_state[kStagingSlots] = {};
+    uint32_t slot_batch[kStagingSlots] = {};  // number of the batch that used the slot last
+    volatile uint32_t* slot_flag = nullptr;   // pinned host memory, one flag in kFlagStride words for each slot
+    uint32_t* slot_flag_dev = nullptr;        // the same, as the device addresses it
     int next_slot = 0;
     bool overlap_attention = true;  // a small prefill part of a batch shares the launch of decode attention
     bool alias_check = true;
@@ -201,6 +210,31 @@ bool worth_looking_through(const gllm_stage* s, int64_t entries, int64_t tokens)
     const double hidden_us = 12.0 + std::max(2.0 * nk / 6e6, 2.0 * nk * tokens / 1e9);
     const double saved_us = (5.0 + 8.0 * s->n_qkv_pad * tokens / 5e6) * (s->layer_end - s->layer_begin);
     return entries * 0.24e-3 <= hidden_us + saved_us;
+}
+
+// Waits until staging slot `slot` may be written.  An event recorded for every batch did this before: it cost the host and the device 4 to
+// 5 us a batch (52 rows, one tiny layer 42 -> 37 us or 34 -> 30: a launch takes the host 3 or 4 us, by process).  Should the flag not come
+// within seconds, or where none was asked for, the device is waited for as a whole, which also reports its errors.
+hipError_t await_slot(gllm_stage* s, int slot) {
+    using Slot = gllm_stage::Slot;
+    const Slot state = s->slot_state[slot];
+    if (state == Slot::kFree) return hipSuccess;
+    bool done = false;
+    if (state == Slot::kFlagged) {
+        const auto start = std::chrono::steady_clock::now();
+        for (int64_t n = 1; !(done = s->slot_flag[slot * kFlagStride] == s->slot_batch[slot]); ++n) {
+            if (n % 64 != 0) continue;
+            std::this_thread::yield();
+            if (n % 65536 == 0 && std::chrono::steady_clock::now() - start > std::chrono::seconds(5)) break;
+        }
+        std::atomic_thread_fence(std::memory_order_acquire);
+    }
+    if (!done) {
+        const hipError_t e = hipDeviceSynchronize();
+        if (e != hipSuccess) return e;
+    }
+    s->slot_state[slot] = Slot::kFree;
+    return hipSuccess;
 }
 
 hipEvent_t get_event(gllm_stage* s) {
@@ -345,9 +379,12 @@ gllm_status gllm_stage_create(const gllm_stage_config* cfg, gllm_stage** out) {
                 return bail(e, "hipHostMalloc(staging)");
             if ((e = hipHostGetDevicePointer((void**)&s->staging_dev[i], s->staging[i], 0)) != hipSuccess)
                 return bail(e, "hipHostGetDevicePointer(staging)");
-            if ((e = hipEventCreateWithFlags(&s->staging_ev[i], hipEventDisableTiming)) != hipSuccess)
-                return bail(e, "hipEventCreate");
         }
+        void* flags = nullptr;
+        if ((e = hipHostMalloc(&flags, kStagingSlots * kFlagStride * 4, hipHostMallocCoherent)) != hipSuccess) return bail(e, "hipHostMalloc(flags)");
+        std::memset(flags, 0, kStagingSlots * kFlagStride * 4);
+        s->slot_flag = (volatile uint32_t*)flags;
+        if ((e = hipHostGetDevicePointer((void**)&s->slot_flag_dev, flags, 0)) != hipSuccess) return bail(e, "hipHostGetDevicePointer(flags)");
     }
     s->ws_bytes = workspace_layout(s, nullptr);
     *out = s;
@@ -363,8 +400,8 @@ void gllm_stage_destroy(gllm_stage* s) {
     if (s->meta_dev) (void)hipFree(s->meta_dev);
     for (int i = 0; i < kStagingSlots; ++i) {
         if (s->staging[i]) (void)hipHostFree(s->staging[i]);
-        if (s->staging_ev[i]) (void)hipEventDestroy(s->staging_ev[i]);
     }
+    if (s->slot_flag) (void)hipHostFree((void*)s->slot_flag);
     for (auto& sp : s->spans) { (void)hipEventDestroy(sp.a); (void)hipEventDestroy(sp.b); }
     for (auto ev : s->ev_pool) (void)hipEventDestroy(ev);
     delete s;
@@ -598,7 +635,7 @@ gllm_status gllm_stage_forward(gllm_stage* s, const gllm_batch* b, const void* h
     // ---- metadata into a pinned staging slot ----
     const int slot = s->next_slot;
     s->next_slot = (slot + 1) % kStagingSlots;
-    if (s->staging_used[slot]) HIP_TRY(s, hipEventSynchronize(s->staging_ev[slot]));
+    HIP_TRY(s, await_slot(s, slot));
     unsigned char* st_base = s->staging[slot];
     // compact layout for this batch: only what is used travels to the device
     int64_t cnt_items = 0, cnt_pre = 0, cnt_vt = 0;
@@ -796,8 +833,7 @@ gllm_status gllm_stage_forward(gllm_stage* s, const gllm_batch* b, const void* h
                 // left the GPU idle for 20 us in front of the batch
                 HIP_TRY(s, launch_rmsnorm_from_bf16((const bf16_t*)hidden_in, s->x, L.norm1, s->h, H, Ti, H, eps, s->staging_dev[slot],
                                                     s->meta_dev, ml.total, st));
-                HIP_TRY(s, hipEventRecord(s->staging_ev[slot], st));
-                s->staging_used[slot] = true;
+                s->slot_state[slot] = gllm_stage::Slot::kCopied;
             } else HIP_TRY(s, launch_add_rmsnorm(s->x, s->y, pending, y_plane, L.norm1, s->h, H, Ti, H, eps, st));
         }
         {
@@ -852,7 +888,10 @@ gllm_status gllm_stage_forward(gllm_stage* s, const gllm_batch* b, const void* h
         }
         {
             ProfScope ps(s, st, PC_RMSNORM);
-            HIP_TRY(s, launch_add_rmsnorm(s->x, s->y, split_o, y_plane, L.norm2, s->h, H, Ti, H, eps, st));
+            const bool first = l == s->layer_begin;
+            HIP_TRY(s, launch_add_rmsnorm(s->x, s->y, split_o, y_plane, L.norm2, s->h, H, Ti, H, eps, st,
+                                          first ? s->slot_flag_dev + slot * kFlagStride : nullptr, first ? ++s->slot_batch[slot] : 0));
+            if (first) s->slot_state[slot] = gllm_stage::Slot::kFlagged;
         }
         {
             ProfScope ps(s, st, PC_GEMM_GATEUP);

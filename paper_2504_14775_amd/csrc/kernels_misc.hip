@@ -39,6 +39,9 @@ struct CopyIn {
     const u32x4* src;
     u32x4* dst;
     int vecs, workgroups;
+    // a later launch of the batch tells the host that the source may be written again: *done = done_value (pinned host memory)
+    uint32_t* done;
+    uint32_t done_value;
 };
 
 // One workgroup per row.  FROM_BF16: the row comes from the bf16 stage input and is also written out
@@ -67,6 +70,8 @@ __global__ __launch_bounds__(THREADS) void rmsnorm_kernel(const bf16_t* __restri
             return;
         }
         row -= copy.workgroups;
+    } else {
+        if (copy.done && blockIdx.x == 0 && threadIdx.x == 0) __hip_atomic_store(copy.done, copy.done_value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     }
     float* xr = x + row * hidden;
     f32x4 keep[MAXV];
@@ -398,14 +403,16 @@ hipError_t launch_rmsnorm_any(const bf16_t* in, float* x, const float* y, int pl
 hipError_t launch_rmsnorm_from_bf16(const bf16_t* in, float* x, const bf16_t* gamma, bf16_t* h, int64_t ldh,
                                     int rows, int hidden, float eps, const void* copy_src, void* copy_dst, size_t copy_bytes,
                                     hipStream_t stream) {
-    const CopyIn copy{(const u32x4*)copy_src, (u32x4*)copy_dst, (int)(copy_bytes / 16), 0};
+    const CopyIn copy{(const u32x4*)copy_src, (u32x4*)copy_dst, (int)(copy_bytes / 16), 0, nullptr, 0};
     if (copy_bytes % 16 != 0 || copy_bytes / 16 > INT32_MAX / 2 || (((uintptr_t)copy_src | (uintptr_t)copy_dst) & 15)) return hipErrorInvalidValue;
     return launch_rmsnorm_any<true>(in, x, nullptr, 0, 0, gamma, h, ldh, rows, hidden, eps, copy, stream);
 }
 
 hipError_t launch_add_rmsnorm(float* x, const float* y, int planes, int64_t plane_stride, const bf16_t* gamma,
-                              bf16_t* h, int64_t ldh, int rows, int hidden, float eps, hipStream_t stream) {
-    return launch_rmsnorm_any<false>(nullptr, x, y, planes, plane_stride, gamma, h, ldh, rows, hidden, eps, CopyIn{}, stream);
+                              bf16_t* h, int64_t ldh, int rows, int hidden, float eps, hipStream_t stream, uint32_t* done,
+                              uint32_t done_value) {
+    return launch_rmsnorm_any<false>(nullptr, x, y, planes, plane_stride, gamma, h, ldh, rows, hidden, eps,
+                                     CopyIn{nullptr, nullptr, 0, 0, done, done_value}, stream);
 }
 
 hipError_t launch_add_cast_out(const float* x, const float* y, int planes, int64_t plane_stride, bf16_t* out,

@@ -751,3 +751,37 @@ def test_decode_rows_of_as_many_partials_as_are_merged_at_once(d):
     stage.stage.set_option("decode_min_workgroups", 10 ** 6)
     r = run_both(shape, w, batch, kp0, vp0, hidden_np(shape, 23, batch.num_tokens), stage)
     assert_output("partials", r, literal=False)
+
+
+def test_batches_queued_deeper_than_the_staging_slots():
+    """Twelve batches of different sequences and page tables enqueued without a wait on two streams in turn, the same ones one at a
+    time: a slot of the metadata that were written again before its batch has been copied would give another batch's pages."""
+    shape = dataclasses.replace(MID, num_layers=1, name="mid1")
+    batches = [synth.build_batch([(1 + (i * 7) % 5, 20 + 11 * i), (1, 90 - 5 * i), (9, i)], 40 + i, spare_blocks=2 + i) for i in range(12)]
+    w = layer_weights_np(shape, 41)
+    blocks = max(b.num_blocks for b in batches)
+    stage = GpuStage(shape, w, batches)
+    pools = [torch.randn(shape.num_layers * blocks * shape.n_kv_heads * 16 * shape.head_dim, device=DEV).to(torch.bfloat16) for _ in range(2)]
+    xs = [to_dev_bits(hidden_np(shape, 50 + i, b.num_tokens)) for i, b in enumerate(batches)]
+
+    def run(wait):
+        kv = [p.clone() for p in pools]
+        stage.stage.bind_kv_pool(kv[0], kv[1], blocks)
+        outs = [torch.empty(b.num_tokens, shape.hidden, dtype=torch.bfloat16, device=DEV) for b in batches]
+        torch.cuda.synchronize()
+        streams, last = [torch.cuda.Stream(), torch.cuda.Stream()], None
+        for i, b in enumerate(batches):
+            st = streams[i % 2]
+            if last is not None:
+                st.wait_event(last)       # one workspace: the batches of a stage run one after the other
+            stage.stage.forward(b.new_tokens, b.cached_len, b.block_tables, xs[i], outs[i], stream=st)
+            last = st.record_event()
+            if wait:
+                torch.cuda.synchronize()
+        torch.cuda.synchronize()
+        return outs + kv
+
+    one_by_one = run(True)
+    for _ in range(3):
+        for got, want in zip(run(False), one_by_one):
+            assert torch.equal(got, want)
