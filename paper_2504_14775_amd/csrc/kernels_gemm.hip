@@ -702,7 +702,7 @@ struct TileCost {
 };
 constexpr double kCacheRate = 121;
 constexpr TileCost kCost128x128{512, 128, 0.867, 7.42, {0.3, 0.77, 0.26}, 2.05, 0.24, 4.61}, kCost128x128Deep{256, 128, 0.454, 3.05, {0.99, 1, 1}, 1.15, 1.55, 6.72}, kCost128x64Deep{256, 64, 0.37, 2.9, {0.99, 1, 1}, 0.9, 0.5, 6.72},
-    kCost256x192{256, 192, 0.996, 6.74, {0.34, 0.82, 0.92}, 0, 1.09, 6.87}, kCost288x192{256, 192, 1.134, 3, {0.6, 0.58, 0.58}, 7.1, 0.4, 6.5};
+    kCost256x192{256, 192, 0.996, 6.74, {0.34, 0.82, 0.92}, 0, 1.09, 6.87}, kCost288x192{256, 192, 1.134, 3, {0.8, 0.58, 0.58}, 7.1, 0.4, 6.5};
 // tiles of 160, 192, 224 and 256 rows x 128 and x 256 columns, and of 288, 320, 352 and 384 rows x 128
 constexpr TileCost narrow_cost(double step) { return {256, 128, step, 3.5, {0.67, 0.86, 0.66}, 2.89, 0.58, 6.15}; }
 constexpr TileCost tall_cost(double step) { return {256, 128, step, 4.89, {0.87, 0.63, 0.17}, 1.34, 0.61, 5.73}; }
