@@ -416,20 +416,25 @@ bool write_through(int64_t tiles, int m, int n, int splits, int64_t ldc) {
     return tiles >= kThroughMinTiles && (int64_t)m * n * splits * 4 >= kThroughMinBytes && ldc <= kThroughMaxLd;
 }
 
+// LDS that two workgroups do not have room for: launches whose results are written through ask for it where `alone` says that one
+// tile at a time on a compute unit is better (see launch_skinny).
+constexpr size_t kAloneLds = 84 * 1024;
+
 template <int BM, int BN, int WGM, int WGN, int MODE, int NS, int NSW, bool W_ONCE, bool W_FAR = false, bool THROUGH = false>
 hipError_t launch_tile_w(const bf16_t* a, int64_t lda, const bf16_t* w, int64_t ldw, void* out, int64_t ldc, int m,
-                         int n, int k, int splits, int64_t split_stride, hipStream_t stream) {
+                         int n, int k, int splits, int64_t split_stride, hipStream_t stream, bool alone = false) {
     if constexpr (MODE == GEMM_STORE_F32 && W_ONCE && !THROUGH) {
         if (m <= BM && write_through((int64_t)(n / BN) * splits, m, n, splits, ldc))
-            return launch_tile_w<BM, BN, WGM, WGN, MODE, NS, NSW, W_ONCE, W_FAR, true>(a, lda, w, ldw, out, ldc, m, n, k, splits, split_stride, stream);
+            return launch_tile_w<BM, BN, WGM, WGN, MODE, NS, NSW, W_ONCE, W_FAR, true>(a, lda, w, ldw, out, ldc, m, n, k, splits, split_stride, stream, alone);
     }
     const int tiles_m = (int)ceil_div(m, BM), tiles_n = n / BN;
-    const size_t smem = (NS * BM + NSW * BN) * BK * sizeof(bf16_t);
+    constexpr size_t kStages = (NS * BM + NSW * BN) * BK * sizeof(bf16_t), kMost = std::max(kStages, kAloneLds);
+    const size_t smem = THROUGH && alone ? kMost : kStages;
     auto kern = gemm_bf16_kernel<BM, BN, WGM, WGN, MODE, NS, NSW, W_ONCE, W_FAR, THROUGH>;
     static bool configured = false;
     if (!configured) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMost);
         if (e != hipSuccess) return e;
         configured = true;
     }
@@ -470,6 +475,8 @@ int gemm_band_height(int m, int mode) {
 // last round is a long tail (128256 x 4096, 64 rows: the first tiles end between 62 and 91 us, so between 77 and 82).
 // 128256 x 4096: one row 157 -> 153 us, 32 rows 178 -> 170, 64 rows 199 -> 179; 128256 x 8192, 64 rows 355 -> 338.  Where the
 // last round is short the tiles had better end at different times (152064 x 8192, 0.3 of a round left, 64 rows: 433 and 453).
+// There, with results that are written through, one tile at a time on a compute unit keeps its four to five rounds together
+// (two tiles end apart, and the last ones run alone): 152064 x 5120, 64 rows 254 -> 246 us, 28 rows 249 -> 242; x 4096 the same.
 // Two against three stages of A at 1.06 to 4 rounds, k of 4096, 5120 and 8192, one to 64 rows: a full last round takes 0.96 to
 // 1.0 of the time, 0.75 and 0.88 of one 0.85 to 1.0, 0.62 of one 0.95 to 0.99, half of one 0.98 to 1.12, a quarter 0.95 to 1.15.
 constexpr int kSkinnySlots = 512;  // 128-column tiles of three stages that run at one time, two per compute unit
@@ -487,7 +494,7 @@ hipError_t launch_skinny(const bf16_t* a, int64_t lda, const bf16_t* w, int64_t 
         if (tiles <= 256) return launch_tile_w<H, COLS, WM, 4 / WM, MODE, 4, 4, true>(a, lda, w, ldw, out, ldc, m, n, k, splits, split_stride, stream);
         if (tiles > kSkinnySlots && (last == 0 || last >= kSkinnySlots * 3 / 4))
             return launch_tile_w<H, COLS, WM, 4 / WM, MODE, 2, 3, true>(a, lda, w, ldw, out, ldc, m, n, k, splits, split_stride, stream);
-        return launch_tile_w<H, COLS, WM, 4 / WM, MODE, 3, 3, true>(a, lda, w, ldw, out, ldc, m, n, k, splits, split_stride, stream);
+        return launch_tile_w<H, COLS, WM, 4 / WM, MODE, 3, 3, true>(a, lda, w, ldw, out, ldc, m, n, k, splits, split_stride, stream, tiles > kSkinnySlots);
     }
 }
 int skinny_columns(int m, int n, int k, int mode, int splits);
