@@ -7,7 +7,9 @@
 // into LDS (no staging registers, no address arithmetic: the k position is the scalar offset).
 //
 // What bounds it: many rows, the 1400 W power limit (a bare MFMA loop on random operands reaches 1.6-1.8 PFLOP/s); few
-// rows, the stream of the weights (5.5-6 TB/s) and the ~5 us a launch costs before and after it; in between both.  Under
+// rows, the stream of the weights (5.5-6.8 TB/s) and the ~5 us a launch costs before and after it; in between what a compute unit
+// loads: weights from HBM and activations from the L2 pass through it in one order, 68 KB/us of both together whatever the number
+// of LDS stages (activations alone 150), so that a result of a narrow tile costs more.  Under
 // the power limit the clock follows the busy share of the matrix cores, so cycles in the k-loop count in full, and so does
 // the energy of a product.  16x16x32 MFMAs touch an accumulator half as often per product as 32x32x16 ones: the same tile at
 // the same order of loads took 99.3 -> 90.6 us for gate/up at 512 rows (28672 x 4096), 859 -> 833 at 2048 rows of 55296 x
@@ -473,7 +475,8 @@ int gemm_band_height(int m, int mode) {
 // as many in (deeper 128-column tiles at 432 and 448 tiles 1.02, 64-column ones 1.01 to 1.04).  In several rounds of which
 // the last is nearly full two stages of A and three of W: with more loads in flight some compute units run ahead of others and the
 // last round is a long tail (128256 x 4096, 64 rows: the first tiles end between 62 and 91 us, so between 77 and 82).
-// 128256 x 4096: one row 157 -> 153 us, 32 rows 178 -> 170, 64 rows 199 -> 179; 128256 x 8192, 64 rows 355 -> 338.  Where the
+// 128256 x 4096: one row 157 -> 153 us, 32 rows 178 -> 170, 64 rows 199 -> 179 (results written through: 192 -> 162); 128256 x 8192, 64
+// rows 355 -> 338.  Where the
 // last round is short the tiles had better end at different times (152064 x 8192, 0.3 of a round left, 64 rows: 433 and 453).
 // There, with results that are written through, one tile at a time on a compute unit keeps its four to five rounds together
 // (two tiles end apart, and the last ones run alone): 152064 x 5120, 64 rows 254 -> 246 us, 28 rows 249 -> 242; x 4096 the same.
