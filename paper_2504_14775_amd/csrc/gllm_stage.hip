@@ -224,7 +224,8 @@ hipError_t await_slot(gllm_stage* s, int slot) {
         const auto start = std::chrono::steady_clock::now();
         for (int64_t n = 1; !(done = s->slot_flag[slot * kFlagStride] == s->slot_batch[slot]); ++n) {
             if (n % 64 != 0) continue;
-            std::this_thread::yield();
+            if (n < 64 * 1024) std::this_thread::yield();
+            else std::this_thread::sleep_for(std::chrono::microseconds(20));  // long batches: three more are queued meanwhile
             if (n % 65536 == 0 && std::chrono::steady_clock::now() - start > std::chrono::seconds(5)) break;
         }
         std::atomic_thread_fence(std::memory_order_acquire);
