@@ -25,7 +25,9 @@
  *     gllm_last_error() gives a message.  Errors found by validation are reported before
  *     anything is enqueued, so a failed call has no side effects on device memory.
  *   - `stream` arguments are hipStream_t values passed as void* (NULL = the null stream).
- *     gllm_stage_forward only enqueues work; it does not synchronise.
+ *     gllm_stage_forward only enqueues work.  Page tables and lengths travel through a ring of four host buffers: a call waits on the
+ *     host until the first launch of the call four before it has ended, for as long as that takes, and for nothing else.
+ *     A call recorded into a graph reads its buffer at every replay; the fourth call behind it writes the buffer anew.
  *   - A stage object is not thread safe; use one per stream.
  *   - There is no CPU fallback: without a usable HIP device create() fails.
  */

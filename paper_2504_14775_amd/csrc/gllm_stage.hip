@@ -13,16 +13,14 @@
 // overlaps the execution of batch i, the "metadata ahead of data" idea of section 3.3).
 #include "../../include/gllm_stage.h"
 #include "common.h"
+#include "staging_slot.h"
 
 #include <algorithm>
-#include <atomic>
-#include <chrono>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
 #include <new>
 #include <string>
-#include <thread>
 #include <vector>
 
 namespace {
@@ -88,11 +86,9 @@ struct gllm_stage {
     unsigned char* meta_dev = nullptr;
     unsigned char* staging[kStagingSlots] = {};      // pinned host memory
     unsigned char* staging_dev[kStagingSlots] = {};  // the same, as the device addresses it
-    // A slot may be written again once the launch that copies it to the device has ended.  A later launch of the batch says so:
-    // it stores the batch's number in the slot's flag.
-    enum class Slot { kFree, kCopied, kFlagged };  // kCopied: no such launch was enqueued (an error came before it)
-    Slot slot_state[kStagingSlots] = {};
-    uint32_t slot_batch[kStagingSlots] = {};  // number of the batch that used the slot last
+    StagingSlot slots[kStagingSlots];
+    hipStream_t slot_stream[kStagingSlots] = {};     // of the batch that used the slot last
+    hipEvent_t slot_event[kStagingSlots] = {};       // behind a batch that ended in an error after its copy was enqueued
     volatile uint32_t* slot_flag = nullptr;   // pinned host memory, one flag in kFlagStride words for each slot
     uint32_t* slot_flag_dev = nullptr;        // the same, as the device addresses it
     int next_slot = 0;
@@ -212,31 +208,40 @@ bool worth_looking_through(const gllm_stage* s, int64_t entries, int64_t tokens)
     return entries * 0.24e-3 <= hidden_us + saved_us;
 }
 
-// Waits until staging slot `slot` may be written.  An event recorded for every batch did this before: it cost the host and the device 4 to
-// 5 us a batch (52 rows, one tiny layer 42 -> 37 us or 34 -> 30: a launch takes the host 3 or 4 us, by process).  Should the flag not come
-// within seconds, or where none was asked for, the device is waited for as a whole, which also reports its errors.
-hipError_t await_slot(gllm_stage* s, int slot) {
-    using Slot = gllm_stage::Slot;
-    const Slot state = s->slot_state[slot];
-    if (state == Slot::kFree) return hipSuccess;
-    bool done = false;
-    if (state == Slot::kFlagged) {
-        const auto start = std::chrono::steady_clock::now();
-        for (int64_t n = 1; !(done = s->slot_flag[slot * kFlagStride] == s->slot_batch[slot]); ++n) {
-            if (n % 64 != 0) continue;
-            if (n < 64 * 1024) std::this_thread::yield();
-            else std::this_thread::sleep_for(std::chrono::microseconds(20));  // long batches: three more are queued meanwhile
-            if (n % 65536 == 0 && std::chrono::steady_clock::now() - start > std::chrono::seconds(5)) break;
-        }
-        std::atomic_thread_fence(std::memory_order_acquire);
+// The error that keeps a stream's work from ending, if there is one.  Anything else (not ready, the stream destroyed by its owner, a
+// capture that forbids the question) does not end the wait: what was enqueued is done all the same.
+hipError_t stream_error(hipStream_t st) {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;  // a capture in another thread stays valid
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    hipError_t e = st ? hipStreamIsCapturing(st, &capture) : hipSuccess;
+    if (e == hipSuccess && capture == hipStreamCaptureStatusNone) e = hipStreamQuery(st);
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    switch (e) {
+        case hipErrorIllegalAddress: case hipErrorLaunchFailure: case hipErrorLaunchTimeOut: case hipErrorAssert:
+        case hipErrorECCNotCorrectable: case hipErrorNoDevice: return e;
+        default: (void)hipGetLastError(); return hipSuccess;
     }
-    if (!done) {
-        const hipError_t e = hipDeviceSynchronize();
-        if (e != hipSuccess) return e;
-    }
-    s->slot_state[slot] = Slot::kFree;
-    return hipSuccess;
 }
+
+// Waits until staging slot `slot` may be written: for the launch that copies it, and nothing else on any stream or device.  An event
+// recorded for every batch did this before; the flag costs less on the host and on the device (52 rows, one tiny layer, 43.7 -> 40.4 us
+// with a process for each side, 40.6 -> 40.0 in turn in one).
+hipError_t await_slot(gllm_stage* s, int slot) {
+    return (hipError_t)await_staging_slot(s->slots[slot], s->slot_flag + slot * kFlagStride,
+                                          [&] { return (int)hipEventSynchronize(s->slot_event[slot]); },
+                                          [&] { return (int)stream_error(s->slot_stream[slot]); });
+}
+
+// Where a forward pass ends between the copy and the launch that stores the flag, an event stands behind the copy.
+struct CopiedSlot {
+    gllm_stage* s;
+    int slot;
+    ~CopiedSlot() {
+        if (s->slots[slot].state != StagingSlot::State::kCopied) return;
+        if (hipEventRecord(s->slot_event[slot], s->slot_stream[slot]) != hipSuccess) (void)hipStreamSynchronize(s->slot_stream[slot]);
+    }
+};
 
 hipEvent_t get_event(gllm_stage* s) {
     if (!s->ev_pool.empty()) {
@@ -380,6 +385,8 @@ gllm_status gllm_stage_create(const gllm_stage_config* cfg, gllm_stage** out) {
                 return bail(e, "hipHostMalloc(staging)");
             if ((e = hipHostGetDevicePointer((void**)&s->staging_dev[i], s->staging[i], 0)) != hipSuccess)
                 return bail(e, "hipHostGetDevicePointer(staging)");
+            if ((e = hipEventCreateWithFlags(&s->slot_event[i], hipEventDisableTiming)) != hipSuccess)
+                return bail(e, "hipEventCreate");
         }
         void* flags = nullptr;
         if ((e = hipHostMalloc(&flags, kStagingSlots * kFlagStride * 4, hipHostMallocCoherent)) != hipSuccess) return bail(e, "hipHostMalloc(flags)");
@@ -401,6 +408,7 @@ void gllm_stage_destroy(gllm_stage* s) {
     if (s->meta_dev) (void)hipFree(s->meta_dev);
     for (int i = 0; i < kStagingSlots; ++i) {
         if (s->staging[i]) (void)hipHostFree(s->staging[i]);
+        if (s->slot_event[i]) (void)hipEventDestroy(s->slot_event[i]);
     }
     if (s->slot_flag) (void)hipHostFree((void*)s->slot_flag);
     for (auto& sp : s->spans) { (void)hipEventDestroy(sp.a); (void)hipEventDestroy(sp.b); }
@@ -634,9 +642,16 @@ gllm_status gllm_stage_forward(gllm_stage* s, const gllm_batch* b, const void* h
     }
 
     // ---- metadata into a pinned staging slot ----
+    hipStream_t st = (hipStream_t)stream_;
+    // (a call that is recorded into a graph enqueues nothing: nobody waits for its copy, and its replays store no flag)
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (st) HIP_TRY(s, hipStreamIsCapturing(st, &capture));
+    const bool recorded = capture != hipStreamCaptureStatusNone;
     const int slot = s->next_slot;
     s->next_slot = (slot + 1) % kStagingSlots;
     HIP_TRY(s, await_slot(s, slot));
+    s->slot_stream[slot] = st;
+    const CopiedSlot copied{s, slot};
     unsigned char* st_base = s->staging[slot];
     // compact layout for this batch: only what is used travels to the device
     int64_t cnt_items = 0, cnt_pre = 0, cnt_vt = 0;
@@ -800,7 +815,6 @@ gllm_status gllm_stage_forward(gllm_stage* s, const gllm_batch* b, const void* h
         return s->item_list[x].kv_end - s->item_list[x].kv_begin > s->item_list[y].kv_end - s->item_list[y].kv_begin;
     });
     for (int i = 0; i < n_items; ++i) dec_items[i] = s->item_list[s->item_order[i]];
-    hipStream_t st = (hipStream_t)stream_;
 
     const int32_t* d_tok_pos = (const int32_t*)(s->meta_dev + ml.tok_pos);
     const int32_t* d_tok_page = (const int32_t*)(s->meta_dev + ml.tok_page);
@@ -834,7 +848,7 @@ gllm_status gllm_stage_forward(gllm_stage* s, const gllm_batch* b, const void* h
                 // left the GPU idle for 20 us in front of the batch
                 HIP_TRY(s, launch_rmsnorm_from_bf16((const bf16_t*)hidden_in, s->x, L.norm1, s->h, H, Ti, H, eps, s->staging_dev[slot],
                                                     s->meta_dev, ml.total, st));
-                s->slot_state[slot] = gllm_stage::Slot::kCopied;
+                if (!recorded) s->slots[slot].state = StagingSlot::State::kCopied;
             } else HIP_TRY(s, launch_add_rmsnorm(s->x, s->y, pending, y_plane, L.norm1, s->h, H, Ti, H, eps, st));
         }
         {
@@ -889,10 +903,10 @@ gllm_status gllm_stage_forward(gllm_stage* s, const gllm_batch* b, const void* h
         }
         {
             ProfScope ps(s, st, PC_RMSNORM);
-            const bool first = l == s->layer_begin;
+            const bool flags = l == s->layer_begin && !recorded;
             HIP_TRY(s, launch_add_rmsnorm(s->x, s->y, split_o, y_plane, L.norm2, s->h, H, Ti, H, eps, st,
-                                          first ? s->slot_flag_dev + slot * kFlagStride : nullptr, first ? ++s->slot_batch[slot] : 0));
-            if (first) s->slot_state[slot] = gllm_stage::Slot::kFlagged;
+                                          flags ? s->slot_flag_dev + slot * kFlagStride : nullptr, flags ? ++s->slots[slot].batch : 0));
+            if (flags) s->slots[slot].state = StagingSlot::State::kFlagged;
         }
         {
             ProfScope ps(s, st, PC_GEMM_GATEUP);

@@ -7,6 +7,7 @@ large, within the scale-aware form: y_bf16 == RNE(y_f32) bit-exactly, max|y_f32 
 sum|y_bf16 - ref| / sum|ref| <= 5e-3.
 """
 import dataclasses
+import time
 
 import numpy as np
 import pytest
@@ -754,8 +755,9 @@ def test_decode_rows_of_as_many_partials_as_are_merged_at_once(d):
 
 
 def test_batches_queued_deeper_than_the_staging_slots():
-    """Twelve batches of different sequences and page tables enqueued without a wait on two streams in turn, the same ones one at a
-    time: a slot of the metadata that were written again before its batch has been copied would give another batch's pages."""
+    """Twelve batches of different sequences and page tables enqueued behind 50 ms and more of other work, on two streams in turn, and
+    the same ones one at a time: a slot of the metadata that were written again before its batch has been copied would give
+    another batch's pages.  Four batches wait in their slots, the fifth call returns when the first has been copied."""
     shape = dataclasses.replace(MID, num_layers=1, name="mid1")
     batches = [synth.build_batch([(1 + (i * 7) % 5, 20 + 11 * i), (1, 90 - 5 * i), (9, i)], 40 + i, spare_blocks=2 + i) for i in range(12)]
     w = layer_weights_np(shape, 41)
@@ -763,18 +765,28 @@ def test_batches_queued_deeper_than_the_staging_slots():
     stage = GpuStage(shape, w, batches)
     pools = [torch.randn(shape.num_layers * blocks * shape.n_kv_heads * 16 * shape.head_dim, device=DEV).to(torch.bfloat16) for _ in range(2)]
     xs = [to_dev_bits(hidden_np(shape, 50 + i, b.num_tokens)) for i, b in enumerate(batches)]
+    big = torch.randn(8192, 8192, device=DEV)
 
     def run(wait):
         kv = [p.clone() for p in pools]
         stage.stage.bind_kv_pool(kv[0], kv[1], blocks)
         outs = [torch.empty(b.num_tokens, shape.hidden, dtype=torch.bfloat16, device=DEV) for b in batches]
         torch.cuda.synchronize()
-        streams, last = [torch.cuda.Stream(), torch.cuda.Stream()], None
+        streams, last, front = [torch.cuda.Stream(), torch.cuda.Stream()], None, None
+        if not wait:
+            with torch.cuda.stream(streams[0]):
+                for _ in range(12):       # (1.1e12 operations each, in 32 bits: milliseconds)
+                    torch.mm(big, big)
+            front = streams[0].record_event()
         for i, b in enumerate(batches):
             st = streams[i % 2]
             if last is not None:
                 st.wait_event(last)       # one workspace: the batches of a stage run one after the other
+            if front is not None and i <= 4:
+                assert not front.query(), i
             stage.stage.forward(b.new_tokens, b.cached_len, b.block_tables, xs[i], outs[i], stream=st)
+            if front is not None and i >= 4:
+                assert front.query(), i
             last = st.record_event()
             if wait:
                 torch.cuda.synchronize()
@@ -785,3 +797,39 @@ def test_batches_queued_deeper_than_the_staging_slots():
     for _ in range(3):
         for got, want in zip(run(False), one_by_one):
             assert torch.equal(got, want)
+
+
+def test_a_forward_in_a_graph_leaves_the_calls_behind_it_alone():
+    """Recorded and not replayed: nothing waits for its copy.  Replayed between other calls: they go on without a wait, with the same
+    results."""
+    shape = dataclasses.replace(MID, num_layers=2, name="mid2")
+    batch = synth.build_batch([(1, 40), (9, 23), (1, 100)], 44, spare_blocks=2)
+    w = layer_weights_np(shape, 44)
+    stage = GpuStage(shape, w, [batch])
+    pool = torch.randn(2, shape.num_layers * batch.num_blocks * shape.n_kv_heads * 16 * shape.head_dim, device=DEV).to(torch.bfloat16)
+    stage.stage.bind_kv_pool(pool[0], pool[1], batch.num_blocks)
+    x = to_dev_bits(hidden_np(shape, 44, batch.num_tokens))
+    out = torch.empty(batch.num_tokens, shape.hidden, dtype=torch.bfloat16, device=DEV)
+
+    def forward(stream=None):
+        stage.stage.forward(batch.new_tokens, batch.cached_len, batch.block_tables, x, out, stream=stream)
+
+    def timed(f):
+        out.zero_()
+        torch.cuda.synchronize()
+        t = time.monotonic()
+        f()
+        torch.cuda.synchronize()
+        assert torch.equal(out, want)
+        return time.monotonic() - t
+
+    forward()
+    torch.cuda.synchronize()
+    want = out.clone()
+    stream, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        forward(stream)
+    assert max(timed(forward) for _ in range(9)) < 1.0
+    for _ in range(3):
+        assert timed(graph.replay) < 1.0
+        assert max(timed(forward) for _ in range(5)) < 1.0
