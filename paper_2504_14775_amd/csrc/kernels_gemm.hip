@@ -412,10 +412,11 @@ __global__ __launch_bounds__(256) void gemm_any_address_kernel(const bf16_t* __r
 // unit, and the results are more than the L2s keep until the launch ends.  us, left in the L2 / written through: 128256 x 4096, 8 rows (4
 // MB) 160 / 158, 16 rows (8 MB) 164 / 161, 32 rows 172 / 160, 128 rows 197 / 175; 152064 x 5120, 16 rows (10 MB) 245 / 247, 32 rows 264 / 249;
 // 49152 x 4096, 16 rows (3 MB) 64 / 65, 64 rows (13 MB) 80 / 75; 10240 x 8192, 17 rows in eight planes (6 MB) 29 / 31 (a workgroup ends
-// when its stores have arrived).  With several bands there is no difference (4160 rows).  Rows must be near enough for 32-bit offsets over 16.
+// when its stores have arrived).  With several bands there is no difference (4160 rows).  Rows must be near enough for 32-bit offsets over 16, and
+// follow one another upwards.
 constexpr int64_t kThroughMinTiles = 257, kThroughMinBytes = 12000000, kThroughMaxLd = ((int64_t)1 << 26) - 1;
 bool write_through(int64_t tiles, int m, int n, int splits, int64_t ldc) {
-    return tiles >= kThroughMinTiles && (int64_t)m * n * splits * 4 >= kThroughMinBytes && ldc <= kThroughMaxLd;
+    return tiles >= kThroughMinTiles && (int64_t)m * n * splits * 4 >= kThroughMinBytes && ldc >= 0 && ldc <= kThroughMaxLd;
 }
 
 // LDS that two workgroups do not have room for: launches whose results are written through ask for it where `alone` says that one

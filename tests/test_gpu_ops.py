@@ -534,6 +534,22 @@ def test_gemm_fp32_results_of_one_round_and_of_more(M, N, ldc, tile):
         assert bool((flat[r * ldc + N: min((r + 1) * ldc, flat.numel())] == 7.0).all()), r
 
 
+@pytest.mark.parametrize("M,N,tile", [(64, 128 * 512, 7), (100, 192 * 257, 5), (257, 192 * 412, 13)])
+def test_gemm_fp32_results_with_rows_in_descending_order(M, N, tile):
+    """A negative row stride of the results, of sizes that are stored by 32-bit offsets from a row where the stride allows it: the
+    same bits as upwards, nothing beside them."""
+    K = 64
+    print(f"gemm descending rows M={M} N={N} tile={tile}", flush=True)
+    a, w = to_dev_bits(padded_rows(rand_bits(32, 1, (M, K), 1.0), 288)), to_dev_weight(rand_bits(32, 2, (N, K), 0.05))
+    up = torch.full((M, N), 7.0, device=DEV)
+    down = torch.full((M + 2, N), 7.0, device=DEV)
+    B.gllm_op_gemm_bf16(a, w, up, M, N, K, B.GEMM_STORE_F32, tile)
+    B.gllm_op_gemm_bf16(a, w, down[M], M, N, K, B.GEMM_STORE_F32, tile, ldc=-N)
+    torch.cuda.synchronize()
+    assert torch.equal(down[1:M + 1].flip(0), up)
+    assert bool((down[0] == 7.0).all()) and bool((down[M + 1] == 7.0).all())
+
+
 @pytest.mark.parametrize("M", [257, 288])
 @pytest.mark.parametrize("N", [32896, 49152, 79104])
 def test_gemm_one_band_of_288_rows_by_either_width(M, N):
