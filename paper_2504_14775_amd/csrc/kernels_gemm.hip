@@ -479,11 +479,15 @@ int gemm_band_height(int m, int mode) {
 // 128256 x 4096: one row 157 -> 153 us, 32 rows 178 -> 170, 64 rows 199 -> 179 (results written through: 192 -> 162); 128256 x 8192, 64
 // rows 355 -> 338.  Where the
 // last round is short the tiles had better end at different times (152064 x 8192, 0.3 of a round left, 64 rows: 433 and 453).
-// There, with results that are written through, one tile at a time on a compute unit keeps its four to five rounds together
-// (two tiles end apart, and the last ones run alone): 152064 x 5120, 64 rows 254 -> 246 us, 28 rows 249 -> 242; x 4096 the same.
+// There, with results that are written through, one tile at a time on a compute unit keeps the rounds of 256 together (two tiles end
+// apart, and the last ones run alone), from more than four of them on: norm, projection and sampling together 0.96 to 1.00 of the time at 24
+// to 64 rows, 1.02 at most, k of 2048 to 8320 and 4.0 to 7.0 rounds alike (152064 x 5120, 64 rows 266 -> 258 us), up to 3.4 rounds 0.97 to
+// 1.05; but 1.00 to 1.06 where the tiles lie 1 MiB apart (k of 4096; 3840 and 4224 gain; why is not known).  All of them:
+// profiles/gemm_one_tile_at_a_time.txt.
 // Two against three stages of A at 1.06 to 4 rounds, k of 4096, 5120 and 8192, one to 64 rows: a full last round takes 0.96 to
 // 1.0 of the time, 0.75 and 0.88 of one 0.85 to 1.0, 0.62 of one 0.95 to 0.99, half of one 0.98 to 1.12, a quarter 0.95 to 1.15.
 constexpr int kSkinnySlots = 512;  // 128-column tiles of three stages that run at one time, two per compute unit
+constexpr int64_t kAloneMinTiles = 1025, kNotAloneApart = (int64_t)1 << 20;  // tiles, bytes from the weights of a tile to those of the next
 template <int MODE, int H, int COLS>
 hipError_t launch_skinny(const bf16_t* a, int64_t lda, const bf16_t* w, int64_t ldw, void* out, int64_t ldc, int m,
                          int n, int k, int splits, int64_t split_stride, hipStream_t stream) {
@@ -498,7 +502,8 @@ hipError_t launch_skinny(const bf16_t* a, int64_t lda, const bf16_t* w, int64_t 
         if (tiles <= 256) return launch_tile_w<H, COLS, WM, 4 / WM, MODE, 4, 4, true>(a, lda, w, ldw, out, ldc, m, n, k, splits, split_stride, stream);
         if (tiles > kSkinnySlots && (last == 0 || last >= kSkinnySlots * 3 / 4))
             return launch_tile_w<H, COLS, WM, 4 / WM, MODE, 2, 3, true>(a, lda, w, ldw, out, ldc, m, n, k, splits, split_stride, stream);
-        return launch_tile_w<H, COLS, WM, 4 / WM, MODE, 3, 3, true>(a, lda, w, ldw, out, ldc, m, n, k, splits, split_stride, stream, tiles > kSkinnySlots);
+        return launch_tile_w<H, COLS, WM, 4 / WM, MODE, 3, 3, true>(a, lda, w, ldw, out, ldc, m, n, k, splits, split_stride, stream,
+                                                                    tiles >= kAloneMinTiles && ldw * COLS * 2 != kNotAloneApart);
     }
 }
 int skinny_columns(int m, int n, int k, int mode, int splits);

@@ -516,10 +516,12 @@ def test_gemm_splits_that_are_no_powers_of_two(splits, K):
 
 
 @pytest.mark.parametrize("M,N,ldc,tile", [(62, 49152, 49152, 5), (60, 49344, 49350, 5), (61, 49344, 49350, 5), (64, 128 * 512, 128 * 512, 7), (92, 32896, 32896, 6),
+                                          (19, 152064, 152064, 7), (20, 152064, 152070, 7), (64, 152064, 152064, 7), (33, 131840, 131844, 7), (33, 131072, 131072, 7),
                                           (70, 65792, 65800, 4), (15, 192 * 1372, (1 << 26) - 4, 5), (15, 192 * 1372, 1 << 26, 5)])
 def test_gemm_fp32_results_of_one_round_and_of_more(M, N, ldc, tile):
     """Results of one round of tiles and of more, of less than 12 MB and of more, which are stored in another way, packed and with
-    rows as far apart as the 32-bit byte offsets of that way reach and one step farther; nothing between the rows changes."""
+    rows as far apart as the 32-bit byte offsets of that way reach and one step farther; nothing between the rows changes.  Of tile 7
+    128-column tiles: 1024 of two stages of A, 1030 and 1188 with a compute unit each (of 32 rows for M = 20, of 64 above 32)."""
     K = 64
     print(f"gemm results M={M} N={N} ldc={ldc} tile={tile}", flush=True)
     a, w = rand_bits(31, 1, (M, K), 1.0), rand_bits(31, 2, (N, K), 0.05)
