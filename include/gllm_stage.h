@@ -238,6 +238,11 @@ gllm_status gllm_op_gemm_bf16_splitk(const void* a, int64_t lda, const void* w, 
 gllm_status gllm_op_gemm_plan(int32_t m, int32_t n, int32_t k, int32_t mode, int32_t max_splits, int32_t* tile,
                               int32_t* splits);
 
+/* Host only: the columns of the workgroup tiles by which a tile id covers a product, where one id stands for several widths; 0 where a
+ * launch has tiles of two.  GLLM_E_UNSUPPORTED where the id does not fit the shape. */
+gllm_status gllm_op_gemm_tile_columns(int32_t m, int32_t n, int32_t k, int32_t mode, int32_t tile, int32_t splits,
+                                      int32_t* columns);
+
 /* h[t][j] = bf16(x[t][j] * rsqrt(mean_j x^2 + eps) * gamma[j]); x fp32 [rows][hidden]. */
 gllm_status gllm_op_rmsnorm(const float* x, const void* gamma_bf16, void* h_bf16, int32_t rows, int32_t hidden,
                             double eps, void* stream);

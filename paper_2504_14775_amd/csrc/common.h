@@ -64,6 +64,8 @@ int gemm_rowmix_rem_rows(int m, int n);
 // whether it may pick tile 8.  Result planes count twice: as they are written and as the next kernel reads them back.
 struct GemmPlan { int tile; int splits; };
 GemmPlan gemm_plan(int m, int n, int k, int mode, int max_splits, bool row_mixed = true);
+// Columns of the tiles that a launch of this tile id has (0: of two widths), or -1 where it does not cover the product.
+int gemm_tile_columns(int m, int n, int k, int mode, int tile, int splits);
 
 // Residual stream entry: x = float(in_bf16), h = bf16(rmsnorm(x) * gamma).  The launch also copies copy_bytes (a multiple
 // of 16) from copy_src, which may be pinned host memory, to copy_dst; both 16-byte aligned.

@@ -960,6 +960,15 @@ gllm_status gllm_op_gemm_plan(int32_t m, int32_t n, int32_t k, int32_t mode, int
     return GLLM_OK;
 }
 
+gllm_status gllm_op_gemm_tile_columns(int32_t m, int32_t n, int32_t k, int32_t mode, int32_t tile, int32_t splits,
+                                      int32_t* columns) {
+    if (!columns || m < 1 || n < 1 || k < 1 || n % 64 != 0 || k % 64 != 0 || splits < 1 || (k / 64) % splits != 0 || mode < 0 ||
+        mode > GEMM_SWIGLU_BF16)
+        return GLLM_E_INVALID;
+    *columns = gemm_tile_columns(m, n, k, mode, tile, splits);
+    return *columns < 0 ? GLLM_E_UNSUPPORTED : GLLM_OK;
+}
+
 gllm_status gllm_op_rmsnorm(const float* x, const void* gamma, void* h, int32_t rows, int32_t hidden, double eps,
                             void* stream) {
     if (!x || !gamma || !h || hidden % 4 != 0) return GLLM_E_INVALID;

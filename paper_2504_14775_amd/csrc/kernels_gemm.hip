@@ -509,7 +509,7 @@ hipError_t launch_skinny(const bf16_t* a, int64_t lda, const bf16_t* w, int64_t 
 int skinny_columns(int m, int n, int k, int mode, int splits);
 // One band of 257..288 rows in store mode: tiles of 128 or of 192 columns, or whole rounds of 192 and a last one of 128.
 enum class Tall { k128, k192, kMixed };
-Tall tall_form(int m, int n, int k, int splits, double* us = nullptr);
+Tall tall_form(int m, int n, int splits);
 int tall_mixed_cols(int n);
 
 // Tile 6 up to 128 rows: 64 columns where half of the compute units would be without a tile of 128 and nearly all have one of 64.
@@ -584,7 +584,7 @@ hipError_t launch_mode(const bf16_t* a, int64_t lda, const bf16_t* w, int64_t ld
             return launch_tile_w<64, 128, 2, 2, MODE, 3, 3, false>(GLLM_TILE_ARGS);
         case 13:  // one band of 257..384 rows
             if constexpr (MODE == GEMM_STORE_F32) {
-                const Tall form = tall_form(m, n, k, splits);
+                const Tall form = tall_form(m, n, splits);
                 if (form == Tall::k192) return launch_tile_w<288, 192, 2, 2, MODE, 2, 3, true>(GLLM_TILE_ARGS);
                 if (form == Tall::kMixed)
                     return write_through(kThroughMinTiles, m, n, 1, ldc) ? launch_tall_mixed<true>(a, lda, w, ldw, out, ldc, m, n, k, stream)
@@ -793,30 +793,43 @@ int tall_mixed_cols(int n) {
     return 0;
 }
 
-// 257..288 rows (n a multiple of 128).  A wider tile loads a fifth less for a result, and has the better of it where it fills the
-// rounds (264 rows, 128 columns -> 192: 49152 x 4096 123 -> 91 us, 89856 x 8192 358 -> 330, 128256 x 4096 the same, 152064 x 5120
-// 379 -> 397, 6144 x 4096 in four shares 26 -> 31); its costs are fitted to 14 products of one to four shares of k.  In loops of one
-// product the costs of both widths come out 11 % too low from two rounds on (the power limit).
-Tall tall_form(int m, int n, int k, int splits, double* us) {
-    if (m <= 256 || m > 288) return Tall::k128;
+// 257..288 rows in one share of k (n a multiple of 128).  A wider tile loads a fifth less for a result; tiles are one to a compute unit and
+// end together, so that a round that is begun counts in full, one of 192 columns 1.3 of one of 128.  Norm, projection and sampling of 257
+// to 288 rows, us, by 128 / 192 / both: 49152 x 4096 137 / 111 / -, 65664 x 4096 201 / 176 / 160, 89856 x 4096 218 / 201 / 227, 100352 x 8192 475 / - /
+// 448, 128256 x 4096 308 / 295 / 282, 152064 x 4096 354 / 366 / 346, 196608 x 8192 845 / 789 / 831.  At 13 column counts, k of 4096, 5120
+// and 8192 and three row counts the form picked so is the fastest one each time (profiles/gemm_288_rows_by_width.txt); by the costs of the
+// planner, which decided before, it was up to 27 % behind (65664 x 4096).  In more shares 128 columns are better (6144 x 4096 in four, 264 rows 26 and 31).
+constexpr double kRoundOf192 = 1.3;
+Tall tall_form(int m, int n, int splits) {
+    if (m <= 256 || m > 288 || splits != 1) return Tall::k128;
+    const double rounds128 = (double)ceil_div(n / 128, 256);
+    double best = rounds128;
+    Tall form = Tall::k128;
+    if (n % 192 == 0 && kRoundOf192 * ceil_div(n / 192, 256) < best) {
+        best = kRoundOf192 * ceil_div(n / 192, 256);
+        form = Tall::k192;
+    }
+    if (const int big = tall_mixed_cols(n); big > 0 && kRoundOf192 * (big / 256) + ceil_div((n - big * 192) / 128, 256) < best) form = Tall::kMixed;
+    return form;
+}
+
+// What the planner takes them to cost beside other tiles.  The costs of 192 columns are fitted to 14 products of one to four shares of k, with
+// the share of a lone round raised by hand to that of 20160 x 4096; from two rounds on those of all widths are about a tenth
+// too low (the power limit).
+double tall_us(int m, int n, int k, int splits) {
     const TileCost &c128 = kCostTall[0], &c192 = kCost288x192;
     const double steps = (double)(k / BK) / splits, plane = plane_us(m, n, GEMM_STORE_F32, splits);
     auto cost_of = [&](const TileCost& c, double rounds, double full) { return launch_us(c, m, n, k, steps, plane, rounds, full); };
     const double tiles = (double)(n / 128) * splits;
     double best = cost_of(c128, rounds_of(c128, tiles), tiles / 256);
-    Tall form = Tall::k128;
-    auto consider = [&](Tall f, double cost) {
-        if (cost < best) { best = cost; form = f; }
-    };
     if (splits == 1) {
-        if (n % 192 == 0) consider(Tall::k192, cost_of(c192, rounds_of(c192, n / 192), n / 192 / 256.0));
+        if (n % 192 == 0) best = std::min(best, cost_of(c192, rounds_of(c192, n / 192), n / 192 / 256.0));
         if (const int big = tall_mixed_cols(n); big > 0) {
             const double whole = big / 256, low = rounds_of(c128, (n - big * 192) / 128) * (c128.step * steps + c128.per_tile) / (c192.step * steps + c192.per_tile);
-            consider(Tall::kMixed, cost_of(c192, whole + low, n / 192.0 / 256.0));
+            best = std::min(best, cost_of(c192, whole + low, n / 192.0 / 256.0));
         }
     }
-    if (us) *us = best;
-    return form;
+    return best;
 }
 
 // Tile shape and split-K factor (a divisor of the k-steps from min_splits to max_splits) of the lowest cost.  Up to 64 rows the
@@ -874,8 +887,7 @@ GemmPlan cheapest(int m, int n, int k, int mode, int min_splits, int max_splits,
             const int h1 = gemm_low_bands(m) ? 192 : 256;
             if (h1 != height) consider(1, narrow_cost_of(h1), (double)ceil_div(m, h1) * cols);
             if (m > 256 && m <= 288 && mode == GEMM_STORE_F32) {
-                double us;
-                tall_form(m, n, k, s, &us);
+                const double us = tall_us(m, n, k, s);
                 if (us < best_cost) { best_cost = us; best = GemmPlan{13, s}; }
             } else if (m > 256 && m <= 384 && mode != GEMM_ADD_F32) consider(13, kCostTall[(m - 257) / 32], cols);
             if (mode == GEMM_STORE_F32 && half_width_deep(m, n, s)) consider(6, kCost128x64Deep, 2 * cols);
@@ -911,6 +923,24 @@ bool tile_fits(int tile, int m, int n, int mode, int splits) {
 }
 
 }  // namespace
+
+int gemm_tile_columns(int m, int n, int k, int mode, int tile, int splits) {
+    if (!tile_fits(tile, m, n, mode, splits)) return -1;
+    if (tile == 9 && n % 128 == 0 && mode != GEMM_ADD_F32) tile = 13;
+    const bool store = mode == GEMM_STORE_F32;
+    switch (tile) {
+        case 0: case 1: case 15: return 128;
+        case 5: case 9: return 192;
+        case 4: case 11: return 0;
+        case 6: return store && half_width_deep(m, n, splits) ? 64 : 128;
+        case 7: return store && m <= 64 ? skinny_columns(m, n, k, mode, splits) : 128;
+        case 13: {
+            const Tall form = store ? tall_form(m, n, splits) : Tall::k128;
+            return form == Tall::k192 ? 192 : form == Tall::kMixed ? 0 : 128;
+        }
+        default: return 256;
+    }
+}
 
 hipError_t launch_gemm_bf16(const bf16_t* a, int64_t lda, const bf16_t* w, int64_t ldw, void* out, int64_t ldc,
                             int m, int n, int k, int mode, int tile, int splits, int64_t split_stride,

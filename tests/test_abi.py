@@ -159,3 +159,39 @@ def test_gemm_planner_stays_near_the_fastest_measured_form(problem, us):
     measured (runs differ by up to 3 %)."""
     tile, splits = B.gllm_op_gemm_plan(*problem)
     assert us.get((tile, splits), float("inf")) <= 1.06 * min(us.values()), (problem, tile, splits)
+
+
+# us of norm, projection and greedy sampling on MI355X by the width of the tiles of one band (0: whole rounds of 192 columns, a last one of 128)
+MEASURED_WIDTHS = [
+    ((257, 32896, 4096), {128: 123}),
+    ((257, 49152, 4096), {128: 137, 192: 112}),
+    ((257, 65664, 4096), {128: 203, 192: 176, 0: 160}),
+    ((288, 79104, 8192), {128: 381, 192: 352, 0: 330}),
+    ((272, 89856, 5120), {128: 262, 192: 239, 0: 277}),
+    ((257, 100352, 4096), {128: 259, 0: 246}),
+    ((257, 128256, 4096), {128: 310, 192: 293, 0: 281}),
+    ((272, 131328, 8192), {128: 612, 192: 537, 0: 579}),
+    ((288, 152064, 4096), {128: 356, 192: 369, 0: 352}),
+    ((288, 196608, 8192), {128: 857, 192: 800, 0: 841}),
+]
+
+
+@pytest.mark.parametrize("problem,us", MEASURED_WIDTHS)
+def test_one_band_of_288_rows_goes_by_the_fastest_width(problem, us):
+    m, n, k = problem
+    assert us[B.gllm_op_gemm_tile_columns(m, n, k, 0, 13)] == min(us.values())
+    if n % 192 == 0:
+        assert B.gllm_op_gemm_tile_columns(m, n, k, 0, 9) == B.gllm_op_gemm_tile_columns(m, n, k, 0, 13)
+
+
+def test_tile_columns_of_other_tiles():
+    for tile, want in ((0, 128), (1, 128), (2, 256), (3, 256), (5, 192), (6, 128), (14, 256), (15, 128)):
+        assert B.gllm_op_gemm_tile_columns(200, 768, 4096, 0, tile) == want, tile
+    assert B.gllm_op_gemm_tile_columns(257, 576, 4096, 0, 9) == 192 and B.gllm_op_gemm_tile_columns(257, 768, 4096, 1, 9) == 192
+    assert B.gllm_op_gemm_tile_columns(300, 49152, 4096, 0, 13) == 128 and B.gllm_op_gemm_tile_columns(257, 49152, 4096, 0, 13, 2) == 128
+    assert B.gllm_op_gemm_tile_columns(257, 49152, 4096, 2, 13) == 128
+    assert B.gllm_op_gemm_tile_columns(64, 4096, 4096, 0, 7, 4) == 64 and B.gllm_op_gemm_tile_columns(64, 152064, 5120, 0, 7) == 128
+    assert B.gllm_op_gemm_tile_columns(80, 4096, 4096, 0, 6, 4) == 64
+    for bad in ((257, 576, 4096, 2, 9, 1), (256, 768, 4096, 0, 13, 1), (200, 768, 4096, 0, 99, 1), (200, 100, 4096, 0, 0, 1), (200, 768, 4096, 0, 0, 3)):
+        with pytest.raises(B.GllmError):
+            B.gllm_op_gemm_tile_columns(*bad)

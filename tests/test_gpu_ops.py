@@ -524,6 +524,7 @@ def test_gemm_fp32_results_of_one_round_and_of_more(M, N, ldc, tile):
     128-column tiles: 1024 of two stages of A, 1030 and 1188 with a compute unit each (of 32 rows for M = 20, of 64 above 32)."""
     K = 64
     print(f"gemm results M={M} N={N} ldc={ldc} tile={tile}", flush=True)
+    assert tile != 7 or B.gllm_op_gemm_tile_columns(M, N, K, B.GEMM_STORE_F32, tile) == 128
     a, w = rand_bits(31, 1, (M, K), 1.0), rand_bits(31, 2, (N, K), 0.05)
     ref = oracle.linear(oracle.bf16_to_f64(a), w)
     flat = torch.full(((M - 1) * ldc + N + 64,), 7.0, dtype=torch.float32, device=DEV)
@@ -559,6 +560,7 @@ def test_gemm_one_band_of_288_rows_by_either_width(M, N):
     the last one and the padding of a row stay as they are."""
     K = 4096
     print(f"gemm one band M={M} N={N}", flush=True)
+    assert B.gllm_op_gemm_tile_columns(M, N, K, B.GEMM_STORE_F32, 13) == {32896: 128, 49152: 192, 79104: 0}[N]
     torch.manual_seed(5)
     a = torch.randn(M, K, device=DEV).to(torch.bfloat16)
     w = (torch.randn(N, K, device=DEV) * 0.02).to(torch.bfloat16)
