@@ -8,8 +8,8 @@
 //
 // What bounds it: many rows, the 1400 W power limit (a bare MFMA loop on random operands reaches 1.6-1.8 PFLOP/s); few
 // rows, the stream of the weights (5.5-6.8 TB/s) and the ~5 us a launch costs before and after it; in between what a compute unit
-// loads: weights from HBM and activations from the L2 pass through it in one order, 68 KB/us of both together whatever the number
-// of LDS stages (activations alone 150), so that a result of a narrow tile costs more.  Under
+// loads: a k-step's weights from HBM and activations from the L2 take nearly as long as one after the other, 66 KB/us of both together
+// where activations alone come at 120 (profiles/gemm_loads_of_a_k_step.txt), so that a result of a narrow tile costs more.  Under
 // the power limit the clock follows the busy share of the matrix cores, so cycles in the k-loop count in full, and so does
 // the energy of a product.  16x16x32 MFMAs touch an accumulator half as often per product as 32x32x16 ones: the same tile at
 // the same order of loads took 99.3 -> 90.6 us for gate/up at 512 rows (28672 x 4096), 859 -> 833 at 2048 rows of 55296 x
@@ -78,8 +78,8 @@ __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ A, int64_t 
     constexpr int kAuxNonTemporal = 2;        // cache-policy operand of a buffer load: the nt bit
     // ... and of a buffer store: the sc1 bit.  Results that stay in the L2 are written back when the stream of the weights
     // displaces them, in pieces, and the reads wait for those writes all along; written through they are on their way at once.
-    // Logits of 64 rows: 152064 x 5120 296 -> 255 us (5.3 -> 6.1 TB/s of weights, 6.6 without any stores; with the nt hint 262),
-    // 128256 x 4096 181 -> 162 (165); 257 rows 328 -> 308.  In a single round all results are stored when the stream has ended, and the
+    // 152064 x 5120 at 64 rows in a loop 296 -> 255 us (5.3 -> 6.1 TB/s of weights, 6.6 without any stores; with the nt hint 262); norm,
+    // projection and sampling of 128256 x 4096, 64 rows 195 -> 176, 128 rows 213 -> 192.  In a single round all results are stored when the stream has ended, and the
     // next kernel reads them: there they are left to the L2 (197 rows, eight layers 1243 us, written through 1257).
     constexpr int kAuxWriteThrough = 16;
     constexpr int kBufferFlags = 0x00027000;  // raw buffer of 32-bit words, bounds checked in bytes
@@ -476,9 +476,9 @@ int gemm_band_height(int m, int mode) {
 // as many in (deeper 128-column tiles at 432 and 448 tiles 1.02, 64-column ones 1.01 to 1.04).  In several rounds of which
 // the last is nearly full two stages of A and three of W: with more loads in flight some compute units run ahead of others and the
 // last round is a long tail (128256 x 4096, 64 rows: the first tiles end between 62 and 91 us, so between 77 and 82).
-// 128256 x 4096: one row 157 -> 153 us, 32 rows 178 -> 170, 64 rows 199 -> 179 (results written through: 192 -> 162); 128256 x 8192, 64
-// rows 355 -> 338.  Where the
-// last round is short the tiles had better end at different times (152064 x 8192, 0.3 of a round left, 64 rows: 433 and 453).
+// 128256 x 4096: one row 157 -> 153 us, 32 rows 178 -> 170, 64 rows 199 -> 179 (all with results left in
+// the L2s); 128256 x 8192, 64 rows 355 -> 338.  Where the last round is short the tiles had better end at different times (152064 x
+// 8192, 0.3 of a round left, 64 rows: 433 and 453).
 // There, with results that are written through, one tile at a time on a compute unit keeps the rounds of 256 together (two tiles end
 // apart, and the last ones run alone), from more than four of them on: norm, projection and sampling together 0.96 to 1.00 of the time at 24
 // to 64 rows, 1.02 at most, k of 2048 to 8320 and 4.0 to 7.0 rounds alike (152064 x 5120, 64 rows 266 -> 258 us), up to 3.4 rounds 0.97 to
@@ -708,7 +708,9 @@ namespace {
 // The picks are 0.37 % behind the fastest forms on average, at most 10 % (profiles/gemm_plan_sweep.txt); fitted to three quarters
 // of the products, 0.44 % and 14 % on the rest, of other row counts.  Before, with one `lone` for all and the low tiles of a
 // row-mixed launch in a round of their own: 1.2 %, at most 28 % (28672 x 4096 at 1050 rows 240 -> 192 us, 4096 x 4096 at 800
-// rows 41 -> 35).  Tile 6 of 96 rows goes by the costs of 128 rows (0.99 of the time), that of 64 columns by costs set by hand: of
+// rows 41 -> 35).  All that was measured before results were written through and before 288x192 tiles of four waves and of both
+// widths; with these, of 78 vocabulary products at 65 to 384 rows the pick is the fastest in 74, 3 % behind at most
+// (profiles/gemm_vocabulary_by_tile.txt).  Tile 6 of 96 rows goes by the costs of 128 rows (0.99 of the time), that of 64 columns by costs set by hand: of
 // the products where it is in question 4.6 % behind the fastest form on average, 2.5 % from 2048 columns on (360 products of 65 to 128
 // rows, profiles/gemm_65_to_128_rows.txt).
 struct TileCost {

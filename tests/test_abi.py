@@ -124,13 +124,15 @@ def test_gemm_planner_ends_on_the_largest_problems():
 # near the best one and of those that a planner could confuse with them; products in several planes include reading these at
 # 6 TB/s
 MEASURED_PRODUCTS = [
-    ((65, 128256, 4096, 0, 1), {(0, 1): 183, (14, 1): 183, (3, 1): 193, (6, 1): 218, (15, 1): 220}),
-    ((128, 128256, 4096, 0, 1), {(14, 1): 195, (0, 1): 209, (3, 1): 210, (5, 1): 241, (6, 1): 246, (15, 1): 248}),
-    ((160, 128256, 4096, 0, 1), {(14, 1): 201, (3, 1): 222, (5, 1): 250, (15, 1): 254}),
-    ((257, 128256, 4096, 0, 1), {(13, 1): 283, (14, 1): 330, (15, 1): 370, (3, 1): 388}),
-    ((320, 128256, 4096, 0, 1), {(13, 1): 312, (14, 1): 345, (15, 1): 397, (3, 1): 401}),
-    ((128, 128256, 8192, 0, 1), {(14, 1): 352, (0, 1): 383, (3, 1): 398, (6, 1): 406}),
-    ((128, 152064, 5120, 0, 1), {(4, 1): 291, (14, 1): 307, (3, 1): 344, (6, 1): 350, (0, 1): 350}),
+    ((65, 128256, 4096, 0, 1), {(0, 1): 169, (14, 1): 169, (3, 1): 183, (6, 1): 203, (15, 1): 204}),
+    ((128, 128256, 4096, 0, 1), {(14, 1): 173, (0, 1): 187, (3, 1): 190, (5, 1): 216, (6, 1): 217, (15, 1): 218}),
+    ((160, 128256, 4096, 0, 1), {(14, 1): 178, (3, 1): 192, (15, 1): 223, (5, 1): 224}),
+    ((256, 128256, 4096, 0, 1), {(14, 1): 216, (3, 1): 222, (1, 1): 249, (15, 1): 251, (5, 1): 253}),
+    ((257, 128256, 4096, 0, 1), {(13, 1): 237, (14, 1): 327, (8, 1): 341, (15, 1): 360, (3, 1): 379}),
+    ((320, 128256, 4096, 0, 1), {(13, 1): 289, (14, 1): 343, (15, 1): 384, (3, 1): 389}),
+    ((128, 128256, 8192, 0, 1), {(14, 1): 323, (6, 1): 361, (0, 1): 364, (3, 1): 378}),
+    ((128, 152064, 5120, 0, 1), {(4, 1): 261, (14, 1): 279, (6, 1): 290, (0, 1): 290, (3, 1): 321}),
+    ((288, 152064, 8192, 0, 1), {(13, 1): 608, (14, 1): 744, (8, 1): 782, (15, 1): 838, (3, 1): 883}),
     ((800, 57344, 8192, 2, 1), {(4, 1): 608, (14, 1): 660, (8, 1): 682, (15, 1): 721, (3, 1): 735}),
     ((773, 55296, 5120, 2, 1), {(4, 1): 384, (8, 1): 389, (14, 1): 410, (15, 1): 452, (3, 1): 464}),
     ((160, 55296, 5120, 2, 1), {(14, 1): 97.5, (3, 1): 121, (15, 1): 130}),
