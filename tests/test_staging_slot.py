@@ -35,8 +35,9 @@ def lib(tmp_path_factory):
     return lib
 
 
-def wait(lib, state, batch, flag, settle=0, errors=(), write=None):
-    """(result, state after, calls of settle, calls of error); write = (delay, number) stores a flag meanwhile."""
+def wait(lib, state, batch, flag, settle=0, errors=(), write=None, write_when_asked=None):
+    """(result, state after, calls of settle, calls of error); write = (delay, number) stores a flag meanwhile, write_when_asked
+    one when the second question for an error comes."""
     calls = {"settle": 0, "error": 0}
 
     def on_settle():
@@ -45,6 +46,8 @@ def wait(lib, state, batch, flag, settle=0, errors=(), write=None):
 
     def on_error():
         calls["error"] += 1
+        if write_when_asked is not None and calls["error"] == 2:
+            word.value = write_when_asked
         return errors[min(calls["error"], len(errors)) - 1] if errors else 0
 
     st, word = C.c_int(state), C.c_uint32(flag)
@@ -76,9 +79,8 @@ def test_an_older_number_is_waited_out(lib, delay):
 
 
 def test_there_is_no_limit_of_time_and_no_error_means_on(lib):
-    """Asked for an error at least once, none there: the flag is waited for."""
-    e, state, settle, error = wait(lib, FLAGGED, 8, 7, write=(4.0, 8))
-    assert (e, state, settle) == (0, FREE, 0) and error >= 1
+    """Asked for an error twice, none there: the flag is waited for."""
+    assert wait(lib, FLAGGED, 8, 7, write_when_asked=8) == (0, FREE, 0, 2)
 
 
 def test_an_error_ends_the_wait_and_the_slot_stays_taken(lib):
